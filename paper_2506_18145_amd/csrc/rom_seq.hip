@@ -3,6 +3,8 @@
 //   (Eq. (5), (6)/(13)), the per-token sums over the K selected experts (Eq. (10)/(11)) and the
 //   gate-weighted combine (Eq. (12)), plus the small helpers of the FFN-MoE layer (row map,
 //   1 / rms per routed row, SwiGLU for fp32).  All of this is bandwidth / plain-ALU work: no MFMA here.
+#include <type_traits>
+
 #include "rom_internal.h"
 
 namespace rom {
@@ -745,6 +747,215 @@ __global__ __launch_bounds__(HELPERS ? 512 : 256) void scan_pipe_kernel(
   if (computes && h_out && chunk == n_chunks - 1) h_out[(b * d_inner + ch) * 16 + n] = r.h;
 }
 
+// ------------------------------------------------------------------ selective scan, lane = channel
+// A lane owns one channel with its 16 states in registers, a wavefront 64 neighbouring channels of one time
+// chunk; there is no LDS and no barrier.  B_t and C_t are the same for every channel, so they come through the
+// scalar cache into SGPRs (two s_load_dwordx16 per step, one step ahead) and feed the multiplies as scalar
+// operands; dt, u and z of a step are one 128-byte line per wavefront, kLaneRun steps ahead in registers.  A step
+// is, per state, v_mul, v_exp, v_mul, v_fma and (outputs) v_fma: five instructions for 64 (channel, state) pairs
+// where the lane = (channel, state) layout pays nine, four of them for the sum over the states.
+// The price is parallelism (d_inner / 64 wavefronts per sequence), so time is cut into chunks until the chip has
+// kLaneWaves wavefronts: a state-only pass leaves every chunk's end state from zero (chunk_q [B][chunk][16][d_inner])
+// and its sum of dt (chunk_s [B][chunk][d_inner]); scan_fold_kernel walks h <- exp(A sum dt_k) h + q_k over them and
+// leaves every chunk's start state in place of its end state, from which the full pass runs.
+// Bound by ALU issue: 95 vector instructions per step of the full pass, at 4.4 clocks each (v_exp takes 8; an
+// instruction with an SGPR operand takes 4.4 where two register-only ones of different wavefronts take 5.5 together);
+// 16384 x 4096 bf16: 188 us full pass + 137 us state-only pass + 10 us fold = 342 us, lane = (channel, state) 384 us.
+constexpr int kLaneRun = 8;
+constexpr int kLaneWaves = 4096;
+constexpr int kLaneMinLen = 64;
+typedef float f32x16s_t __attribute__((ext_vector_type(16)));
+typedef const __attribute__((address_space(4))) f32x16s_t const_f32x16_t;
+typedef __attribute__((address_space(1))) char global_char_t;
+
+template <typename T, bool kStateOnly>
+__global__ __launch_bounds__(256) void scan_lane_kernel(
+    const T *__restrict__ u, const T *__restrict__ dt, const float *__restrict__ bc,
+    const T *__restrict__ z, int64_t ld_z, const float *__restrict__ A_log,
+    const float *__restrict__ D, const float *__restrict__ h_in, float *__restrict__ h_out,
+    T *__restrict__ g, int64_t L, int d_inner, int64_t chunk_len, int n_chunks,
+    float *__restrict__ chunk_q, float *__restrict__ chunk_s) {
+  const int lane = threadIdx.x & 63;
+  const int grp = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (grp * 64 >= d_inner) return;
+  const int ch0 = grp * 64;
+  const bool active = ch0 + lane < d_inner;
+  const int cl = active ? lane : d_inner - 1 - ch0;   // idle lanes of a ragged last group repeat its last channel, stores included
+  const int ch = ch0 + cl;
+  const int64_t b = blockIdx.z;
+  const int chunk = blockIdx.y;
+  const int64_t t_begin = chunk * chunk_len;
+  const int64_t t_end = (t_begin + chunk_len < L) ? t_begin + chunk_len : L;
+  const int len = static_cast<int>(t_end - t_begin);
+
+  float a2[16], h[16];
+#pragma unroll
+  for (int n = 0; n < 16; n += 4) {
+    const float4 v = ld_f4(A_log + static_cast<int64_t>(ch) * 16 + n);
+    a2[n] = -__expf(v.x) * 1.44269504088896341f; a2[n + 1] = -__expf(v.y) * 1.44269504088896341f;
+    a2[n + 2] = -__expf(v.z) * 1.44269504088896341f; a2[n + 3] = -__expf(v.w) * 1.44269504088896341f;
+  }
+  auto load_h_in = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < 16; n += 4) {
+      const float4 v = h_in ? ld_f4(h_in + (b * d_inner + ch) * 16 + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+      h[n] = v.x; h[n + 1] = v.y; h[n + 2] = v.z; h[n + 3] = v.w;
+    }
+  };
+  // slots 0 .. n_chunks-2 of chunk_q are the chunk summaries, the last one a copy of the incoming state taken by
+  // the state-only pass, so that the full pass of a chunked launch never reads h_in (h_out may alias it, and the
+  // last chunk's wavefronts write h_out while earlier chunks may still be starting)
+  const auto q_at = [&](int k) { return chunk_q + ((b * n_chunks + k) * 16) * d_inner + ch; };
+  if constexpr (kStateOnly) {
+    if (chunk == 0) {
+      load_h_in();
+      float *q = q_at(n_chunks - 1);
+#pragma unroll
+      for (int n = 0; n < 16; ++n) q[static_cast<int64_t>(n) * d_inner] = h[n];
+    }
+#pragma unroll
+    for (int n = 0; n < 16; ++n) h[n] = 0.0f;
+  } else if (n_chunks > 1) {                 // scan_fold_kernel has left the chunk's start state
+    const float *q = q_at(chunk);
+#pragma unroll
+    for (int n = 0; n < 16; ++n) h[n] = q[static_cast<int64_t>(n) * d_inner];
+  } else {
+    load_h_in();
+  }
+  const float d_skip = kStateOnly ? 0.0f : D[ch];
+  float dt_sum = 0.0f;
+
+  // every address is a uniform base, a uniform 32-bit row offset (the launcher keeps a chunk's rows within 2 GiB)
+  // and one lane offset
+  const int64_t row0 = b * L + t_begin;
+  const uint32_t loff = static_cast<uint32_t>(cl) * sizeof(T);
+  const uint32_t pitch = static_cast<uint32_t>(d_inner * sizeof(T)), pitch_z = static_cast<uint32_t>(ld_z * sizeof(T));
+  const uintptr_t u_p = reinterpret_cast<uintptr_t>(u + row0 * d_inner + ch0);
+  const uintptr_t dt_p = reinterpret_cast<uintptr_t>(dt + row0 * d_inner + ch0);
+  const uintptr_t z_p = kStateOnly ? 0 : reinterpret_cast<uintptr_t>(z + row0 * ld_z + ch0);
+  const uintptr_t g_p = kStateOnly ? 0 : reinterpret_cast<uintptr_t>(g + row0 * d_inner + ch0);
+  typedef __attribute__((address_space(1))) T global_t;
+  const uintptr_t bc_p = reinterpret_cast<uintptr_t>(bc + row0 * 32);
+
+  // (the empty asm statements keep the compiler from adding lane offset and base first, or widening the lane offset
+  // outside the loop: either would make every address a vector addition)
+  auto row = [](uintptr_t base, uint32_t off) __attribute__((always_inline)) {
+    uintptr_t p = base + off;
+    asm("" : "+s"(p));
+    return reinterpret_cast<global_char_t *>(p);
+  };
+  // ring of the next kLaneRun rows: a slot is requested anew as soon as its step has taken the values out
+  T ru[kLaneRun], rdt[kLaneRun], rz[kLaneRun];
+  auto fetch = [&](int t, uint32_t lo, auto slot) __attribute__((always_inline)) {
+    constexpr int j = decltype(slot)::value;
+    const uint32_t r = static_cast<uint32_t>(t < len ? t : len - 1);    // past the chunk's end: its last row again
+    rdt[j] = *reinterpret_cast<global_t *>(row(dt_p, r * pitch) + lo);
+    ru[j] = *reinterpret_cast<global_t *>(row(u_p, r * pitch) + lo);
+    if constexpr (!kStateOnly) rz[j] = *reinterpret_cast<global_t *>(row(z_p, r * pitch_z) + lo);
+  };
+  f32x16s_t bv = *reinterpret_cast<const_f32x16_t *>(bc_p);
+  auto step = [&](int t, auto slot) __attribute__((always_inline)) {
+    constexpr int j = decltype(slot)::value;
+    const float d = to_f32(rdt[j]), uu = to_f32(ru[j]), du = d * uu, zz = kStateOnly ? 0.0f : to_f32(rz[j]);
+    uint32_t lo = loff;
+    asm volatile("" : "+v"(lo));
+    fetch(t + kLaneRun, lo, slot);
+    // B of the next step and C of this one travel while the states advance
+    const uint32_t tn = static_cast<uint32_t>(t + 1 < len ? t + 1 : len - 1);
+    const f32x16s_t bn = *reinterpret_cast<const_f32x16_t *>(bc_p + tn * 128u);
+    f32x16s_t cv;
+    if constexpr (!kStateOnly) cv = *reinterpret_cast<const_f32x16_t *>(bc_p + static_cast<uint32_t>(t) * 128u + 64u);
+#pragma unroll
+    for (int n = 0; n < 16; ++n) h[n] = fmaf(fast_exp2(d * a2[n]), h[n], du * bv[n]);
+    if constexpr (kStateOnly) {
+      dt_sum += d;
+    } else {
+      float y0 = d_skip * uu, y1 = h[1] * cv[1];
+#pragma unroll
+      for (int n = 0; n < 16; n += 2) {
+        y0 = fmaf(h[n], cv[n], y0);
+        if (n) y1 = fmaf(h[n + 1], cv[n + 1], y1);
+      }
+      *reinterpret_cast<global_t *>(row(g_p, static_cast<uint32_t>(t) * pitch) + lo) = from_f32<T>((y0 + y1) * silu_f32(zz));
+    }
+    bv = bn;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // every slot by its number, as a constant
+  auto each = [](auto fn) __attribute__((always_inline)) {
+    fn(std::integral_constant<int, 0>{}); fn(std::integral_constant<int, 1>{}); fn(std::integral_constant<int, 2>{});
+    fn(std::integral_constant<int, 3>{}); fn(std::integral_constant<int, 4>{}); fn(std::integral_constant<int, 5>{});
+    fn(std::integral_constant<int, 6>{}); fn(std::integral_constant<int, 7>{});
+  };
+  static_assert(kLaneRun == 8, "slots of each()");
+  each([&](auto slot) __attribute__((always_inline)) { fetch(decltype(slot)::value, loff, slot); });
+  int t = 0;
+  // The SIMD's arbiter serves its oldest wavefront first: left alone, the wavefronts of a SIMD finish one after the
+  // other and the last ones run without company at half the issue rate.  A wavefront's priority falls as it advances.
+  const int p2 = len / 2, p1 = p2 + len / 4, p0 = p1 + len / 8;
+  __builtin_amdgcn_s_setprio(3);
+  for (; t + kLaneRun <= len; t += kLaneRun) {
+    if (t >= p0) __builtin_amdgcn_s_setprio(0);
+    else if (t >= p1) __builtin_amdgcn_s_setprio(1);
+    else if (t >= p2) __builtin_amdgcn_s_setprio(2);
+    // brings the B / C rows of the next run into L2 (lane l: 16 bytes of row l / 8); the scalar loads run only one
+    // step ahead and would wait for HBM
+    const int wr = t + kLaneRun + (lane >> 3) < len ? t + kLaneRun + (lane >> 3) : len - 1;
+    const f32x4v_t warm = *reinterpret_cast<const f32x4v_t *>(bc + (row0 + wr) * 32 + (lane & 7) * 4);
+    each([&](auto slot) __attribute__((always_inline)) { step(t + decltype(slot)::value, slot); });
+    asm volatile("" ::"v"(warm));
+  }
+  each([&](auto slot) __attribute__((always_inline)) {
+    if (t + decltype(slot)::value < len) step(t + decltype(slot)::value, slot);
+  });
+
+  if (!active) return;
+  if constexpr (kStateOnly) {
+    float *q = q_at(chunk);
+#pragma unroll
+    for (int n = 0; n < 16; ++n) q[static_cast<int64_t>(n) * d_inner] = h[n];
+    chunk_s[(b * n_chunks + chunk) * d_inner + ch] = dt_sum;
+  } else if (h_out && chunk == n_chunks - 1) {
+    float4 *hp = reinterpret_cast<float4 *>(h_out + (b * d_inner + ch) * 16);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) hp[n] = make_float4(h[4 * n], h[4 * n + 1], h[4 * n + 2], h[4 * n + 3]);
+  }
+}
+
+// thread = (sequence, state, channel): q_k <- state at the start of chunk k (slot n_chunks - 1 holds the incoming state)
+__global__ __launch_bounds__(256) void scan_fold_kernel(const float *__restrict__ A_log, int64_t n_seq, int d_inner,
+                                                        int n_chunks, float *__restrict__ chunk_q,
+                                                        const float *__restrict__ chunk_s) {
+  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t per_seq = static_cast<int64_t>(d_inner) * 16;
+  if (idx >= n_seq * per_seq) return;
+  const int64_t b = idx / per_seq;
+  const int r = static_cast<int>(idx % per_seq), n = r / d_inner, ch = r % d_inner;
+  const float a2 = -__expf(A_log[static_cast<int64_t>(ch) * 16 + n]) * 1.44269504088896341f;
+  float *q = chunk_q + b * n_chunks * per_seq + r;
+  const float *s = chunk_s + b * n_chunks * d_inner + ch;
+  float h = q[(n_chunks - 1) * per_seq];
+  constexpr int kAhead = 8;
+  float qv[kAhead], sv[kAhead];
+  for (int k0 = 0; k0 < n_chunks - 1; k0 += kAhead) {
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int k = k0 + j < n_chunks - 2 ? k0 + j : n_chunks - 2;
+      qv[j] = q[k * per_seq];
+      sv[j] = s[static_cast<int64_t>(k) * d_inner];
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (k0 + j < n_chunks - 1) {
+        q[(k0 + j) * per_seq] = h;
+        h = fmaf(fast_exp2(a2 * sv[j]), h, qv[j]);
+      }
+    }
+  }
+  q[(n_chunks - 1) * per_seq] = h;
+}
+
 // ------------------------------------------------------------------ single-step scan (L == 1)
 // One recurrence update per (sequence, channel, state): bound by reading and writing the fp32
 // state.  A lane owns four consecutive states of one channel (one 16-byte load and store), four
@@ -1179,6 +1390,29 @@ hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const floa
   return hipGetLastError();
 }
 
+// Which scan takes a call (measured on MI355X, both kernels in one process, bf16):
+//   * 2048 wavefronts of 64 channels or more need no time chunks: lane = channel, one pass
+//     (64 x 256 steps x 4096 channels 300 -> 203 us, 32 x 512 x 4096 298 -> 237 us);
+//   * few (sequence, 16 channel) blocks, at most three per CU, leave the lane = (channel, state) kernels at one or two
+//     wavefronts per SIMD: with enough steps to cut, lane = channel wins in spite of its second pass
+//     (1 x 16384 x 4096: 384 -> 342 us, 2 x 4096 x 3072: 196 -> 151 us, 4 x 4096 x 2048: 197 -> 185 us; below about
+//     24 M (step, channel) pairs its three launches and short chunks cost the gain: 4 x 2048 x 2048 105 -> 108 us);
+//   * in between (8 x 2048 x 4096: 312 against 338 us) and for short calls the lane = (channel, state) kernels stay.
+bool scan_by_lane(int64_t B, int64_t L, int d_inner) {
+  if (B * ceil_div(d_inner, 64) >= 2048) return true;
+  return B * (d_inner / kScanCh) <= 768 && B * L * d_inner >= (24ll << 20);
+}
+
+int scan_lane_chunks(int64_t B, int64_t L, int d_inner) {
+  const int64_t waves = B * ceil_div(d_inner, 64);
+  if (waves >= 2048) return 1;
+  int64_t nc = kLaneWaves / (waves > 0 ? waves : 1);
+  const int64_t by_len = L / kLaneMinLen;
+  if (nc > by_len) nc = by_len;
+  if (nc < 1) nc = 1;
+  return static_cast<int>(nc);
+}
+
 int scan_chunks(int64_t B, int64_t L, int d_inner) {
   // chunk only when there are fewer workgroups than CUs (256): the state-only pass costs about as
   // much as the better occupancy of the full pass gains once every SIMD has a wavefront; chunks are whole tiles and at least 256 steps long
@@ -1192,7 +1426,8 @@ int scan_chunks(int64_t B, int64_t L, int d_inner) {
 }
 
 size_t scan_chunk_state_bytes(int64_t B, int64_t L, int d_inner) {
-  const int nc = scan_chunks(B, L, d_inner);
+  const int a = scan_chunks(B, L, d_inner), b = scan_by_lane(B, L, d_inner) ? scan_lane_chunks(B, L, d_inner) : 1;
+  const int nc = a > b ? a : b;
   return static_cast<size_t>(B) * (nc > 1 ? nc : 0) * d_inner * 16 * sizeof(float);
 }
 
@@ -1206,6 +1441,24 @@ static hipError_t scan_dispatch(const T *u, const T *dt, const float *bc, const 
     hipLaunchKernelGGL((scan_step_kernel<T>), dim3(static_cast<unsigned>(ceil_div(lanes, 256))), dim3(256),
                        0, s, u, dt, bc, z, ld_z, A_log, D, h_in, h_out, g, B, d_inner);
     return hipGetLastError();
+  }
+  if (scan_by_lane(B, L, d_inner)) {
+    const int64_t chunk_len = ceil_div(ceil_div(L, scan_lane_chunks(B, L, d_inner)), kLaneRun) * kLaneRun;
+    const int nc = static_cast<int>(ceil_div(L, chunk_len));      // no empty chunk after rounding
+    // the kernel addresses a chunk's rows with 32-bit byte offsets; grid.y and grid.z are 16-bit
+    if (chunk_len * ld_z * static_cast<int64_t>(sizeof(T)) < (1ll << 31) && B < 65536) {
+      const unsigned gx = static_cast<unsigned>(ceil_div(d_inner, 256)), gz = static_cast<unsigned>(B);
+      if (nc > 1) {
+        hipLaunchKernelGGL((scan_lane_kernel<T, true>), dim3(gx, nc - 1, gz), dim3(256), 0, s, u, dt, bc,
+                           static_cast<const T *>(nullptr), ld_z, A_log, D, h_in, static_cast<float *>(nullptr),
+                           static_cast<T *>(nullptr), L, d_inner, chunk_len, nc, chunk_q, chunk_p);
+        hipLaunchKernelGGL(scan_fold_kernel, dim3(static_cast<unsigned>(ceil_div(B * d_inner * 16, 256))), dim3(256), 0,
+                           s, A_log, B, d_inner, nc, chunk_q, chunk_p);
+      }
+      hipLaunchKernelGGL((scan_lane_kernel<T, false>), dim3(gx, nc, gz), dim3(256), 0, s, u, dt, bc, z, ld_z, A_log, D,
+                         h_in, h_out, g, L, d_inner, chunk_len, nc, chunk_q, chunk_p);
+      return hipGetLastError();
+    }
   }
   const int nc_max = scan_chunks(B, L, d_inner);
   const int64_t chunk_len = ceil_div(ceil_div(L, nc_max), kScanTile) * kScanTile;
