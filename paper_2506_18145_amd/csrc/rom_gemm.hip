@@ -534,51 +534,51 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_mfma_kernel(const GemmA
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, LDS-DMA loads
-// Same 256x256 tile and 4x2 wavefront layout, but the operand slabs travel from global memory
-// straight into LDS (global_load_lds_dwordx4: lane l of a wave deposits its 16 bytes at M0 + 16 l),
-// so no registers, no LDS-write instructions and no load->store dependency sit in the MFMA loop.
+// The operand slabs travel from global memory straight into LDS (global_load_lds_dwordx4: lane l of
+// a wave deposits its 16 bytes at M0 + 16 l), so no registers, no LDS-write instructions and no
+// load->store dependency sit in the MFMA loop.
 // K is walked in 64-wide slabs so that every row contributes one whole 128-byte cache line per
-// slab.  A slab is two "half slabs" of 32 KiB (the 256 A rows, then the 256 W rows) and LDS is a
+// slab.  A slab is two "half slabs" of up to 32 KiB (the A rows, then the W rows) and LDS is a
 // ring of five such slots: while slab m (two slots) is multiplied, A(m+1), W(m+1) and A(m+2) are in
 // flight or landed; the barrier before the last 16-wide step of slab m frees its two slots, which
 // then receive W(m+2) and A(m+3).
 // The XOR swizzle is applied on the global side: the lane that fills 16-byte position c' of row r
 // fetches chunk c' ^ ((r >> 1) & 7), which keeps the 16-lane fragment reads conflict-free for
 // 128-byte rows.  The compiler does not see these loads (inline asm), so the waits are explicit:
-// every wave issues exactly four loads per half slab, in ring order, and "vmcnt(4)" therefore
-// means "everything but the newest half slab I asked for has landed".
+// every wave issues the same number of loads per half slab, in ring order, and a vmcnt of that number
+// therefore means "everything but the newest half slab I asked for has landed".
+// dma_tile is one tile of that kind: the x projection's (256 rows, one narrow column tile) and the pieces
+// of the stream kernel's last round.
 constexpr int kDmaBK = 64, kDmaRC = kDmaBK / 8, kDmaSlots = 5;
 constexpr bool kUseDma = true;
 constexpr int kSkinnyMinWgs = 100;
 constexpr int kSkinnyColsMaxWgs = 600;    // fewer 64 x 128 tiles than this (about two per CU): 64 x 64 tiles instead
 constexpr bool kUseSmallK = true;
-constexpr int kBigWM = 4, kBigWN = 2;     // wave layout of the 256x256 DMA tile
 
 __device__ __forceinline__ void dma_load_16(unsigned lds_addr, unsigned voff, const void *base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n"
                :: "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
 }
 
-// BN < 256 (a single, narrow column tile: the x projection) keeps the 256-row activation tile and
-// the five 32 KiB ring slots; the weight half slabs just fill less of theirs.  grid.y slices the
-// inner dimension (fp32 partial sums, plain epilogue only).
+// BN < 256 or BM < 256 keep the five 32 KiB ring slots; the half slabs just fill less of theirs.
+// grid.y slices the inner dimension (fp32 partial sums, plain epilogue only).
 // WT: the weight is stored contraction-major, [group][K][N] (a forward weight used for the input
 // gradient without a transposed copy; BN = 256, N a multiple of 256).  Its half slab is then 64
 // contraction rows x 256 output columns as they lie in memory, two rows per DMA instruction, chunk c
 // of row r at position c ^ 4 (r & 3), and the MFMA fragments - eight consecutive contraction indices of
 // one output column per lane - come out of it through the transposing LDS read (ds_read_b64_tr_b16:
 // the 16 lanes of a group name four rows x 16 columns, lane i receives column i of the four rows).
-template <int BN, int WM, int WN, int EPI, bool WT = false>
+template <int BN, int WM, int WN, int EPI, bool WT = false, int BM = 256>
 __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc, uint4 *smem) {
-  constexpr int BM = 256, NW = WM * WN;
-  static_assert(kDmaSlots == 4 || kDmaSlots == 5, "ring of four or five half-slab slots");
-  static_assert((NW == 16 || NW == 8 || NW == 4) && BN <= BM && BN % (32 * WN) == 0, "4, 8 or 16 waves, 32-wide MFMA tiles");
+  constexpr int NW = WM * WN;
+  static_assert(kDmaSlots == 5, "ring of five half-slab slots");
+  static_assert((NW == 16 || NW == 8 || NW == 4) && BN <= 256 && BM <= 256 && BN % (32 * WN) == 0, "4, 8 or 16 waves, 32-wide MFMA tiles");
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
-  constexpr int kSlotChunks = BM * kDmaRC;                    // 16-byte chunks per ring slot
+  constexpr int kSlotChunks = 256 * kDmaRC;                   // 16-byte chunks per ring slot
   constexpr int kSlotBytes = kSlotChunks * 16;                // 32 KiB
   constexpr int kAInstr = BM / (8 * NW);                      // DMA instructions per wave and half slab: 8 rows each
   constexpr int kWInstr = (BN + 8 * NW - 1) / (8 * NW);       // (rows past BN are clamped re-reads into unused slot space)
-  static_assert(!WT || (BN == 256 && NW == 8), "contraction-major weights: the 256 x 256 tile on eight waves");
+  static_assert(!WT || BN == 256, "contraction-major weights: whole 256-column slabs");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM;
@@ -617,20 +617,13 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
   const unsigned lds_wave_w = __builtin_amdgcn_readfirstlane(lds_base + wave * (kWInstr * 1024));
   const int KT = k_len / kDmaBK;
 
-  // half slab h: the A rows (h even) or the W rows (h odd) of slab h / 2, into ring slot h % 5
-  auto issue = [&](int h) __attribute__((always_inline)) {
+  // DMA instruction j of half slab h: the A rows (h even) or the W rows (h odd) of slab h / 2, into ring slot h % 5
+  auto issue1 = [&](int h, int j) __attribute__((always_inline)) {
     const int m = h >> 1;
     const int sl = m < KT ? m : KT - 1;                        // past the end: harmless reload
     const unsigned slot = static_cast<unsigned>(h % kDmaSlots) * kSlotBytes;
-    if (h & 1) {
-      const bf16_t *wb = Wp + (WT ? static_cast<int64_t>(sl) * kDmaBK * a.N : static_cast<int64_t>(sl) * kDmaBK);
-#pragma unroll
-      for (int j = 0; j < kWInstr; ++j) dma_load_16(lds_wave_w + slot + j * 1024, b_voff[j], wb);
-    } else {
-      const bf16_t *ab = Ap + sl * kDmaBK;
-#pragma unroll
-      for (int j = 0; j < kAInstr; ++j) dma_load_16(lds_wave_a + slot + j * 1024, a_voff[j], ab);
-    }
+    if (h & 1) dma_load_16(lds_wave_w + slot + j * 1024, b_voff[j], Wp + static_cast<int64_t>(sl) * kDmaBK * (WT ? a.N : 1));
+    else dma_load_16(lds_wave_a + slot + j * 1024, a_voff[j], Ap + sl * kDmaBK);
   };
 
   f32x16_t acc[TM][TN];
@@ -655,64 +648,69 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
     }
   }
   bf16x8_t fa0[TM], fa1[TM], fb0[TN], fb1[TN];
-  auto load_frags = [&](int m, int kk, bf16x8_t(&af)[TM], bf16x8_t(&bfr)[TN]) __attribute__((always_inline)) {
-    const int c = (kk * 2 + frag_half) ^ swz;
-    const uint4 *sa = smem + ((2 * m) % kDmaSlots) * kSlotChunks;
+  auto read_a = [&](int m, int kk, int i) __attribute__((always_inline)) {
+    const uint4 v = smem[((2 * m) % kDmaSlots) * kSlotChunks + a_base + i * 32 * kDmaRC + ((kk * 2 + frag_half) ^ swz)];
+    return *reinterpret_cast<const bf16x8_t *>(&v);
+  };
+  auto read_w = [&](int m, int kk, int j) __attribute__((always_inline)) {
     const uint4 *sb = smem + ((2 * m + 1) % kDmaSlots) * kSlotChunks;
-    {
-      const uint4 v = sa[a_base + c];
-      af[0] = *reinterpret_cast<const bf16x8_t *>(&v);
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      if constexpr (WT) {
-        typedef short i16x4_t __attribute__((ext_vector_type(4)));
-        typedef short i16x8_t __attribute__((ext_vector_type(8)));
-        typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
-        const __attribute__((address_space(3))) unsigned char *pb =
-            (const __attribute__((address_space(3))) unsigned char *)sb + kk * (16 * 512) + wt_off[j];
-        const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)pb);
-        const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(pb + 4 * 512));
-        bfr[j] = __builtin_bit_cast(bf16x8_t, (i16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      } else {
-        const uint4 v = sb[b_base + j * 32 * kDmaRC + c];
-        bfr[j] = *reinterpret_cast<const bf16x8_t *>(&v);
-      }
-    }
-#pragma unroll
-    for (int i = 1; i < TM; ++i) {
-      const uint4 v = sa[a_base + i * 32 * kDmaRC + c];
-      af[i] = *reinterpret_cast<const bf16x8_t *>(&v);
+    if constexpr (WT) {
+      typedef short i16x4_t __attribute__((ext_vector_type(4)));
+      typedef short i16x8_t __attribute__((ext_vector_type(8)));
+      typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+      const __attribute__((address_space(3))) unsigned char *pb =
+          (const __attribute__((address_space(3))) unsigned char *)sb + kk * (16 * 512) + wt_off[j];
+      const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)pb);
+      const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(pb + 4 * 512));
+      return __builtin_bit_cast(bf16x8_t, (i16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    } else {
+      const uint4 v = sb[b_base + j * 32 * kDmaRC + ((kk * 2 + frag_half) ^ swz)];
+      return *reinterpret_cast<const bf16x8_t *>(&v);
     }
   };
-  auto mma = [&](const bf16x8_t(&af)[TM], const bf16x8_t(&bfr)[TN]) __attribute__((always_inline)) {
+  // One 16-wide step: between its MFMAs, one by one and held there by scheduling fences, the fragment reads of the next
+  // step (step kn of slab mn) and DMA instructions j0 .. j1 - 1 of half slab h.  All DMA of a slab issued at once behind
+  // its barrier fills the L1's request queue and blocks the wavefronts at issue.
+  constexpr int kMma = TM * TN, kReads = TM + TN;
+  auto step = [&](const bf16x8_t(&fa)[TM], const bf16x8_t(&fb)[TN], bf16x8_t(&na)[TM], bf16x8_t(&nb)[TN], int mn, int kn, int h,
+                  int j0, int j1) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int q = 0; q < kMma; ++q) {
+      acc[q / TN][q % TN] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[q % TN], fa[q / TN], acc[q / TN][q % TN], 0, 0, 0);
+      // in the order of first use: A row 0, the W columns, the other A rows (the last MFMA takes what is left over)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-    InterleaveHints<TM * TN, TM + TN, 0, false, 0>::run();
+      for (int r = q; r < (q == kMma - 1 ? kReads : q + 1) && r < kReads; ++r) {
+        if (r == 0) na[0] = read_a(mn, kn, 0);
+        else if (r <= TN) nb[r - 1] = read_w(mn, kn, r - 1);
+        else na[r - TN] = read_a(mn, kn, r - TN);
+      }
+#pragma unroll
+      for (int j = j0 + (j1 - j0) * q / kMma; j < j0 + (j1 - j0) * (q + 1) / kMma; ++j) issue1(h, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 
+  // A(0), W(0), A(1) and half of W(1): the loop requests the rest
+  constexpr int kWh = (kWInstr + 1) / 2, kAh = (kAInstr + 1) / 2;
 #pragma unroll
-  for (int h = 0; h < kDmaSlots; ++h) issue(h);
-  // slab 0 is in LDS once only A(1), W(1), A(2) are outstanding
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDmaSlots == 5 ? 2 * kAInstr + kWInstr : kAInstr + kWInstr) : "memory");
-  load_frags(0, 0, fa0, fb0);
+  for (int h = 0; h < 4; ++h)
+#pragma unroll
+    for (int j = 0; j < (h == 3 ? kWh : (h & 1) ? kWInstr : kAInstr); ++j) issue1(h, j);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kAInstr + kWh) : "memory");     // slab 0 is in LDS
+  fa0[0] = read_a(0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) fb0[j] = read_w(0, 0, j);
+#pragma unroll
+  for (int i = 1; i < TM; ++i) fa0[i] = read_a(0, 0, i);
 
   for (int m = 0; m < KT; ++m) {
-    load_frags(m, 1, fa1, fb1);
-    mma(fa0, fb0);
-    load_frags(m, 2, fa0, fb0);
-    mma(fa1, fb1);
-    load_frags(m, 3, fa1, fb1);
-    mma(fa0, fb0);
+    step(fa0, fb0, fa1, fb1, m, 1, 2 * m + 3, kWh, kWInstr);      // second half of W(m+1)
+    step(fa1, fb1, fa0, fb0, m, 2, 2 * m + 4, 0, kAh);            // A(m+2)
+    step(fa0, fb0, fa1, fb1, m, 3, 2 * m + 4, kAh, kAInstr);
     // slab m+1 has landed for everyone (only A(m+2) is outstanding) and nobody reads slab m any more
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kDmaSlots == 5 ? kAInstr : 0) : "memory");
-    issue(2 * m + kDmaSlots);                                            // W(m+2) into the slot of A(m)
-    issue(2 * m + kDmaSlots + 1);                                        // A(m+3) into the slot of W(m)
-    load_frags(m + 1, 0, fa0, fb0);
-    mma(fa1, fb1);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kAInstr) : "memory");
+    step(fa1, fb1, fa0, fb0, m + 1, 0, 2 * m + 5, 0, kWh);        // first half of W(m+2)
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // LDS is reused by the epilogue
   mfma_epilogue<EPI, TM, TN, WTM, WTN>(a, tc, acc, smem, wave, wm, wn, lane);
@@ -724,6 +722,456 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
   const TileCoord tc = locate_tile(a, 256, BN);
   if (!tc.valid) return;
   dma_tile<BN, WM, WN, EPI, WT>(a, tc, smem);
+}
+
+// ------------------------------------------------------------------ bf16 MFMA kernel, one stream of slabs per CU
+// The large routed projections: bound by the power the matrix pipe draws (a slab of random operands takes 1.49 us, of zeros
+// 0.97; 0.85 is the pipe's own at 2.4 GHz), then by what stops it: the stores and the last round.  16384 rows in 8 groups,
+// 8192 x 2048: 526 -> 487 us, 2048 x 4096: 299 -> 257 us (one 256 x 256 tile per workgroup of eight wavefronts before).
+// One workgroup of four wavefronts per CU (2 x 2, 128 x 128 each: 256 accumulator
+// registers, a third less LDS traffic per flop than eight 64 x 128 ones) walks its share of the 256 x 256 tiles; the ring
+// of five half-slab slots above runs on across tile boundaries: the last two slabs of a tile already request the next
+// tile's, so that between tiles only the epilogue (registers -> bf16 -> stores, no LDS) stops the matrix pipe.
+//   * a 64-wide slab is four 16-wide steps of 16 MFMAs; between them, one by one and held there by scheduling fences,
+//     the eight fragment reads of the next step and four DMA instructions.  All DMA issued at once behind the slab's
+//     barrier (16 per wavefront) fills the L1's request queue and blocks the wavefront at issue.
+//   * the workgroups that share an activation (weight) tile request its rows in rotated order: each line's first
+//     request, the one that waits for HBM, comes from another CU, and the others find it in L2.
+//   * tiles are dealt out from the device-side tile count, an equal contiguous run per XCD in patches of 4 x 8 tiles.
+// Slab m's schedule, P = the one barrier per slab (slab m + 1 landed, slab m in registers):
+//   step 0: W(m+1) second half | 1, 2: A(m+2) | P | 3: W(m+2) first half, first fragments of slab m + 1
+// Rows past a group's end re-read the tile's first row and store that row's result over itself, so that every
+// wavefront issues the same number of stores and the waits can count them.  Half of a tile's stores go out at once, the
+// rest behind the next two barriers: loads and stores retire in order, and 128 KiB per CU at one time keep the memory
+// busy for longer than the ring lasts.
+// An XCD's tiles rarely fill a whole number of rounds: its last, partial round is cut into 2, 4 or 8 pieces a tile, as
+// many as give every CU one (dma_tile), and pieces without a row of their group do nothing.
+struct StreamTile {
+  int group, row0, row_end, n0;
+};
+
+template <int EPI, bool WT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_stream_kernel(const GemmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint4 smem[];
+  constexpr int TM = 4, TN = 4, NI = 8;                       // NI: DMA instructions per wavefront and half slab
+  constexpr unsigned kSlotBytes = 256 * kDmaBK * 2;           // 32 KiB
+  constexpr int kPieces = EPI == kEpiSwiGLU ? TN : 2 * TN;    // 16-byte stores per lane and 32-row block
+
+  // ---- this workgroup's tiles
+  const int n_tiles = (a.N + 255) / 256;
+  int m_tiles = 0;
+  if (a.offsets == nullptr) {
+    m_tiles = static_cast<int>((a.M + 255) / 256);
+  } else {
+    for (int e = 0; e < a.n_groups; ++e) m_tiles += (a.offsets[e + 1] - a.offsets[e] + 255) / 256;
+  }
+  const int pn = patch_n_for(n_tiles), pm = kPatchTiles / pn;
+  const int xcd = blockIdx.x % 8, cu = blockIdx.x / 8, cus = gridDim.x / 8;
+  const int64_t total = static_cast<int64_t>(m_tiles) * n_tiles;
+  const int tile_lo = static_cast<int>(total * xcd / 8), tile_hi = static_cast<int>(total * (xcd + 1) / 8);
+  auto locate = [&](int t) __attribute__((always_inline)) {
+    StreamTile tl;
+    const int band = t / (pm * n_tiles);                      // pm tile rows (fewer in the last band) x all columns
+    const int rows = m_tiles - band * pm < pm ? m_tiles - band * pm : pm;
+    const int r = t - band * pm * n_tiles;
+    const int patch = r / (rows * pn), in = r - patch * (rows * pn);
+    int mt = band * pm + in % rows;
+    tl.n0 = (patch * pn + in / rows) * 256;
+    tl.group = 0;
+    tl.row0 = mt * 256;
+    tl.row_end = static_cast<int>(a.M);
+    if (a.offsets != nullptr) {
+      for (int e = 0; e < a.n_groups; ++e) {
+        const int lo = a.offsets[e], hi = a.offsets[e + 1], tiles = (hi - lo + 255) / 256;
+        if (mt < tiles) {
+          tl.group = e;
+          tl.row0 = lo + mt * 256;
+          tl.row_end = hi;
+          break;
+        }
+        mt -= tiles;
+      }
+    }
+    if (tl.row_end > tl.row0 + 256) tl.row_end = tl.row0 + 256;
+    return tl;
+  };
+  const int rounds = (tile_hi - tile_lo) / cus, rest = (tile_hi - tile_lo) % cus;
+  // pieces per tile of the last round: 1 (then it is a round like the others), 2, 4 or 8
+  const int cut = rest == 0 || rest * 2 > cus ? 1 : rest * 4 > cus ? 2 : rest * 8 > cus ? 4 : 8;
+  const int tile_end = cut == 1 ? tile_hi : tile_lo + rounds * cus;
+  int t = tile_lo + cu;
+  if (t < tile_end) {
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+  const int frag_row = lane & 31, frag_half = lane >> 5;
+  const int KT = a.K / kDmaBK;
+
+  // ---- DMA side.  Instruction j of a half slab fills 1 KiB block (4 j + wave + rotation) mod 32 of its slot: eight rows
+  // of 128 bytes (contraction-major W: two rows of 512)
+  const int rot_a = (cu / pm % pn) * (32 / pn), rot_w = (cu % pm) * (32 / pm);
+  const unsigned lds_base =
+      static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void *)smem));
+  unsigned a_lds[NI], w_lds[NI], a_voff[NI], w_voff[NI], a_next[NI];
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    const int ba = (4 * j + wave + rot_a) & 31, bw = (4 * j + wave + rot_w) & 31;
+    a_lds[j] = __builtin_amdgcn_readfirstlane(lds_base + ba * 1024);
+    w_lds[j] = __builtin_amdgcn_readfirstlane(lds_base + bw * 1024);
+  }
+  // tile row / weight row that this lane fetches with instruction j; the lane number passes through an empty asm so that
+  // the compiler forms these (once a tile) anew instead of keeping them in registers it would have to spill
+  auto here = [&]() __attribute__((always_inline)) {
+    int l = threadIdx.x & 63;
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  auto a_row = [&](int j, int l) __attribute__((always_inline)) { return ((4 * j + wave + rot_a) & 31) * 8 + (l >> 3); };
+  auto w_row = [&](int j, int l) __attribute__((always_inline)) {
+    const int b = (4 * j + wave + rot_w) & 31;
+    return WT ? b * 2 + (l >> 5) : b * 8 + (l >> 3);
+  };
+  const char *const a_base_g = static_cast<const char *>(a.A);
+  auto a_offset = [&](int j, int l, int64_t row) __attribute__((always_inline)) {
+    return static_cast<unsigned>((row * a.lda + ((l & 7) ^ ((a_row(j, l) >> 1) & 7)) * 8) * 2);
+  };
+  auto set_w = [&](const StreamTile &tl) __attribute__((always_inline)) {
+    const int l = here();
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      if constexpr (WT) {
+        w_voff[j] = static_cast<unsigned>((static_cast<int64_t>(w_row(j, l)) * a.N + ((l & 31) ^ (4 * (w_row(j, l) & 3))) * 8) * 2);
+      } else {
+        const int r = w_row(j, l) < a.N - tl.n0 ? w_row(j, l) : a.N - tl.n0 - 1;     // rows past N: never stored
+        w_voff[j] = static_cast<unsigned>((static_cast<int64_t>(r) * a.K + ((l & 7) ^ ((w_row(j, l) >> 1) & 7)) * 8) * 2);
+      }
+    }
+    const int64_t at = WT ? static_cast<int64_t>(tl.group) * a.N * a.K + tl.n0
+                          : (static_cast<int64_t>(tl.group) * a.N + tl.n0) * a.K;
+    return static_cast<const char *>(a.W) + at * 2;
+  };
+  const int64_t a_step = kDmaBK * 2, w_step = WT ? static_cast<int64_t>(kDmaBK) * a.N * 2 : kDmaBK * 2;
+  // an index load whose result may be used behind the next slab's barrier only (the waits there count every vector
+  // memory instruction, the compiler's own count would not know the DMA ones)
+  auto load_idx = [](const void *base, unsigned voff) __attribute__((always_inline)) {
+    int v;
+    asm volatile("global_load_dword %0, %1, %2" : "=v"(v) : "v"(voff), "s"(base) : "memory");
+    return v;
+  };
+
+  // ---- MFMA side
+  const int a_frag = (wm * 128 + frag_row) * kDmaRC, w_frag = (wn * 128 + frag_row) * kDmaRC;
+  const int swz = (frag_row >> 1) & 7;
+  unsigned wt_off[TN];
+  if constexpr (WT) {
+    const int i16 = lane & 15, grp = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int chunk = (wn * 16 + j * 4 + 2 * (grp & 1) + ((i16 >> 1) & 1)) ^ (4 * (i16 >> 2));
+      wt_off[j] = static_cast<unsigned>((8 * (grp >> 1) + (i16 >> 2)) * 512 + chunk * 16 + (i16 & 1) * 8);
+    }
+  }
+  f32x16_t acc[TM][TN];
+  bf16x8_t fa0[TM], fa1[TM], fb0[TN], fb1[TN];
+  auto read_a = [&](unsigned slot, int kk, int i) __attribute__((always_inline)) {
+    const uint4 v = smem[slot * (kSlotBytes / 16) + a_frag + i * 32 * kDmaRC + ((kk * 2 + frag_half) ^ swz)];
+    return *reinterpret_cast<const bf16x8_t *>(&v);
+  };
+  auto read_w = [&](unsigned slot, int kk, int j) __attribute__((always_inline)) {
+    if constexpr (WT) {
+      typedef short i16x4_t __attribute__((ext_vector_type(4)));
+      typedef short i16x8_t __attribute__((ext_vector_type(8)));
+      typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+      const __attribute__((address_space(3))) unsigned char *pb =
+          (const __attribute__((address_space(3))) unsigned char *)(smem + slot * (kSlotBytes / 16)) + kk * (16 * 512) + wt_off[j];
+      const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)pb);
+      const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(pb + 4 * 512));
+      return __builtin_bit_cast(bf16x8_t, (i16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    } else {
+      const uint4 v = smem[slot * (kSlotBytes / 16) + w_frag + j * 32 * kDmaRC + ((kk * 2 + frag_half) ^ swz)];
+      return *reinterpret_cast<const bf16x8_t *>(&v);
+    }
+  };
+  // one 16-wide step on (fa, fb); (na, nb) receive the fragments of step kn of the slab in slots (sa, sw); dma(q) runs
+  // behind MFMA q
+  auto step = [&](auto zero, const bf16x8_t(&fa)[TM], const bf16x8_t(&fb)[TN], bf16x8_t(&na)[TM], bf16x8_t(&nb)[TN],
+                  unsigned sa, unsigned sw, int kn, auto dma) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int q = i * TN + j;
+        if constexpr (decltype(zero)::value) {
+          f32x16_t z;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) z[v] = 0.0f;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], z, 0, 0, 0);
+        } else {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+        }
+        // in the order of first use by the next step
+        if (q == 0) na[0] = read_a(sa, kn, 0);
+        else if (q <= TN) nb[q - 1] = read_w(sw, kn, q - 1);
+        else if (q < TN + TM) na[q - TN] = read_a(sa, kn, q - TN);
+        dma(q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+  const auto mod5 = [](unsigned s) { return s >= 5 ? s - 5 : s; };
+  using True = std::true_type;
+  using False = std::false_type;
+  const char *a_ptr = a_base_g, *w_ptr;
+  auto dma_a = [&](unsigned slot, int j) __attribute__((always_inline)) { dma_load_16(a_lds[j] + slot * kSlotBytes, a_voff[j], a_ptr); };
+  auto dma_w = [&](unsigned slot, int j) __attribute__((always_inline)) { dma_load_16(w_lds[j] + slot * kSlotBytes, w_voff[j], w_ptr); };
+  const auto none = [](int) {};
+
+  // ---- fill the ring for the first tile: A(0) W(0) A(1) W(1) A(2)
+  StreamTile cur = locate(t);
+  w_ptr = set_w(cur);
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    const int l = here();
+    int p = cur.row0 + a_row(j, l);
+    if (p >= cur.row_end) p = cur.row0;
+    a_voff[j] = a_offset(j, l, a.a_rows ? a.a_rows[p] : p);
+  }
+#pragma unroll
+  for (unsigned h = 0; h < 5; ++h) {
+    if (h & 1) {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) dma_w(h, j);
+      w_ptr += w_step;
+    } else {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) dma_a(h, j);
+      a_ptr += a_step;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * NI) : "memory");
+  unsigned ra = 0;                                            // slot of A(m); W(m) and the next slabs follow it in the ring
+  fa0[0] = read_a(0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) fb0[j] = read_w(1, 0, j);
+#pragma unroll
+  for (int i = 1; i < TM; ++i) fa0[i] = read_a(0, 0, i);
+  bool strict = true;                                         // fewer stores than counted behind the outstanding DMA
+  u32x4_t held[TM / 2][kPieces];                              // the previous tile's last two row blocks
+  bf16_t *held_row[TM / 2];
+  int held_cols = 0;                                          // columns of those rows that exist, 0: nothing held
+  auto store_held = [&](int i) __attribute__((always_inline)) {
+    if (held_cols >= 128) {
+#pragma unroll
+      for (int pc = 0; pc < kPieces; ++pc) *reinterpret_cast<u32x4_t *>(held_row[i] + pc * 16) = held[i][pc];
+    } else if (held_cols > 0) {
+#pragma unroll
+      for (int pc = 0; pc < kPieces; ++pc)
+        if (pc * 16 + frag_half * 8 < held_cols) *reinterpret_cast<u32x4_t *>(held_row[i] + pc * 16) = held[i][pc];
+    }
+  };
+
+  // a slab of the steady state; at the tile's end the caller has pointed a_ptr / w_ptr at the next tile
+  auto slab_head = [&]() __attribute__((always_inline)) {
+    const unsigned rw = mod5(ra + 1), rw1 = mod5(ra + 3);
+    step(False{}, fa0, fb0, fa1, fb1, ra, rw, 1, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_w(rw1, 4 + q / 4); });
+    w_ptr += w_step;
+  };
+  auto slab_mid = [&]() __attribute__((always_inline)) {
+    const unsigned rw = mod5(ra + 1), ra2 = mod5(ra + 4);
+    step(False{}, fa1, fb1, fa0, fb0, ra, rw, 2, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_a(ra2, q / 4); });
+    step(False{}, fa0, fb0, fa1, fb1, ra, rw, 3, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_a(ra2, 4 + q / 4); });
+    a_ptr += a_step;
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NI) : "memory");
+  };
+  auto slab_tail = [&]() __attribute__((always_inline)) {
+    const unsigned r0 = ra;
+    ra = mod5(ra + 2);
+    step(False{}, fa1, fb1, fa0, fb0, ra, mod5(ra + 1), 0, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_w(r0, q / 4); });
+  };
+
+  for (;;) {
+    const bool last = t + cus >= tile_end;
+    const StreamTile nxt = last ? cur : locate(t + cus);      // after the last tile: its own first slabs again, unused
+    // slab 0: its W(1) and A(2) were requested before the previous tile's stores
+    {
+      const unsigned rw = mod5(ra + 1);
+      step(True{}, fa0, fb0, fa1, fb1, ra, rw, 1, none);
+      step(False{}, fa1, fb1, fa0, fb0, ra, rw, 2, none);
+      step(False{}, fa0, fb0, fa1, fb1, ra, rw, 3, none);
+      if (strict) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI + TM / 2 * kPieces) : "memory");
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      store_held(0);
+      slab_tail();
+    }
+    // slab 1: with the row numbers of the next tile's A and of this tile's C
+    int idx_a[NI], idx_c[TM];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      int p = nxt.row0 + a_row(j, here());
+      if (p >= nxt.row_end) p = nxt.row0;
+      a_next[j] = static_cast<unsigned>(p);
+      idx_a[j] = load_idx(a.a_rows ? static_cast<const void *>(a.a_rows) : a.A, a.a_rows ? static_cast<unsigned>(p) * 4u : 0u);
+    }
+    int c_pos[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      int p = cur.row0 + wm * 128 + i * 32 + (here() & 31);
+      if (p >= cur.row_end) p = cur.row0;
+      c_pos[i] = p;
+      idx_c[i] = load_idx(a.c_rows ? static_cast<const void *>(a.c_rows) : a.A, a.c_rows ? static_cast<unsigned>(p) * 4u : 0u);
+    }
+    slab_head();
+    slab_mid();
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      asm volatile("" : "+v"(idx_a[j]));
+      a_next[j] = a_offset(j, here(), a.a_rows ? idx_a[j] : static_cast<int>(a_next[j]));
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      asm volatile("" : "+v"(idx_c[i]));
+      if (a.c_rows) c_pos[i] = idx_c[i];
+    }
+    store_held(1);
+    slab_tail();
+    // slab 2: with the row scales
+    float scale[TM];
+    if constexpr (EPI == kEpiPlain) {
+      slab_head();
+      slab_mid();
+    } else {
+      int sc[TM];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        sc[i] = load_idx(a.row_scale ? static_cast<const void *>(a.row_scale) : a.A, a.row_scale ? static_cast<unsigned>(c_pos[i]) * 4u : 0u);
+      slab_head();
+      slab_mid();
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        asm volatile("" : "+v"(sc[i]));
+        scale[i] = a.row_scale ? __int_as_float(sc[i]) : 1.0f;
+      }
+    }
+    slab_tail();
+    for (int m = 3; m < KT - 2; ++m) {
+      slab_head();
+      slab_mid();
+      slab_tail();
+    }
+    // slab KT - 2: A and W of the next tile from here on
+    slab_head();
+    a_ptr = a_base_g;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) a_voff[j] = a_next[j];
+    slab_mid();
+    w_ptr = set_w(nxt);
+    slab_tail();
+    // slab KT - 1: everything that slab 0 of the next tile would request goes before the stores
+    slab_head();
+    slab_mid();
+    {
+      const unsigned r0 = ra, r1 = mod5(ra + 1);
+      ra = mod5(ra + 2);
+      step(False{}, fa1, fb1, fa0, fb0, ra, mod5(ra + 1), 0, [&](int q) __attribute__((always_inline)) {
+        if (q < 8) dma_w(r0, q); else dma_a(r1, q - 8);
+      });
+      w_ptr += w_step;
+      a_ptr += a_step;
+    }
+
+    // ---- epilogue: a lane holds, for row frag_row of each 32-row block, columns 8 q + 4 frag_half + (0..3) of each
+    // 32-column block in elements 4 q ..; lanes l and l + 32 trade halves so that each has 8 neighbouring columns
+    // (held_cols counts output columns from this wavefront's first; kFull says that all of them exist)
+    constexpr int kWaveCols = EPI == kEpiSwiGLU ? 64 : 128;
+    const int col0 = (EPI == kEpiSwiGLU ? cur.n0 / 2 : cur.n0) + wn * kWaveCols;
+    const int n_cols = (EPI == kEpiSwiGLU ? a.N / 2 : a.N) - col0;
+    auto finish = [&](auto all) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int64_t at = static_cast<int64_t>(c_pos[i]) * a.ldc + col0 + frag_half * 8;
+        bf16_t *crow = static_cast<bf16_t *>(a.C) + at;
+        u32x4_t res[EPI == kEpiRowScaleResidual ? kPieces : 1];
+        if constexpr (EPI == kEpiRowScaleResidual) {
+#pragma unroll
+          for (int pc = 0; pc < kPieces; ++pc) {
+            res[pc] = u32x4_t{0u, 0u, 0u, 0u};
+            if (decltype(all)::value || pc * 16 + frag_half * 8 < n_cols)
+              res[pc] = *reinterpret_cast<const u32x4_t *>(static_cast<const bf16_t *>(a.residual) + at + pc * 16);
+          }
+        }
+#pragma unroll
+        for (int pc = 0; pc < kPieces; ++pc) {
+          unsigned x0, x1, y0, y1;
+          if constexpr (EPI == kEpiSwiGLU) {
+            float o[2][4];
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                o[m][r] = silu_f32(acc[i][pc][8 * m + r] * scale[i]) * (acc[i][pc][8 * m + 4 + r] * scale[i]);
+            x0 = pack_bf16x2(o[0][0], o[0][1]); x1 = pack_bf16x2(o[0][2], o[0][3]);
+            y0 = pack_bf16x2(o[1][0], o[1][1]); y1 = pack_bf16x2(o[1][2], o[1][3]);
+          } else {
+            const int j = pc / 2, q = (pc % 2) * 8;
+            float v[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] = EPI == kEpiPlain ? acc[i][j][q + r] : acc[i][j][q + r] * scale[i];
+            x0 = pack_bf16x2(v[0], v[1]); x1 = pack_bf16x2(v[2], v[3]);
+            y0 = pack_bf16x2(v[4], v[5]); y1 = pack_bf16x2(v[6], v[7]);
+          }
+          const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+          u32x4_t o = {s0[0], s1[0], s0[1], s1[1]};
+          if constexpr (EPI == kEpiRowScaleResidual) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+              o[w] = pack_bf16x2(__uint_as_float(o[w] << 16) + __uint_as_float(res[pc][w] << 16),
+                                 __uint_as_float(o[w] & 0xFFFF0000u) + __uint_as_float(res[pc][w] & 0xFFFF0000u));
+          }
+          if (i >= TM / 2) held[i - TM / 2][pc] = o;
+          else if (decltype(all)::value || pc * 16 + frag_half * 8 < n_cols) *reinterpret_cast<u32x4_t *>(crow + pc * 16) = o;
+          __builtin_amdgcn_sched_barrier(0);                  // (registers: one piece at a time)
+        }
+        if (i >= TM / 2) held_row[i - TM / 2] = crow;
+      }
+    };
+    const bool full = n_cols >= kWaveCols;
+    if (full) finish(True{});
+    else finish(False{});
+    held_cols = full ? 128 : n_cols;                          // (a partial wavefront may hold no column at all)
+    if (last) break;
+    strict = !full;
+    cur = nxt;
+    t += cus;
+  }
+  store_held(0);
+  store_held(1);
+  }
+
+  // ---- the last, partial round in pieces
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the ring's last requests have landed
+  if (cut == 1 || cu >= rest * cut) return;
+  const StreamTile tl = locate(tile_end + cu / cut);
+  TileCoord tc;
+  const int piece = cu % cut;
+  // rows x columns of a piece: 128 x 256, 128 x 128, 64 x 128 (a contraction-major weight comes in whole 256-column
+  // slabs: 64 x 256, 32 x 256); fewest lines of both operands per product
+  const int col_cuts = WT || cut == 2 ? 1 : 2, rows = 256 * col_cuts / cut;
+  tc.group = tl.group;
+  tc.n0 = tl.n0 + piece % col_cuts * 128;
+  tc.row0 = tl.row0 + piece / col_cuts * rows;
+  tc.row_end = tl.row_end < tc.row0 + rows ? tl.row_end : tc.row0 + rows;
+  tc.valid = true;
+  if (tc.row0 >= tc.row_end || tc.n0 >= a.N) return;
+  if (cut == 2) {
+    dma_tile<256, 1, 4, EPI, WT, 128>(a, tc, smem);
+  } else if constexpr (WT) {
+    if (cut == 4) dma_tile<256, 1, 4, EPI, WT, 64>(a, tc, smem);
+    else dma_tile<256, 1, 4, EPI, WT, 32>(a, tc, smem);
+  } else {
+    if (cut == 4) dma_tile<128, 2, 2, EPI, WT, 128>(a, tc, smem);
+    else dma_tile<128, 2, 2, EPI, WT, 64>(a, tc, smem);
+  }
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, short inner dimension
@@ -979,27 +1427,45 @@ hipError_t launch_dma(const GemmArgs &a, hipStream_t s) {
                      dim3(WM * WN * 64), kSmem, s, a);
   return hipGetLastError();
 }
+constexpr int kStreamWgs = 256;      // one workgroup per CU
+template <int EPI, bool WT = false>
+hipError_t launch_stream(const GemmArgs &a, hipStream_t s) {
+  constexpr int kSmem = kDmaSlots * 256 * kDmaRC * 16;     // 160 KiB
+  static LdsAttrOnce attr;
+  const hipError_t e = attr.ensure(reinterpret_cast<const void *>(&gemm_bf16_stream_kernel<EPI, WT>), kSmem);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((gemm_bf16_stream_kernel<EPI, WT>), dim3(kStreamWgs), dim3(256), kSmem, s, a);
+  return hipGetLastError();
+}
 // the DMA kernel addresses both operands with unsigned 32-bit byte offsets and walks whole 64-wide slabs
 inline bool dma_ok(const GemmArgs &a) {
   return kUseDma && a.K % kDmaBK == 0 && a.k_per_split % kDmaBK == 0 && a.lda >= a.K &&
          a.a_span < (1ll << 31) && static_cast<int64_t>(a.N) * a.K < (1ll << 31);
 }
 
+// Which calls take the stream kernel.  It needs five slabs at least, 32-bit positions, and a residual that is not the
+// output itself (rows past a group's end are stored again).  Eight slabs make its start and end worth while
+// (9000 x 1024 x 320 loses 11 %, 16384 x 2048 x 512 gains 3 %).  Below 384 rows a group most of a 256-row tile would be
+// padding: it then takes the call only where 192 tiles and 192 Ki tile-columns of work keep the CUs busy
+// (1024 x 8192 x 2048 in 8 groups: 107 -> 89 us, but 1024 x 2048 x 4096: 56 -> 66, 2048 x 3072 x 768: 29 -> 31 us).
+inline bool stream_takes(const GemmArgs &a) {
+  if (!dma_ok(a) || a.k_splits != 1 || a.K < 512 || a.N < 256 || a.M >= (1ll << 30) || a.residual == a.C) return false;
+  const int groups = a.n_groups > 0 ? a.n_groups : 1;
+  if (a.M / groups >= 384) return true;
+  const int64_t tiles = (a.M / 256 + groups) * ceil_div(a.N, 256);
+  return a.M / groups >= 96 && tiles >= 192 && tiles * a.K >= (192 << 10);
+}
+
 template <int EPI>
 hipError_t launch_mfma_tiles(const GemmArgs &a, hipStream_t s) {
   const int64_t rows_per_group = a.M / (a.n_groups > 0 ? a.n_groups : 1);
+  if constexpr (EPI != kEpiPlainF32 && EPI != kEpiBiasSoftplus) {
+    if (stream_takes(a)) return launch_stream<EPI>(a, s);
+  } else {
+    if (rows_per_group >= 1024 && a.N >= 256 && a.K > 256) return launch_mfma<256, 256, 4, 2, EPI>(a, s);
+  }
   // a short inner dimension makes the launch epilogue-bound: smaller tiles put several
   // workgroups on a CU so that loads, MFMAs and stores of different tiles overlap
-  if (rows_per_group >= 1024 && a.N >= 256 && a.K > 256) {
-    // Between one and one and a half rounds of 256 x 256 tiles on the 256 CUs the second round runs
-    // nearly empty: 128 x 128 tiles (several workgroups per CU) finish sooner.  16384 x 1024 x 2048
-    // out projection, 288 big tiles: 0.106 -> 0.096 ms.  (From two rounds on the big tile wins again:
-    // 544 tiles of the 16384 x 2048 x 4096 out projection 0.310 against 0.324 ms.)
-    const int64_t tiles256 = (a.M / 256 + (a.n_groups > 0 ? a.n_groups : 1)) * ceil_div(a.N, 256);
-    if (tiles256 > 256 && tiles256 < 384 && a.k_splits == 1) return launch_mfma<128, 128, 2, 2, EPI>(a, s);
-    if (dma_ok(a) && a.k_splits == 1) return launch_dma<256, kBigWM, kBigWN, EPI>(a, s);
-    return launch_mfma<256, 256, 4, 2, EPI>(a, s);
-  }
   if (rows_per_group >= 96) return launch_mfma<128, 128, 2, 2, EPI>(a, s);
   // One row tile per group at most (the recurrent step): every weight tile is read by exactly one
   // workgroup, so there is no L2 sharing for the XCD runs to protect, while a run of logical tiles
@@ -1018,15 +1484,14 @@ hipError_t launch_mfma_tiles(const GemmArgs &a, hipStream_t s) {
 
 }  // namespace
 
-// whether a call with a contraction-major weight (GemmArgs::w_kmajor) is taken: the 256 x 256 DMA tile with a
+// whether a call with a contraction-major weight (GemmArgs::w_kmajor) is taken: the stream kernel with a
 // plain epilogue only; the caller otherwise makes a transposed copy of the weight
 bool grouped_gemm_takes_kmajor(const GemmArgs &args) {
   GemmArgs a = args;
   a.k_splits = 1;
   a.k_per_split = static_cast<int>(ceil_div(a.K, 64) * 64);
-  const int64_t rows_per_group = a.M / (a.n_groups > 0 ? a.n_groups : 1);
   return grouped_gemm_on_mfma(a) && !a.c_is_f32 && !a.bias && !a.row_scale && !a.residual && !a.swiglu &&
-         rows_per_group >= 1024 && a.N % 256 == 0 && a.K > 256 && dma_ok(a);
+         a.N % 256 == 0 && stream_takes(a);
 }
 
 // whether the call takes the MFMA kernels (else the plain FMA kernel, which has no fused SwiGLU)
@@ -1052,7 +1517,7 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
   const bool mfma_ok = grouped_gemm_on_mfma(a);
   if (a.w_kmajor) {                                           // the caller asks grouped_gemm_takes_kmajor first
     if (!grouped_gemm_takes_kmajor(args)) return hipErrorInvalidValue;
-    return launch_dma<256, kBigWM, kBigWN, kEpiPlain, true>(a, s);
+    return launch_stream<kEpiPlain, true>(a, s);
   }
   if (a.swiglu && !mfma_ok) return hipErrorInvalidValue;      // the caller asks grouped_gemm_on_mfma first
   if (a.swiglu) return launch_mfma_tiles<kEpiSwiGLU>(a, s);
