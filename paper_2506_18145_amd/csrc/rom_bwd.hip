@@ -6,6 +6,7 @@
 // Correct-first: plain ALU kernels, deterministic (fixed summation orders, no atomics).
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 #include "rom_internal.h"
 
 namespace rom {
@@ -15,16 +16,6 @@ namespace {
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-// sum of v over the 16 lanes of a DPP row, in every lane (fixed order)
-__device__ __forceinline__ float row_sum16(float v) {
-#pragma clang fp contract(off)
-  v = dpp<0x140>(v) + v;      // row_mirror
-  v = dpp<0x141>(v) + v;      // row_half_mirror
-  v = dpp<0x1B>(v) + v;       // quad_perm [3,2,1,0]
-  v = dpp<0xB1>(v) + v;       // quad_perm [1,0,3,2]
-  return v;
-}
-
 // Sixteen values per lane, each to be summed over the 16 lanes of a row: a butterfly that halves
 // the number of live values at every stage (the lanes with bit 3 / 2 / 1 / 0 of n set keep the upper
 // half) leaves the row total of p[n] in lane n - 30 DPP adds and 15 selects instead of 64 adds.
@@ -54,30 +45,6 @@ __device__ __forceinline__ float transpose_sum16(const float *p, int n) {
   const float hi = dpp<0xB1>(c[1]) + c[1];
   return hi1 ? hi : lo;
 }
-// the same for eight values: lane n ends up with the row total of p[n & 7]
-__device__ __forceinline__ float transpose_sum8(const float *p, int n) {
-#pragma clang fp contract(off)
-  float a[8], b[4], c[2];
-  const bool hi4 = (n & 4) != 0, hi2 = (n & 2) != 0, hi1 = (n & 1) != 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) a[j] = dpp<0x140>(p[j]) + p[j];       // pairs (i, 15 - i): both halves of the row alike
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float lo = dpp<0x141>(a[j]) + a[j];
-    const float hi = dpp<0x141>(a[j + 4]) + a[j + 4];
-    b[j] = hi4 ? hi : lo;
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const float lo = dpp<0x1B>(b[j]) + b[j];
-    const float hi = dpp<0x1B>(b[j + 2]) + b[j + 2];
-    c[j] = hi2 ? hi : lo;
-  }
-  const float lo = dpp<0xB1>(c[0]) + c[0];
-  const float hi = dpp<0xB1>(c[1]) + c[1];
-  return hi1 ? hi : lo;
-}
-
 __device__ __forceinline__ float sigmoid_f32(float v) { return fast_rcp(1.0f + fast_exp2(-1.44269504088896341f * v)); }
 
 inline dim3 grid1d(int64_t work, int block) { return dim3(static_cast<unsigned>(ceil_div(work, block))); }
@@ -89,93 +56,55 @@ inline dim3 grid1d(int64_t work, int block) { return dim3(static_cast<unsigned>(
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // ------------------------------------------------------------------ adjoint of the selective scan
-// Same lane = (channel, state) layout as the forward kernel.  A 256-thread block is one unit of work:
-// 16 channels of one sequence over one chunk of its steps; the grid is (channel blocks, sequences x
-// chunks).  A lone wavefront per SIMD issues an instruction every five clocks at best and hides no
-// LDS latency, so the launcher cuts the sequences into enough chunks for two blocks per CU.  Per unit:
-//   prologue: the state at the chunk's start and the adjoint state flowing in at its end, from the
-//           per-chunk carries (decay product P, end state Q from a zero start, start adjoint R from a
-//           zero end) that scan_bwd_carry_kernel left, combined in chunk order;
-//   pass 1 (forward in time): the state recurrence alone, leaving the state at the start of every
-//           16-step group in the checkpoint buffer;
-//   pass 2 (backward in time, 64-step tiles of four groups): a group's states are recomputed from
-//           its checkpoint into registers, then the adjoint recurrence d_h[t-1] = exp(dt_t a) d_h[t]
-//           walks the group backwards.  The group body is unrolled, the loop over groups is not
-//           (unrolled over a whole tile the body spills registers).
-// Sums over the 16 states of a channel (d_dt, d_u, y) are DPP row sums; sums over the block's 16
-// channels (d_B, d_C) go through LDS in channel order; the sum of those over the channel groups of
-// the whole layer is left to bwd_reduce_bc_kernel (per-block partial rows in global memory); the
-// parameter gradients of a unit go to per-unit partials that scan_bwd_finish_kernel sums in unit order.
-constexpr int kBwdTile = 64, kBwdCh = 16, kBwdPitch = kBwdCh + 1, kBwdGroup = 16, kBwdHalf = 8;
-constexpr int kGroupsPerTile = kBwdTile / kBwdGroup;
+// Sequences are cut into chunks of 128 steps, so that the chip is full whatever the batch.  Three kernels:
+//   scan_bwd_carry_kernel: a lane owns a channel with its 16 states (B and C through the scalar cache, as in the
+//           forward's lane = channel scan) and walks one chunk forwards once, leaving its end state Q from a zero start,
+//           the adjoint state R that leaves its start from a zero adjoint at its end (sum over t of the decay from the
+//           start to t times C_t d y_t), and its sum of dt;
+//   scan_bwd_fold_kernel: every chunk's start state and incoming adjoint state from those, in chunk order;
+//   scan_bwd_kernel: the chunk itself.  A wavefront owns 16 channels; lane (q, c) = (lane / 16, lane % 16) holds states
+//           4 q .. 4 q + 3 of channel c.  Pass 1 (forward in time) leaves the state at the start of every group of 16
+//           steps in LDS; pass 2 (backward, group by group) recomputes the group's states into registers and walks the
+//           adjoint recurrence d_h[t-1] = exp(dt_t a) d_h[t] back over it.
+// With four states a lane, three quarters of the sums over a channel's states need no other lane; the rest (y, the
+// input term, d dt: four rows of lanes) are three swap-and-add per four steps that leave step 4 i + q with row q, whose
+// lanes own that step's loads, activation derivatives and stores.  The sums over channels (d B, d C) go over the 16
+// lanes of a row by a transposing butterfly, over the block's four wavefronts through LDS (the only barrier, one per
+// group), over the channel blocks in bwd_reduce_bc_kernel; parameter gradients go to per-unit partials that
+// scan_bwd_finish_kernel sums in unit order.  All sums in fixed order, no atomics.
+// Bound by ALU issue: about 120 vector instructions, 9 of them exponentials, per step of 256 (channel, state) pairs, the
+// pipe busy nine tenths of the time.  16384 x 4096: carries 0.29, fold 0.04, main 1.05, block sums 0.05 ms (a lane per
+// (channel, state) pair with row sums over the states and channel sums through LDS: 2.43 ms).
+constexpr int kBwdChunk = 128, kBwdGroup = 16, kBwdCh = 64, kBwdHalf = 8, kBwdGroups = kBwdChunk / kBwdGroup;
+constexpr int kBwdStPitch = kBwdGroup + 4;   // floats per channel row: 16 rows of four-step reads or writes cover the banks
 
 // Scratch of the adjoint scan, all f32.  Units are numbered (sequence * n_chunks + chunk) * n_cb + channel block.
 struct ScanBwdLayout {
-  int n_cb, n_chunks, n_fine;  // channel blocks; chunks of the main kernel and of the carry kernel per sequence
-  int64_t chunk_len, fine_len; // steps per chunk, multiples of the tile; chunk_len is a multiple of fine_len
+  int n_cb, n_chunks;          // channel blocks; chunks per sequence
   int64_t n_units;
-  size_t ckpt, carry_p, carry_q, carry_r, part_a, part_d, part_bias, total;   // offsets in floats
+  size_t carry_q, carry_r, carry_s, part_a, part_d, part_bias, total;   // offsets in floats
 };
 inline ScanBwdLayout scan_bwd_layout(int64_t B, int64_t L, int d_inner) {
   ScanBwdLayout l;
-  l.n_cb = d_inner / kBwdCh;
-  const int64_t tiles = ceil_div(L, kBwdTile);
-  int64_t nc = ceil_div(512, static_cast<int64_t>(l.n_cb) * B);       // two blocks for each of the 256 CUs
-  const int64_t max_nc = tiles / 8 > 0 ? tiles / 8 : 1;                 // a chunk is at least 512 steps
-  nc = nc < 1 ? 1 : (nc > max_nc ? max_nc : nc);
-  int64_t tiles_per_chunk = ceil_div(tiles, nc);
-  // the carry kernel is light and latency-bound: it gets chunks of at most 16 tiles, so that many
-  // more of its (small) blocks are resident; the main kernel folds the fine carries
-  const int64_t tiles_per_fine = tiles_per_chunk >= 16 ? 16 : tiles_per_chunk;
-  tiles_per_chunk = ceil_div(tiles_per_chunk, tiles_per_fine) * tiles_per_fine;
-  l.n_chunks = static_cast<int>(ceil_div(tiles, tiles_per_chunk));
-  l.n_fine = static_cast<int>(ceil_div(tiles, tiles_per_fine));
-  l.chunk_len = tiles_per_chunk * kBwdTile;
-  l.fine_len = tiles_per_fine * kBwdTile;
+  l.n_cb = static_cast<int>(ceil_div(d_inner, kBwdCh));
+  l.n_chunks = static_cast<int>(ceil_div(L, kBwdChunk));
   l.n_units = B * l.n_chunks * l.n_cb;
-  const size_t n_fine_units = static_cast<size_t>(B) * l.n_fine * l.n_cb;
   size_t off = 0;
   auto take = [&](size_t n) { size_t o = off; off += (n + 63) / 64 * 64; return o; };
-  l.ckpt = take(static_cast<size_t>(l.n_units) * tiles_per_chunk * kGroupsPerTile * 256);
-  l.carry_p = take(n_fine_units * 256);
-  l.carry_q = take(n_fine_units * 256);
-  l.carry_r = take(n_fine_units * 256);
-  l.part_a = take(static_cast<size_t>(l.n_units) * 256);
+  const size_t carries = l.n_chunks > 1 ? static_cast<size_t>(B) * l.n_chunks * d_inner : 0;
+  l.carry_q = take(carries * 16);
+  l.carry_r = take(carries * 16);
+  l.carry_s = take(carries);
+  l.part_a = take(static_cast<size_t>(l.n_units) * kBwdCh * 16);
   l.part_d = take(static_cast<size_t>(l.n_units) * kBwdCh);
   l.part_bias = take(static_cast<size_t>(l.n_units) * kBwdCh);
   l.total = off;
   return l;
 }
 
-struct BwdSmem {
-  // per (step, channel), prepared once when the tile is loaded: dt, u, d y = gate * dg * SiLU(z) and
-  // the factor gate * dg * SiLU'(z) of d z
-  float dt[kBwdTile][kBwdPitch], u[kBwdTile][kBwdPitch], dy[kBwdTile][kBwdPitch], dzf[kBwdTile][kBwdPitch];
-  float bc[kBwdTile][33];                    // B_0..15, C_0..15 of every step
-  float o_pre[kBwdTile][kBwdPitch], o_u[kBwdTile][kBwdPitch], o_z[kBwdTile][kBwdPitch];   // outputs of the tile
-  float o_bc[kBwdTile][33];                  // this block's share of d_B, d_C of the tile
-  // [step in half group][channel][state] terms of d_B, d_C.  The channel sums read both arrays with
-  // one instruction (32 lanes per step: 16 states of each); the pad puts part_c half the banks away
-  // from part_b, so that the 64 lanes of a wave (two steps) touch 64 different banks.
-  float part_b[kBwdHalf][kBwdCh][17];
-  float bank_pad[32];
-  float part_c[kBwdHalf][kBwdCh][17];
-};
-
-// What the carry kernel needs of a tile: a third of the LDS, so that seven of its blocks fit a CU
-struct BwdCarrySmem {
-  float dt[kBwdTile][kBwdPitch], u[kBwdTile][kBwdPitch], dy[kBwdTile][kBwdPitch];     // (u: dt * u)
-  float bc[kBwdTile][33];
-};
-
-// A tile travels from global memory to LDS in two steps, so that the loads of the next tile are in
-// flight while this one is worked on: bwd_fetch_tile (global -> registers), bwd_park_tile (registers -> LDS).
-struct BwdTileRegs {
-  float dt[4], u[4], z[4], dg[4], bc[8];
-};
-
 typedef unsigned int bwd_u32x2 __attribute__((ext_vector_type(2)));
 typedef float bwd_f32x4 __attribute__((ext_vector_type(4)));
+typedef float bwd_f32x16 __attribute__((ext_vector_type(16)));
 // four consecutive elements as floats, one 8-byte (bf16) or 16-byte (f32) load
 __device__ __forceinline__ void bwd_load4(const bf16_t *p, float *f) {
   const bwd_u32x2 w = *reinterpret_cast<const bwd_u32x2 *>(p);
@@ -199,351 +128,442 @@ __device__ __forceinline__ void bwd_store4(float *p, const float *f) {
   *reinterpret_cast<bwd_f32x4 *>(p) = w;
 }
 
-// thread -> (step row = tid / 4, channels 4 (tid % 4) .. + 3) of every [64][16] tensor and the
-// eight B/C values 8 (tid % 4) .. + 7 of that step
-template <typename T>
-__device__ __forceinline__ void bwd_fetch_tile(BwdTileRegs &r, const T *u_b, const T *dt_b, const T *z_b, int64_t ld_z,
-                                               const T *dg_b, const float *bc_b, const float *gate_b, int64_t t0,
-                                               int64_t t_end, int d_inner, int tid, bool full) {
-  const int row = tid >> 2, c = (tid & 3) * 4;
-  const int64_t t = t0 + row;
-  if (t < t_end) {
-    bwd_load4(dt_b + t * d_inner + c, r.dt);
-    bwd_load4(u_b + t * d_inner + c, r.u);
-    if (full) {
-      bwd_load4(z_b + t * ld_z + c, r.z);
-      bwd_load4(dg_b + t * d_inner + c, r.dg);
-      const float gw = gate_b ? gate_b[t] : 1.0f;                    // gate weight of Eq. (12)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r.dg[q] *= gw;
-    }
-    bwd_load4(bc_b + t * 32 + (tid & 3) * 8, r.bc);
-    bwd_load4(bc_b + t * 32 + (tid & 3) * 8 + 4, r.bc + 4);
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) r.dt[q] = r.u[q] = r.z[q] = r.dg[q] = 0.0f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) r.bc[q] = 0.0f;
-  }
-}
-
-// kWithDz: the full set of factors the main kernel's second pass needs; without it (the carry kernel)
-// the u slot holds dt * u, the only form that kernel uses u in
-template <typename Smem, bool kWithDz>
-__device__ __forceinline__ void bwd_park_tile(Smem &sm, const BwdTileRegs &r, int tid, bool full) {
-  const int row = tid >> 2, c = (tid & 3) * 4;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    sm.dt[row][c + q] = r.dt[q];
-    sm.u[row][c + q] = kWithDz ? r.u[q] : r.dt[q] * r.u[q];
-    if (full) {
-      const float zs = r.z[q], dgs = r.dg[q];
-      const float sig = sigmoid_f32(zs);
-      sm.dy[row][c + q] = dgs * zs * sig;                             // g = y * SiLU(z)
-      if constexpr (kWithDz) sm.dzf[row][c + q] = dgs * sig * (1.0f + zs * (1.0f - sig));
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) sm.bc[row][(tid & 3) * 8 + q] = r.bc[q];
-}
-
-// Carries of one fine chunk (only launched when the sequences are cut into chunks): grid (n_cb, B * n_fine).
-//   P = prod_t exp(dt_t a)                       decay over the chunk
-//   Q = state at the chunk's end from a zero state at its start
-//   R = adjoint state leaving the chunk's start from a zero adjoint state at its end
+// grid.x: (sequence * n_chunks + chunk) * gx + block of 256 channels.  carry_q, carry_r: f32 [B][n_chunks][16][d_inner],
+// carry_s [B][n_chunks][d_inner]
 template <typename T>
 __global__ __launch_bounds__(256) void scan_bwd_carry_kernel(
     const T *__restrict__ u, const T *__restrict__ dt, const float *__restrict__ bc, const T *__restrict__ z,
     int64_t ld_z, const T *__restrict__ dg, const float *__restrict__ gate, const float *__restrict__ A_log, int64_t L,
-    int d_inner, int n_chunks, int64_t chunk_len, int fine_per_main, int n_main, float *__restrict__ carry_p,
-    float *__restrict__ carry_q, float *__restrict__ carry_r) {
-  __shared__ BwdCarrySmem sm;
-  const int tid = threadIdx.x;
-  const int n = tid & 15, cl = tid >> 4;
-  const int c0 = blockIdx.x * kBwdCh, ch = c0 + cl;
-  const int64_t b = blockIdx.y / n_chunks, k = blockIdx.y % n_chunks;
-  const int64_t ts = k * chunk_len, te = ts + chunk_len < L ? ts + chunk_len : L;
-  const int64_t n_tiles = (te - ts + kBwdTile - 1) / kBwdTile;
-  const float a2 = -__expf(A_log[static_cast<int64_t>(ch) * 16 + n]) * 1.44269504088896341f;
-  const T *u_b = u + b * L * d_inner + c0;
-  const T *dt_b = dt + b * L * d_inner + c0;
-  const T *z_b = z + b * L * ld_z + c0;
-  const T *dg_b = dg + b * L * d_inner + c0;
-  const float *bc_b = bc + b * L * 32;
-  const float *gate_b = gate ? gate + b * L : nullptr;
+    int d_inner, int gx, int n_chunks, float *__restrict__ carry_q, float *__restrict__ carry_r,
+    float *__restrict__ carry_s) {
+  typedef const __attribute__((address_space(4))) bwd_f32x16 const_f32x16_t;
+  typedef const __attribute__((address_space(4))) float const_f32_t;
+  typedef __attribute__((address_space(1))) char global_char_t;
+  typedef __attribute__((address_space(1))) T global_t;
+  const int lane = threadIdx.x & 63;
+  const int64_t bk = blockIdx.x / gx;                          // sequence * n_chunks + chunk
+  const int ch0 = (blockIdx.x % gx * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 64;
+  if (ch0 >= d_inner) return;
+  const int cl = ch0 + lane < d_inner ? lane : d_inner - 1 - ch0;      // idle lanes repeat the last channel, stores included
+  const int ch = ch0 + cl;
+  const int64_t b = bk / n_chunks, ts = bk % n_chunks * kBwdChunk, row0 = b * L + ts;
+  const int len = static_cast<int>(L - ts < kBwdChunk ? L - ts : kBwdChunk);
 
-  // The main kernel folds end states of the fine chunks that lie before its own chunk and start
-  // adjoints of those that lie after it: a fine chunk of the last main chunk needs no end state, one of
-  // the first main chunk no start adjoint (with two main chunks every block runs one pass, not two).
-  // The decay product is needed either way and comes from whichever pass runs.
-  const int64_t main_idx = k / fine_per_main;
-  const bool need_fwd = main_idx + 1 < n_main, need_bwd = main_idx >= 1;
-  BwdTileRegs regs;
-  float h = 0.0f, sum_dt = 0.0f;
-  if (need_fwd) {
-    bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts, te, d_inner, tid, false);
-    for (int64_t ti = 0; ti < n_tiles; ++ti) {
-      lds_barrier();
-      bwd_park_tile<BwdCarrySmem, false>(sm, regs, tid, false);
-      lds_barrier();
-      if (ti + 1 < n_tiles)
-        bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts + (ti + 1) * kBwdTile, te, d_inner, tid, false);
-      else
-        bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts + ti * kBwdTile, te, d_inner, tid, true);
-#pragma unroll 16
-      for (int s2 = 0; s2 < kBwdTile; ++s2) {
-        const float dts = sm.dt[s2][cl];
-        sum_dt += dts;
-        h = fmaf(fast_exp2(dts * a2), h, sm.u[s2][cl] * sm.bc[s2][n]);      // (u slot: dt * u)
-      }
-    }
-  } else {
-    bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts + (n_tiles - 1) * kBwdTile, te, d_inner, tid, true);
+  float a2[16], h[16], e[16], r[16], sum = 0.0f;
+#pragma unroll
+  for (int n = 0; n < 16; n += 4) bwd_load4(A_log + static_cast<int64_t>(ch) * 16 + n, a2 + n);
+#pragma unroll
+  for (int n = 0; n < 16; ++n) {
+    a2[n] = -__expf(a2[n]) * 1.44269504088896341f;
+    h[n] = r[n] = 0.0f;
+    e[n] = 1.0f;
   }
-  float gq = 0.0f;
-  if (need_bwd || !need_fwd) {                  // (a lone main chunk never launches this kernel; kept total)
-    for (int64_t ti = n_tiles - 1; ti >= 0; --ti) {
-      lds_barrier();
-      bwd_park_tile<BwdCarrySmem, false>(sm, regs, tid, true);
-      lds_barrier();
-      if (ti > 0)
-        bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts + (ti - 1) * kBwdTile, te, d_inner, tid, true);
-      if (need_fwd) {
-#pragma unroll 16
-        for (int s2 = kBwdTile - 1; s2 >= 0; --s2)
-          gq = fmaf(sm.bc[s2][16 + n], sm.dy[s2][cl], gq) * fast_exp2(sm.dt[s2][cl] * a2);
-      } else {
-#pragma unroll 16
-        for (int s2 = kBwdTile - 1; s2 >= 0; --s2) {
-          const float dts = sm.dt[s2][cl];
-          sum_dt += dts;
-          gq = fmaf(sm.bc[s2][16 + n], sm.dy[s2][cl], gq) * fast_exp2(dts * a2);
-        }
-      }
+  // uniform row address plus one 32-bit lane offset (see scan_lane_kernel for the empty asm)
+  const uintptr_t u_p = reinterpret_cast<uintptr_t>(u + row0 * d_inner + ch0), dt_p = reinterpret_cast<uintptr_t>(dt + row0 * d_inner + ch0);
+  const uintptr_t dg_p = reinterpret_cast<uintptr_t>(dg + row0 * d_inner + ch0), z_p = reinterpret_cast<uintptr_t>(z + row0 * ld_z + ch0);
+  const uintptr_t bc_p = reinterpret_cast<uintptr_t>(bc + row0 * 32), gate_p = gate ? reinterpret_cast<uintptr_t>(gate + row0) : bc_p;
+  const uint32_t pitch = static_cast<uint32_t>(d_inner * sizeof(T)), pitch_z = static_cast<uint32_t>(ld_z * sizeof(T));
+  auto at = [](uintptr_t base, uint32_t off, uint32_t lo) __attribute__((always_inline)) {
+    uintptr_t p = base + off;
+    asm("" : "+s"(p));
+    return *reinterpret_cast<global_t *>(reinterpret_cast<global_char_t *>(p) + lo);
+  };
+  // ring of the next kRun rows: a slot is requested anew as soon as its step has taken the values out
+  constexpr int kRun = 4;
+  T rdt[kRun], ru[kRun], rz[kRun], rg[kRun];
+  auto fetch = [&](int t, int j, uint32_t lo) __attribute__((always_inline)) {
+    const uint32_t rr = static_cast<uint32_t>(t < len ? t : len - 1);    // past the chunk's end: its last row again
+    rdt[j] = at(dt_p, rr * pitch, lo);
+    ru[j] = at(u_p, rr * pitch, lo);
+    rz[j] = at(z_p, rr * pitch_z, lo);
+    rg[j] = at(dg_p, rr * pitch, lo);
+  };
+  const uint32_t loff = static_cast<uint32_t>(cl) * sizeof(T);
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) fetch(j, j, loff);
+  // B and the gate weight of Eq. (12) one step ahead, C within the step
+  bwd_f32x16 bv = *reinterpret_cast<const_f32x16_t *>(bc_p);
+  // (no gate: any readable word, replaced by 1 - a branch here would part the step's loads from its arithmetic)
+  const uint32_t gate_step = gate ? 4 : 0;
+  float gw = *reinterpret_cast<const_f32_t *>(gate_p);
+  auto step = [&](int t, int j) __attribute__((always_inline)) {
+    const int tn = t + 1 < len ? t + 1 : t;
+    const float d = to_f32(rdt[j]), du = d * to_f32(ru[j]), dy = to_f32(rg[j]) * (gate ? gw : 1.0f) * silu_f32(to_f32(rz[j]));
+    const bwd_f32x16 cv = *reinterpret_cast<const_f32x16_t *>(bc_p + t * 128 + 64);
+    const bwd_f32x16 bn = *reinterpret_cast<const_f32x16_t *>(bc_p + tn * 128);
+    gw = *reinterpret_cast<const_f32_t *>(gate_p + static_cast<uint32_t>(tn) * gate_step);
+    uint32_t lo = loff;
+    asm volatile("" : "+v"(lo));
+    fetch(t + kRun, j, lo);
+    sum += d;
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+      const float da = fast_exp2(d * a2[n]);
+      h[n] = fmaf(da, h[n], du * bv[n]);
+      e[n] *= da;
     }
+#pragma unroll
+    for (int n = 0; n < 16; ++n) r[n] = fmaf(e[n] * dy, cv[n], r[n]);
+    bv = bn;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int t = 0;
+  const int p2 = len / 2, p1 = p2 + len / 4, p0 = p1 + len / 8;          // (priorities: see scan_lane_kernel)
+  __builtin_amdgcn_s_setprio(3);
+  for (; t + kRun <= len; t += kRun) {
+    if (t >= p0) __builtin_amdgcn_s_setprio(0);
+    else if (t >= p1) __builtin_amdgcn_s_setprio(1);
+    else if (t >= p2) __builtin_amdgcn_s_setprio(2);
+    // brings the B / C rows of the run after the next into L2, ahead of the scalar loads
+    const int wr = t + 2 * kRun + (lane >> 4) < len ? t + 2 * kRun + (lane >> 4) : len - 1;
+    const bwd_u32x2 warm = *reinterpret_cast<const bwd_u32x2 *>(bc + (row0 + wr) * 32 + (lane & 15) * 2);
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) step(t + j, j);
+    asm volatile("" ::"v"(warm));
   }
-  const int64_t unit = (static_cast<int64_t>(blockIdx.y)) * gridDim.x + blockIdx.x;
-  carry_p[unit * 256 + tid] = fast_exp2(sum_dt * a2);
-  carry_q[unit * 256 + tid] = h;
-  carry_r[unit * 256 + tid] = gq;
+#pragma unroll
+  for (int j = 0; j < kRun - 1; ++j)
+    if (t + j < len) step(t + j, j);
+  float *q_out = carry_q + bk * 16 * d_inner + ch, *r_out = carry_r + bk * 16 * d_inner + ch;
+#pragma unroll
+  for (int n = 0; n < 16; ++n) {
+    q_out[static_cast<int64_t>(n) * d_inner] = h[n];
+    r_out[static_cast<int64_t>(n) * d_inner] = r[n];
+  }
+  carry_s[bk * d_inner + ch] = sum;
 }
 
-// grid (n_cb, B * n_chunks).  ckpt: f32 [unit][groups of the chunk][16 channels][16 states].
-// d_bc_part: f32 [n_cb][N][32].  Outputs d_pre (w.r.t. the softplus argument), d_u, d_z have type T.
+// thread = (sequence, state, channel); blockIdx.y 0: q_k <- state at the start of chunk k (zero before the first),
+// 1: r_k <- adjoint state flowing into the end of chunk k (zero behind the last)
+__global__ __launch_bounds__(256) void scan_bwd_fold_kernel(const float *__restrict__ A_log, int64_t n_seq, int d_inner,
+                                                            int n_chunks, float *__restrict__ carry_q,
+                                                            float *__restrict__ carry_r, const float *__restrict__ carry_s) {
+  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t per_seq = static_cast<int64_t>(d_inner) * 16;
+  if (idx >= n_seq * per_seq) return;
+  const int64_t b = idx / per_seq;
+  const int w = static_cast<int>(idx % per_seq), n = w / d_inner, ch = w % d_inner;
+  const float a2 = -__expf(A_log[static_cast<int64_t>(ch) * 16 + n]) * 1.44269504088896341f;
+  const bool rev = blockIdx.y == 1;
+  float *x = (rev ? carry_r : carry_q) + b * n_chunks * per_seq + w;
+  const float *s = carry_s + b * n_chunks * d_inner + ch;
+  float v = 0.0f;
+  constexpr int kAhead = 8;
+  float xv[kAhead], sv[kAhead];
+  for (int k0 = 0; k0 < n_chunks; k0 += kAhead) {
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      int k = k0 + j < n_chunks ? k0 + j : n_chunks - 1;
+      if (rev) k = n_chunks - 1 - k;
+      xv[j] = x[k * per_seq];
+      sv[j] = s[static_cast<int64_t>(k) * d_inner];
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (k0 + j < n_chunks) {
+        const int k = rev ? n_chunks - 1 - k0 - j : k0 + j;
+        x[k * per_seq] = v;
+        v = fmaf(fast_exp2(a2 * sv[j]), v, xv[j]);
+      }
+    }
+  }
+}
+
+// v_s (s = 0 .. 3): partial sums of four steps, one part per row of 16 lanes; row q receives the total of step q
+__device__ __forceinline__ float sum_rows4(const float (&v)[4]) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+  const float s02 = __uint_as_float(a[0]) + __uint_as_float(a[1]), s13 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s02), __float_as_uint(s13), false, false);
+  return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+
+struct BwdSmem {
+  float ck[4][kBwdGroups][256];                        // [wave][group][lane * 4 + j]: state at the group's start
+  float dt[4][16 * kBwdStPitch], dtu[4][16 * kBwdStPitch], dy[4][16 * kBwdStPitch];     // [wave][channel][step of the group]
+  float bc[4][kBwdGroup * 32];                         // [wave][step][B_0..15, C_0..15]
+  float o_bc[2][4][kBwdGroup * 32];                    // each wavefront's share of d_B, d_C of a group, two groups in turn
+};
+
+// grid.x: units.  start_h / start_dh: f32 [B][n_chunks][16][d_inner] or NULL (one chunk: zeros).  d_bc_part: f32
+// [n_cb][N][32].  Outputs d_pre (w.r.t. the softplus argument), d_u, d_z have type T.
 template <typename T>
-__global__ __launch_bounds__(256) void scan_bwd_kernel(
+__global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
     const T *__restrict__ u, const T *__restrict__ dt, const float *__restrict__ bc, const T *__restrict__ z,
     int64_t ld_z, const T *__restrict__ dg, const float *__restrict__ gate, const float *__restrict__ A_log,
-    const float *__restrict__ D, int64_t n_seq, int64_t L, int d_inner, int n_chunks, int64_t chunk_len, int n_fine,
-    int fine_per_chunk, float *__restrict__ ckpt, const float *__restrict__ carry_p, const float *__restrict__ carry_q,
-    const float *__restrict__ carry_r, T *__restrict__ d_pre, T *__restrict__ d_u, T *__restrict__ d_z, int64_t ld_dz,
-    float *__restrict__ d_bc_part, float *__restrict__ part_a, float *__restrict__ part_d,
-    float *__restrict__ part_bias) {
-  __shared__ BwdSmem sm;
-  const int tid = threadIdx.x;
-  const int n = tid & 15, cl = tid >> 4;
-  const int c0 = blockIdx.x * kBwdCh, ch = c0 + cl;
-  const int64_t b = blockIdx.y / n_chunks, k = blockIdx.y % n_chunks;
-  const int64_t ts = k * chunk_len, te = ts + chunk_len < L ? ts + chunk_len : L;
-  const int64_t n_tiles = (te - ts + kBwdTile - 1) / kBwdTile;
-  const int64_t unit = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
-  const float a_nat = -__expf(A_log[static_cast<int64_t>(ch) * 16 + n]);      // A = -exp(A_log)
-  const float a2 = a_nat * 1.44269504088896341f;
-  const float d_skip = D[ch];
-  float *ck = ckpt + unit * (chunk_len / kBwdGroup) * 256;
-  const int64_t n_tok = n_seq * L;
-  float acc_a = 0.0f, acc_d = 0.0f, acc_bias = 0.0f;       // d_A (this lane's state); d_D, d_dt_bias (the steps this lane finishes)
-
-  const T *u_b = u + b * L * d_inner + c0;
-  const T *dt_b = dt + b * L * d_inner + c0;
-  const T *z_b = z + b * L * ld_z + c0;
-  const T *dg_b = dg + b * L * d_inner + c0;
-  const float *bc_b = bc + b * L * 32;
-  const float *gate_b = gate ? gate + b * L : nullptr;
-
-  // ---- prologue: the carries of the fine chunks before (state) and after (adjoint state) this chunk
-  float h = 0.0f, dh = 0.0f;
-  if (n_chunks > 1) {
-    const int64_t unit0 = b * n_fine * gridDim.x + blockIdx.x;        // fine chunk 0 of this sequence and channel block
-    const int64_t f0 = k * fine_per_chunk;
-    for (int64_t j = 0; j < f0; ++j) {
-      const int64_t at = (unit0 + j * gridDim.x) * 256 + tid;
-      h = fmaf(carry_p[at], h, carry_q[at]);
-    }
-    for (int64_t j = n_fine - 1; j >= f0 + fine_per_chunk; --j) {
-      const int64_t at = (unit0 + j * gridDim.x) * 256 + tid;
-      dh = fmaf(carry_p[at], dh, carry_r[at]);
+    const float *__restrict__ D, int64_t n_tok, int64_t L, int d_inner, int n_cb, int n_chunks,
+    const float *__restrict__ start_h, const float *__restrict__ start_dh, T *__restrict__ d_pre, T *__restrict__ d_u,
+    T *__restrict__ d_z, int64_t ld_dz, float *__restrict__ d_bc_part, float *__restrict__ part_a,
+    float *__restrict__ part_d, float *__restrict__ part_bias) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char bwd_smem[];
+  BwdSmem &sm = *reinterpret_cast<BwdSmem *>(bwd_smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, q = lane >> 4;
+  const int64_t unit = blockIdx.x;
+  const int cb = static_cast<int>(unit % n_cb);
+  const int64_t bk = unit / n_cb, b = bk / n_chunks, ts = bk % n_chunks * kBwdChunk, row0 = b * L + ts;
+  const int len = static_cast<int>(L - ts < kBwdChunk ? L - ts : kBwdChunk);
+  const int n_grp = (len + kBwdGroup - 1) / kBwdGroup;
+  const int c0 = cb * kBwdCh + wave * 16;
+  const bool active = c0 < d_inner;                     // (d_inner is a multiple of 16)
+  const int ch = active ? c0 + c : c;
+  float a_nat[4], a2[4], h[4] = {0.f, 0.f, 0.f, 0.f}, dh[4] = {0.f, 0.f, 0.f, 0.f};
+  bwd_load4(A_log + static_cast<int64_t>(ch) * 16 + q * 4, a_nat);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    a_nat[j] = -__expf(a_nat[j]);                       // A = -exp(A_log)
+    a2[j] = a_nat[j] * 1.44269504088896341f;
+    if (start_h) {
+      const int64_t at = (bk * 16 + q * 4 + j) * d_inner + ch;
+      h[j] = start_h[at];
+      dh[j] = start_dh[at];
     }
   }
+  const float d_skip = D[ch];
+  float acc_a[4] = {0.f, 0.f, 0.f, 0.f}, acc_d = 0.0f, acc_bias = 0.0f;
+
+  // what lane (q, c) brings of a group: steps 4 i + q of channel c, and 2 x 16 bytes of the B / C rows.  Addresses are a
+  // uniform base and a 32-bit byte offset (the launcher keeps a chunk's rows within 2 GiB).
+  struct Raw {
+    T dt[4], u[4], z[4], dg[4];
+    float gate[4];
+    bwd_f32x4 bc0, bc1;
+  } raw;
+  const unsigned pitch = static_cast<unsigned>(d_inner * sizeof(T)), pitch_z = static_cast<unsigned>(ld_z * sizeof(T));
+  const unsigned pitch_dz = static_cast<unsigned>(ld_dz * sizeof(T)), ch_off = static_cast<unsigned>(ch * sizeof(T));
+  const char *const dt_p = reinterpret_cast<const char *>(dt + row0 * d_inner), *const u_p = reinterpret_cast<const char *>(u + row0 * d_inner);
+  const char *const dg_p = reinterpret_cast<const char *>(dg + row0 * d_inner), *const z_p = reinterpret_cast<const char *>(z + row0 * ld_z);
+  const char *const bc_p = reinterpret_cast<const char *>(bc + row0 * 32);
+  auto fetch = [&](int g, bool full) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int tt = g * kBwdGroup + 4 * i + q;
+      const unsigned t = static_cast<unsigned>(tt < len ? tt : len - 1), at = __umul24(t, pitch) + ch_off;
+      raw.dt[i] = *reinterpret_cast<const T *>(dt_p + at);
+      raw.u[i] = *reinterpret_cast<const T *>(u_p + at);
+      if (full) {
+        raw.z[i] = *reinterpret_cast<const T *>(z_p + (__umul24(t, pitch_z) + ch_off));
+        raw.dg[i] = *reinterpret_cast<const T *>(dg_p + at);
+        raw.gate[i] = gate ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(gate + row0) + t * 4u) : 1.0f;
+      }
+    }
+    const int r0 = g * kBwdGroup + (lane >> 3), r1 = r0 + 8;
+    const unsigned o0 = static_cast<unsigned>(r0 < len ? r0 : len - 1) * 128u, o1 = static_cast<unsigned>(r1 < len ? r1 : len - 1) * 128u;
+    raw.bc0 = *reinterpret_cast<const bwd_f32x4 *>(bc_p + (o0 + (lane & 7) * 16u));
+    raw.bc1 = *reinterpret_cast<const bwd_f32x4 *>(bc_p + (o1 + (lane & 7) * 16u));
+  };
+  // steps past the end (and wavefronts past the last channel): dt = dt u = d y = 0, which leaves states and sums alone
+  float dt_o[4], u_o[4], dy_o[4], dzf_o[4];
+  auto park = [&](int g, bool full) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool ok = active && g * kBwdGroup + 4 * i + q < len;
+      const float dv = ok ? to_f32(raw.dt[i]) : 0.0f, uv = ok ? to_f32(raw.u[i]) : 0.0f;
+      sm.dt[wave][c * kBwdStPitch + 4 * i + q] = dv;
+      sm.dtu[wave][c * kBwdStPitch + 4 * i + q] = dv * uv;
+      if (full) {
+        const float zs = to_f32(raw.z[i]), dgs = ok ? to_f32(raw.dg[i]) * raw.gate[i] : 0.0f;
+        const float sig = sigmoid_f32(zs);
+        dt_o[i] = dv;
+        u_o[i] = uv;
+        dy_o[i] = dgs * zs * sig;                       // g = y * SiLU(z)
+        dzf_o[i] = dgs * sig * (1.0f + zs * (1.0f - sig));
+        sm.dy[wave][c * kBwdStPitch + 4 * i + q] = dy_o[i];
+      }
+    }
+    const int r0 = g * kBwdGroup + (lane >> 3);
+    const bwd_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    *reinterpret_cast<bwd_f32x4 *>(&sm.bc[wave][lane * 4]) = r0 < len ? raw.bc0 : zero;
+    *reinterpret_cast<bwd_f32x4 *>(&sm.bc[wave][256 + lane * 4]) = r0 + 8 < len ? raw.bc1 : zero;
+    // (a wavefront's own LDS accesses are served in program order: its lanes may read what the others wrote)
+    asm volatile("" ::: "memory");
+  };
+  auto ld4 = [](const float *p) __attribute__((always_inline)) { return *reinterpret_cast<const bwd_f32x4 *>(p); };
+
+  // the states of steps 4 i .. 4 i + 3 of the parked group
+  auto walk = [&](int i, float(&x)[4]) __attribute__((always_inline)) {
+    const bwd_f32x4 d4 = ld4(&sm.dt[wave][c * kBwdStPitch + 4 * i]), x4 = ld4(&sm.dtu[wave][c * kBwdStPitch + 4 * i]);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bwd_f32x4 b4 = ld4(&sm.bc[wave][(4 * i + s) * 32 + q * 4]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = fmaf(fast_exp2(d4[s] * a2[j]), x[j], x4[s] * b4[j]);
+    }
+  };
 
   // ---- pass 1: the state at the start of every group
-  BwdTileRegs regs;
-  bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts, te, d_inner, tid, false);
-  for (int64_t ti = 0; ti < n_tiles; ++ti) {
-    lds_barrier();
-    bwd_park_tile<BwdSmem, true>(sm, regs, tid, false);
-    lds_barrier();
-    if (ti + 1 < n_tiles)      // the next tile; after the last one, the same tile again with the factors pass 2 needs
-      bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts + (ti + 1) * kBwdTile, te, d_inner, tid, false);
-    else
-      bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, ts + ti * kBwdTile, te, d_inner, tid, true);
-#pragma unroll 1
-    for (int grp = 0; grp < kGroupsPerTile; ++grp) {
-      ck[(ti * kGroupsPerTile + grp) * 256 + tid] = h;
+  fetch(0, n_grp == 1);
+  for (int g = 0; g < n_grp; ++g) {
+    *reinterpret_cast<bwd_f32x4 *>(&sm.ck[wave][g][lane * 4]) = bwd_f32x4{h[0], h[1], h[2], h[3]};
+    if (g + 1 == n_grp) break;
+    park(g, false);
+    fetch(g + 1, g + 2 == n_grp);                       // pass 2 starts with the last group
 #pragma unroll
-      for (int j = 0; j < kBwdGroup; ++j) {
-        const int s2 = grp * kBwdGroup + j;
-        const float dts = sm.dt[s2][cl];
-        h = fmaf(fast_exp2(dts * a2), h, dts * sm.u[s2][cl] * sm.bc[s2][n]);
-      }
-    }
+    for (int i = 0; i < 4; ++i) walk(i, h);
+    asm volatile("" ::: "memory");
   }
 
-  // ---- pass 2: tiles in reverse, groups in reverse
-  for (int64_t ti = n_tiles - 1; ti >= 0; --ti) {
-    const int64_t t0 = ts + ti * kBwdTile;
-    // the checkpoint of a group is fetched one group ahead of its use
-    float ck_next = ck[(ti * kGroupsPerTile + kGroupsPerTile - 1) * 256 + tid];
-    lds_barrier();
-    bwd_park_tile<BwdSmem, true>(sm, regs, tid, true);
-    lds_barrier();
-    if (ti > 0)
-      bwd_fetch_tile<T>(regs, u_b, dt_b, z_b, ld_z, dg_b, bc_b, gate_b, t0 - kBwdTile, te, d_inner, tid, true);
-#pragma unroll 1
-    for (int grp = kGroupsPerTile - 1; grp >= 0; --grp) {
-      float hs[kBwdGroup + 1], da[kBwdGroup], dts[kBwdGroup], dtu[kBwdGroup], bn[kBwdGroup];
-      hs[0] = ck_next;
-      if (grp > 0) ck_next = ck[(ti * kGroupsPerTile + grp - 1) * 256 + tid];
+  // ---- pass 2: groups in reverse
+  char *const dpre_p = reinterpret_cast<char *>(d_pre + row0 * d_inner), *const du_p = reinterpret_cast<char *>(d_u + row0 * d_inner);
+  char *const dz_p = reinterpret_cast<char *>(d_z + row0 * ld_dz);
+  // (all: every step of the group and every channel of the wavefront exists - no branch around the stores, which would
+  // cut the group into pieces too short to schedule)
+  auto group = [&](int g, auto all) __attribute__((always_inline)) {
+    // the group in two halves of eight steps, the later one first, so that its states and decays (68 registers) leave room
+    // for three wavefronts per SIMD; the state between the halves is walked to once more
+    float mid[4];
+    {
+      const bwd_f32x4 k4 = ld4(&sm.ck[wave][g][lane * 4]);
 #pragma unroll
-      for (int j = 0; j < kBwdGroup; ++j) {
-        const int s2 = grp * kBwdGroup + j;
-        dts[j] = sm.dt[s2][cl];
-        dtu[j] = dts[j] * sm.u[s2][cl];
-        bn[j] = sm.bc[s2][n];
-        da[j] = fast_exp2(dts[j] * a2);
-        hs[j + 1] = fmaf(da[j], hs[j], dtu[j] * bn[j]);
+      for (int j = 0; j < 4; ++j) mid[j] = k4[j];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) walk(i, mid);
+    float *o_bc = sm.o_bc[g & 1][wave];
+#pragma unroll
+    for (int half = 1; half >= 0; --half) {
+      __builtin_amdgcn_sched_barrier(0);
+      float hs[kBwdHalf + 1][4], da[kBwdHalf][4];
+      if (half == 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hs[0][j] = mid[j];
+      } else {
+        const bwd_f32x4 k4 = ld4(&sm.ck[wave][g][lane * 4]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hs[0][j] = k4[j];
       }
 #pragma unroll
-      for (int half = 1; half >= 0; --half) {
-        // the eight steps' LDS operands in one batch: one wait instead of one per step behind the
-        // step's own LDS writes
-        float us8[kBwdHalf], cn8[kBwdHalf], dy8[kBwdHalf];
+      for (int i2 = 0; i2 < 2; ++i2) {
+        const int i = 2 * half + i2;
+        const bwd_f32x4 d4 = ld4(&sm.dt[wave][c * kBwdStPitch + 4 * i]), x4 = ld4(&sm.dtu[wave][c * kBwdStPitch + 4 * i]);
 #pragma unroll
-        for (int jj = 0; jj < kBwdHalf; ++jj) {
-          const int s2 = grp * kBwdGroup + half * kBwdHalf + jj;
-          us8[jj] = sm.u[s2][cl];
-          cn8[jj] = sm.bc[s2][16 + n];
-          dy8[jj] = sm.dy[s2][cl];
-        }
-        // per (step, state) part: the adjoint recurrence and the terms whose sums over the 16 states
-        // the step's outputs need: y (p16[jj]), the input term (p16[8 + jj]), d dt (q8[jj])
-        float p16[2 * kBwdHalf], q8[kBwdHalf];
+        for (int s = 0; s < 4; ++s) {
+          const int t = 4 * i2 + s;
+          const bwd_f32x4 b4 = ld4(&sm.bc[wave][(4 * i + s) * 32 + q * 4]);
 #pragma unroll
-        for (int jj = kBwdHalf - 1; jj >= 0; --jj) {
-          const int j = half * kBwdHalf + jj;
-          dh = fmaf(cn8[jj], dy8[jj], dh);                      // y_t = C_t . h_t
-          p16[jj] = cn8[jj] * hs[j + 1];
-          const float darg = dh * hs[j] * da[j];                // d / d (dt_t * A)
-          const float inj = dh * bn[j];                         // input term dt * B * u
-          p16[kBwdHalf + jj] = inj;
-          q8[jj] = fmaf(darg, a_nat, inj * us8[jj]);
-          acc_a = fmaf(darg, dts[j], acc_a);
-          sm.part_b[jj][cl][n] = dh * dtu[j];
-          sm.part_c[jj][cl][n] = dy8[jj] * hs[j + 1];
-          dh *= da[j];
-        }
-        // sums over the states, transposed: lane n < 8 holds C.h of step n, lane n >= 8 the input-term
-        // sum of step n - 8, every lane the d dt sum of step n & 7
-        const float yi = transpose_sum16(p16, n);
-        const float ddt = transpose_sum8(q8, n);
-        // per (step, channel) part, once per step instead of once per lane: lane n works on step n & 7
-        {
-          const int s2 = grp * kBwdGroup + half * kBwdHalf + (n & 7);
-          const float dt_k = sm.dt[s2][cl], u_k = sm.u[s2][cl], dy_k = sm.dy[s2][cl];
-          if (n < 8) {
-            sm.o_z[s2][cl] = sm.dzf[s2][cl] * fmaf(d_skip, u_k, yi);
-            // dt = softplus(pre): d pre = d dt * sigmoid(pre) = d dt * (1 - exp(-dt))
-            const float dpre = ddt * (1.0f - fast_exp2(-1.44269504088896341f * dt_k));
-            sm.o_pre[s2][cl] = dpre;
-            acc_bias += dpre;
-            acc_d = fmaf(dy_k, u_k, acc_d);
-          } else {
-            sm.o_u[s2][cl] = fmaf(yi, dt_k, d_skip * dy_k);
+          for (int j = 0; j < 4; ++j) {
+            da[t][j] = fast_exp2(d4[s] * a2[j]);
+            hs[t + 1][j] = fmaf(da[t][j], hs[t][j], x4[s] * b4[j]);
           }
         }
-        lds_barrier();
-        // d_B, d_C of these eight steps: sum over the block's channels in channel order
-        {
-          const int jj = tid / 32, c = tid % 32;             // 8 steps x 32 values = 256 threads
-          const float(*src)[kBwdCh][17] = c < 16 ? sm.part_b : sm.part_c;
-          float tot = 0.0f;
+      }
 #pragma unroll
-          for (int q = 0; q < kBwdCh; ++q) tot += src[jj][q][c & 15];
-          sm.o_bc[grp * kBwdGroup + half * kBwdHalf + jj][c] = tot;
+      for (int i2 = 1; i2 >= 0; --i2) {
+        const int i = 2 * half + i2;
+        const bwd_f32x4 d4 = ld4(&sm.dt[wave][c * kBwdStPitch + 4 * i]), x4 = ld4(&sm.dtu[wave][c * kBwdStPitch + 4 * i]);
+        const bwd_f32x4 y4 = ld4(&sm.dy[wave][c * kBwdStPitch + 4 * i]);
+        float v_y[4], v_in[4], v_dt[4];                 // this lane's part of C.h, of the input term and of d (dt A) A
+#pragma unroll
+        for (int pair = 1; pair >= 0; --pair) {
+          float p16[16];                                // [step of the pair][d_B of four states, d_C]
+#pragma unroll
+          for (int s1 = 1; s1 >= 0; --s1) {
+            const int s = 2 * pair + s1, t = 4 * i2 + s;
+            const bwd_f32x4 b4 = ld4(&sm.bc[wave][(4 * i + s) * 32 + q * 4]), c4 = ld4(&sm.bc[wave][(4 * i + s) * 32 + 16 + q * 4]);
+            float y = 0.0f, in = 0.0f, ddt = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              dh[j] = fmaf(c4[j], y4[s], dh[j]);        // y_t = C_t . h_t
+              y = j == 0 ? c4[j] * hs[t + 1][j] : fmaf(c4[j], hs[t + 1][j], y);
+              in = j == 0 ? dh[j] * b4[j] : fmaf(dh[j], b4[j], in);           // input term dt * B * u
+              p16[8 * s1 + j] = dh[j] * x4[s];
+              p16[8 * s1 + 4 + j] = y4[s] * hs[t + 1][j];
+              dh[j] *= da[t][j];
+              const float darg = dh[j] * hs[t][j];      // d / d (dt_t * A)
+              ddt = j == 0 ? darg * a_nat[j] : fmaf(darg, a_nat[j], ddt);
+              acc_a[j] = fmaf(darg, d4[s], acc_a[j]);
+            }
+            v_y[s] = y;
+            v_in[s] = in;
+            v_dt[s] = ddt;
+          }
+          o_bc[(4 * i + 2 * pair + (c >> 3)) * 32 + ((c >> 2) & 1) * 16 + q * 4 + (c & 3)] = transpose_sum16(p16, c);
         }
-        lds_barrier();
+        // step 4 i + q belongs to this lane from here on
+        const float y = sum_rows4(v_y), in = sum_rows4(v_in), ddt = fmaf(in, u_o[i], sum_rows4(v_dt));
+        const float o_z = dzf_o[i] * fmaf(d_skip, u_o[i], y);
+        // dt = softplus(pre): d pre = d dt * sigmoid(pre) = d dt * (1 - exp(-dt))
+        const float o_pre = ddt * (1.0f - fast_exp2(-1.44269504088896341f * dt_o[i]));
+        const float o_u = fmaf(in, dt_o[i], d_skip * dy_o[i]);
+        acc_bias += o_pre;
+        acc_d = fmaf(dy_o[i], u_o[i], acc_d);
+        const int t = g * kBwdGroup + 4 * i + q;
+        if (decltype(all)::value || (active && t < len)) {
+          const unsigned at = __umul24(static_cast<unsigned>(t), pitch) + ch_off;
+          *reinterpret_cast<T *>(dpre_p + at) = from_f32<T>(o_pre);
+          *reinterpret_cast<T *>(du_p + at) = from_f32<T>(o_u);
+          *reinterpret_cast<T *>(dz_p + (__umul24(static_cast<unsigned>(t), pitch_dz) + ch_off)) = from_f32<T>(o_z);
+        }
+        __builtin_amdgcn_sched_barrier(0);              // (registers: no more than four steps in flight)
       }
     }
-    // the tile's outputs, in the fetch's thread map
+  };
+  for (int g = n_grp - 1; g >= 0; --g) {
+    park(g, true);
+    if (g > 0) fetch(g - 1, true);
+    if (active && (g + 1) * kBwdGroup <= len) group(g, std::true_type{});
+    else group(g, std::false_type{});
+    lds_barrier();
+    // d_B, d_C of the group: the four wavefronts' shares in wavefront order, two values per thread.  (The next group
+    // writes the other copy; this one is written again only behind the next barrier.)
     {
-      const int row = tid >> 2, c = (tid & 3) * 4;
-      const int64_t t = t0 + row;
-      if (t < te) {
-        const int64_t at = (b * L + t) * d_inner + c0 + c;
-        float v[4];
+      const int row = tid / 16;
+      float v0 = 0.0f, v1 = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = sm.o_pre[row][c + q];
-        bwd_store4(d_pre + at, v);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = sm.o_u[row][c + q];
-        bwd_store4(d_u + at, v);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = sm.o_z[row][c + q];
-        bwd_store4(d_z + (b * L + t) * ld_dz + c0 + c, v);
-        float *dst = d_bc_part + (static_cast<int64_t>(blockIdx.x) * n_tok + b * L + t) * 32 + (tid & 3) * 8;
-        float w[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) w[q] = sm.o_bc[row][(tid & 3) * 8 + q];
-        bwd_store4(dst, w);
-        bwd_store4(dst + 4, w + 4);
+      for (int w = 0; w < 4; ++w) {
+        v0 += sm.o_bc[g & 1][w][2 * tid];
+        v1 += sm.o_bc[g & 1][w][2 * tid + 1];
+      }
+      if (g * kBwdGroup + row < len) {
+        float *dst = d_bc_part + (static_cast<int64_t>(cb) * n_tok + row0 + g * kBwdGroup) * 32 + 2 * tid;
+        dst[0] = v0;
+        dst[1] = v1;
       }
     }
   }
-  part_a[unit * 256 + tid] = acc_a * a_nat;                            // d A_log = d A * A
-  // (lanes 0..7 of a channel each hold the sums over the steps they worked on, lanes 8..15 zero)
-  acc_d = row_sum16(acc_d);
-  acc_bias = row_sum16(acc_bias);
-  if (n == 0) {
-    part_d[unit * kBwdCh + cl] = acc_d;
-    part_bias[unit * kBwdCh + cl] = acc_bias;
+  // d A_log = d A * A; the rows' shares of d_D, d_dt_bias added in row order
+  float *pa = part_a + (unit * kBwdCh + wave * 16 + c) * 16 + q * 4;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) pa[j] = acc_a[j] * a_nat[j];
+  acc_d += __shfl_xor(acc_d, 16, 64);
+  acc_d += __shfl_xor(acc_d, 32, 64);
+  acc_bias += __shfl_xor(acc_bias, 16, 64);
+  acc_bias += __shfl_xor(acc_bias, 32, 64);
+  if (q == 0) {
+    part_d[unit * kBwdCh + wave * 16 + c] = acc_d;
+    part_bias[unit * kBwdCh + wave * 16 + c] = acc_bias;
   }
 }
 
 // d_A_log, d_D, d_dt_bias: the units' partials summed in unit order.  One thread per (channel, state).
 __global__ __launch_bounds__(256) void scan_bwd_finish_kernel(const float *__restrict__ part_a,
                                                               const float *__restrict__ part_d,
-                                                              const float *__restrict__ part_bias, int n_cb,
+                                                              const float *__restrict__ part_bias, int n_cb, int d_inner,
                                                               int64_t n_rep, float *__restrict__ d_A_log,
                                                               float *__restrict__ d_D, float *__restrict__ d_dt_bias) {
-  const int cb = blockIdx.x, tid = threadIdx.x;
+  const int idx = blockIdx.x * 256 + threadIdx.x, ch = idx / 16, n = idx % 16;
+  if (ch >= d_inner) return;
+  const int64_t stride = static_cast<int64_t>(n_cb) * kBwdCh;
   float a = 0.0f;
-  for (int64_t r = 0; r < n_rep; ++r) a += part_a[(r * n_cb + cb) * 256 + tid];
-  d_A_log[static_cast<int64_t>(cb) * 256 + tid] = a;
-  if (tid < 2 * kBwdCh) {
-    const float *src = tid < kBwdCh ? part_d : part_bias;
-    const int c = tid % kBwdCh;
+#pragma unroll 8
+  for (int64_t r = 0; r < n_rep; ++r) a += part_a[r * stride * 16 + idx];
+  d_A_log[idx] = a;
+  if (n < 2) {
+    const float *src = (n == 0 ? part_d : part_bias) + ch;
     float v = 0.0f;
-    for (int64_t r = 0; r < n_rep; ++r) v += src[(r * n_cb + cb) * kBwdCh + c];
-    (tid < kBwdCh ? d_D : d_dt_bias)[cb * kBwdCh + c] = v;
+#pragma unroll 8
+    for (int64_t r = 0; r < n_rep; ++r) v += src[r * stride];
+    (n == 0 ? d_D : d_dt_bias)[ch] = v;
   }
 }
 
-// d_bc[t, :] = sum over the channel-group partials, in group order
+// d_bc[t, :] = sum over the channel-block partials, in block order
 __global__ __launch_bounds__(256) void bwd_reduce_bc_kernel(const float *__restrict__ part, int n_parts, int64_t n_tok,
                                                             float *__restrict__ d_bc) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n_tok * 32) return;
   float tot = 0.0f;
+#pragma unroll 8
   for (int p = 0; p < n_parts; ++p) tot += part[static_cast<int64_t>(p) * n_tok * 32 + i];
   d_bc[i] = tot;
 }
@@ -1452,7 +1472,7 @@ size_t scan_bwd_ckpt_bytes(int64_t B, int64_t L, int d_inner) {
   return scan_bwd_layout(B, L, d_inner).total * sizeof(float);
 }
 size_t scan_bwd_part_bytes(int64_t n_tok, int d_inner) {
-  return static_cast<size_t>(d_inner / kBwdCh) * static_cast<size_t>(n_tok) * 32 * sizeof(float);
+  return static_cast<size_t>(ceil_div(d_inner, kBwdCh)) * static_cast<size_t>(n_tok) * 32 * sizeof(float);
 }
 
 template <typename T>
@@ -1462,25 +1482,44 @@ static hipError_t launch_scan_backward_t(const void *u, const void *dt, const fl
                                          void *d_z, int64_t ld_dz, float *d_A_log, float *d_D, float *d_dt_bias,
                                          hipStream_t s) {
   const ScanBwdLayout l = scan_bwd_layout(B, L, d_inner);
-  const dim3 grid(static_cast<unsigned>(l.n_cb), static_cast<unsigned>(B * l.n_chunks));
-  if (l.n_chunks > 1) {
-    const dim3 fine_grid(static_cast<unsigned>(l.n_cb), static_cast<unsigned>(B * l.n_fine));
-    hipLaunchKernelGGL((scan_bwd_carry_kernel<T>), fine_grid, dim3(256), 0, s, static_cast<const T *>(u),
-                       static_cast<const T *>(dt), bc, static_cast<const T *>(z), ld_z, static_cast<const T *>(dg), gate,
-                       A_log, L, d_inner, l.n_fine, l.fine_len, static_cast<int>(l.chunk_len / l.fine_len), l.n_chunks,
-                       ws + l.carry_p, ws + l.carry_q, ws + l.carry_r);
-    hipError_t e = hipGetLastError();
+  const bool chunked = l.n_chunks > 1;
+  if (chunked) {
+    const int gx = static_cast<int>(ceil_div(d_inner, 256));
+    hipLaunchKernelGGL((scan_bwd_carry_kernel<T>), dim3(static_cast<unsigned>(B * l.n_chunks * gx)), dim3(256), 0, s,
+                       static_cast<const T *>(u), static_cast<const T *>(dt), bc, static_cast<const T *>(z), ld_z,
+                       static_cast<const T *>(dg), gate, A_log, L, d_inner, gx, l.n_chunks, ws + l.carry_q, ws + l.carry_r,
+                       ws + l.carry_s);
+    hipLaunchKernelGGL(scan_bwd_fold_kernel, dim3(static_cast<unsigned>(ceil_div(B * d_inner * 16, 256)), 2), dim3(256), 0, s,
+                       A_log, B, d_inner, l.n_chunks, ws + l.carry_q, ws + l.carry_r, ws + l.carry_s);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((scan_bwd_kernel<T>), grid, dim3(256), 0, s, static_cast<const T *>(u), static_cast<const T *>(dt),
-                     bc, static_cast<const T *>(z), ld_z, static_cast<const T *>(dg), gate, A_log, D, B, L, d_inner,
-                     l.n_chunks, l.chunk_len, l.n_fine, static_cast<int>(l.chunk_len / l.fine_len), ws + l.ckpt, ws + l.carry_p, ws + l.carry_q, ws + l.carry_r,
-                     static_cast<T *>(d_pre), static_cast<T *>(d_u), static_cast<T *>(d_z), ld_dz, d_bc_part,
-                     ws + l.part_a, ws + l.part_d, ws + l.part_bias);
-  hipError_t e = hipGetLastError();
+  // more than 64 KiB of LDS: a function attribute, set once per device
+  static std::mutex mu;
+  static std::atomic<bool> done[64] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scan_bwd_finish_kernel, dim3(static_cast<unsigned>(l.n_cb)), dim3(256), 0, s, ws + l.part_a,
-                     ws + l.part_d, ws + l.part_bias, l.n_cb, B * l.n_chunks, d_A_log, d_D, d_dt_bias);
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!done[dev].load(std::memory_order_acquire)) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (!done[dev].load(std::memory_order_relaxed)) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&scan_bwd_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(sizeof(BwdSmem)));
+      if (e != hipSuccess) return e;
+      done[dev].store(true, std::memory_order_release);
+    }
+  }
+  hipLaunchKernelGGL((scan_bwd_kernel<T>), dim3(static_cast<unsigned>(l.n_units)), dim3(256), sizeof(BwdSmem), s,
+                     static_cast<const T *>(u), static_cast<const T *>(dt), bc, static_cast<const T *>(z), ld_z,
+                     static_cast<const T *>(dg), gate, A_log, D, B * L, L, d_inner, l.n_cb, l.n_chunks,
+                     chunked ? ws + l.carry_q : nullptr, chunked ? ws + l.carry_r : nullptr, static_cast<T *>(d_pre),
+                     static_cast<T *>(d_u), static_cast<T *>(d_z), ld_dz, d_bc_part, ws + l.part_a, ws + l.part_d,
+                     ws + l.part_bias);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(scan_bwd_finish_kernel, dim3(static_cast<unsigned>(ceil_div(d_inner * 16, 256))), dim3(256), 0, s,
+                     ws + l.part_a, ws + l.part_d, ws + l.part_bias, l.n_cb, d_inner, B * l.n_chunks, d_A_log, d_D, d_dt_bias);
   return hipGetLastError();
 }
 
@@ -1489,7 +1528,10 @@ hipError_t launch_scan_backward(int dtype, const void *u, const void *dt, const 
                                 int64_t L, int d_inner, float *ckpt, float *d_bc_part, void *d_pre, void *d_u, void *d_z,
                                 int64_t ld_dz, float *d_bc, float *d_A_log, float *d_D, float *d_dt_bias,
                                 hipStream_t s) {
-  if (B * scan_bwd_layout(B, L, d_inner).n_fine > 65535) return hipErrorInvalidValue;
+  const ScanBwdLayout l = scan_bwd_layout(B, L, d_inner);
+  // 32-bit row offsets inside a chunk, 24-bit pitches
+  const int64_t widest = (ld_z > ld_dz ? ld_z : ld_dz) > d_inner ? (ld_z > ld_dz ? ld_z : ld_dz) : d_inner;
+  if (l.n_units >= (1ll << 31) || widest * 4 >= (1 << 24)) return hipErrorInvalidValue;
   hipError_t e = dtype == ROM_DTYPE_BF16
                      ? launch_scan_backward_t<bf16_t>(u, dt, bc, z, ld_z, dg, gate, A_log, D, B, L, d_inner, ckpt, d_bc_part,
                                                       d_pre, d_u, d_z, ld_dz, d_A_log, d_D, d_dt_bias, s)
@@ -1497,8 +1539,7 @@ hipError_t launch_scan_backward(int dtype, const void *u, const void *dt, const 
                                                      d_pre, d_u, d_z, ld_dz, d_A_log, d_D, d_dt_bias, s);
   if (e != hipSuccess) return e;
   const int64_t n_tok = B * L;
-  hipLaunchKernelGGL(bwd_reduce_bc_kernel, grid1d(n_tok * 32, 256), dim3(256), 0, s, d_bc_part, d_inner / kBwdCh, n_tok,
-                     d_bc);
+  hipLaunchKernelGGL(bwd_reduce_bc_kernel, grid1d(n_tok * 32, 256), dim3(256), 0, s, d_bc_part, l.n_cb, n_tok, d_bc);
   return hipGetLastError();
 }
 
