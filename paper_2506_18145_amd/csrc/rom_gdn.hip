@@ -11,9 +11,10 @@
 // and then  O = diag(gamma) Q S_0^T + (Q K^T o exp(cum_t - cum_s), s <= t) U,
 //           S_new = gamma_64 S_0 + sum_s exp(cum_64 - cum_s) u_s k_s^T.
 // Everything but the inverse is a small matrix product on v_mfma_f32_16x16x32_bf16; T = (I + A)^-1 is
-// computed in fp32 by one wavefront: the four 16 x 16 diagonal blocks by forward substitution (a lane
-// per column), the six blocks below them by block substitution on v_mfma_f32_16x16x4_f32.
-// A workgroup (4 wavefronts) owns one (sequence, head, segment of the sequence) and walks its chunks in
+// computed in fp32: the four 16 x 16 diagonal blocks by forward substitution (one wavefront, a lane per
+// column), the six blocks below them by block substitution on v_mfma_f32_16x16x4_f32.  T and the decayed
+// scores Q K^T do not depend on the state: gdn_prep_kernel forms them for all chunks at once.
+// In the recurrence a workgroup (4 wavefronts) owns one (sequence, head, segment of the sequence) and walks its chunks in
 // order.  Few (sequence, head) pairs: the sequences are cut into segments.  A segment's effect on the
 // state is S_end = S_start Phi + Z with Phi = prod_t exp(g_t)(I - beta_t k_t k_t^T) a d_k x d_k MATRIX, so
 // the carry pass runs the same rule on the state augmented by d_k more "value" rows that start from the
@@ -35,25 +36,36 @@ using namespace chunk;
 constexpr int kV = 64;          // value channels per head
 constexpr float kL2Eps = 1e-6f;
 
+// The step-parallel part of a chunk needs no state: it runs over all chunks at once, ahead of the recurrence.
 template <int NS>
-struct GdnSmem {
+struct GdnPrepSmem {
   union {
     struct {
       bf16_t kn[kQ][NS + 8];    // normalised keys, step-major
       bf16_t qr[kQ][NS + 8];    // raw queries, step-major
     } in;
-    float tm[kQ][kQ + 4];       // after the scores: T = (I + A)^-1 in fp32
+    float tm[kQ][kQ + 4];       // after the scores: T = (I + A)^-1
   } u;
-  union {
-    float am[kQ][kQ + 4];       // A (strictly lower triangle), fp32
-    float y[kQ][kV + 4];        // later in the chunk: the output tile
-  } a;
-  bf16_t vt[kQ][kV + 8];        // values, step-major
-  bf16_t kw_t[NS][kQ + 8];      // exp(cum_64 - cum_s) k_s, channel-major, 16-byte pieces swizzled
-  bf16_t tb[kQ][kQ + 8];        // T in bf16 [t][s]
-  bf16_t gs[kQ][kQ + 8];        // exp(cum_t - cum_s) (q_t . k_s), s <= t, [t][s]
-  float cum[kQ], ecum[kQ], beta[kQ], rq[kQ];
+  float am[kQ][kQ + 4];         // A (strictly lower triangle)
+  float cum[kQ], beta[kQ];
 };
+
+template <int NS, bool CARRY>
+struct GdnSmem {
+  bf16_t kn[kQ][NS + 8];                  // normalised keys, step-major
+  bf16_t vt[kQ][kV + 8];                  // values, step-major
+  bf16_t kw_t[NS][kQ + 8];                // exp(cum_64 - cum_s) k_s, channel-major, 16-byte pieces swizzled
+  bf16_t qr[CARRY ? 1 : kQ][NS + 8];      // raw queries, step-major
+  float y[CARRY ? 1 : kQ][kV + 4];        // the output tile
+  float ecum[kQ], beta[kQ], rq[kQ];
+};
+
+// Operand fragments of a chunk in HBM: T, then G = exp(cum_t - cum_s) (q_t . k_s), s <= t, both in bf16 and
+// lower triangular.  Fragment (tb, k2) covers rows 16 tb .. +15 and columns 32 k2 .. +31; the two that lie
+// above the diagonal do not exist.  Lane (g, c) owns row 16 tb + c, columns 32 k2 + 4 g .. +3 and 32 k2 + 16 + 4 g .. +3.
+constexpr int kFrags = 6;
+constexpr size_t kFragFloats = 2 * kFrags * 64 * 4;       // of one chunk, in floats
+__device__ __forceinline__ constexpr int frag_id(int tb, int k2) { return k2 == 0 ? tb : 2 + tb; }
 
 __device__ __forceinline__ float sum_sq8(const u32x4_t &v) {
   float s = 0.0f;
@@ -72,10 +84,10 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
-// T = (I + A)^-1 for the 64 x 64 unit lower-triangular I + A: am -> tm (fp32), tb (bf16).  Called by the
+// T = (I + A)^-1 for the 64 x 64 unit lower-triangular I + A: am -> tm (blocks on and below the diagonal).  Called by the
 // whole workgroup (it contains barriers): wavefront 0 solves the four diagonal blocks, then the blocks
 // at distance 1, 2, 3 below the diagonal are computed level by level, one block per wavefront.
-__device__ __forceinline__ void invert_unit_lower(const float (*am)[kQ + 4], float (*tm)[kQ + 4], bf16_t (*tb)[kQ + 8],
+__device__ __forceinline__ void invert_unit_lower(const float (*am)[kQ + 4], float (*tm)[kQ + 4],
                                                   int lane, int wave) {
   const int g = lane >> 4, c = lane & 15;
   // diagonal blocks: lane (g, c) solves column c of block g by forward substitution
@@ -91,13 +103,7 @@ __device__ __forceinline__ void invert_unit_lower(const float (*am)[kQ + 4], flo
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      tm[16 * g + r][16 * g + c] = x[r];
-      tb[16 * g + r][16 * g + c] = f32_to_bf16(x[r]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)            // blocks above the diagonal are zero
-        if (j > g) tb[16 * g + r][16 * j + c] = 0;
-    }
+    for (int r = 0; r < 16; ++r) tm[16 * g + r][16 * g + c] = x[r];
   }
   __syncthreads();
   // blocks below the diagonal, by distance d from it: T_ij = -T_ii sum_{m = j .. i-1} A_im T_mj, i = j + d
@@ -121,33 +127,131 @@ __device__ __forceinline__ void invert_unit_lower(const float (*am)[kQ + 4], flo
       for (int q = 0; q < 4; ++q)
         res = __builtin_amdgcn_mfma_f32_16x16x4f32(tm[16 * i + c][16 * i + 4 * g + q], macc[q], res, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        tm[16 * i + 4 * g + r][16 * j + c] = -res[r];
-        tb[16 * i + 4 * g + r][16 * j + c] = f32_to_bf16(-res[r]);
-      }
+      for (int r = 0; r < 4; ++r) tm[16 * i + 4 * g + r][16 * j + c] = -res[r];
     }
     __syncthreads();
   }
 }
 
-// Grid (n_heads, B).
+// What a chunk needs besides the state: T and the decayed scores G of every (sequence, chunk, head), one
+// workgroup each (grid 1-D: heads fastest, then chunks, then sequences), written as operand fragments.
+// The inverse is a serial chain (forward substitution, then three levels of small products); inside the
+// recurrence, one workgroup per CU, it stood in every chunk's critical path and was done twice, in the carry
+// and in the main pass.  Here three or four workgroups share a CU and cover one another's waits, and the
+// recurrence, without the inverse's LDS and registers, runs two to a CU.  Layer at 1 x 16384 x 2048, 32 heads:
+// 1.33 -> 1.20 ms (d_k 64); recurrence with carry and fold 0.60 -> 0.37 ms.
+template <int NS>
+__global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
+    const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col, const bf16_t *__restrict__ proj, int64_t ld_p,
+    int b_col, int a_col, const float *__restrict__ dt_bias, const float *__restrict__ A_log, int64_t L, int n_chunks,
+    int n_heads, u32x4_t *__restrict__ frags) {
+  __shared__ GdnPrepSmem<NS> sm;
+  constexpr int kKS = NS / 32;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int h = blockIdx.x % n_heads;
+  const int64_t bc = blockIdx.x / n_heads;
+  const int64_t b = bc / n_chunks, chunk = bc % n_chunks, t0 = chunk * kQ;
+  const bf16_t *qkv_b = qkv + b * L * ld_qkv;
+
+  u32x4_t pk[NS / 32], pq[NS / 32];
+#pragma unroll
+  for (int i = 0; i < NS / 32; ++i) {
+    const int piece = tid + 256 * i;
+    const int64_t t = t0 + piece / (NS / 8);
+    const bf16_t *row = qkv_b + (t < L ? t : L - 1) * ld_qkv + h * NS + 8 * (piece % (NS / 8));
+    pk[i] = *reinterpret_cast<const u32x4_t *>(row + k_col);
+    pq[i] = *reinterpret_cast<const u32x4_t *>(row + q_col);
+  }
+  if (wave == 3) {
+    const bool live = t0 + lane < L;
+    const bf16_t *row = proj + (b * L + (live ? t0 + lane : L - 1)) * ld_p;
+    const float pb = bf16_to_f32(row[b_col + h]), pa = bf16_to_f32(row[a_col + h]);
+    const float beta = live ? fast_rcp(1.0f + __expf(-pb)) : 0.0f;
+    const float gl = live ? -__expf(A_log[h]) * softplus_f32(pa + dt_bias[h]) : 0.0f;
+    sm.cum[lane] = wave_inclusive_sum(gl);
+    sm.beta[lane] = beta;
+  }
+#pragma unroll
+  for (int i = 0; i < NS / 32; ++i) {
+    const int piece = tid + 256 * i;
+    const int row = piece / (NS / 8), oc = piece % (NS / 8);
+    if (t0 + row >= L) pk[i] = pq[i] = u32x4_t{0u, 0u, 0u, 0u};
+    const float rk = rsqrtf(group_sum<NS / 8>(sum_sq8(pk[i])) + kL2Eps);
+    *reinterpret_cast<u32x4_t *>(&sm.u.in.kn[row][8 * oc]) = scale8(pk[i], rk);
+    *reinterpret_cast<u32x4_t *>(&sm.u.in.qr[row][8 * oc]) = pq[i];
+  }
+  __syncthreads();
+
+  // scores of this wavefront's 16 steps t = 16 wave + c against all s <= t, computed transposed: a lane's
+  // values of G are the row segment that its fragments hold
+  u32x4_t *out = frags + ((b * n_heads + h) * n_chunks + chunk) * (2 * kFrags * 64) + lane;
+  {
+    const float cum_t = sm.cum[16 * wave + c], beta_t = sm.beta[16 * wave + c];
+    u32x2_t gpk[4];
+#pragma unroll
+    for (int sb = 0; sb < 4; ++sb) {
+      f32x4_t kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = {0.0f, 0.0f, 0.0f, 0.0f};
+      gpk[sb] = u32x2_t{0u, 0u};
+      if (sb > wave) continue;
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks) {
+        const bf16x8_t fa = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.in.kn[16 * sb + c][32 * ks + 8 * g]));
+        const bf16x8_t fk = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.in.kn[16 * wave + c][32 * ks + 8 * g]));
+        const bf16x8_t fq = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.in.qr[16 * wave + c][32 * ks + 8 * g]));
+        kk = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fk, kk, 0, 0, 0);
+        qk = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fq, qk, 0, 0, 0);
+      }
+      const f32x4_t cum_s = *reinterpret_cast<const f32x4_t *>(&sm.cum[16 * sb + 4 * g]);
+      f32x4_t av;
+      float gv[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = 16 * sb + 4 * g + r, t = 16 * wave + c;
+        const float dec = s <= t ? fast_exp2((cum_t - cum_s[r]) * kLog2e) : 0.0f;
+        av[r] = s < t ? beta_t * dec * kk[r] : 0.0f;
+        gv[r] = dec * qk[r];
+      }
+      *reinterpret_cast<f32x4_t *>(&sm.am[16 * wave + c][16 * sb + 4 * g]) = av;
+      gpk[sb] = u32x2_t{pack_bf16x2(gv[0], gv[1]), pack_bf16x2(gv[2], gv[3])};
+    }
+    out[(kFrags + frag_id(wave, 0)) * 64] = u32x4_t{gpk[0][0], gpk[0][1], gpk[1][0], gpk[1][1]};
+    if (wave >= 2) out[(kFrags + frag_id(wave, 1)) * 64] = u32x4_t{gpk[2][0], gpk[2][1], gpk[3][0], gpk[3][1]};
+  }
+  __syncthreads();                // A is complete; the step-major keys and queries are no longer read
+  invert_unit_lower(sm.am, sm.u.tm, lane, wave);
+
+#pragma unroll
+  for (int k2 = 0; k2 < 2; ++k2) {
+    if (k2 == 1 && wave < 2) break;
+    const float *row = &sm.u.tm[16 * wave + c][32 * k2 + 4 * g];
+    f32x4_t lo = *reinterpret_cast<const f32x4_t *>(row), hi = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (2 * k2 + 1 <= wave) hi = *reinterpret_cast<const f32x4_t *>(row + 16);       // blocks above the diagonal are zero
+    out[frag_id(wave, k2) * 64] = u32x4_t{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(hi[0], hi[1]),
+                                          pack_bf16x2(hi[2], hi[3])};
+  }
+}
+
 //   qkv   bf16 [B*L, ld_qkv] after conv + SiLU: q of head h at q_col + NS h, k at k_col + NS h, v at v_col + 64 h
 //   proj  bf16 [B*L, ld_p]: z of head h at columns 64 h, the beta logit at b_col + h, the decay logit at a_col + h
 //   s_in / s_out f32 [B][H][NS][64] (S^T: [d_k][d_v]) or NULL;   y bf16 [B*L, ld_y]: RMSNorm_head(o) * norm_w * SiLU(z)
 // Grid (n_heads, B * n_seg).  CARRY: the carry pass (no queries, no outputs; segments before the last):
 //   carry_z f32 [B][H][n_seg][NS][64] <- Z^T, carry_m f32 [B][H][n_seg][NS][NS] <- [n][j] = Phi[j][n].
+//   frags: gdn_prep_kernel's T and G of every chunk
 // Main pass with n_seg > 1: segment `seg` starts from s_start f32 [B][H][n_seg][NS][64].
 template <int NS, bool CARRY>
-__global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col,
+__global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col,
                                                      int v_col, const bf16_t *__restrict__ proj, int64_t ld_p, int b_col,
                                                      int a_col, const float *__restrict__ dt_bias,
                                                      const float *__restrict__ A_log, const float *__restrict__ norm_w,
-                                                     float eps, int64_t L, int n_seg, int64_t seg_len,
+                                                     float eps, int64_t L, int n_seg, int64_t seg_len, int n_chunks,
+                                                     const u32x4_t *__restrict__ frags,
                                                      float *__restrict__ carry_z, float *__restrict__ carry_m,
                                                      const float *__restrict__ s_start, const float *s_in, float *s_out,
                                                      bf16_t *__restrict__ y, int64_t ld_y) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  GdnSmem<NS> &sm = *reinterpret_cast<GdnSmem<NS> *>(smem_raw);
+  GdnSmem<NS, CARRY> &sm = *reinterpret_cast<GdnSmem<NS, CARRY> *>(smem_raw);
   constexpr int kNB = NS / 16, kKS = NS / 32;
   constexpr int kG = CARRY ? 1 + NS / 64 : 1;      // groups of 64 "value" columns: the state, and in the carry pass Phi
   const int tid = threadIdx.x, lane = tid & 63;
@@ -192,7 +296,6 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
   const int lt = is_k ? tid : tid - NS;
   const int n_co = is_k ? NS / 8 : kV / 8;
   const int so = lt / n_co, co = lt % n_co;
-  const int so_phys = so ^ (co & 7);
   const int t_col = is_k ? k_col + h * NS + 8 * co : v_col + h * kV + 8 * co;
   const int e_row = tid >> 3, e_po = tid & 7;
 
@@ -232,6 +335,7 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
   };
   fetch_main(ts);
   fetch_out(ts);
+  const u32x4_t *frag_ptr = frags + ((b * n_heads + h) * n_chunks + ts / kQ) * (2 * kFrags * 64) + lane;
 
   for (int64_t t0 = ts; t0 < te; t0 += kQ) {
     // The lane's coordinates go through an opaque copy every chunk: with them loop-invariant the compiler
@@ -261,7 +365,7 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const float rk = rsqrtf(group_sum<NS / 8>(sum_sq8(pv[i])) + kL2Eps);
-          *reinterpret_cast<u32x4_t *>(&sm.u.in.kn[8 * soq + i][8 * coq]) = scale8(pv[i], rk);
+          *reinterpret_cast<u32x4_t *>(&sm.kn[8 * soq + i][8 * coq]) = scale8(pv[i], rk);
           kw[i] = scale8(pv[i], rk * __shfl(w_lane, 8 * soq + i));
         }
         park_8x8<kQ + 8>(kw, sm.kw_t, 8 * coq, 8 * sopq);
@@ -277,55 +381,26 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
         const int row = piece / (NS / 8), oc = piece % (NS / 8);
         u32x4_t v = pq[i];
         if (t0 + row >= te) v = u32x4_t{0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4_t *>(&sm.u.in.qr[row][8 * oc]) = v;
+        *reinterpret_cast<u32x4_t *>(&sm.qr[row][8 * oc]) = v;
         const float ss = group_sum<NS / 8>(sum_sq8(v));
         if (oc == 0) sm.rq[row] = rsqrtf(ss + kL2Eps) * q_scale;
       }
     }
     if (wave == 3) {
-      sm.cum[lane] = cum;
       sm.ecum[lane] = fast_exp2(cum * kLog2e);
       sm.beta[lane] = beta;
     }
     __syncthreads();
     fetch_main(t0 + kQ);
 
-    // ---- scores of this wavefront's 16 steps t = 16 wave + cq against all s (computed transposed),
-    //      and the two products with the state the chunk starts from
-    {
-      const float cum_t = sm.cum[16 * wave + cq], beta_t = sm.beta[16 * wave + cq];
+    // this chunk's T and G, wanted after the products with the state the chunk starts from
+    u32x4_t tfr[kFrags], gfr[kFrags];
 #pragma unroll
-      for (int sb = 0; sb < 4; ++sb) {
-        f32x4_t kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (sb <= wave) {
-#pragma unroll
-          for (int ks = 0; ks < kKS; ++ks) {
-            const bf16x8_t fa = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.in.kn[16 * sb + cq][32 * ks + 8 * gq]));
-            const bf16x8_t fk = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.in.kn[16 * wave + cq][32 * ks + 8 * gq]));
-            kk = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fk, kk, 0, 0, 0);
-            if (!CARRY) {
-              const bf16x8_t fq = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.in.qr[16 * wave + cq][32 * ks + 8 * gq]));
-              qk = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fq, qk, 0, 0, 0);
-            }
-          }
-        }
-        const f32x4_t cum_s = *reinterpret_cast<const f32x4_t *>(&sm.cum[16 * sb + 4 * gq]);
-        f32x4_t av;
-        float gv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int s = 16 * sb + 4 * gq + r, t = 16 * wave + cq;
-          const float dec = s <= t ? fast_exp2((cum_t - cum_s[r]) * kLog2e) : 0.0f;
-          av[r] = s < t ? beta_t * dec * kk[r] : 0.0f;
-          gv[r] = dec * qk[r];
-        }
-        *reinterpret_cast<f32x4_t *>(&sm.a.am[16 * wave + cq][16 * sb + 4 * gq]) = av;
-        if (!CARRY) {
-          const u32x2_t packed = {pack_bf16x2(gv[0], gv[1]), pack_bf16x2(gv[2], gv[3])};
-          *reinterpret_cast<u32x2_t *>(&sm.gs[16 * wave + cq][16 * sb + 4 * gq]) = packed;
-        }
-      }
+    for (int i = 0; i < kFrags; ++i) {
+      tfr[i] = frag_ptr[i * 64];
+      if (!CARRY) gfr[i] = frag_ptr[(kFrags + i) * 64];
     }
+    frag_ptr += 2 * kFrags * 64;
     bf16x8_t sop[kG][kKS];
 #pragma unroll
     for (int grp = 0; grp < kG; ++grp)
@@ -340,11 +415,11 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
       oacc[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks) {
-        const bf16x8_t fk = frag_perm<NS + 8>(sm.u.in.kn, 16 * tb + cq, 32 * ks, gq);
+        const bf16x8_t fk = frag_perm<NS + 8>(sm.kn, 16 * tb + cq, 32 * ks, gq);
 #pragma unroll
         for (int grp = 0; grp < kG; ++grp) pacc[grp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fk, sop[grp][ks], pacc[grp], 0, 0, 0);
         if (!CARRY)
-          oacc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_perm<NS + 8>(sm.u.in.qr, 16 * tb + cq, 32 * ks, gq), sop[0][ks],
+          oacc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_perm<NS + 8>(sm.qr, 16 * tb + cq, 32 * ks, gq), sop[0][ks],
                                                              oacc[tb], 0, 0, 0);
       }
       const f32x4_t e = *reinterpret_cast<const f32x4_t *>(&sm.ecum[16 * tb + 4 * gq]);
@@ -358,10 +433,6 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
         oacc[tb][r] *= e[r];                                  // gamma_t S_0 q_t
       }
     }
-    __syncthreads();                // A is complete; the step-major keys and queries are no longer read
-
-    invert_unit_lower(sm.a.am, sm.u.tm, sm.tb, opaque(lane), wave);
-
     // ---- U = T rhs (rows t, this wavefront's 16 value channels); the contraction runs over steps,
     //      with rhs taken from the accumulators
     f32x4_t uacc[kG][4];
@@ -378,7 +449,7 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2)
           if (k2 == 0 || tb >= 2) {
-            const bf16x8_t ft = frag_perm<kQ + 8>(sm.tb, 16 * tb + cq, 32 * k2, gq);
+            const bf16x8_t ft = as_frag(tfr[frag_id(tb, k2)]);
 #pragma unroll
             for (int grp = 0; grp < kG; ++grp)
               uacc[grp][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft, rop[grp][k2], uacc[grp][tb], 0, 0, 0);
@@ -397,8 +468,7 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2)
           if (k2 == 0 || tb >= 2)
-            oacc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_perm<kQ + 8>(sm.gs, 16 * tb + cq, 32 * k2, gq), uop[0][k2],
-                                                               oacc[tb], 0, 0, 0);
+            oacc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(gfr[frag_id(tb, k2)]), uop[0][k2], oacc[tb], 0, 0, 0);
     }
     // state at the chunk's end: S^T = gamma_64 S^T + sum_s (exp(cum_64 - cum_s) k_s) u_s^T
     {
@@ -429,15 +499,15 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
     for (int tb = 0; tb < 4; ++tb) {
       const f32x4_t rq = *reinterpret_cast<const f32x4_t *>(&sm.rq[16 * tb + 4 * gq]);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sm.a.y[16 * tb + 4 * gq + r][16 * wave + cq] = oacc[tb][r] * rq[r];
+      for (int r = 0; r < 4; ++r) sm.y[16 * tb + 4 * gq + r][16 * wave + cq] = oacc[tb][r] * rq[r];
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int row = erq + 32 * i;
       const int64_t t = t0 + row;
-      const f32x4_t y0 = *reinterpret_cast<const f32x4_t *>(&sm.a.y[row][8 * epq]);
-      const f32x4_t y1 = *reinterpret_cast<const f32x4_t *>(&sm.a.y[row][8 * epq + 4]);
+      const f32x4_t y0 = *reinterpret_cast<const f32x4_t *>(&sm.y[row][8 * epq]);
+      const f32x4_t y1 = *reinterpret_cast<const f32x4_t *>(&sm.y[row][8 * epq + 4]);
       float ss = 0.0f;
 #pragma unroll
       for (int m = 0; m < 4; ++m) ss = fmaf(y0[m], y0[m], fmaf(y1[m], y1[m], ss));
@@ -475,54 +545,61 @@ __global__ __launch_bounds__(256, 1) void gdn_kernel(const bf16_t *__restrict__ 
   }
 }
 
-// The state every segment starts from: start[0] = s_in (or 0), start[j + 1]^T = M_j start[j]^T + Z_j^T with the
-// carry pass's arrays as stored (M_j[n][m] = Phi_j[m][n]).  Grid (n_heads, B); a thread owns NS / 4 columns of one row.
 // Workgroup barrier for data that travels through LDS only: __syncthreads() also waits for the wave's
-// outstanding global stores, a memory round trip behind every barrier that follows one (the fold stores a
-// segment's start state right before it parks it)
+// outstanding global accesses, a memory round trip behind every barrier
 __device__ __forceinline__ void fold_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// The state every segment starts from: start[0] = s_in (or 0), start[j + 1]^T = M_j start[j]^T + Z_j^T with the
+// carry pass's arrays as stored (M_j[n][m] = Phi_j[m][n]).  The value channels are independent: grid
+// (n_heads, B, 4), 16 of them per workgroup; a thread owns NS / 16 columns of one row and holds its row of M,
+// requested a whole segment ahead.  The chain over the segments is latency: one workgroup per head that fetched M in
+// batches took 7.5 us a segment.
 template <int NS>
 __global__ __launch_bounds__(256) void gdn_fold_kernel(const float *__restrict__ carry_z, const float *__restrict__ carry_m,
                                                        const float *__restrict__ s_in, float *__restrict__ s_start,
                                                        int n_seg) {
-  constexpr int kCols = NS / 4, kPerRow = kV / kCols;       // columns per thread, threads per row
-  __shared__ float cur[NS][kV + 1];
+  constexpr int kCols = NS / 16, kPerRow = 16 / kCols;      // columns per thread, threads per row
+  __shared__ float cur[2][NS][16];
   const int tid = threadIdx.x, n = tid / kPerRow, v0 = (tid % kPerRow) * kCols;
   const int h = blockIdx.x, n_heads = gridDim.x;
   const int64_t bh = static_cast<int64_t>(blockIdx.y) * n_heads + h;
   const int64_t s_stride = static_cast<int64_t>(NS) * kV;
-  float acc[kCols];
-#pragma unroll
-  for (int i = 0; i < kCols; ++i) acc[i] = s_in ? s_in[bh * s_stride + n * kV + v0 + i] : 0.0f;
-  for (int j = 0; j < n_seg; ++j) {
+  const int64_t at = n * kV + 16 * blockIdx.z + v0;         // this thread's columns within a state
+  f32x4_t m_next[NS / 4], z_next[kCols / 4];
+  auto fetch = [&](int j) {
     const int64_t unit = bh * n_seg + j;
-#pragma unroll
-    for (int i = 0; i < kCols; ++i) {
-      s_start[unit * s_stride + n * kV + v0 + i] = acc[i];
-      cur[n][v0 + i] = acc[i];
-    }
-    if (j == n_seg - 1) break;
-    fold_barrier();
     const float *mrow = carry_m + unit * static_cast<int64_t>(NS) * NS + static_cast<int64_t>(n) * NS;
 #pragma unroll
-    for (int i = 0; i < kCols; ++i) acc[i] = carry_z[unit * s_stride + n * kV + v0 + i];
-    // (the row of M in batches of 16 values, four 16-byte loads at a time: value by value the loop is a
-    // chain of memory round trips)
-    for (int m0 = 0; m0 < NS; m0 += 16) {
-      float4 a4[4];
+    for (int q = 0; q < NS / 4; ++q) m_next[q] = *reinterpret_cast<const f32x4_t *>(mrow + 4 * q);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) a4[q] = *reinterpret_cast<const float4 *>(mrow + m0 + 4 * q);
+    for (int q = 0; q < kCols / 4; ++q) z_next[q] = *reinterpret_cast<const f32x4_t *>(carry_z + unit * s_stride + at + 4 * q);
+  };
+  f32x4_t acc[kCols / 4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float a[4] = {a4[q].x, a4[q].y, a4[q].z, a4[q].w};
+  for (int i = 0; i < kCols; ++i) acc[i / 4][i % 4] = s_in ? s_in[bh * s_stride + at + i] : 0.0f;
+  fetch(0);                                                 // n_seg >= 2 here: segment 0 has a carry
+  for (int j = 0; j < n_seg; ++j) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int i = 0; i < kCols; ++i) acc[i] = fmaf(a[r], cur[m0 + 4 * q + r][v0 + i], acc[i]);
-      }
+    for (int q = 0; q < kCols / 4; ++q) {
+      *reinterpret_cast<f32x4_t *>(s_start + (bh * n_seg + j) * s_stride + at + 4 * q) = acc[q];
+      *reinterpret_cast<f32x4_t *>(&cur[j & 1][n][v0 + 4 * q]) = acc[q];
     }
-    fold_barrier();
+    if (j == n_seg - 1) break;
+    fold_barrier();                                         // two buffers: one barrier a segment
+    f32x4_t m_cur[NS / 4];
+#pragma unroll
+    for (int q = 0; q < NS / 4; ++q) m_cur[q] = m_next[q];
+#pragma unroll
+    for (int q = 0; q < kCols / 4; ++q) acc[q] = z_next[q];
+    if (j + 1 < n_seg - 1) fetch(j + 1);
+#pragma unroll
+    for (int m = 0; m < NS; ++m)
+#pragma unroll
+      for (int q = 0; q < kCols / 4; ++q) {
+        const f32x4_t cv = *reinterpret_cast<const f32x4_t *>(&cur[j & 1][m][v0 + 4 * q]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[q][i] = fmaf(m_cur[m / 4][m % 4], cv[i], acc[q][i]);
+      }
   }
 }
 
@@ -605,9 +682,11 @@ struct GdnPlanSeg {
   int64_t seg_len;
 };
 GdnPlanSeg gdn_plan(int64_t B, int64_t L, int n_heads) {
-  // one workgroup for each of the 256 CUs; a segment is whole chunks and at least four of them
+  // Fewer than one workgroup for each of the 256 CUs: segments until there are two per CU (whole chunks, at least
+  // four).  Two against one per CU, layer at 1 x 16384 x 2048: 1.20 against 1.26 ms (d_k 64), 1.63 against 1.68 (128),
+  // 4 x 4096: 1.06 against 1.16.  From 256 workgroups on, the carry pass would cost what the second one gains.
   const int64_t chunks = ceil_div(L, kQ);
-  int64_t n_seg = ceil_div(256, B * n_heads);
+  int64_t n_seg = B * n_heads >= 256 ? 1 : ceil_div(512, B * n_heads);
   const int64_t max_seg = chunks / 4 > 0 ? chunks / 4 : 1;
   n_seg = n_seg < 1 ? 1 : (n_seg > max_seg ? max_seg : n_seg);
   GdnPlanSeg p;
@@ -629,7 +708,7 @@ hipError_t gdn_allow_lds() {
     std::lock_guard<std::mutex> lock(mu);
     if (!done[dev].load(std::memory_order_relaxed)) {
       e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gdn_kernel<NS, CARRY>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizeof(GdnSmem<NS>)));
+                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizeof(GdnSmem<NS, CARRY>)));
       if (e != hipSuccess) return e;
       done[dev].store(true, std::memory_order_release);
     }
@@ -649,23 +728,31 @@ hipError_t gdn_dispatch(const bf16_t *qkv, int64_t ld_qkv, int q_col, int k_col,
     return hipGetLastError();
   }
   const GdnPlanSeg p = gdn_plan(B, L, n_heads);
+  const int64_t n_chunks = ceil_div(L, kQ);
   const size_t units = static_cast<size_t>(B) * n_heads * p.n_seg;
+  u32x4_t *frags = reinterpret_cast<u32x4_t *>(carry);
+  carry += static_cast<size_t>(B) * n_heads * n_chunks * kFragFloats;
   float *carry_z = carry, *carry_m = carry + units * NS * kV, *s_start = carry_m + units * NS * NS;
   const dim3 grid(static_cast<unsigned>(n_heads), static_cast<unsigned>(B * p.n_seg));
   hipError_t e;
+  hipLaunchKernelGGL((gdn_prep_kernel<NS>), dim3(static_cast<unsigned>(B * n_chunks * n_heads)), dim3(256), 0, s, qkv, ld_qkv,
+                     q_col, k_col, proj, ld_p, b_col, a_col, dt_bias, A_log, L, static_cast<int>(n_chunks), n_heads, frags);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (p.n_seg > 1) {
     if ((e = gdn_allow_lds<NS, true>()) != hipSuccess) return e;
-    hipLaunchKernelGGL((gdn_kernel<NS, true>), grid, dim3(256), sizeof(GdnSmem<NS>), s, qkv, ld_qkv, q_col, k_col, v_col, proj,
-                       ld_p, b_col, a_col, dt_bias, A_log, norm_w, eps, L, p.n_seg, p.seg_len, carry_z, carry_m, s_start, s_in,
+    hipLaunchKernelGGL((gdn_kernel<NS, true>), grid, dim3(256), sizeof(GdnSmem<NS, true>), s, qkv, ld_qkv, q_col, k_col, v_col, proj,
+                       ld_p, b_col, a_col, dt_bias, A_log, norm_w, eps, L, p.n_seg, p.seg_len, static_cast<int>(n_chunks),
+                       frags, carry_z, carry_m, s_start, s_in,
                        s_out, y, ld_y);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((gdn_fold_kernel<NS>), dim3(static_cast<unsigned>(n_heads), static_cast<unsigned>(B)), dim3(256), 0, s,
+    hipLaunchKernelGGL((gdn_fold_kernel<NS>), dim3(static_cast<unsigned>(n_heads), static_cast<unsigned>(B), 4), dim3(256), 0, s,
                        carry_z, carry_m, s_in, s_start, p.n_seg);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = gdn_allow_lds<NS, false>()) != hipSuccess) return e;
-  hipLaunchKernelGGL((gdn_kernel<NS, false>), grid, dim3(256), sizeof(GdnSmem<NS>), s, qkv, ld_qkv, q_col, k_col, v_col, proj,
-                     ld_p, b_col, a_col, dt_bias, A_log, norm_w, eps, L, p.n_seg, p.seg_len, carry_z, carry_m, s_start, s_in,
+  hipLaunchKernelGGL((gdn_kernel<NS, false>), grid, dim3(256), sizeof(GdnSmem<NS, false>), s, qkv, ld_qkv, q_col, k_col, v_col, proj,
+                     ld_p, b_col, a_col, dt_bias, A_log, norm_w, eps, L, p.n_seg, p.seg_len, static_cast<int>(n_chunks),
+                       frags, carry_z, carry_m, s_start, s_in,
                      s_out, y, ld_y);
   return hipGetLastError();
 }
@@ -676,8 +763,10 @@ bool gdn_supported(int d_k, int d_v) { return d_v == kV && (d_k == 64 || d_k == 
 
 size_t gdn_carry_bytes(int64_t B, int64_t L, int n_heads, int d_k) {
   const GdnPlanSeg p = gdn_plan(B, L, n_heads);
-  if (p.n_seg <= 1) return 0;
-  return static_cast<size_t>(B) * n_heads * p.n_seg * (2 * static_cast<size_t>(d_k) * kV + static_cast<size_t>(d_k) * d_k) *
+  if (L <= 1) return 0;
+  const size_t frag_bytes = static_cast<size_t>(B) * n_heads * ceil_div(L, kQ) * kFragFloats * sizeof(float);
+  if (p.n_seg <= 1) return frag_bytes;
+  return frag_bytes + static_cast<size_t>(B) * n_heads * p.n_seg * (2 * static_cast<size_t>(d_k) * kV + static_cast<size_t>(d_k) * d_k) *
          sizeof(float);
 }
 
