@@ -239,7 +239,7 @@ def test_gdn_random_shapes(seed):
 def test_gdn_prepared_chunks_and_segments(seq_len, d_k):
     """T and the scores come from their own launch and are found by (sequence, head, chunk): more than one of
     each, sequences that end inside a chunk, states handed in."""
-    cfg = get_gdn_config("gdn_small", cfg_id=90, batch=2, seq_len=seq_len, d_model=136, n_heads=5, d_k=d_k, weight_std=0.05)
+    cfg = get_gdn_config("gdn_small", cfg_id=90, batch=2, seq_len=seq_len, d_model=136, n_heads=12, d_k=d_k, weight_std=0.05)
     rng = np.random.default_rng(cfg.cfg_id)
     cs = rng.standard_normal((cfg.batch, cfg.d_conv_ch, 3)).astype(np.float32)
     ss = (0.3 * rng.standard_normal((cfg.batch, cfg.n_heads, cfg.d_k, cfg.d_v))).astype(np.float32)
