@@ -724,6 +724,106 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
   dma_tile<BN, WM, WN, EPI, WT>(a, tc, smem);
 }
 
+// ------------------------------------------------------------------ bf16 MFMA kernel, few rows
+// A few sequences' recurrent step (kFewRows positions at most): the call is one pass over the weights of the picked
+// experts, bound by how much of it is in flight.  The 64-row tiles of the general kernel park 64 rows for the one or two
+// that exist, walk K serially with two slabs in flight and a barrier each.  Here a workgroup of eight wavefronts owns
+// 16 CT output columns of one expert's rows (CT = 2 from kFewWideCols columns on); the wavefronts deal the 64-wide units
+// of K among themselves, read both operands straight into fragments (no LDS, no barrier; four units of both requested at
+// once), and their partial sums are added through LDS in wavefront order.  The weight is the MFMA's row operand: lane
+// (c, g) ends with columns 4 g .. 4 g + 3 of position c.  Positions past the group's end repeat its first row and are not
+// stored.  One sequence, d_model 2048: with 64 x 64 tiles the in and out projections take 30 us each of a step of 91 us;
+// the step now takes 47 us.
+constexpr int kFewRows = 8, kFewWideCols = 4096;          // (a row tile holds 16)
+constexpr int kFewWaves = 8, kFewUnits = 4;
+typedef float f32x4_few_t __attribute__((ext_vector_type(4)));
+
+template <int CT, int EPI>
+__global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(const GemmArgs a) {
+  __shared__ float red[kFewWaves][CT][16][20];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, g = lane >> 4;
+  // blockIdx.z -> the z-th group that has a row: a lane per group (n_groups <= 64)
+  int group = 0, row0 = 0, row_end = static_cast<int>(a.M);
+  if (a.offsets) {
+    const int e = lane < a.n_groups ? lane : a.n_groups - 1;
+    const int lo = a.offsets[e], hi = a.offsets[e + 1];
+    unsigned long long used = __ballot(lane < a.n_groups && hi > lo);
+    for (unsigned skip = blockIdx.z; skip > 0 && used; --skip) used &= used - 1;
+    if (used == 0) return;                                     // fewer such groups than the grid allows for
+    group = __builtin_ctzll(used);
+    row0 = __shfl(lo, group);
+    row_end = __shfl(hi, group);
+  }
+  const int n0 = blockIdx.x * (16 * CT);
+  const int k0 = blockIdx.y * a.k_per_split;
+  const int k_end = k0 + a.k_per_split < a.K ? k0 + a.k_per_split : a.K;
+  const int units = (k_end - k0) / 64;
+  const int p_in = row0 + c < row_end ? row0 + c : row0;
+  const bf16_t *Ap = static_cast<const bf16_t *>(a.A) + (a.a_rows ? a.a_rows[p_in] : p_in) * a.lda + k0 + 8 * g;
+  const bf16_t *Wp[CT];
+#pragma unroll
+  for (int t = 0; t < CT; ++t) {
+    const int n = n0 + 16 * t + c < a.N ? n0 + 16 * t + c : a.N - 1;
+    Wp[t] = static_cast<const bf16_t *>(a.W) + (static_cast<int64_t>(group) * a.N + n) * a.K + k0 + 8 * g;
+  }
+  f32x4_few_t acc[CT];
+#pragma unroll
+  for (int t = 0; t < CT; ++t) acc[t] = f32x4_few_t{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int u0 = wave; u0 < units; u0 += kFewWaves * kFewUnits) {
+    bf16x8_t fw[kFewUnits][CT][2], fx[kFewUnits][2];
+#pragma unroll
+    for (int i = 0; i < kFewUnits; ++i) {
+      const int u = u0 + i * kFewWaves < units ? u0 + i * kFewWaves : u0;      // past the end: re-read, not multiplied
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t) fw[i][t][h] = *reinterpret_cast<const bf16x8_t *>(Wp[t] + u * 64 + h * 32);
+        fx[i][h] = *reinterpret_cast<const bf16x8_t *>(Ap + u * 64 + h * 32);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);                         // all requests ahead of the first wait
+#pragma unroll
+    for (int i = 0; i < kFewUnits; ++i) {
+      if (u0 + i * kFewWaves < units) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int t = 0; t < CT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i][t][h], fx[i][h], acc[t], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < CT; ++t) *reinterpret_cast<f32x4_few_t *>(&red[wave][t][c][4 * g]) = acc[t];
+  __syncthreads();
+  const int row = tid / (16 * CT), lc = tid % (16 * CT);
+  if (row >= 16 || row0 + row >= row_end || n0 + lc >= a.N) return;
+  const auto total = [&](int t, int q) __attribute__((always_inline)) {
+    float v = red[0][t][row][q];
+#pragma unroll
+    for (int w = 1; w < kFewWaves; ++w) v += red[w][t][row][q];
+    return v;
+  };
+  const int64_t crow = a.c_rows ? a.c_rows[row0 + row] : row0 + row;
+  float v = total(lc >> 4, lc & 15);
+  if constexpr (EPI == kEpiPlainF32) {
+    static_cast<float *>(a.C)[blockIdx.y * a.c_split_stride + crow * a.ldc + n0 + lc] = v;
+  } else if constexpr (EPI == kEpiSwiGLU) {                    // a block of 16 columns: 8 gate, then their 8 up features
+    if ((lc & 15) >= 8) return;
+    const float scale = a.row_scale ? a.row_scale[crow] : 1.0f;
+    const float up = total(lc >> 4, (lc & 15) + 8);
+    static_cast<bf16_t *>(a.C)[crow * a.ldc + (n0 + lc - (lc & 15)) / 2 + (lc & 15)] =
+        f32_to_bf16(silu_f32(v * scale) * (up * scale));
+  } else {
+    if constexpr (EPI == kEpiRowScale || EPI == kEpiRowScaleResidual) v *= a.row_scale ? a.row_scale[crow] : 1.0f;
+    bf16_t o = f32_to_bf16(v);
+    if constexpr (EPI == kEpiRowScaleResidual)                 // added to the rounded branch output, as in mfma_epilogue
+      o = f32_to_bf16(bf16_to_f32(o) + bf16_to_f32(static_cast<const bf16_t *>(a.residual)[crow * a.ldc + n0 + lc]));
+    static_cast<bf16_t *>(a.C)[crow * a.ldc + n0 + lc] = o;
+  }
+}
+
 // ------------------------------------------------------------------ bf16 MFMA kernel, one stream of slabs per CU
 // The large routed projections: bound by the power the matrix pipe draws (a slab of random operands takes 1.49 us, of zeros
 // 0.97; 0.85 is the pipe's own at 2.4 GHz), then by what stops it: the stores and the last round.  16384 rows in 8 groups,
@@ -1456,6 +1556,26 @@ inline bool stream_takes(const GemmArgs &a) {
   return a.M / groups >= 96 && tiles >= 192 && tiles * a.K >= (192 << 10);
 }
 
+// Which calls take the few-rows kernel: it gains while most experts have no row and few workgroups stream the weights; from
+// about 16 rows on, the tiled kernel's many workgroups keep the memory as busy.  Steps of 1 / 4 / 16 / 32 sequences, us,
+// against the tiled kernels: d_model 2048 52 / 80 / 121 / 133 against 93 / 98 / 123 / 126, d_model 768 38 / 44 / 58 / 63
+// against 49 / 51 / 55 / 56, delta rule 36 / 59 / 90 / 98 against 65 / 74 / 99 / 105.
+inline bool few_rows_takes(const GemmArgs &a) {
+  return a.M <= kFewRows && a.K % 64 == 0 && (a.offsets == nullptr || a.n_groups <= 64) && !a.w_kmajor;
+}
+
+template <int EPI>
+hipError_t launch_few_rows(const GemmArgs &a, hipStream_t s) {
+  const unsigned gz = static_cast<unsigned>(!a.offsets ? 1 : a.M < a.n_groups ? a.M : a.n_groups);
+  if (a.N >= kFewWideCols)
+    hipLaunchKernelGGL((gemm_bf16_few_rows_kernel<2, EPI>), dim3(static_cast<unsigned>(ceil_div(a.N, 32)), a.k_splits, gz),
+                       dim3(kFewWaves * 64), 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_bf16_few_rows_kernel<1, EPI>), dim3(static_cast<unsigned>(ceil_div(a.N, 16)), a.k_splits, gz),
+                       dim3(kFewWaves * 64), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int EPI>
 hipError_t launch_mfma_tiles(const GemmArgs &a, hipStream_t s) {
   const int64_t rows_per_group = a.M / (a.n_groups > 0 ? a.n_groups : 1);
@@ -1520,7 +1640,8 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
     return launch_stream<kEpiPlain, true>(a, s);
   }
   if (a.swiglu && !mfma_ok) return hipErrorInvalidValue;      // the caller asks grouped_gemm_on_mfma first
-  if (a.swiglu) return launch_mfma_tiles<kEpiSwiGLU>(a, s);
+  const bool few = mfma_ok && few_rows_takes(a);
+  if (a.swiglu) return few ? launch_few_rows<kEpiSwiGLU>(a, s) : launch_mfma_tiles<kEpiSwiGLU>(a, s);
   if (!mfma_ok) {
     const dim3 grid(grid_tiles(a, kSB, kSB), a.k_splits);
     if (a.dtype == ROM_DTYPE_BF16)
@@ -1529,6 +1650,7 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
       hipLaunchKernelGGL(gemm_simple_kernel<float>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
   }
+  if (few && a.c_is_f32) return launch_few_rows<kEpiPlainF32>(a, s);
   if (a.c_is_f32) {
     if (a.N <= 192) {
       // one column tile: every workgroup re-reads the whole weight slice of its group, so take the
@@ -1568,6 +1690,8 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
     if (a.K == 64) return launch_smallk<4, true>(a, s);
     return launch_smallk<2, true>(a, s);
   }
+  if (few) return a.residual ? launch_few_rows<kEpiRowScaleResidual>(a, s)
+                : a.row_scale ? launch_few_rows<kEpiRowScale>(a, s) : launch_few_rows<kEpiPlain>(a, s);
   if (a.residual) return launch_mfma_tiles<kEpiRowScaleResidual>(a, s);
   if (a.row_scale) return launch_mfma_tiles<kEpiRowScale>(a, s);
   return launch_mfma_tiles<kEpiPlain>(a, s);
