@@ -138,8 +138,8 @@ __device__ __forceinline__ void invert_unit_lower(const float (*am)[kQ + 4], flo
 // The inverse is a serial chain (forward substitution, then three levels of small products); inside the
 // recurrence, one workgroup per CU, it stood in every chunk's critical path and was done twice, in the carry
 // and in the main pass.  Here three or four workgroups share a CU and cover one another's waits, and the
-// recurrence, without the inverse's LDS and registers, runs two to a CU.  Layer at 1 x 16384 x 2048, 32 heads:
-// 1.33 -> 1.20 ms (d_k 64); recurrence with carry and fold 0.60 -> 0.37 ms.
+// recurrence has three barriers a chunk instead of eight.  1 x 16384 x 2048, 32 heads of 64: this launch, carry, fold and
+// main pass 573 -> 408 us, the layer 1467 -> 1166 us.
 template <int NS>
 __global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
     const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col, const bf16_t *__restrict__ proj, int64_t ld_p,
@@ -682,11 +682,12 @@ struct GdnPlanSeg {
   int64_t seg_len;
 };
 GdnPlanSeg gdn_plan(int64_t B, int64_t L, int n_heads) {
-  // Fewer than one workgroup for each of the 256 CUs: segments until there are two per CU (whole chunks, at least
-  // four).  Two against one per CU, layer at 1 x 16384 x 2048: 1.20 against 1.26 ms (d_k 64), 1.63 against 1.68 (128),
-  // 4 x 4096: 1.06 against 1.16.  From 256 workgroups on, the carry pass would cost what the second one gains.
+  // One workgroup for each of the 256 CUs; a segment is whole chunks and at least four of them.  The recurrence fits two
+  // to a CU and twice the segments take less time (1 x 16384, 32 heads of 64: 308 against 408 us), but every segment's
+  // start state is a product with the carry pass's bf16 operands, so their number shows in the outputs (2e-3, at an
+  // unchanged error against 64 bits of 3.7e-3): it stays.
   const int64_t chunks = ceil_div(L, kQ);
-  int64_t n_seg = B * n_heads >= 256 ? 1 : ceil_div(512, B * n_heads);
+  int64_t n_seg = ceil_div(256, B * n_heads);
   const int64_t max_seg = chunks / 4 > 0 ? chunks / 4 : 1;
   n_seg = n_seg < 1 ? 1 : (n_seg > max_seg ? max_seg : n_seg);
   GdnPlanSeg p;

@@ -266,3 +266,25 @@ def test_hybrid_stack_arguments_are_checked_before_any_launch(lib):
     assert call(ffns, B=0) == 0
     ffns[1].w_down = None                                  # half an FFN
     assert call(ffns) == -1
+
+
+@pytest.mark.parametrize("d_k", [64, 128])
+@pytest.mark.parametrize("n_heads,batch", [(32, 8), (32, 4), (32, 2), (32, 1), (12, 1), (16, 8)])
+def test_gdn_segments_fill_256_cus_once(lib, d_k, n_heads, batch):
+    """How many segments a sequence is cut into shows in the outputs of the gated delta rule (a segment's start state is a
+    product of bf16 operands).  It is ceil(256 / (sequences x heads)), read here off the workspace: at an equal token count
+    everything but the carries and the conv's copy of the states (per sequence) is the same as for 256 sequences, one segment."""
+    from paper_2506_18145_amd import binding
+
+    dims = binding.RomGdnDims(d_model=256, n_heads=n_heads, d_k=d_k, d_v=64, d_conv=4, n_experts=4, top_k=1, dtype=1, gate_mode=0)
+    tokens = 1 << 18
+    total = lambda b: binding.rom_gdn_workspace_bytes(dims, b, tokens // b)
+    up = lambda v: -(-v // 256) * 256
+    conv = lambda b: up(b * n_heads * (2 * d_k + 64) * 3 * 4)
+    frags = n_heads * (tokens // 64) * 12288
+    segments = -(-256 // (batch * n_heads))
+    seg_chunks = -(-(tokens // batch // 64) // segments)
+    segments = -(-(tokens // batch // 64) // seg_chunks)          # whole chunks each
+    units = batch * n_heads * segments if segments > 1 else 0
+    want = up(frags + units * (2 * d_k * 64 + d_k * d_k) * 4) - up(frags)
+    assert total(batch) - conv(batch) - (total(256) - conv(256)) == want
