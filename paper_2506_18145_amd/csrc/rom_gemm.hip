@@ -951,12 +951,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     return static_cast<const char *>(a.W) + at * 2;
   };
   const int64_t a_step = kDmaBK * 2, w_step = WT ? static_cast<int64_t>(kDmaBK) * a.N * 2 : kDmaBK * 2;
-  // an index load whose result may be used behind the next slab's barrier only (the waits there count every vector
-  // memory instruction, the compiler's own count would not know the DMA ones)
+  // A row number or scale word, asked for a slab before its use.  An ordinary load: the compiler waits for it wherever it
+  // touches the register, be it to spill it.  Its count does not know the DMA requests, which only makes that wait
+  // longer (it ends when the newest of them has landed).
   auto load_idx = [](const void *base, unsigned voff) __attribute__((always_inline)) {
-    int v;
-    asm volatile("global_load_dword %0, %1, %2" : "=v"(v) : "v"(voff), "s"(base) : "memory");
-    return v;
+    typedef const __attribute__((address_space(1))) char gbyte_t;
+    return *reinterpret_cast<const __attribute__((address_space(1))) int *>(reinterpret_cast<gbyte_t *>(reinterpret_cast<uintptr_t>(base)) + voff);
   };
 
   // ---- MFMA side
