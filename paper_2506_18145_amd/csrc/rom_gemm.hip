@@ -16,6 +16,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "rom_gemm_rule.h"
 #include "rom_internal.h"
 
 namespace rom {
@@ -547,8 +548,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_mfma_kernel(const GemmA
 // 128-byte rows.  The compiler does not see these loads (inline asm), so the waits are explicit:
 // every wave issues the same number of loads per half slab, in ring order, and a vmcnt of that number
 // therefore means "everything but the newest half slab I asked for has landed".
-// dma_tile is one tile of that kind: the x projection's (256 rows, one narrow column tile) and the pieces
-// of the stream kernel's last round.
+// dma_tile is one tile of that kind: the x projection's (256 rows, one narrow column tile), a whole 256 x 256 one for the
+// epilogues that the stream kernel has not, and the pieces of the stream kernel's last round.
 constexpr int kDmaBK = 64, kDmaRC = kDmaBK / 8, kDmaSlots = 5;
 constexpr bool kUseDma = true;
 constexpr int kSkinnyMinWgs = 100;
@@ -716,12 +717,12 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
   mfma_epilogue<EPI, TM, TN, WTM, WTN>(a, tc, acc, smem, wave, wm, wn, lane);
 }
 
-template <int BN, int WM, int WN, int EPI, bool WT = false>
+template <int BN, int WM, int WN, int EPI>
 __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint4 smem[];
   const TileCoord tc = locate_tile(a, 256, BN);
   if (!tc.valid) return;
-  dma_tile<BN, WM, WN, EPI, WT>(a, tc, smem);
+  dma_tile<BN, WM, WN, EPI>(a, tc, smem);
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, few rows
@@ -1517,13 +1518,13 @@ bool smallk_takes(const GemmArgs &a) {
          !a.row_scale && !a.c_is_f32;
 }
 
-template <int BN, int WM, int WN, int EPI, bool WT = false>
+template <int BN, int WM, int WN, int EPI>
 hipError_t launch_dma(const GemmArgs &a, hipStream_t s) {
   constexpr int kSmem = kDmaSlots * 256 * kDmaRC * 16;     // 160 KiB
   static LdsAttrOnce attr;
-  const hipError_t e = attr.ensure(reinterpret_cast<const void *>(&gemm_bf16_dma_kernel<BN, WM, WN, EPI, WT>), kSmem);
+  const hipError_t e = attr.ensure(reinterpret_cast<const void *>(&gemm_bf16_dma_kernel<BN, WM, WN, EPI>), kSmem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gemm_bf16_dma_kernel<BN, WM, WN, EPI, WT>), dim3(grid_tiles(a, 256, BN), a.k_splits),
+  hipLaunchKernelGGL((gemm_bf16_dma_kernel<BN, WM, WN, EPI>), dim3(grid_tiles(a, 256, BN), a.k_splits),
                      dim3(WM * WN * 64), kSmem, s, a);
   return hipGetLastError();
 }
@@ -1543,17 +1544,12 @@ inline bool dma_ok(const GemmArgs &a) {
          a.a_span < (1ll << 31) && static_cast<int64_t>(a.N) * a.K < (1ll << 31);
 }
 
-// Which calls take the stream kernel.  It needs five slabs at least, 32-bit positions, and a residual that is not the
-// output itself (rows past a group's end are stored again).  Eight slabs make its start and end worth while
-// (9000 x 1024 x 320 loses 11 %, 16384 x 2048 x 512 gains 3 %).  Below 384 rows a group most of a 256-row tile would be
-// padding: it then takes the call only where 192 tiles and 192 Ki tile-columns of work keep the CUs busy
-// (1024 x 8192 x 2048 in 8 groups: 107 -> 89 us, but 1024 x 2048 x 4096: 56 -> 66, 2048 x 3072 x 768: 29 -> 31 us).
-inline bool stream_takes(const GemmArgs &a) {
-  if (!dma_ok(a) || a.k_splits != 1 || a.K < 512 || a.N < 256 || a.M >= (1ll << 30) || a.residual == a.C) return false;
-  const int groups = a.n_groups > 0 ? a.n_groups : 1;
-  if (a.M / groups >= 384) return true;
-  const int64_t tiles = (a.M / 256 + groups) * ceil_div(a.N, 256);
-  return a.M / groups >= 96 && tiles >= 192 && tiles * a.K >= (192 << 10);
+inline GemmShape shape_of(const GemmArgs &a, bool f32_or_softplus) {
+  GemmArgs narrow = a;
+  narrow.a_span = 0;
+  const bool whole_k = a.k_splits == 1;
+  return {a.M, a.n_groups, a.N, a.K, whole_k && dma_ok(a), whole_k && !dma_ok(a) && dma_ok(narrow), a.w_kmajor != 0,
+          a.residual == a.C, f32_or_softplus};
 }
 
 // Which calls take the few-rows kernel: it gains while most experts have no row and few workgroups stream the weights; from
@@ -1578,15 +1574,15 @@ hipError_t launch_few_rows(const GemmArgs &a, hipStream_t s) {
 
 template <int EPI>
 hipError_t launch_mfma_tiles(const GemmArgs &a, hipStream_t s) {
-  const int64_t rows_per_group = a.M / (a.n_groups > 0 ? a.n_groups : 1);
-  if constexpr (EPI != kEpiPlainF32 && EPI != kEpiBiasSoftplus) {
-    if (stream_takes(a)) return launch_stream<EPI>(a, s);
+  constexpr bool kNoStream = EPI == kEpiPlainF32 || EPI == kEpiBiasSoftplus;
+  const GemmTile tile = gemm_tile(shape_of(a, kNoStream));
+  if constexpr (kNoStream) {
+    if (tile == GemmTile::kDma256) return launch_dma<256, 4, 2, EPI>(a, s);
   } else {
-    if (rows_per_group >= 1024 && a.N >= 256 && a.K > 256) return launch_mfma<256, 256, 4, 2, EPI>(a, s);
+    if (tile == GemmTile::kStream) return launch_stream<EPI>(a, s);
+    if (tile == GemmTile::kReg256) return launch_mfma_k<256, 256, 4, 2, EPI, false>(a, s);
   }
-  // a short inner dimension makes the launch epilogue-bound: smaller tiles put several
-  // workgroups on a CU so that loads, MFMAs and stores of different tiles overlap
-  if (rows_per_group >= 96) return launch_mfma<128, 128, 2, 2, EPI>(a, s);
+  if (tile == GemmTile::k128) return launch_mfma<128, 128, 2, 2, EPI>(a, s);
   // One row tile per group at most (the recurrent step): every weight tile is read by exactly one
   // workgroup, so there is no L2 sharing for the XCD runs to protect, while a run of logical tiles
   // is one expert's column tiles - with few active experts the runs would put all the work on a
@@ -1597,7 +1593,8 @@ hipError_t launch_mfma_tiles(const GemmArgs &a, hipStream_t s) {
   // without a workgroup while the weights stream past once: halve the column tile.  The same helps while
   // there are only about two workgroups per CU (the step's in projection, 8 x 64 tiles: twice the
   // workgroups keep more of the weight stream in flight; 256 sequences: step 173 -> 161 us)
-  const int64_t row_tiles = (a.n_groups > 0 ? a.n_groups : 1) * ceil_div(rows_per_group > 0 ? rows_per_group : 1, 64);
+  const int64_t groups = a.n_groups > 0 ? a.n_groups : 1;
+  const int64_t row_tiles = groups * ceil_div(a.M / groups > 0 ? a.M / groups : 1, 64);
   if (row_tiles * ceil_div(a.N, 128) < kSkinnyColsMaxWgs && a.N % 64 == 0) return launch_mfma<64, 64, 2, 2, EPI>(spread, s);
   return launch_mfma<64, 128, 2, 2, EPI>(spread, s);
 }
@@ -1611,7 +1608,7 @@ bool grouped_gemm_takes_kmajor(const GemmArgs &args) {
   a.k_splits = 1;
   a.k_per_split = static_cast<int>(ceil_div(a.K, 64) * 64);
   return grouped_gemm_on_mfma(a) && !a.c_is_f32 && !a.bias && !a.row_scale && !a.residual && !a.swiglu &&
-         a.N % 256 == 0 && stream_takes(a);
+         a.N % 256 == 0 && gemm_tile(shape_of(a, false)) == GemmTile::kStream;
 }
 
 // whether the call takes the MFMA kernels (else the plain FMA kernel, which has no fused SwiGLU)

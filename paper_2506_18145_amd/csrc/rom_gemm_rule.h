@@ -1,0 +1,63 @@
+// Which tile kernel of the bf16 routed GEMM takes a call (host code, no HIP).  Kernels and their launches: rom_gemm.hip.
+#pragma once
+
+#include <cstdint>
+
+namespace rom {
+
+enum class GemmTile {
+  kStream,     // one persistent stream of 256 x 256 tiles per CU
+  kDma256,     // a 256 x 256 tile per workgroup, operands straight to LDS
+  kReg256,     // the same through registers
+  k128,        // 128 x 128 tiles, several workgroups per CU
+  kSkinny,     // 64 rows: a few rows per group
+};
+
+struct GemmShape {
+  int64_t M;             // rows of all groups
+  int groups, N, K;
+  bool dma;              // whole 64-wide slabs, both operands within 32-bit byte offsets, no slices of K
+  bool wide;             // dma but for rows of A beyond 32-bit byte offsets
+  bool w_kmajor;         // contraction-major weight
+  bool in_place;         // the residual is the output
+  bool f32_or_softplus;  // fp32 output, or bias and softplus: the stream kernel has no such epilogue
+};
+
+constexpr int kStreamMinK = 320;          // its schedule needs five slabs
+
+// The times below are us on MI355X, plain or scaled bf16 output, experts drawn at random, kernel alone.
+inline GemmTile gemm_tile(const GemmShape &s) {
+  const int groups = s.groups > 0 ? s.groups : 1;
+  const int64_t rows = s.M / groups, cols = (s.N + 255) / 256;
+  if (rows < 96) return GemmTile::kSkinny;
+  if (s.f32_or_softplus) {
+    // fp32 output, 256 x 256 tiles against 128 x 128: too few to fill the CUs 16384 x 256 x 4096 (72 tiles) 77.7 / 65.0;
+    // about one each 15373 x 1024 x 768 (256) 34.7 / 42.1; just above that, where the second round runs nearly empty,
+    // 16695 x 1024 x 1536 (276) 85.0 / 76.4
+    const int64_t tiles = (s.M / 256 + groups) * cols;
+    const bool fills = (tiles >= 192 && tiles <= 256) || tiles >= 384;
+    return s.dma && rows >= 1024 && s.N >= 256 && s.K > 256 && fills ? GemmTile::kDma256 : GemmTile::k128;
+  }
+  // 524288 x 2048 x 4096 in 8 groups: 7.72 against 9.41 ms with 128 x 128 tiles
+  if (s.wide && rows >= 1024 && s.N >= 256 && s.K > 256) return GemmTile::kReg256;
+  if (!s.dma || s.K < kStreamMinK || s.N < 256 || s.M >= (int64_t{1} << 30) || s.in_place) return GemmTile::k128;
+  // Otherwise the weight would be transposed first: 16384 x 1536 x 384 in 8 groups 39.1 / 47.9
+  if (s.w_kmajor) return GemmTile::kStream;
+  // Stream or 128 x 128 tiles (us, in that order).  `tiles`: 256 x 256, with half a tile of padding per group.
+  //   * a lone column tile and a bit is half padding: 14736 x 384 x 1536 in 16 groups 32.5 / 30.8
+  //   * few slabs and few columns, start and end weigh most: 23704 x 640 x 384 in 8 groups 29.3 / 24.6
+  //   * more than three quarters of a round of the CUs: 16384 x 8192 x 2048 in 8 groups 508 / 703, x 2048 x 512 54.1 / 57.7
+  //   * its partial round is cut into pieces of half a tile, one per CU, from 64 tiles on, which gains if K is long
+  //     (7664 x 1024 x 1536 in 8 groups 31.7 / 42.6) and loses if not (5387 x 1024 x 768 in 8 groups 19.9 / 18.7);
+  //   * in quarters it has the 128 x 128 kernel's work per CU without a second workgroup to fill its waits
+  //     (3072 x 1024 x 2048 in 8 groups 26.8 / 22.7, 1536 x 2048 x 4096 in 4 groups 59.9 / 47.9);
+  //   * in eighths it reaches twice the CUs: 2476 x 256 x 640 in 4 groups 8.2 / 9.6, until K is so long that only the
+  //     time per slab counts (400 x 1024 x 2048 20.6 / 18.9)
+  const int64_t tiles = (s.M / 128 + (groups > 1 ? groups : 2)) * cols / 2;
+  if (s.N > 256 && s.N <= 384) return GemmTile::k128;
+  if (s.K < 512 && s.N < 1024 && tiles > 32) return GemmTile::k128;
+  const bool stream = tiles > 192 || (tiles > 64 && s.K >= 1536) || (tiles <= 32 && s.K < 1024);
+  return stream ? GemmTile::kStream : GemmTile::k128;
+}
+
+}  // namespace rom

@@ -1,0 +1,76 @@
+"""Which tile kernel a routed GEMM takes (rom_gemm_rule.h, host code): the kernel measured fastest on either side of each line
+of the rule, and what the kernels cannot do."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2506_18145_amd", "csrc")
+NAMES = ("stream", "dma256", "reg256", "t128", "skinny")
+MAIN = """
+#include <cstdio>
+#include "rom_gemm_rule.h"
+int main() {
+  long long M; int g, N, K, dma, wide, km, ip, f;
+  while (std::scanf("%lld %d %d %d %d %d %d %d %d", &M, &g, &N, &K, &dma, &wide, &km, &ip, &f) == 9)
+    std::printf("%d\\n", static_cast<int>(rom::gemm_tile({M, g, N, K, dma != 0, wide != 0, km != 0, ip != 0, f != 0})));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def tile(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rule")
+    (d / "main.cpp").write_text(MAIN)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "main.cpp"), "-o", str(d / "rule")], check=True)
+
+    def ask(M, groups, N, K, dma=None, wide=False, w_kmajor=False, in_place=False, f32_or_softplus=False):
+        dma = (K % 64 == 0 and not wide) if dma is None else dma
+        line = " ".join(str(int(v)) for v in (M, groups, N, K, dma, wide, w_kmajor, in_place, f32_or_softplus))
+        out = subprocess.run([str(d / "rule")], input=line + "\n", capture_output=True, text=True, check=True).stdout
+        return NAMES[int(out)]
+
+    return ask
+
+
+@pytest.mark.parametrize("M,groups,N,K,want", [
+    (16384, 8, 8192, 2048, "stream"), (16384, 8, 2048, 4096, "stream"), (16384, 8, 4096, 1024, "stream"),
+    (16384, 8, 1024, 2048, "stream"), (1024, 8, 8192, 2048, "stream"), (7664, 8, 1024, 1536, "stream"), (2476, 4, 256, 640, "stream"),
+    (16384, 8, 1536, 448, "stream"), (16384, 8, 2048, 512, "stream"),
+    # slower as a stream of big tiles: a partial round in quarters, in halves over a short K, mostly padding
+    (3072, 8, 1024, 2048, "t128"), (1536, 4, 2048, 4096, "t128"), (768, 2, 2048, 4096, "t128"), (5387, 8, 1024, 768, "t128"),
+    (400, 1, 1024, 2048, "t128"), (14736, 16, 384, 1536, "t128"), (23704, 8, 640, 384, "t128"),
+    # no whole slabs
+    (16384, 8, 4000, 1000, "t128"), (16384, 8, 2080, 520, "t128"),
+    # the recurrent step
+    (256, 8, 8192, 2048, "skinny"),
+])
+def test_measured_shapes(tile, M, groups, N, K, want):
+    assert tile(M, groups, N, K) == want
+
+
+def test_wide_activations_keep_the_big_tile(tile):
+    assert tile(524288, 8, 2048, 4096, wide=True) == "reg256"
+
+
+@pytest.mark.parametrize("K", [320, 384, 448, 512, 2048])
+@pytest.mark.parametrize("M", [4096, 16384])
+def test_contraction_major_weights_are_not_transposed(tile, M, K):
+    assert tile(M, 4, 1536, K, w_kmajor=True) == "stream"
+
+
+def test_fp32_and_softplus_epilogues(tile):
+    assert tile(16384, 8, 4096, 512, f32_or_softplus=True) == "dma256"
+    assert tile(15373, 4, 1024, 768, f32_or_softplus=True) == "dma256"
+    assert tile(16695, 4, 1024, 1536, f32_or_softplus=True) == "t128"
+    assert tile(4096, 1, 256, 4096, f32_or_softplus=True) == "t128"
+    assert tile(16384, 8, 4096, 512, dma=False, f32_or_softplus=True) == "t128"
+
+
+def test_what_the_stream_kernel_cannot_do(tile):
+    big = dict(M=16384, groups=8, N=2048)
+    assert tile(K=256, **big) == "t128"                              # its schedule needs five slabs
+    assert tile(K=2048, dma=False, **big) == "t128"
+    assert tile(K=2048, in_place=True, **big) == "t128"              # rows past a group's end are stored twice
+    assert tile(M=1 << 30, groups=8, N=2048, K=512) == "t128"        # 32-bit positions
