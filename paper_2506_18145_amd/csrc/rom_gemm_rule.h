@@ -43,17 +43,17 @@ inline GemmTile gemm_tile(const GemmShape &s) {
   if (!s.dma || s.K < kStreamMinK || s.N < 256 || s.M >= (int64_t{1} << 30) || s.in_place) return GemmTile::k128;
   // Otherwise the weight would be transposed first: 16384 x 1536 x 384 in 8 groups 39.1 / 47.9
   if (s.w_kmajor) return GemmTile::kStream;
-  // Stream or 128 x 128 tiles (us, in that order).  `tiles`: 256 x 256, with half a tile of padding per group.
+  // Stream or 128 x 128 tiles (us, in that order).  `tiles`: 256 x 256, with half a tile of padding per group where there are several.
   //   * a lone column tile and a bit is half padding: 14736 x 384 x 1536 in 16 groups 32.5 / 30.8
   //   * few slabs and few columns, start and end weigh most: 23704 x 640 x 384 in 8 groups 29.3 / 24.6
   //   * more than three quarters of a round of the CUs: 16384 x 8192 x 2048 in 8 groups 508 / 703, x 2048 x 512 54.1 / 57.7
   //   * its partial round is cut into pieces of half a tile, one per CU, from 64 tiles on, which gains if K is long
   //     (7664 x 1024 x 1536 in 8 groups 31.7 / 42.6) and loses if not (5387 x 1024 x 768 in 8 groups 19.9 / 18.7);
   //   * in quarters it has the 128 x 128 kernel's work per CU without a second workgroup to fill its waits
-  //     (3072 x 1024 x 2048 in 8 groups 26.8 / 22.7, 1536 x 2048 x 4096 in 4 groups 59.9 / 47.9);
+  //     (3072 x 1024 x 2048 in 8 groups 26.8 / 22.7, 512 x 8192 x 2048 31.7 / 26.6);
   //   * in eighths it reaches twice the CUs: 2476 x 256 x 640 in 4 groups 8.2 / 9.6, until K is so long that only the
   //     time per slab counts (400 x 1024 x 2048 20.6 / 18.9)
-  const int64_t tiles = (s.M / 128 + (groups > 1 ? groups : 2)) * cols / 2;
+  const int64_t tiles = groups > 1 ? (s.M / 128 + groups) * cols / 2 : (s.M + 255) / 256 * cols;
   if (s.N > 256 && s.N <= 384) return GemmTile::k128;
   if (s.K < 512 && s.N < 1024 && tiles > 32) return GemmTile::k128;
   const bool stream = tiles > 192 || (tiles > 64 && s.K >= 1536) || (tiles <= 32 && s.K < 1024);
