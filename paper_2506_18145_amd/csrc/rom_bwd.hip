@@ -8,6 +8,7 @@
 #include <mutex>
 #include <type_traits>
 #include "rom_internal.h"
+#include "rom_scan_rule.h"
 
 namespace rom {
 
@@ -56,7 +57,8 @@ inline dim3 grid1d(int64_t work, int block) { return dim3(static_cast<unsigned>(
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // ------------------------------------------------------------------ adjoint of the selective scan
-// Sequences are cut into chunks of 128 steps, so that the chip is full whatever the batch.  Three kernels:
+// Sequences are cut into chunks (of 128 steps where there are enough, see scan_bwd_chunk), so that the chip is full whatever
+// the batch.  Three kernels:
 //   scan_bwd_carry_kernel: a lane owns a channel with its 16 states (B and C through the scalar cache, as in the
 //           forward's lane = channel scan) and walks one chunk forwards once, leaving its end state Q from a zero start,
 //           the adjoint state R that leaves its start from a zero adjoint at its end (sum over t of the decay from the
@@ -75,19 +77,20 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // Bound by ALU issue: about 120 vector instructions, 9 of them exponentials, per step of 256 (channel, state) pairs, the
 // pipe busy nine tenths of the time.  16384 x 4096: carries 0.29, fold 0.04, main 1.05, block sums 0.05 ms (a lane per
 // (channel, state) pair with row sums over the states and channel sums through LDS: 2.43 ms).
-constexpr int kBwdChunk = 128, kBwdGroup = 16, kBwdCh = 64, kBwdHalf = 8, kBwdGroups = kBwdChunk / kBwdGroup;
+constexpr int kBwdMaxChunk = 128, kBwdGroup = 16, kBwdCh = 64, kBwdHalf = 8, kBwdGroups = kBwdMaxChunk / kBwdGroup;
 constexpr int kBwdStPitch = kBwdGroup + 4;   // floats per channel row: 16 rows of four-step reads or writes cover the banks
 
 // Scratch of the adjoint scan, all f32.  Units are numbered (sequence * n_chunks + chunk) * n_cb + channel block.
 struct ScanBwdLayout {
-  int n_cb, n_chunks;          // channel blocks; chunks per sequence
+  int n_cb, n_chunks, chunk;   // channel blocks; chunks per sequence; steps per chunk (whole groups)
   int64_t n_units;
   size_t carry_q, carry_r, carry_s, part_a, part_d, part_bias, total;   // offsets in floats
 };
 inline ScanBwdLayout scan_bwd_layout(int64_t B, int64_t L, int d_inner) {
   ScanBwdLayout l;
   l.n_cb = static_cast<int>(ceil_div(d_inner, kBwdCh));
-  l.n_chunks = static_cast<int>(ceil_div(L, kBwdChunk));
+  l.chunk = scan_bwd_chunk(B, L, d_inner);
+  l.n_chunks = static_cast<int>(ceil_div(L, l.chunk));
   l.n_units = B * l.n_chunks * l.n_cb;
   size_t off = 0;
   auto take = [&](size_t n) { size_t o = off; off += (n + 63) / 64 * 64; return o; };
@@ -134,7 +137,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void scan_bwd_carry_kernel(
     const T *__restrict__ u, const T *__restrict__ dt, const float *__restrict__ bc, const T *__restrict__ z,
     int64_t ld_z, const T *__restrict__ dg, const float *__restrict__ gate, const float *__restrict__ A_log, int64_t L,
-    int d_inner, int gx, int n_chunks, float *__restrict__ carry_q, float *__restrict__ carry_r,
+    int d_inner, int gx, int n_chunks, int chunk, float *__restrict__ carry_q, float *__restrict__ carry_r,
     float *__restrict__ carry_s) {
   typedef const __attribute__((address_space(4))) bwd_f32x16 const_f32x16_t;
   typedef const __attribute__((address_space(4))) float const_f32_t;
@@ -146,8 +149,8 @@ __global__ __launch_bounds__(256) void scan_bwd_carry_kernel(
   if (ch0 >= d_inner) return;
   const int cl = ch0 + lane < d_inner ? lane : d_inner - 1 - ch0;      // idle lanes repeat the last channel, stores included
   const int ch = ch0 + cl;
-  const int64_t b = bk / n_chunks, ts = bk % n_chunks * kBwdChunk, row0 = b * L + ts;
-  const int len = static_cast<int>(L - ts < kBwdChunk ? L - ts : kBwdChunk);
+  const int64_t b = bk / n_chunks, ts = bk % n_chunks * chunk, row0 = b * L + ts;
+  const int len = static_cast<int>(L - ts < chunk ? L - ts : chunk);
 
   float a2[16], h[16], e[16], r[16], sum = 0.0f;
 #pragma unroll
@@ -291,7 +294,7 @@ template <typename T>
 __global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
     const T *__restrict__ u, const T *__restrict__ dt, const float *__restrict__ bc, const T *__restrict__ z,
     int64_t ld_z, const T *__restrict__ dg, const float *__restrict__ gate, const float *__restrict__ A_log,
-    const float *__restrict__ D, int64_t n_tok, int64_t L, int d_inner, int n_cb, int n_chunks,
+    const float *__restrict__ D, int64_t n_tok, int64_t L, int d_inner, int n_cb, int n_chunks, int chunk,
     const float *__restrict__ start_h, const float *__restrict__ start_dh, T *__restrict__ d_pre, T *__restrict__ d_u,
     T *__restrict__ d_z, int64_t ld_dz, float *__restrict__ d_bc_part, float *__restrict__ part_a,
     float *__restrict__ part_d, float *__restrict__ part_bias) {
@@ -301,8 +304,8 @@ __global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
   const int c = lane & 15, q = lane >> 4;
   const int64_t unit = blockIdx.x;
   const int cb = static_cast<int>(unit % n_cb);
-  const int64_t bk = unit / n_cb, b = bk / n_chunks, ts = bk % n_chunks * kBwdChunk, row0 = b * L + ts;
-  const int len = static_cast<int>(L - ts < kBwdChunk ? L - ts : kBwdChunk);
+  const int64_t bk = unit / n_cb, b = bk / n_chunks, ts = bk % n_chunks * chunk, row0 = b * L + ts;
+  const int len = static_cast<int>(L - ts < chunk ? L - ts : chunk);
   const int n_grp = (len + kBwdGroup - 1) / kBwdGroup;
   const int c0 = cb * kBwdCh + wave * 16;
   const bool active = c0 < d_inner;                     // (d_inner is a multiple of 16)
@@ -1487,7 +1490,7 @@ static hipError_t launch_scan_backward_t(const void *u, const void *dt, const fl
     const int gx = static_cast<int>(ceil_div(d_inner, 256));
     hipLaunchKernelGGL((scan_bwd_carry_kernel<T>), dim3(static_cast<unsigned>(B * l.n_chunks * gx)), dim3(256), 0, s,
                        static_cast<const T *>(u), static_cast<const T *>(dt), bc, static_cast<const T *>(z), ld_z,
-                       static_cast<const T *>(dg), gate, A_log, L, d_inner, gx, l.n_chunks, ws + l.carry_q, ws + l.carry_r,
+                       static_cast<const T *>(dg), gate, A_log, L, d_inner, gx, l.n_chunks, l.chunk, ws + l.carry_q, ws + l.carry_r,
                        ws + l.carry_s);
     hipLaunchKernelGGL(scan_bwd_fold_kernel, dim3(static_cast<unsigned>(ceil_div(B * d_inner * 16, 256)), 2), dim3(256), 0, s,
                        A_log, B, d_inner, l.n_chunks, ws + l.carry_q, ws + l.carry_r, ws + l.carry_s);
@@ -1512,7 +1515,7 @@ static hipError_t launch_scan_backward_t(const void *u, const void *dt, const fl
   }
   hipLaunchKernelGGL((scan_bwd_kernel<T>), dim3(static_cast<unsigned>(l.n_units)), dim3(256), sizeof(BwdSmem), s,
                      static_cast<const T *>(u), static_cast<const T *>(dt), bc, static_cast<const T *>(z), ld_z,
-                     static_cast<const T *>(dg), gate, A_log, D, B * L, L, d_inner, l.n_cb, l.n_chunks,
+                     static_cast<const T *>(dg), gate, A_log, D, B * L, L, d_inner, l.n_cb, l.n_chunks, l.chunk,
                      chunked ? ws + l.carry_q : nullptr, chunked ? ws + l.carry_r : nullptr, static_cast<T *>(d_pre),
                      static_cast<T *>(d_u), static_cast<T *>(d_z), ld_dz, d_bc_part, ws + l.part_a, ws + l.part_d,
                      ws + l.part_bias);

@@ -1,4 +1,4 @@
-"""The adjoint scan at the edges of its 128-step chunks, 16-step groups and 64-channel blocks."""
+"""The adjoint scan at the edges of its chunks (16, 32 and 128 steps), 16-step groups and 64-channel blocks."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,L,d_inner,dtype,top_k", [
     (2, 1, 16, "fp32", 1), (1, 15, 80, "fp32", 1), (3, 17, 64, "fp32", 2), (1, 127, 48, "fp32", 1), (2, 128, 32, "bf16", 1),
     (2, 129, 144, "fp32", 1), (1, 300, 272, "fp32", 2), (2, 513, 96, "bf16", 1),
+    (1, 33, 144, "fp32", 1), (2, 1000, 272, "bf16", 1), (1, 1025, 512, "fp32", 1),               # 16, 32, 32 steps
+    (128, 129, 96, "fp32", 1), (64, 257, 176, "fp32", 1), (43, 300, 272, "bf16", 1), (256, 128, 80, "fp32", 2),      # 128 steps
 ])
 def test_scan_backward(B, L, d_inner, dtype, top_k):
     cfg = RomConfig(f"sb_{L}", 700 + L % 97, B, L, 32, d_inner, 16, 4, 8, 4, top_k, dtype, int(top_k > 1), weight_std=0.1)
