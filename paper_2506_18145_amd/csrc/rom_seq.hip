@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "rom_internal.h"
+#include "rom_scan_rule.h"
 
 namespace rom {
 
@@ -1388,19 +1389,6 @@ hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const floa
     hipLaunchKernelGGL(conv_silu_kernel<float>, grid, dim3(256), 0, s, static_cast<const float *>(xz),
                        ld_xz, conv_w, conv_b, state_in, state_out, static_cast<float *>(u), L, d_inner);
   return hipGetLastError();
-}
-
-// Which scan takes a call (measured on MI355X, both kernels in one process, bf16):
-//   * 2048 wavefronts of 64 channels or more need no time chunks: lane = channel, one pass
-//     (64 x 256 steps x 4096 channels 300 -> 203 us, 32 x 512 x 4096 298 -> 237 us);
-//   * few (sequence, 16 channel) blocks, at most three per CU, leave the lane = (channel, state) kernels at one or two
-//     wavefronts per SIMD: with enough steps to cut, lane = channel wins in spite of its second pass
-//     (1 x 16384 x 4096: 384 -> 342 us, 2 x 4096 x 3072: 196 -> 151 us, 4 x 4096 x 2048: 197 -> 185 us; below about
-//     24 M (step, channel) pairs its three launches and short chunks cost the gain: 4 x 2048 x 2048 105 -> 108 us);
-//   * in between (8 x 2048 x 4096: 312 against 338 us) and for short calls the lane = (channel, state) kernels stay.
-bool scan_by_lane(int64_t B, int64_t L, int d_inner) {
-  if (B * ceil_div(d_inner, 64) >= 2048) return true;
-  return B * (d_inner / kScanCh) <= 768 && B * L * d_inner >= (24ll << 20);
 }
 
 int scan_lane_chunks(int64_t B, int64_t L, int d_inner) {

@@ -1,5 +1,5 @@
-"""How the adjoint scan is cut into chunks (rom_scan_rule.h, host code): the length measured fastest on either side of each
-line of the rule."""
+"""Which selective scan takes a call and how the adjoint is cut into chunks (rom_scan_rule.h, host code): what was measured
+fastest on either side of each line of the rules."""
 import os
 import subprocess
 
@@ -11,18 +11,22 @@ MAIN = """
 #include "rom_scan_rule.h"
 int main() {
   long long B, L; int d;
-  while (std::scanf("%lld %lld %d", &B, &L, &d) == 3) std::printf("%d\\n", rom::scan_bwd_chunk(B, L, d));
+  while (std::scanf("%lld %lld %d", &B, &L, &d) == 3) std::printf("%d %d\\n", rom::scan_bwd_chunk(B, L, d), rom::scan_by_lane(B, L, d));
 }
 """
 
 
 @pytest.fixture(scope="module")
-def chunk(tmp_path_factory):
+def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rule")
     (d / "main.cpp").write_text(MAIN)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "main.cpp"), "-o", str(d / "rule")], check=True)
-    return lambda *a: int(subprocess.run([str(d / "rule")], input=" ".join(map(str, a)) + "\n", capture_output=True, text=True,
-                                         check=True).stdout)
+
+    def ask(*a):
+        out = subprocess.run([str(d / "rule")], input=" ".join(map(str, a)) + "\n", capture_output=True, text=True, check=True)
+        return [int(v) for v in out.stdout.split()]
+
+    return ask
 
 
 @pytest.mark.parametrize("B,L,d_inner,want", [
@@ -31,5 +35,14 @@ def chunk(tmp_path_factory):
     (2, 200, 512, 16), (1, 300, 64, 16), (1, 129, 128, 16), (1, 128, 512, 16), (1, 64, 128, 16),
     (8, 128, 2048, 128), (1, 16, 128, 128), (1, 32, 128, 128), (1, 1, 16, 128),
 ])
-def test_adjoint_scan_chunks(chunk, B, L, d_inner, want):
-    assert chunk(B, L, d_inner) == want
+def test_adjoint_scan_chunks(rules, B, L, d_inner, want):
+    assert rules(B, L, d_inner)[0] == want
+
+
+@pytest.mark.parametrize("B,L,d_inner,want", [
+    (64, 256, 4096, 1), (128, 2, 2048, 1), (64, 64, 2048, 1), (2048, 2, 64, 1), (8192, 40, 16, 1),
+    (4096, 40, 16, 0), (2048, 40, 48, 0), (63, 256, 2048, 0),          # wavefronts with idle lanes do not count whole
+    (1, 16384, 4096, 1), (2, 4096, 3072, 1), (4, 4096, 2048, 1), (4, 2048, 2048, 0), (8, 2048, 4096, 0), (1, 64, 128, 0),
+])
+def test_lane_scan(rules, B, L, d_inner, want):
+    assert rules(B, L, d_inner)[1] == want
