@@ -726,7 +726,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, few rows
-// A few sequences' recurrent step (kFewRows positions at most): the call is one pass over the weights of the picked
+// A few sequences' recurrent step (kGemmFewRows positions at most; a row tile holds 16): the call is one pass over the weights of the picked
 // experts, bound by how much of it is in flight.  The 64-row tiles of the general kernel park 64 rows for the one or two
 // that exist, walk K serially with two slabs in flight and a barrier each.  Here a workgroup of eight wavefronts owns
 // 16 CT output columns of one expert's rows (CT = 2 from kFewWideCols columns on); the wavefronts deal the 64-wide units
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
 // (c, g) ends with columns 4 g .. 4 g + 3 of position c.  Positions past the group's end repeat its first row and are not
 // stored.  One sequence, d_model 2048: with 64 x 64 tiles the in and out projections take 30 us each of a step of 91 us;
 // the step now takes 47 us.
-constexpr int kFewRows = 8, kFewWideCols = 4096;          // (a row tile holds 16)
+constexpr int kFewWideCols = 4096;
 constexpr int kFewWaves = 8, kFewUnits = 4;
 typedef float f32x4_few_t __attribute__((ext_vector_type(4)));
 
@@ -1552,12 +1552,8 @@ inline GemmShape shape_of(const GemmArgs &a, bool f32_or_softplus) {
           a.residual == a.C, f32_or_softplus};
 }
 
-// Which calls take the few-rows kernel: it gains while most experts have no row and few workgroups stream the weights; from
-// about 16 rows on, the tiled kernel's many workgroups keep the memory as busy.  Steps of 1 / 4 / 16 / 32 sequences, us,
-// against the tiled kernels: d_model 2048 52 / 80 / 121 / 133 against 93 / 98 / 123 / 126, d_model 768 38 / 44 / 58 / 63
-// against 49 / 51 / 55 / 56, delta rule 36 / 59 / 90 / 98 against 65 / 74 / 99 / 105.
 inline bool few_rows_takes(const GemmArgs &a) {
-  return a.M <= kFewRows && a.K % 64 == 0 && (a.offsets == nullptr || a.n_groups <= 64) && !a.w_kmajor;
+  return !a.w_kmajor && gemm_few_rows(a.M, a.offsets ? a.n_groups : 1, a.N, a.K);
 }
 
 template <int EPI>

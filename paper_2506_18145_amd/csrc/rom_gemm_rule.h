@@ -60,4 +60,17 @@ inline GemmTile gemm_tile(const GemmShape &s) {
   return stream ? GemmTile::kStream : GemmTile::k128;
 }
 
+// Which calls take the few-rows kernel: it gains while most experts have no row and few workgroups stream the weights.  Kernel
+// alone, us, against the tiled kernels' (weights not read just before): one row, 8 groups, 8192 x 2048 8.7 / 27.9, 8 rows
+// 33 / 47, 2048 x 4096 19.7 / 30.2, 3072 x 1536 13.7 / 13.5.  Over a short K, with more workgroups than the CUs hold at
+// once (two each) and not many experts, the tiled kernel has as much in flight: 6 rows, 8 groups, 2048 x 1024 12.8 / 10.3, 8 rows
+// 4096 x 1024 16.2 / 12.0, but in 64 groups 20.6 / 28.0.  From about 16 rows on it does everywhere (steps of 16 / 32 sequences,
+// d_model 2048, 121 / 133 against 123 / 126 us).
+constexpr int kGemmFewRows = 8;
+inline bool gemm_few_rows(int64_t M, int groups, int N, int K) {
+  if (M > kGemmFewRows || K % 64 != 0 || groups > 64) return false;
+  const int64_t used = M < groups ? M : groups;
+  return K > 1024 || groups > 16 || used * ((N + 15) / 16) <= 512;
+}
+
 }  // namespace rom

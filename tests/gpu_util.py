@@ -223,3 +223,20 @@ def compare_layer(cfg, gpu, x_np, w_np, conv_state=None, ssm_state=None, stages=
     bad = {k: v for k, v in scaled.items() if not v <= etol}
     assert not bad, f"error beyond {etol} of the summed terms' size: {bad}"
     return ref, errs
+
+
+def grouped(a, w, idx):
+    """a [N, K] by the experts idx [N], w [E, M, K], in fp32."""
+    out = torch.empty(a.shape[0], w.shape[1], device=a.device)
+    for e in range(w.shape[0]):
+        rows = (idx == e).nonzero().flatten()
+        out[rows] = a[rows].float() @ w[e].float().T
+    return out
+
+
+def check_rounded(got, branch, skip=None):
+    """got: bf16 (branch + skip) with branch rounded first; two roundings of 2^-8 and the fp32 sums' order."""
+    ref = branch if skip is None else branch + skip.float()
+    bound = 2.0 ** -8 * (ref.abs() + (0 if skip is None else branch.abs())) * 1.01 + 2e-4 * branch.square().mean().sqrt()
+    worst = ((got.float() - ref).abs() / bound).max().item()
+    assert worst <= 1.0, worst

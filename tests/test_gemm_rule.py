@@ -14,13 +14,14 @@ MAIN = """
 int main() {
   long long M; int g, N, K, dma, wide, km, ip, f;
   while (std::scanf("%lld %d %d %d %d %d %d %d %d", &M, &g, &N, &K, &dma, &wide, &km, &ip, &f) == 9)
-    std::printf("%d\\n", static_cast<int>(rom::gemm_tile({M, g, N, K, dma != 0, wide != 0, km != 0, ip != 0, f != 0})));
+    std::printf("%d %d\\n", static_cast<int>(rom::gemm_tile({M, g, N, K, dma != 0, wide != 0, km != 0, ip != 0, f != 0})),
+                rom::gemm_few_rows(M, g, N, K));
 }
 """
 
 
 @pytest.fixture(scope="module")
-def tile(tmp_path_factory):
+def rule(tmp_path_factory):
     d = tmp_path_factory.mktemp("rule")
     (d / "main.cpp").write_text(MAIN)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "main.cpp"), "-o", str(d / "rule")], check=True)
@@ -29,9 +30,15 @@ def tile(tmp_path_factory):
         dma = (K % 64 == 0 and not wide) if dma is None else dma
         line = " ".join(str(int(v)) for v in (M, groups, N, K, dma, wide, w_kmajor, in_place, f32_or_softplus))
         out = subprocess.run([str(d / "rule")], input=line + "\n", capture_output=True, text=True, check=True).stdout
-        return NAMES[int(out)]
+        which, few = out.split()
+        return NAMES[int(which)], few == "1"
 
     return ask
+
+
+@pytest.fixture(scope="module")
+def tile(rule):
+    return lambda *a, **k: rule(*a, **k)[0]
 
 
 @pytest.mark.parametrize("M,groups,N,K,want", [
@@ -74,3 +81,14 @@ def test_what_the_stream_kernel_cannot_do(tile):
     assert tile(K=2048, dma=False, **big) == "t128"
     assert tile(K=2048, in_place=True, **big) == "t128"              # rows past a group's end are stored twice
     assert tile(M=1 << 30, groups=8, N=2048, K=512) == "t128"        # 32-bit positions
+
+
+@pytest.mark.parametrize("M,groups,N,K,want", [
+    (1, 8, 8192, 2048, True), (8, 8, 8192, 2048, True), (8, 8, 2048, 4096, True), (8, 4, 3072, 1536, True), (9, 8, 8192, 2048, False),
+    (1, 8, 4096, 1024, True), (8, 1, 4096, 1024, True), (8, 64, 4096, 1024, True),
+    # as many workgroups as the CUs hold and a short inner dimension: the tiled kernel is faster
+    (6, 8, 2048, 1024, False), (8, 8, 4096, 1024, False), (5, 16, 2048, 768, False), (8, 16, 1536, 768, False),
+    (4, 8, 2048, 1000, False), (4, 65, 2048, 1024, False),              # no whole units, more groups than lanes
+])
+def test_few_rows(rule, M, groups, N, K, want):
+    assert rule(M, groups, N, K)[1] == want

@@ -10,7 +10,7 @@ import torch
 from oracle import rom_oracle as O
 from paper_2506_18145_amd import RomFfnMoe, RomLayer
 from rom_synth import RomConfig, make_ffn_weights, make_input, make_weights
-from gpu_util import BLOCK_EPS, TOL, compare_layer, rel_err, run_layer, to_np
+from gpu_util import BLOCK_EPS, TOL, check_rounded, compare_layer, grouped, rel_err, run_layer, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -56,23 +56,6 @@ def test_stream_gemm_backward(L, E):
     assert rel_err(to_np(d_x), ref["d_x"]) <= TOL["bf16"]
     for name in ("d_w_in", "d_w_out", "d_w_x", "d_w_dt", "d_A_log", "d_w_router"):
         assert rel_err(to_np(grads[name]), ref[name]) <= TOL["bf16"], name
-
-
-def grouped(a, w, idx):
-    """a [N, K] by the experts idx [N], w [E, M, K], in fp32."""
-    out = torch.empty(a.shape[0], w.shape[1], device=a.device)
-    for e in range(w.shape[0]):
-        rows = (idx == e).nonzero().flatten()
-        out[rows] = a[rows].float() @ w[e].float().T
-    return out
-
-
-def check_rounded(got, branch, skip=None):
-    """got: bf16 (branch + skip) with branch rounded first; two roundings of 2^-8 and the fp32 sums' order."""
-    ref = branch if skip is None else branch + skip.float()
-    bound = 2.0 ** -8 * (ref.abs() + (0 if skip is None else branch.abs())) * 1.01 + 2e-4 * branch.square().mean().sqrt()
-    worst = ((got.float() - ref).abs() / bound).max().item()
-    assert worst <= 1.0, worst
 
 
 @pytest.mark.parametrize("block", [False, True])
