@@ -332,8 +332,10 @@ __global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
     float gate[4];
     bwd_f32x4 bc0, bc1;
   } raw;
-  const unsigned pitch = static_cast<unsigned>(d_inner * sizeof(T)), pitch_z = static_cast<unsigned>(ld_z * sizeof(T));
-  const unsigned pitch_dz = static_cast<unsigned>(ld_dz * sizeof(T)), ch_off = static_cast<unsigned>(ch * sizeof(T));
+  // (rows are whole 32-byte pieces: a 24-bit product and a shift that goes with the addition)
+  const unsigned pitch = static_cast<unsigned>(d_inner * sizeof(T) / 32), pitch_z = static_cast<unsigned>(ld_z * sizeof(T) / 32);
+  const unsigned pitch_dz = static_cast<unsigned>(ld_dz * sizeof(T) / 32), ch_off = static_cast<unsigned>(ch * sizeof(T));
+  auto row_at = [&](unsigned t, unsigned p) __attribute__((always_inline)) { return (__umul24(t, p) << 5) + ch_off; };
   const char *const dt_p = reinterpret_cast<const char *>(dt + row0 * d_inner), *const u_p = reinterpret_cast<const char *>(u + row0 * d_inner);
   const char *const dg_p = reinterpret_cast<const char *>(dg + row0 * d_inner), *const z_p = reinterpret_cast<const char *>(z + row0 * ld_z);
   const char *const bc_p = reinterpret_cast<const char *>(bc + row0 * 32);
@@ -341,11 +343,11 @@ __global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int tt = g * kBwdGroup + 4 * i + q;
-      const unsigned t = static_cast<unsigned>(tt < len ? tt : len - 1), at = __umul24(t, pitch) + ch_off;
+      const unsigned t = static_cast<unsigned>(tt < len ? tt : len - 1), at = row_at(t, pitch);
       raw.dt[i] = *reinterpret_cast<const T *>(dt_p + at);
       raw.u[i] = *reinterpret_cast<const T *>(u_p + at);
       if (full) {
-        raw.z[i] = *reinterpret_cast<const T *>(z_p + (__umul24(t, pitch_z) + ch_off));
+        raw.z[i] = *reinterpret_cast<const T *>(z_p + row_at(t, pitch_z));
         raw.dg[i] = *reinterpret_cast<const T *>(dg_p + at);
         raw.gate[i] = gate ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(gate + row0) + t * 4u) : 1.0f;
       }
@@ -492,10 +494,10 @@ __global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
         acc_d = fmaf(dy_o[i], u_o[i], acc_d);
         const int t = g * kBwdGroup + 4 * i + q;
         if (decltype(all)::value || (active && t < len)) {
-          const unsigned at = __umul24(static_cast<unsigned>(t), pitch) + ch_off;
+          const unsigned at = row_at(static_cast<unsigned>(t), pitch);
           *reinterpret_cast<T *>(dpre_p + at) = from_f32<T>(o_pre);
           *reinterpret_cast<T *>(du_p + at) = from_f32<T>(o_u);
-          *reinterpret_cast<T *>(dz_p + (__umul24(static_cast<unsigned>(t), pitch_dz) + ch_off)) = from_f32<T>(o_z);
+          *reinterpret_cast<T *>(dz_p + row_at(static_cast<unsigned>(t), pitch_dz)) = from_f32<T>(o_z);
         }
         __builtin_amdgcn_sched_barrier(0);              // (registers: no more than four steps in flight)
       }
@@ -1532,9 +1534,9 @@ hipError_t launch_scan_backward(int dtype, const void *u, const void *dt, const 
                                 int64_t ld_dz, float *d_bc, float *d_A_log, float *d_D, float *d_dt_bias,
                                 hipStream_t s) {
   const ScanBwdLayout l = scan_bwd_layout(B, L, d_inner);
-  // 32-bit row offsets inside a chunk, 24-bit pitches
+  // 32-bit row offsets inside a chunk, rows of whole 32-byte pieces
   const int64_t widest = (ld_z > ld_dz ? ld_z : ld_dz) > d_inner ? (ld_z > ld_dz ? ld_z : ld_dz) : d_inner;
-  if (l.n_units >= (1ll << 31) || widest * 4 >= (1 << 24)) return hipErrorInvalidValue;
+  if (l.n_units >= (1ll << 31) || widest * 4 * l.chunk >= (1ll << 32) || ld_z % 16 || ld_dz % 16) return hipErrorInvalidValue;
   hipError_t e = dtype == ROM_DTYPE_BF16
                      ? launch_scan_backward_t<bf16_t>(u, dt, bc, z, ld_z, dg, gate, A_log, D, B, L, d_inner, ckpt, d_bc_part,
                                                       d_pre, d_u, d_z, ld_dz, d_A_log, d_D, d_dt_bias, s)

@@ -30,3 +30,17 @@ def test_scan_backward(B, L, d_inner, dtype, top_k):
     assert rel_err(to_np(d_x), ref["d_x"]) <= TOL[dtype]
     for name in grads:
         assert rel_err(to_np(grads[name]), ref[name]) <= TOL[dtype], name
+
+
+def test_rows_of_many_channels():
+    """Rows whose byte pitch (z's and its gradient's are twice as wide) does not fit 24 bits."""
+    cfg = RomConfig("sb_wide", 799, 1, 2, 8, (1 << 21) + 16, 16, 4, 8, 1, 1, "fp32", 0, weight_std=0.1)
+    w, x = make_weights(cfg), make_input(cfg)
+    layer = RomLayer(cfg, w)
+    d_out = layer.to_device(np.random.default_rng(2).standard_normal((1, 2, 8)).astype(np.float32))
+    d_x, grads = layer.backward(layer.to_device(x), d_out)
+    torch.cuda.synchronize()
+    ref = O.rom_layer_backward(x, w, cfg.top_k, cfg.gate_mode, to_np(d_out), expert_idx=np.zeros((2, 1), np.int32))
+    assert rel_err(to_np(d_x), ref["d_x"]) <= TOL["fp32"]
+    for name in grads:
+        assert rel_err(to_np(grads[name]), ref[name]) <= TOL["fp32"], name
