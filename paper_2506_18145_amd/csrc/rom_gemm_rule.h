@@ -56,7 +56,12 @@ inline GemmTile gemm_tile(const GemmShape &s) {
   const int64_t tiles = groups > 1 ? (s.M / 128 + groups) * cols / 2 : (s.M + 255) / 256 * cols;
   if (s.N > 256 && s.N <= 384) return GemmTile::k128;
   if (s.K < 512 && s.N < 1024 && tiles > 32) return GemmTile::k128;
-  const bool stream = tiles > 192 || (tiles > 64 && s.K >= 1536) || (tiles <= 32 && s.K < 1024);
+  //   * with few rows a group, uneven groups have more padding than that: with half of the rows in one of 16 groups 2859 x 1536 x
+  //     1536 46.5 / 33.5, 2782 x 3072 x 768 47.9 / 39.1 (2720 x 3072 x 768 in even ones 34.6 / 39.9).  With the work below, the
+  //     uneven ones come out even (2475 x 4096 x 768 48.0 / 52.5, 2519 x 4096 x 768 54.5 / 51.1) and the others ahead; up
+  //     to 128 tiles they lose over any K (1886 x 1536 x 3072 67.3 / 57.3)
+  const bool busy = tiles > 192 || (tiles > 64 && s.K >= 1536);
+  const bool stream = tiles <= 32 ? s.K < 1024 : busy && (rows >= 256 || (tiles > 128 && tiles * s.K >= (192 << 10)));
   return stream ? GemmTile::kStream : GemmTile::k128;
 }
 
