@@ -74,9 +74,9 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // lanes of a row by a transposing butterfly, over the block's four wavefronts through LDS (the only barrier, one per
 // group), over the channel blocks in bwd_reduce_bc_kernel; parameter gradients go to per-unit partials that
 // scan_bwd_finish_kernel sums in unit order.  All sums in fixed order, no atomics.
-// Bound by ALU issue: about 120 vector instructions, 9 of them exponentials, per step of 256 (channel, state) pairs, the
-// pipe busy nine tenths of the time.  16384 x 4096: carries 0.29, fold 0.04, main 1.05, block sums 0.05 ms (a lane per
-// (channel, state) pair with row sums over the states and channel sums through LDS: 2.43 ms).
+// Bound by ALU issue: 121 vector instructions, 10 of them transcendental, per step of 256 (channel, state) pairs, issue busy for
+// 98 % of the cycles.  16384 x 4096, launches alone: 1.27 ms (a lane per (channel, state) pair with row sums over the states
+// and channel sums through LDS: 2.27); within a training step carries 0.26, fold 0.04, main 0.96, sums 0.04 ms.
 constexpr int kBwdMaxChunk = 128, kBwdGroup = 16, kBwdCh = 64, kBwdHalf = 8, kBwdGroups = kBwdMaxChunk / kBwdGroup;
 constexpr int kBwdStPitch = kBwdGroup + 4;   // floats per channel row: 16 rows of four-step reads or writes cover the banks
 
@@ -414,8 +414,9 @@ __global__ __launch_bounds__(256, 2) void scan_bwd_kernel(
   // (all: every step of the group and every channel of the wavefront exists - no branch around the stores, which would
   // cut the group into pieces too short to schedule)
   auto group = [&](int g, auto all) __attribute__((always_inline)) {
-    // the group in two halves of eight steps, the later one first, so that its states and decays (68 registers) leave room
-    // for three wavefronts per SIMD; the state between the halves is walked to once more
+    // the group in two halves of eight steps, the later one first, so that its states and decays (68 registers) fit with two
+    // wavefronts per SIMD (253 registers; the 71 KiB of LDS allow no third workgroup either); the state between the
+    // halves is walked to once more
     float mid[4];
     {
       const bwd_f32x4 k4 = ld4(&sm.ck[wave][g][lane * 4]);

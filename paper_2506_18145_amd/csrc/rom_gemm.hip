@@ -733,8 +733,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
 // of K among themselves, read both operands straight into fragments (no LDS, no barrier; four units of both requested at
 // once), and their partial sums are added through LDS in wavefront order.  The weight is the MFMA's row operand: lane
 // (c, g) ends with columns 4 g .. 4 g + 3 of position c.  Positions past the group's end repeat its first row and are not
-// stored.  One sequence, d_model 2048: with 64 x 64 tiles the in and out projections take 30 us each of a step of 91 us;
-// the step now takes 47 us.
+// stored.  One sequence, d_model 2048: with 64 x 64 tiles the in and out projections take 30 us each of a step of 94 us;
+// the step now takes 55 us through twelve layers in turn, 47 (91) with one layer whose expert the last step has just read.
 constexpr int kFewWideCols = 4096;
 constexpr int kFewWaves = 8, kFewUnits = 4;
 typedef float f32x4_few_t __attribute__((ext_vector_type(4)));
@@ -826,9 +826,10 @@ __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(cons
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, one stream of slabs per CU
-// The large routed projections: bound by the power the matrix pipe draws (a slab of random operands takes 1.49 us, of zeros
-// 0.97; 0.85 is the pipe's own at 2.4 GHz), then by what stops it: the stores and the last round.  16384 rows in 8 groups,
-// 8192 x 2048: 526 -> 487 us, 2048 x 4096: 299 -> 257 us (one 256 x 256 tile per workgroup of eight wavefronts before).
+// The large routed projections: bound by the power the matrix pipe draws (a slab of random operands takes 1.5 us, of zeros
+// 1.05; its MFMAs 0.85 us at 2.4 GHz, 1.0 at the 2.06 that the clock falls to), then by what stops it: the stores and the last
+// round; the pipe is busy for 56 % of a launch.  16384 rows in 8 groups, 8192 x 2048: 550 -> 503 us, 2048 x 4096: 309 -> 260 us
+// (one 256 x 256 tile per workgroup of eight wavefronts before).
 // One workgroup of four wavefronts per CU (2 x 2, 128 x 128 each: 256 accumulator
 // registers, a third less LDS traffic per flop than eight 64 x 128 ones) walks its share of the 256 x 256 tiles; the ring
 // of five half-slab slots above runs on across tile boundaries: the last two slabs of a tile already request the next
@@ -921,7 +922,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     w_lds[j] = __builtin_amdgcn_readfirstlane(lds_base + bw * 1024);
   }
   // tile row / weight row that this lane fetches with instruction j; the lane number passes through an empty asm so that
-  // the compiler forms these (once a tile) anew instead of keeping them in registers it would have to spill
+  // the compiler forms these (once a tile) anew instead of keeping them in registers.  (All 512 are in use and 18 to 33,
+  // depending on the epilogue, are spilled: in the first two and the last two slabs of a tile and between tiles.)
   auto here = [&]() __attribute__((always_inline)) {
     int l = threadIdx.x & 63;
     asm volatile("" : "+v"(l));

@@ -759,9 +759,10 @@ __global__ __launch_bounds__(HELPERS ? 512 : 256) void scan_pipe_kernel(
 // kLaneWaves wavefronts: a state-only pass leaves every chunk's end state from zero (chunk_q [B][chunk][16][d_inner])
 // and its sum of dt (chunk_s [B][chunk][d_inner]); scan_fold_kernel walks h <- exp(A sum dt_k) h + q_k over them and
 // leaves every chunk's start state in place of its end state, from which the full pass runs.
-// Bound by ALU issue: 95 vector instructions per step of the full pass, at 4.4 clocks each (v_exp takes 8; an
-// instruction with an SGPR operand takes 4.4 where two register-only ones of different wavefronts take 5.5 together);
-// 16384 x 4096 bf16: 188 us full pass + 137 us state-only pass + 10 us fold = 342 us, lane = (channel, state) 384 us.
+// Bound by ALU issue, which is busy all of the time: 96 vector instructions per step of the full pass, 70 of the state-only
+// one, at 4.7 and 4.9 clocks each (v_exp takes 8; an instruction with an SGPR operand takes 4.4 where two register-only ones of
+// different wavefronts take 5.5 together).  16384 x 4096 bf16, launches alone: 351 us, lane = (channel, state) 385; within
+// a layer, behind a GEMM, the full pass takes 201 us, the state-only pass 150 and the fold 13.
 constexpr int kLaneRun = 8;
 constexpr int kLaneWaves = 4096;
 constexpr int kLaneMinLen = 64;
