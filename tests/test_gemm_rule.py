@@ -48,7 +48,9 @@ def tile(rule):
     # slower as a stream of big tiles: a partial round in quarters, in halves over a short K, mostly padding
     (3072, 8, 1024, 2048, "t128"), (1536, 4, 2048, 4096, "t128"), (768, 2, 2048, 4096, "t128"), (5387, 8, 1024, 768, "t128"),
     (400, 1, 1024, 2048, "t128"), (512, 1, 8192, 2048, "t128"), (400, 1, 8192, 2048, "t128"),
-    (2720, 16, 3072, 768, "t128"), (2800, 16, 1536, 3072, "t128"), (2720, 16, 8192, 2048, "stream"),      # few rows a group (14736, 16, 384, 1536, "t128"), (23704, 8, 640, 384, "t128"),
+    (14736, 16, 384, 1536, "t128"), (23704, 8, 640, 384, "t128"),
+    # few rows a group
+    (2720, 16, 3072, 768, "t128"), (2800, 16, 1536, 3072, "t128"), (2720, 16, 8192, 2048, "stream"),
     # no whole slabs
     (16384, 8, 4000, 1000, "t128"), (16384, 8, 2080, 520, "t128"),
     # the recurrent step
