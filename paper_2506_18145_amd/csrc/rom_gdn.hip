@@ -65,6 +65,12 @@ struct GdnSmem {
 // above the diagonal do not exist.  Lane (g, c) owns row 16 tb + c, columns 32 k2 + 4 g .. +3 and 32 k2 + 16 + 4 g .. +3.
 constexpr int kFrags = 6;
 constexpr size_t kFragFloats = 2 * kFrags * 64 * 4;       // of one chunk, in floats
+template <int NS>
+struct GdnOneSmem {
+  GdnSmem<NS, false> main;
+  GdnPrepSmem<NS> prep;
+  u32x4_t frags[2 * kFrags * 64];
+};
 __device__ __forceinline__ constexpr int frag_id(int tb, int k2) { return k2 == 0 ? tb : 2 + tb; }
 
 __device__ __forceinline__ float sum_sq8(const u32x4_t &v) {
@@ -140,20 +146,17 @@ __device__ __forceinline__ void invert_unit_lower(const float (*am)[kQ + 4], flo
 // and in the main pass.  Here three or four workgroups share a CU and cover one another's waits, and the
 // recurrence has three barriers a chunk instead of eight.  1 x 16384 x 2048, 32 heads of 64: this launch, carry, fold and
 // main pass 573 -> 408 us, the layer 1467 -> 1166 us.
+// T and G of the chunk at step t0 of a sequence of L steps (qkv_b, proj_b: its first step), head h, as fragments: `out` is the
+// calling lane's place in the first of them.
 template <int NS>
-__global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
-    const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col, const bf16_t *__restrict__ proj, int64_t ld_p,
-    int b_col, int a_col, const float *__restrict__ dt_bias, const float *__restrict__ A_log, int64_t L, int n_chunks,
-    int n_heads, u32x4_t *__restrict__ frags) {
-  __shared__ GdnPrepSmem<NS> sm;
+__device__ __forceinline__ void gdn_prep_chunk(GdnPrepSmem<NS> &sm, const bf16_t *__restrict__ qkv_b, int64_t ld_qkv, int q_col,
+                                               int k_col, const bf16_t *__restrict__ proj_b, int64_t ld_p, int b_col, int a_col,
+                                               const float *__restrict__ dt_bias, const float *__restrict__ A_log, int64_t L,
+                                               int64_t t0, int h, u32x4_t *out) {
   constexpr int kKS = NS / 32;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c = lane & 15;
-  const int h = blockIdx.x % n_heads;
-  const int64_t bc = blockIdx.x / n_heads;
-  const int64_t b = bc / n_chunks, chunk = bc % n_chunks, t0 = chunk * kQ;
-  const bf16_t *qkv_b = qkv + b * L * ld_qkv;
 
   u32x4_t pk[NS / 32], pq[NS / 32];
 #pragma unroll
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
   }
   if (wave == 3) {
     const bool live = t0 + lane < L;
-    const bf16_t *row = proj + (b * L + (live ? t0 + lane : L - 1)) * ld_p;
+    const bf16_t *row = proj_b + (live ? t0 + lane : L - 1) * ld_p;
     const float pb = bf16_to_f32(row[b_col + h]), pa = bf16_to_f32(row[a_col + h]);
     const float beta = live ? fast_rcp(1.0f + __expf(-pb)) : 0.0f;
     const float gl = live ? -__expf(A_log[h]) * softplus_f32(pa + dt_bias[h]) : 0.0f;
@@ -186,7 +189,6 @@ __global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
 
   // scores of this wavefront's 16 steps t = 16 wave + c against all s <= t, computed transposed: a lane's
   // values of G are the row segment that its fragments hold
-  u32x4_t *out = frags + ((b * n_heads + h) * n_chunks + chunk) * (2 * kFrags * 64) + lane;
   {
     const float cum_t = sm.cum[16 * wave + c], beta_t = sm.beta[16 * wave + c];
     u32x2_t gpk[4];
@@ -233,6 +235,19 @@ __global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
   }
 }
 
+template <int NS>
+__global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
+    const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col, const bf16_t *__restrict__ proj, int64_t ld_p,
+    int b_col, int a_col, const float *__restrict__ dt_bias, const float *__restrict__ A_log, int64_t L, int n_chunks,
+    int n_heads, u32x4_t *__restrict__ frags) {
+  __shared__ GdnPrepSmem<NS> sm;
+  const int h = blockIdx.x % n_heads;
+  const int64_t bc = blockIdx.x / n_heads;
+  const int64_t b = bc / n_chunks, chunk = bc % n_chunks;
+  gdn_prep_chunk<NS>(sm, qkv + b * L * ld_qkv, ld_qkv, q_col, k_col, proj + b * L * ld_p, ld_p, b_col, a_col, dt_bias, A_log, L,
+                     chunk * kQ, h, frags + ((b * n_heads + h) * n_chunks + chunk) * (2 * kFrags * 64) + (threadIdx.x & 63));
+}
+
 //   qkv   bf16 [B*L, ld_qkv] after conv + SiLU: q of head h at q_col + NS h, k at k_col + NS h, v at v_col + 64 h
 //   proj  bf16 [B*L, ld_p]: z of head h at columns 64 h, the beta logit at b_col + h, the decay logit at a_col + h
 //   s_in / s_out f32 [B][H][NS][64] (S^T: [d_k][d_v]) or NULL;   y bf16 [B*L, ld_y]: RMSNorm_head(o) * norm_w * SiLU(z)
@@ -240,7 +255,8 @@ __global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
 //   carry_z f32 [B][H][n_seg][NS][64] <- Z^T, carry_m f32 [B][H][n_seg][NS][NS] <- [n][j] = Phi[j][n].
 //   frags: gdn_prep_kernel's T and G of every chunk
 // Main pass with n_seg > 1: segment `seg` starts from s_start f32 [B][H][n_seg][NS][64].
-template <int NS, bool CARRY>
+// ONE: the sequences are one chunk, whose T and G this workgroup forms itself and keeps in LDS (frags unused).
+template <int NS, bool CARRY, bool ONE = false>
 __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col,
                                                      int v_col, const bf16_t *__restrict__ proj, int64_t ld_p, int b_col,
                                                      int a_col, const float *__restrict__ dt_bias,
@@ -272,6 +288,9 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
   f32x4_t sacc[kG][kNB];
   const int64_t s_stride = static_cast<int64_t>(NS) * kV;
   const int64_t unit = (b * n_heads + h) * n_seg + seg;
+  GdnOneSmem<NS> &one = *reinterpret_cast<GdnOneSmem<NS> *>(smem_raw);
+  if constexpr (ONE)
+    gdn_prep_chunk<NS>(one.prep, qkv_b, ld_qkv, q_col, k_col, proj_b, ld_p, b_col, a_col, dt_bias, A_log, L, 0, h, one.frags + lane);
 #pragma unroll
   for (int grp = 0; grp < kG; ++grp)
 #pragma unroll
@@ -335,7 +354,7 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
   };
   fetch_main(ts);
   fetch_out(ts);
-  const u32x4_t *frag_ptr = frags + ((b * n_heads + h) * n_chunks + ts / kQ) * (2 * kFrags * 64) + lane;
+  const u32x4_t *frag_ptr = ONE ? one.frags + lane : frags + ((b * n_heads + h) * n_chunks + ts / kQ) * (2 * kFrags * 64) + lane;
 
   for (int64_t t0 = ts; t0 < te; t0 += kQ) {
     // The lane's coordinates go through an opaque copy every chunk: with them loop-invariant the compiler
@@ -677,6 +696,7 @@ __global__ __launch_bounds__(256) void gdn_step_kernel(const bf16_t *__restrict_
   }
 }
 
+constexpr int kGdnOneWgs = 256;
 struct GdnPlanSeg {
   int n_seg;
   int64_t seg_len;
@@ -696,7 +716,7 @@ GdnPlanSeg gdn_plan(int64_t B, int64_t L, int n_heads) {
   return p;
 }
 
-template <int NS, bool CARRY>
+template <int NS, bool CARRY, bool ONE = false>
 hipError_t gdn_allow_lds() {
   // more than 64 KiB of dynamic LDS: a function attribute, set once per device
   static std::mutex mu;
@@ -708,8 +728,8 @@ hipError_t gdn_allow_lds() {
   if (!done[dev].load(std::memory_order_acquire)) {
     std::lock_guard<std::mutex> lock(mu);
     if (!done[dev].load(std::memory_order_relaxed)) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gdn_kernel<NS, CARRY>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizeof(GdnSmem<NS, CARRY>)));
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gdn_kernel<NS, CARRY, ONE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(ONE ? sizeof(GdnOneSmem<NS>) : sizeof(GdnSmem<NS, CARRY>)));
       if (e != hipSuccess) return e;
       done[dev].store(true, std::memory_order_release);
     }
@@ -736,6 +756,15 @@ hipError_t gdn_dispatch(const bf16_t *qkv, int64_t ld_qkv, int q_col, int k_col,
   float *carry_z = carry, *carry_m = carry + units * NS * kV, *s_start = carry_m + units * NS * NS;
   const dim3 grid(static_cast<unsigned>(n_heads), static_cast<unsigned>(B * p.n_seg));
   hipError_t e;
+  // One chunk and no more workgroups than CUs: the preparation has nothing to share a CU with, and the launch costs 2 us
+  // (four sequences of 64 steps, 32 heads of 64: 14.1 us in two launches, 11.2 in one; 12 sequences 18.0 / 22.2).
+  if (n_chunks == 1 && B * n_heads <= kGdnOneWgs) {
+    if ((e = gdn_allow_lds<NS, false, true>()) != hipSuccess) return e;
+    hipLaunchKernelGGL((gdn_kernel<NS, false, true>), grid, dim3(256), sizeof(GdnOneSmem<NS>), s, qkv, ld_qkv, q_col, k_col, v_col, proj,
+                       ld_p, b_col, a_col, dt_bias, A_log, norm_w, eps, L, p.n_seg, p.seg_len, 1, static_cast<const u32x4_t *>(nullptr),
+                       carry_z, carry_m, s_start, s_in, s_out, y, ld_y);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((gdn_prep_kernel<NS>), dim3(static_cast<unsigned>(B * n_chunks * n_heads)), dim3(256), 0, s, qkv, ld_qkv,
                      q_col, k_col, proj, ld_p, b_col, a_col, dt_bias, A_log, L, static_cast<int>(n_chunks), n_heads, frags);
   if ((e = hipGetLastError()) != hipSuccess) return e;

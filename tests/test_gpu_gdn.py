@@ -245,3 +245,15 @@ def test_gdn_prepared_chunks_and_segments(seq_len, d_k):
     ss = (0.3 * rng.standard_normal((cfg.batch, cfg.n_heads, cfg.d_k, cfg.d_v))).astype(np.float32)
     gpu, x_np, w_np = run_gdn(cfg, conv_state=cs, ssm_state=ss)
     compare_gdn(cfg, gpu, x_np, w_np, conv_state=cs, ssm_state=ss)
+
+
+@pytest.mark.parametrize("d_k", [64, 128])
+@pytest.mark.parametrize("batch,seq_len", [(1, 2), (3, 63), (32, 64), (33, 64), (33, 5)])      # 8 heads: up to 256 workgroups, and more
+def test_gdn_single_chunk(batch, seq_len, d_k):
+    """Sequences of one chunk: T and the scores from the recurrence's own workgroup, or from a launch of their own."""
+    cfg = get_gdn_config("gdn_small", cfg_id=93, batch=batch, seq_len=seq_len, d_k=d_k, weight_std=0.05)
+    rng = np.random.default_rng(seq_len)
+    cs = rng.standard_normal((cfg.batch, cfg.d_conv_ch, 3)).astype(np.float32)
+    ss = (0.3 * rng.standard_normal((cfg.batch, cfg.n_heads, cfg.d_k, cfg.d_v))).astype(np.float32)
+    gpu, x_np, w_np = run_gdn(cfg, conv_state=cs, ssm_state=ss)
+    compare_gdn(cfg, gpu, x_np, w_np, conv_state=cs, ssm_state=ss)
