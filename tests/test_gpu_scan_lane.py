@@ -1,4 +1,4 @@
-"""The lane = channel scan: calls with 2048 wavefronts of 64 channels or more (one pass), and few long sequences
+"""The lane = channel scan: calls with 2048 x 64 channels over all sequences or more (one pass), and few long sequences
 (time chunks with a fold between the passes), at chunk remainders, a ragged last channel group and one long L."""
 import numpy as np
 import pytest
