@@ -827,9 +827,15 @@ __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(cons
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, one stream of slabs per CU
 // The large routed projections: bound by the power the matrix pipe draws (a slab of random operands takes 1.5 us, of zeros
-// 1.05; its MFMAs 0.85 us at 2.4 GHz, 1.0 at the 2.06 that the clock falls to), then by what stops it: the stores and the last
-// round; the pipe is busy for 56 % of a launch.  16384 rows in 8 groups, 8192 x 2048: 550 -> 503 us, 2048 x 4096: 309 -> 260 us
-// (one 256 x 256 tile per workgroup of eight wavefronts before).
+// 1.05; its MFMAs 0.85 us at 2.4 GHz, 1.0 at the 2.06 that the clock falls to), then by what stands between two tiles.  Of
+// 16384 rows x 8192 x 2048 a launch without stores and epilogue takes 405 us.  With both, counted with the cycle counter per
+// tile (32 slabs of 2420 cycles): a wavefront alone on its SIMD issues an instruction every five cycles, the L2 of an XCD
+// takes about 16 bytes a cycle from each of its CUs when all store at once, and a wait for a register that came from memory
+// drains the ring.  Hence: the stores spread over eight slabs, each covering 64 bytes of a row; everything else that a tile
+// needs (row numbers, scales, the place of a later tile, offsets) between MFMAs; nothing spilled.  91.9 k cycles a tile
+// (14.5 k more than its slabs) -> 84 k.  16384 rows in 8 even groups, against the same kernel without this: 8192 x 512
+// 167 -> 139 us, x 1024 276 -> 248, x 2048 467 -> 445, 2048 x 4096 217 -> 209; SwiGLU 4096 x 1024 144 -> 131; contraction-major
+// 4096 x 2048 257 -> 245.
 // One workgroup of four wavefronts per CU (2 x 2, 128 x 128 each: 256 accumulator
 // registers, a third less LDS traffic per flop than eight 64 x 128 ones) walks its share of the 256 x 256 tiles; the ring
 // of five half-slab slots above runs on across tile boundaries: the last two slabs of a tile already request the next
@@ -843,9 +849,9 @@ __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(cons
 // Slab m's schedule, P = the one barrier per slab (slab m + 1 landed, slab m in registers):
 //   step 0: W(m+1) second half | 1, 2: A(m+2) | P | 3: W(m+2) first half, first fragments of slab m + 1
 // Rows past a group's end re-read the tile's first row and store that row's result over itself, so that every
-// wavefront issues the same number of stores and the waits can count them.  Half of a tile's stores go out at once, the
-// rest behind the next two barriers: loads and stores retire in order, and 128 KiB per CU at one time keep the memory
-// busy for longer than the ring lasts.
+// wavefront's requests for activations are whole.  Half of a tile's stores go out at once, the rest two a slab behind the
+// barriers of the next slabs: loads and stores retire in order, and 128 KiB per CU at one time keep the L2 busy for longer
+// than the ring lasts.
 // An XCD's tiles rarely fill a whole number of rounds: its last, partial round is cut into 2, 4 or 8 pieces a tile, as
 // many as give every CU one (dma_tile), and pieces without a row of their group do nothing.
 struct StreamTile {
@@ -860,42 +866,71 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int kPieces = EPI == kEpiSwiGLU ? TN : 2 * TN;    // 16-byte stores per lane and 32-row block
 
   // ---- this workgroup's tiles
+  // Lane e keeps where group e's tiles end, and the group's rows: finding a tile's group is a ballot, not a walk over the
+  // offsets in memory (at most 64 groups: gemm_tile).
   const int n_tiles = (a.N + 255) / 256;
-  int m_tiles = 0;
-  if (a.offsets == nullptr) {
-    m_tiles = static_cast<int>((a.M + 255) / 256);
-  } else {
-    for (int e = 0; e < a.n_groups; ++e) m_tiles += (a.offsets[e + 1] - a.offsets[e] + 255) / 256;
+  int m_tiles, grp_end, grp_lo, grp_hi;
+  {
+    const int e = threadIdx.x & 63;
+    const bool have = a.offsets != nullptr && e < a.n_groups;
+    grp_lo = have ? a.offsets[e] : 0;
+    grp_hi = have ? a.offsets[e + 1] : a.offsets == nullptr && e == 0 ? static_cast<int>(a.M) : 0;
+    grp_end = (grp_hi - grp_lo + 255) / 256;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int below = __shfl_up(grp_end, d);
+      if (e >= d) grp_end += below;
+    }
+    m_tiles = __builtin_amdgcn_readlane(grp_end, 63);
   }
   const int pn = patch_n_for(n_tiles), pm = kPatchTiles / pn;
   const int xcd = blockIdx.x % 8, cu = blockIdx.x / 8, cus = gridDim.x / 8;
   const int64_t total = static_cast<int64_t>(m_tiles) * n_tiles;
   const int tile_lo = static_cast<int>(total * xcd / 8), tile_hi = static_cast<int>(total * (xcd + 1) / 8);
-  auto locate = [&](int t) __attribute__((always_inline)) {
+  // x / d for 0 <= x < 2^31 with inv = ceil(2^32 / d), d > 1: the product is less than half too large
+  auto inverse = [](int d) { return d > 1 ? 0xFFFFFFFFu / static_cast<unsigned>(d) + 1u : 0u; };
+  auto divide = [](int x, int d, unsigned inv) __attribute__((always_inline)) {
+    if (d == 1) return x;
+    const int q = static_cast<int>(__umulhi(static_cast<unsigned>(x), inv));
+    return q * d > x ? q - 1 : q;
+  };
+  const int band_tiles = pm * n_tiles, last_rows = m_tiles % pm;
+  const unsigned inv_band = inverse(band_tiles), inv_pm = inverse(pm), inv_last = inverse(last_rows);
+  const int pn_log2 = __builtin_ctz(pn);
+  // in stages short enough to stand between two MFMAs
+  struct Finder {
+    int t, band, rows, in, in_col, mt;
     StreamTile tl;
-    const int band = t / (pm * n_tiles);                      // pm tile rows (fewer in the last band) x all columns
-    const int rows = m_tiles - band * pm < pm ? m_tiles - band * pm : pm;
-    const int r = t - band * pm * n_tiles;
-    const int patch = r / (rows * pn), in = r - patch * (rows * pn);
-    int mt = band * pm + in % rows;
-    tl.n0 = (patch * pn + in / rows) * 256;
-    tl.group = 0;
-    tl.row0 = mt * 256;
-    tl.row_end = static_cast<int>(a.M);
-    if (a.offsets != nullptr) {
-      for (int e = 0; e < a.n_groups; ++e) {
-        const int lo = a.offsets[e], hi = a.offsets[e + 1], tiles = (hi - lo + 255) / 256;
-        if (mt < tiles) {
-          tl.group = e;
-          tl.row0 = lo + mt * 256;
-          tl.row_end = hi;
-          break;
-        }
-        mt -= tiles;
-      }
+  };
+  auto locate_stage = [&](Finder &f, int stage) __attribute__((always_inline)) {
+    if (stage == 0) {
+      f.band = divide(f.t, band_tiles, inv_band);             // pm tile rows (fewer in the last band) x all columns
+      f.rows = m_tiles - f.band * pm >= pm ? pm : last_rows;
+    } else if (stage == 1) {
+      const int r = f.t - f.band * band_tiles, patch = divide(r >> pn_log2, f.rows, f.rows == pm ? inv_pm : inv_last);
+      f.in = r - patch * (f.rows << pn_log2);
+      f.tl.n0 = (patch << pn_log2) * 256;
+    } else if (stage == 2) {
+      f.in_col = divide(f.in, f.rows, f.rows == pm ? inv_pm : inv_last);
+      f.mt = f.band * pm + f.in - f.in_col * f.rows;
+      f.tl.n0 += f.in_col * 256;
+    } else if (stage == 3) {
+      f.tl.group = __builtin_popcountll(__ballot(grp_end <= f.mt));
+    } else if (stage == 4) {
+      f.tl.row0 = __builtin_amdgcn_readlane(grp_lo, f.tl.group);
+      f.tl.row_end = __builtin_amdgcn_readlane(grp_hi, f.tl.group);
+    } else if (stage == 5) {                                  // the group's first tile: its end less its tiles
+      const int first = __builtin_amdgcn_readlane(grp_end, f.tl.group) - (f.tl.row_end - f.tl.row0 + 255) / 256;
+      f.tl.row0 += (f.mt - first) * 256;
+      if (f.tl.row_end > f.tl.row0 + 256) f.tl.row_end = f.tl.row0 + 256;
     }
-    if (tl.row_end > tl.row0 + 256) tl.row_end = tl.row0 + 256;
-    return tl;
+  };
+  auto locate = [&](int t) __attribute__((always_inline)) {
+    Finder f;
+    f.t = t;
+#pragma unroll
+    for (int stage = 0; stage < 6; ++stage) locate_stage(f, stage);
+    return f.tl;
   };
   const int rounds = (tile_hi - tile_lo) / cus, rest = (tile_hi - tile_lo) % cus;
   // pieces per tile of the last round: 1 (then it is a round like the others), 2, 4 or 8
@@ -922,8 +957,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     w_lds[j] = __builtin_amdgcn_readfirstlane(lds_base + bw * 1024);
   }
   // tile row / weight row that this lane fetches with instruction j; the lane number passes through an empty asm so that
-  // the compiler forms these (once a tile) anew instead of keeping them in registers.  (All 512 are in use and 18 to 33,
-  // depending on the epilogue, are spilled: in the first two and the last two slabs of a tile and between tiles.)
+  // the compiler forms these (once a tile) anew instead of keeping them in registers.  (Spilling even a few costs the ring:
+  // a reload waits for everything outstanding.  One epilogue for whole and for partial column tiles for the same reason:
+  // with a branch between two, the compiler moved the work common to both, all 256 sums, ahead of the branch.)
   auto here = [&]() __attribute__((always_inline)) {
     int l = threadIdx.x & 63;
     asm volatile("" : "+v"(l));
@@ -938,17 +974,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto a_offset = [&](int j, int l, int64_t row) __attribute__((always_inline)) {
     return static_cast<unsigned>((row * a.lda + ((l & 7) ^ ((a_row(j, l) >> 1) & 7)) * 8) * 2);
   };
-  auto set_w = [&](const StreamTile &tl) __attribute__((always_inline)) {
-    const int l = here();
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      if constexpr (WT) {
-        w_voff[j] = static_cast<unsigned>((static_cast<int64_t>(w_row(j, l)) * a.N + ((l & 31) ^ (4 * (w_row(j, l) & 3))) * 8) * 2);
-      } else {
-        const int r = w_row(j, l) < a.N - tl.n0 ? w_row(j, l) : a.N - tl.n0 - 1;     // rows past N: never stored
-        w_voff[j] = static_cast<unsigned>((static_cast<int64_t>(r) * a.K + ((l & 7) ^ ((w_row(j, l) >> 1) & 7)) * 8) * 2);
-      }
+  auto set_w = [&](const StreamTile &tl, int j, int l) __attribute__((always_inline)) {
+    if constexpr (WT) {
+      w_voff[j] = static_cast<unsigned>((static_cast<int64_t>(w_row(j, l)) * a.N + ((l & 31) ^ (4 * (w_row(j, l) & 3))) * 8) * 2);
+    } else {
+      const int r = w_row(j, l) < a.N - tl.n0 ? w_row(j, l) : a.N - tl.n0 - 1;       // rows past N: never stored
+      w_voff[j] = static_cast<unsigned>((static_cast<int64_t>(r) * a.K + ((l & 7) ^ ((w_row(j, l) >> 1) & 7)) * 8) * 2);
     }
+  };
+  auto w_at = [&](const StreamTile &tl) __attribute__((always_inline)) {
     const int64_t at = WT ? static_cast<int64_t>(tl.group) * a.N * a.K + tl.n0
                           : (static_cast<int64_t>(tl.group) * a.N + tl.n0) * a.K;
     return static_cast<const char *>(a.W) + at * 2;
@@ -1029,14 +1063,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const auto none = [](int) {};
 
   // ---- fill the ring for the first tile: A(0) W(0) A(1) W(1) A(2)
-  StreamTile cur = locate(t);
-  w_ptr = set_w(cur);
+  StreamTile cur = locate(t), nxt = locate(t + cus < tile_end ? t + cus : t);
+  w_ptr = w_at(cur);
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     const int l = here();
+    set_w(cur, j, l);
     int p = cur.row0 + a_row(j, l);
     if (p >= cur.row_end) p = cur.row0;
     a_voff[j] = a_offset(j, l, a.a_rows ? a.a_rows[p] : p);
+  }
+  int c_pos[TM], c_next[TM];                                  // row of C that lane l & 31 has in each 32-row block
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    int p = cur.row0 + wm * 128 + i * 32 + (here() & 31);
+    if (p >= cur.row_end) p = cur.row0;
+    c_pos[i] = a.c_rows ? a.c_rows[p] : p;
   }
 #pragma unroll
   for (unsigned h = 0; h < 5; ++h) {
@@ -1057,121 +1099,142 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   for (int j = 0; j < TN; ++j) fb0[j] = read_w(1, 0, j);
 #pragma unroll
   for (int i = 1; i < TM; ++i) fa0[i] = read_a(0, 0, i);
-  bool strict = true;                                         // fewer stores than counted behind the outstanding DMA
   u32x4_t held[TM / 2][kPieces];                              // the previous tile's last two row blocks
-  bf16_t *held_row[TM / 2];
-  int held_cols = 0;                                          // columns of those rows that exist, 0: nothing held
-  auto store_held = [&](int i) __attribute__((always_inline)) {
-    if (held_cols >= 128) {
-#pragma unroll
-      for (int pc = 0; pc < kPieces; ++pc) *reinterpret_cast<u32x4_t *>(held_row[i] + pc * 16) = held[i][pc];
-    } else if (held_cols > 0) {
-#pragma unroll
-      for (int pc = 0; pc < kPieces; ++pc)
-        if (pc * 16 + frag_half * 8 < held_cols) *reinterpret_cast<u32x4_t *>(held_row[i] + pc * 16) = held[i][pc];
-    }
+  int held_pos[TM / 2];                                       // their rows of C, as lane l & 31 has them
+  int held_col = 0, held_cols = 0;                            // their first column, and how many exist (0: nothing held)
+  // a store instruction covers 16 rows x 32 columns: lane l has row (l & 15) + 16 h and eight columns from store_col on
+  auto store_col = [&]() __attribute__((always_inline)) {
+    const int l = here();
+    return (l & 16) + (l >> 5) * 8;
+  };
+  auto out_at = [&](int pos, int h, int col) __attribute__((always_inline)) {
+    const auto rows = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(pos), static_cast<unsigned>(pos), false, false);
+    return static_cast<uint64_t>(rows[h]) * static_cast<uint64_t>(a.ldc) + static_cast<uint64_t>(col + store_col());
+  };
+  constexpr int kHeld = TM / 2 * kPieces, kHeldSlabs = kHeld / 2;
+  auto store_held = [&](int k) __attribute__((always_inline)) {
+    const int i = k / kPieces, pc = k % kPieces;
+    const uint64_t at = out_at(held_pos[i], pc & 1, held_col);       // (trades between lanes: with all of them active)
+    if (pc / 2 * 32 + store_col() < held_cols)
+      *reinterpret_cast<u32x4_t *>(static_cast<bf16_t *>(a.C) + at + pc / 2 * 32) = held[i][pc];
   };
 
   // a slab of the steady state; at the tile's end the caller has pointed a_ptr / w_ptr at the next tile
-  auto slab_head = [&]() __attribute__((always_inline)) {
+  auto slab_head = [&](auto other) __attribute__((always_inline)) {
     const unsigned rw = mod5(ra + 1), rw1 = mod5(ra + 3);
-    step(False{}, fa0, fb0, fa1, fb1, ra, rw, 1, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_w(rw1, 4 + q / 4); });
+    step(False{}, fa0, fb0, fa1, fb1, ra, rw, 1, [&](int q) __attribute__((always_inline)) {
+      if (q % 4 == 3) dma_w(rw1, 4 + q / 4);
+      other(q);
+    });
     w_ptr += w_step;
   };
-  auto slab_mid = [&]() __attribute__((always_inline)) {
+  auto slab_mid = [&](auto other) __attribute__((always_inline)) {
     const unsigned rw = mod5(ra + 1), ra2 = mod5(ra + 4);
-    step(False{}, fa1, fb1, fa0, fb0, ra, rw, 2, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_a(ra2, q / 4); });
+    step(False{}, fa1, fb1, fa0, fb0, ra, rw, 2, [&](int q) __attribute__((always_inline)) {
+      if (q % 4 == 3) dma_a(ra2, q / 4);
+      other(q);
+    });
     step(False{}, fa0, fb0, fa1, fb1, ra, rw, 3, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_a(ra2, 4 + q / 4); });
     a_ptr += a_step;
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NI) : "memory");
   };
-  auto slab_tail = [&]() __attribute__((always_inline)) {
+  auto slab_tail = [&](auto other) __attribute__((always_inline)) {
     const unsigned r0 = ra;
     ra = mod5(ra + 2);
-    step(False{}, fa1, fb1, fa0, fb0, ra, mod5(ra + 1), 0, [&](int q) __attribute__((always_inline)) { if (q % 4 == 3) dma_w(r0, q / 4); });
+    step(False{}, fa1, fb1, fa0, fb0, ra, mod5(ra + 1), 0, [&](int q) __attribute__((always_inline)) {
+      if (q % 4 == 3) dma_w(r0, q / 4);
+      other(q);
+    });
   };
 
   for (;;) {
-    const bool last = t + cus >= tile_end;
-    const StreamTile nxt = last ? cur : locate(t + cus);      // after the last tile: its own first slabs again, unused
-    // slab 0: its W(1) and A(2) were requested before the previous tile's stores
+    const bool last = t + cus >= tile_end;                    // after the last tile: its own first slabs again, unused
+    // slab 0: its W(1) and A(2) were requested before the previous tile's stores, so that it requests nothing but the row
+    // numbers of the next tile and this tile's row scales: the wait for these ends with everything landed in any case
+    float scale[TM];
     {
+      int idx_a[NI], idx_c[TM], sc[TM];
       const unsigned rw = mod5(ra + 1);
-      step(True{}, fa0, fb0, fa1, fb1, ra, rw, 1, none);
+      step(True{}, fa0, fb0, fa1, fb1, ra, rw, 1, [&](int q) __attribute__((always_inline)) {
+        if (q < NI) {
+          int p = nxt.row0 + a_row(q, here());
+          if (p >= nxt.row_end) p = nxt.row0;
+          a_next[q] = static_cast<unsigned>(p);
+          idx_a[q] = load_idx(a.a_rows ? static_cast<const void *>(a.a_rows) : a.A, a.a_rows ? static_cast<unsigned>(p) * 4u : 0u);
+        } else if (q < NI + TM) {
+          const int i = q - NI;
+          int p = nxt.row0 + wm * 128 + i * 32 + (here() & 31);
+          if (p >= nxt.row_end) p = nxt.row0;
+          c_next[i] = p;
+          idx_c[i] = load_idx(a.c_rows ? static_cast<const void *>(a.c_rows) : a.A, a.c_rows ? static_cast<unsigned>(p) * 4u : 0u);
+        } else if constexpr (EPI != kEpiPlain) {
+          const int i = q - NI - TM;
+          sc[i] = load_idx(a.row_scale ? static_cast<const void *>(a.row_scale) : a.A, a.row_scale ? static_cast<unsigned>(c_pos[i]) * 4u : 0u);
+        }
+      });
       step(False{}, fa1, fb1, fa0, fb0, ra, rw, 2, none);
       step(False{}, fa0, fb0, fa1, fb1, ra, rw, 3, none);
-      if (strict) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI + TM / 2 * kPieces) : "memory");
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      store_held(0);
-      slab_tail();
-    }
-    // slab 1: with the row numbers of the next tile's A and of this tile's C
-    int idx_a[NI], idx_c[TM];
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      int p = nxt.row0 + a_row(j, here());
-      if (p >= nxt.row_end) p = nxt.row0;
-      a_next[j] = static_cast<unsigned>(p);
-      idx_a[j] = load_idx(a.a_rows ? static_cast<const void *>(a.a_rows) : a.A, a.a_rows ? static_cast<unsigned>(p) * 4u : 0u);
-    }
-    int c_pos[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      int p = cur.row0 + wm * 128 + i * 32 + (here() & 31);
-      if (p >= cur.row_end) p = cur.row0;
-      c_pos[i] = p;
-      idx_c[i] = load_idx(a.c_rows ? static_cast<const void *>(a.c_rows) : a.A, a.c_rows ? static_cast<unsigned>(p) * 4u : 0u);
-    }
-    slab_head();
-    slab_mid();
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      asm volatile("" : "+v"(idx_a[j]));
-      a_next[j] = a_offset(j, here(), a.a_rows ? idx_a[j] : static_cast<int>(a_next[j]));
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      asm volatile("" : "+v"(idx_c[i]));
-      if (a.c_rows) c_pos[i] = idx_c[i];
-    }
-    store_held(1);
-    slab_tail();
-    // slab 2: with the row scales
-    float scale[TM];
-    if constexpr (EPI == kEpiPlain) {
-      slab_head();
-      slab_mid();
-    } else {
-      int sc[TM];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        sc[i] = load_idx(a.row_scale ? static_cast<const void *>(a.row_scale) : a.A, a.row_scale ? static_cast<unsigned>(c_pos[i]) * 4u : 0u);
-      slab_head();
-      slab_mid();
+      for (int j = 0; j < NI; ++j) {
+        asm volatile("" : "+v"(idx_a[j]));
+        if (a.a_rows) a_next[j] = static_cast<unsigned>(idx_a[j]);
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        asm volatile("" : "+v"(sc[i]));
-        scale[i] = a.row_scale ? __int_as_float(sc[i]) : 1.0f;
+        asm volatile("" : "+v"(idx_c[i]));
+        if (a.c_rows) c_next[i] = idx_c[i];
+        if constexpr (EPI != kEpiPlain) {
+          asm volatile("" : "+v"(sc[i]));
+          scale[i] = a.row_scale ? __int_as_float(sc[i]) : 1.0f;
+        }
       }
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
-    slab_tail();
+    // slabs 0 .. kHeldSlabs - 1 each with two of the stores that the previous tile has left
+    auto held_pair = [&](int m, int q) __attribute__((always_inline)) {
+      if (m < kHeldSlabs && (q == 5 || q == 13)) store_held(2 * m + q / 8);
+    };
+    slab_tail([&](int q) __attribute__((always_inline)) { held_pair(0, q); });
+    // slab 1: row numbers of A into offsets
+    slab_head([&](int q) __attribute__((always_inline)) {
+      if (q < NI) a_next[q] = a_offset(q, here(), static_cast<int>(a_next[q]));
+    });
+    slab_mid(none);
+    slab_tail([&](int q) __attribute__((always_inline)) { held_pair(1, q); });
+    // slab 2: where the tile after the next lies
+    Finder after;
+    after.t = t + 2 * cus < tile_end ? t + 2 * cus : t;
+    slab_head([&](int q) __attribute__((always_inline)) { if (q % 2 == 0) locate_stage(after, q / 2); });
+    slab_mid(none);
+    slab_tail([&](int q) __attribute__((always_inline)) { held_pair(2, q); });
     for (int m = 3; m < KT - 2; ++m) {
-      slab_head();
-      slab_mid();
-      slab_tail();
+      slab_head(none);
+      slab_mid(none);
+      slab_tail([&](int q) __attribute__((always_inline)) {
+        if (q == 5 || q == 13) {
+#pragma unroll
+          for (int h = 3; h < kHeldSlabs; ++h)
+            if (m == h) held_pair(h, q);
+        }
+      });
     }
+#pragma unroll
+    for (int h = 3; h < kHeldSlabs; ++h)                      // a short K: what is left
+      if (KT - 2 <= h) {
+        held_pair(h, 5);
+        held_pair(h, 13);
+      }
     // slab KT - 2: A and W of the next tile from here on
-    slab_head();
+    slab_head(none);
     a_ptr = a_base_g;
 #pragma unroll
     for (int j = 0; j < NI; ++j) a_voff[j] = a_next[j];
-    slab_mid();
-    w_ptr = set_w(nxt);
-    slab_tail();
+    slab_mid([&](int q) __attribute__((always_inline)) { if (q % 2 == 0) set_w(nxt, q / 2, here()); });
+    w_ptr = w_at(nxt);
+    slab_tail(none);
     // slab KT - 1: everything that slab 0 of the next tile would request goes before the stores
-    slab_head();
-    slab_mid();
+    slab_head(none);
+    slab_mid(none);
     {
       const unsigned r0 = ra, r1 = mod5(ra + 1);
       ra = mod5(ra + 2);
@@ -1183,37 +1246,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 
     // ---- epilogue: a lane holds, for row frag_row of each 32-row block, columns 8 q + 4 frag_half + (0..3) of each
-    // 32-column block in elements 4 q ..; lanes l and l + 32 trade halves so that each has 8 neighbouring columns
-    // (held_cols counts output columns from this wavefront's first; kFull says that all of them exist)
+    // 32-column block in elements 4 q ..; lanes l and l + 32 trade halves so that each has 8 neighbouring columns, then
+    // lanes l and l + 16 trade rows between two neighbouring 16-column pieces, so that a store writes 64 bytes of each of
+    // 16 rows and not 32 of 32 (an L2 channel takes a request a clock, whatever its width).
+    // (held_cols counts output columns from this wavefront's first; there may be none)
     constexpr int kWaveCols = EPI == kEpiSwiGLU ? 64 : 128;
     const int col0 = (EPI == kEpiSwiGLU ? cur.n0 / 2 : cur.n0) + wn * kWaveCols;
     const int n_cols = (EPI == kEpiSwiGLU ? a.N / 2 : a.N) - col0;
-    auto finish = [&](auto all) __attribute__((always_inline)) {
+    // The residual's rows are asked for kAhead pairs of pieces ahead, and the two blocks that are held go first: few loads
+    // stand behind stores, whose acknowledgement they wait for.
+    constexpr bool kRes = EPI == kEpiRowScaleResidual;
+    constexpr int kPairs = kPieces / 2, kAhead = 3;
+    u32x4_t res[kRes ? kAhead : 1][2];
+    auto block = [](int ii) { return kRes ? (ii + TM / 2) % TM : ii; };
+    auto load_res = [&](int u) __attribute__((always_inline)) {      // u: pair of pieces, in the order of the loops below
+      const int pos = c_pos[block(u / kPairs)], pp = u % kPairs * 2, c = store_col();
+      const int back = pp * 16 + c < n_cols ? 0 : -(col0 + c) - pp * 16;   // past the end: the row's first columns
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int64_t at = static_cast<int64_t>(c_pos[i]) * a.ldc + col0 + frag_half * 8;
-        bf16_t *crow = static_cast<bf16_t *>(a.C) + at;
-        u32x4_t res[EPI == kEpiRowScaleResidual ? kPieces : 1];
-        if constexpr (EPI == kEpiRowScaleResidual) {
+      for (int h = 0; h < 2; ++h)
+        res[u % kAhead][h] = *reinterpret_cast<const u32x4_t *>(static_cast<const bf16_t *>(a.residual) + out_at(pos, h, col0) + back + pp * 16);
+    };
+    if constexpr (kRes) {
 #pragma unroll
-          for (int pc = 0; pc < kPieces; ++pc) {
-            res[pc] = u32x4_t{0u, 0u, 0u, 0u};
-            if (decltype(all)::value || pc * 16 + frag_half * 8 < n_cols)
-              res[pc] = *reinterpret_cast<const u32x4_t *>(static_cast<const bf16_t *>(a.residual) + at + pc * 16);
-          }
-        }
+      for (int u = 0; u < kAhead; ++u) load_res(u);
+    }
 #pragma unroll
-        for (int pc = 0; pc < kPieces; ++pc) {
+    for (int ii = 0; ii < TM; ++ii) {
+      const int i = block(ii);
+      const uint64_t at[2] = {out_at(c_pos[i], 0, col0), out_at(c_pos[i], 1, col0)};
+#pragma unroll
+      for (int pp = 0; pp < kPieces; pp += 2) {
+        u32x4_t o[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int pc = pp + e;
           unsigned x0, x1, y0, y1;
           if constexpr (EPI == kEpiSwiGLU) {
-            float o[2][4];
+            float g[2][4];
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
               for (int r = 0; r < 4; ++r)
-                o[m][r] = silu_f32(acc[i][pc][8 * m + r] * scale[i]) * (acc[i][pc][8 * m + 4 + r] * scale[i]);
-            x0 = pack_bf16x2(o[0][0], o[0][1]); x1 = pack_bf16x2(o[0][2], o[0][3]);
-            y0 = pack_bf16x2(o[1][0], o[1][1]); y1 = pack_bf16x2(o[1][2], o[1][3]);
+                g[m][r] = silu_f32(acc[i][pc][8 * m + r] * scale[i]) * (acc[i][pc][8 * m + 4 + r] * scale[i]);
+            x0 = pack_bf16x2(g[0][0], g[0][1]); x1 = pack_bf16x2(g[0][2], g[0][3]);
+            y0 = pack_bf16x2(g[1][0], g[1][1]); y1 = pack_bf16x2(g[1][2], g[1][3]);
           } else {
             const int j = pc / 2, q = (pc % 2) * 8;
             float v[8];
@@ -1224,31 +1300,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           }
           const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
           const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
-          u32x4_t o = {s0[0], s1[0], s0[1], s1[1]};
-          if constexpr (EPI == kEpiRowScaleResidual) {
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-              o[w] = pack_bf16x2(__uint_as_float(o[w] << 16) + __uint_as_float(res[pc][w] << 16),
-                                 __uint_as_float(o[w] & 0xFFFF0000u) + __uint_as_float(res[pc][w] & 0xFFFF0000u));
-          }
-          if (i >= TM / 2) held[i - TM / 2][pc] = o;
-          else if (decltype(all)::value || pc * 16 + frag_half * 8 < n_cols) *reinterpret_cast<u32x4_t *>(crow + pc * 16) = o;
+          o[e] = u32x4_t{s0[0], s1[0], s0[1], s1[1]};
           __builtin_amdgcn_sched_barrier(0);                  // (registers: one piece at a time)
         }
-        if (i >= TM / 2) held_row[i - TM / 2] = crow;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const auto rows = __builtin_amdgcn_permlane16_swap(o[0][w], o[1][w], false, false);
+          o[0][w] = rows[0];
+          o[1][w] = rows[1];
+        }
+        if constexpr (kRes) {
+          const int u = ii * kPairs + pp / 2;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+              o[h][w] = pack_bf16x2(__uint_as_float(o[h][w] << 16) + __uint_as_float(res[u % kAhead][h][w] << 16),
+                                    __uint_as_float(o[h][w] & 0xFFFF0000u) + __uint_as_float(res[u % kAhead][h][w] & 0xFFFF0000u));
+          if (u + kAhead < TM * kPairs) load_res(u + kAhead);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (i >= TM / 2) held[i - TM / 2][pp + h] = o[h];
+          else if (pp * 16 + store_col() < n_cols) *reinterpret_cast<u32x4_t *>(static_cast<bf16_t *>(a.C) + at[h] + pp * 16) = o[h];
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-    };
-    const bool full = n_cols >= kWaveCols;
-    if (full) finish(True{});
-    else finish(False{});
-    held_cols = full ? 128 : n_cols;                          // (a partial wavefront may hold no column at all)
+      if (i >= TM / 2) held_pos[i - TM / 2] = c_pos[i];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) c_pos[i] = c_next[i];
+    held_col = col0;
+    held_cols = n_cols;
     if (last) break;
-    strict = !full;
     cur = nxt;
+    nxt = after.tl;
     t += cus;
   }
-  store_held(0);
-  store_held(1);
+#pragma unroll
+  for (int k = 0; k < kHeld; ++k) store_held(k);
   }
 
   // ---- the last, partial round in pieces
