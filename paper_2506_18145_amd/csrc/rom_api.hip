@@ -222,6 +222,13 @@ struct BlockOpts {
   float eps;
 };
 
+// conv_out may alias conv_in (rom_step): a sequence of up to kConvInPlaceMaxLen steps is one run of one thread, which
+// reads the old state before it writes the new one; longer sequences are cut into runs for different threads, so a
+// new state that shares memory with the old one goes beside it and is copied over.
+bool conv_state_beside(const float *conv_in, const float *conv_out, int64_t L, int64_t n) {
+  return conv_in && conv_out && L > kConvInPlaceMaxLen && conv_in < conv_out + n && conv_out < conv_in + n;
+}
+
 int route_into(const rom_dims *d, const rom_weights *w, const void *x, int64_t n_tok,
                int32_t *expert_idx, float *gate, int32_t *counts, int32_t *offsets, int32_t *perm,
                int32_t *inv_perm, int32_t *tok_of_pos, int32_t *block_counts, float *logits,
@@ -322,13 +329,9 @@ int forward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_t
   // short conv + SiLU, Eq. (2)
   mark.begin(ROM_STAGE_CONV, s);
   {
-    // conv_out may alias conv_in (rom_step): a sequence of up to kConvInPlaceMaxLen steps is one
-    // run of one thread, which reads the old state before it writes the new one; longer sequences
-    // are cut into runs for different blocks, so the new state goes beside the old one and is
-    // copied over
     float *ctmp = reinterpret_cast<float *>(at(p.conv_tmp));
     float *cdst = conv_out;
-    const bool beside = conv_out && L > kConvInPlaceMaxLen;
+    const bool beside = conv_state_beside(conv_in, conv_out, L, B * De * 3);
     if (beside) cdst = ctmp;
     ROM_TRY(launch_conv_silu(d->dtype, at(p.xz), 2 * De, w->conv_w, w->conv_b, conv_in, cdst, at(p.u), B, L, De, s));
     if (beside) {
@@ -627,7 +630,7 @@ int run_variant(const VariantFrame &f, const void *x, int64_t B, int64_t L, cons
   mark.begin(ROM_STAGE_CONV, s);
   {
     float *ctmp = reinterpret_cast<float *>(at(f.conv_tmp));
-    const bool beside = conv_out && L > kConvInPlaceMaxLen;
+    const bool beside = conv_state_beside(conv_in, conv_out, L, B * f.d_conv_ch * 3);
     ROM_TRY(launch_conv_silu(f.dtype, at(f.proj) + static_cast<size_t>(f.conv_col) * 2, f.d_proj, f.conv_w, f.conv_b, conv_in,
                              beside ? ctmp : conv_out, at(f.conv_dst), B, L, f.d_conv_ch, s));
     if (beside) {

@@ -115,23 +115,47 @@ __global__ __launch_bounds__(256) void split_xdbl_kernel(const float *__restrict
 }
 
 // ------------------------------------------------------------------ conv + SiLU, Eq. (2)
-// A thread owns one 16-byte group of channels and walks kConvRun consecutive time steps with the
-// last three inputs in registers, so every input row is read once (plus a 3-row halo per run).
-constexpr int kConvRun = kConvInPlaceMaxLen;
+// kConvCh elements of T, from and to memory
+constexpr int kConvCh = 4;
+template <typename T> struct Quad;
+template <> struct Quad<bf16_t> {
+  typedef unsigned raw_t __attribute__((ext_vector_type(2)));
+  raw_t raw;
+  __device__ __forceinline__ void load(const bf16_t *p) { raw = *reinterpret_cast<const raw_t *>(p); }
+  __device__ __forceinline__ void store(bf16_t *p) const { *reinterpret_cast<raw_t *>(p) = raw; }
+  __device__ __forceinline__ float get(int i) const { return __uint_as_float((i & 1) ? (raw[i >> 1] & 0xFFFF0000u) : (raw[i >> 1] << 16)); }
+  __device__ __forceinline__ void set_pair(int i, float lo, float hi) { raw[i] = pack_bf16x2(lo, hi); }
+};
+template <> struct Quad<float> {
+  f32x4v_t raw;
+  __device__ __forceinline__ void load(const float *p) { raw = *reinterpret_cast<const f32x4v_t *>(p); }
+  __device__ __forceinline__ void store(float *p) const { *reinterpret_cast<f32x4v_t *>(p) = raw; }
+  __device__ __forceinline__ float get(int i) const { return raw[i]; }
+  __device__ __forceinline__ void set_pair(int i, float lo, float hi) { raw[2 * i] = lo; raw[2 * i + 1] = hi; }
+};
 
-template <typename T>
+// A thread owns four neighbouring channels and walks kRun consecutive time steps with the last three inputs in registers, so
+// every input row is read once (plus a 3-row halo per run); kConvBatch rows are requested before the first is used.
+// Bound by HBM where it is long (2 reads and writes of T per element: 16384 x 4096 bf16 50 us, 5.4 TB/s), else by one chain
+// of weights, history and rows, and launch.  Eight channels a thread, a row requested a step (us, before / now): 16384 x
+// 4096 55 / 50, 16384 x 6144 110 / 81, 3 x 1021 x 3072 20 / 10, 256 x 1 x 4096 11.2 / 7.8; with eight channels in batches
+// 54 / 93 / 15 / 11.8 (twice the registers, and the 48 bytes of state a lane has apart cost L1 half as many lines as 96).
+constexpr int kConvBatch = 8;
+
+template <typename T, int kRun>
 __global__ __launch_bounds__(256) void conv_silu_kernel(
     const T *__restrict__ xz, int64_t ld_xz, const float *__restrict__ conv_w,
     const float *__restrict__ conv_b, const float *__restrict__ state_in,
     float *__restrict__ state_out, T *__restrict__ u, int64_t L, int d_inner) {
-  constexpr int V = Chunk<T>::kElems;
-  const int groups = d_inner / V;
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= groups) return;
-  const int c0 = g * V;
+  static_assert(kRun % kConvBatch == 0, "whole batches");
+  constexpr int V = kConvCh;
+  const unsigned groups = static_cast<unsigned>(d_inner / V);
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x;              // channel group fastest, then run of the sequence
+  const int c0 = static_cast<int>(idx % groups) * V;
   const int64_t b = blockIdx.z;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.y) * kConvRun;
-  const int64_t t1 = (t0 + kConvRun < L) ? t0 + kConvRun : L;
+  const int64_t t0 = static_cast<int64_t>(idx / groups) * kRun;
+  if (t0 >= L) return;
+  const int64_t t1 = (t0 + kRun < L) ? t0 + kRun : L;
 
   float w[V][4], bias[V], h[3][V];
 #pragma unroll
@@ -141,50 +165,62 @@ __global__ __launch_bounds__(256) void conv_silu_kernel(
     bias[i] = conv_b ? conv_b[c0 + i] : 0.0f;
   }
   const T *xrow = xz + b * L * ld_xz + c0;
-  // history: inputs at t0-3, t0-2, t0-1.  The carried state of the V channels of this thread is
-  // 3*V consecutive floats ([channel][3], oldest first): read with 16-byte loads.
-  float st[3 * V];
-  if (t0 < 3) {
-    if (state_in) {
-      const float4 *sp = reinterpret_cast<const float4 *>(state_in + (b * d_inner + c0) * 3);
-#pragma unroll
-      for (int i = 0; i < 3 * V / 4; ++i) {
-        const float4 v = sp[i];
-        st[4 * i] = v.x; st[4 * i + 1] = v.y; st[4 * i + 2] = v.z; st[4 * i + 3] = v.w;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 3 * V; ++i) st[i] = 0.0f;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int64_t t = t0 - 3 + j;
-    if (t >= 0) {
-      Chunk<T> ch;
-      ch.load(xrow + t * ld_xz);
-#pragma unroll
-      for (int i = 0; i < V; ++i) h[j][i] = ch.get(i);
-    } else {
-#pragma unroll
-      for (int i = 0; i < V; ++i) h[j][i] = st[i * 3 + j];   // t0 == 0 here: t = -3..-1 -> slot j
-    }
-  }
   T *urow = u + b * L * d_inner + c0;
-  for (int64_t t = t0; t < t1; ++t) {
-    Chunk<T> ch, out;
-    ch.load(xrow + t * ld_xz);
-    float r[V];
+  Quad<T> row[kConvBatch];
+  auto fetch = [&](int64_t t) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const float cur = ch.get(i);
-      const float c = bias[i] + w[i][0] * h[0][i] + w[i][1] * h[1][i] + w[i][2] * h[2][i] + w[i][3] * cur;
-      h[0][i] = h[1][i]; h[1][i] = h[2][i]; h[2][i] = cur;
-      r[i] = silu_f32(c);
+    for (int j = 0; j < kConvBatch; ++j) row[j].load(xrow + (t + j < t1 ? t + j : t1 - 1) * ld_xz);
+  };
+  fetch(t0);
+  // history: inputs at t0-3, t0-2, t0-1, or the carried state, 3 V consecutive floats ([channel][3], oldest first)
+  if (t0 > 0) {
+    Quad<T> before[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) before[j].load(xrow + (t0 - 3 + j) * ld_xz);
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int i = 0; i < V; ++i) h[j][i] = before[j].get(i);
+  } else if (state_in) {
+    float st[3 * V];
+    const float4 *sp = reinterpret_cast<const float4 *>(state_in + (b * d_inner + c0) * 3);
+#pragma unroll
+    for (int i = 0; i < 3 * V / 4; ++i) {
+      const float4 v = sp[i];
+      st[4 * i] = v.x; st[4 * i + 1] = v.y; st[4 * i + 2] = v.z; st[4 * i + 3] = v.w;
     }
 #pragma unroll
-    for (int i = 0; i < V / 2; ++i) out.set_pair(i, r[2 * i], r[2 * i + 1]);
-    out.store(urow + t * d_inner);
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int i = 0; i < V; ++i) h[j][i] = st[i * 3 + j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int i = 0; i < V; ++i) h[j][i] = 0.0f;
+  }
+  for (int64_t t = t0; t < t1; t += kConvBatch) {
+    Quad<T> cur[kConvBatch];
+#pragma unroll
+    for (int j = 0; j < kConvBatch; ++j) cur[j] = row[j];
+    if (kRun > kConvBatch && t + kConvBatch < t1) fetch(t + kConvBatch);
+#pragma unroll
+    for (int j = 0; j < kConvBatch; ++j) {
+      if (t + j < t1) {
+        float r[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          const float x = cur[j].get(i);
+          const float c = bias[i] + w[i][0] * h[0][i] + w[i][1] * h[1][i] + w[i][2] * h[2][i] + w[i][3] * x;
+          h[0][i] = h[1][i]; h[1][i] = h[2][i]; h[2][i] = x;
+          r[i] = silu_f32(c);
+        }
+        Quad<T> out;
+#pragma unroll
+        for (int i = 0; i < V / 2; ++i) out.set_pair(i, r[2 * i], r[2 * i + 1]);
+        out.store(urow + (t + j) * d_inner);
+      }
+    }
   }
   if (state_out && t1 == L) {
     float4 *sp = reinterpret_cast<float4 *>(state_out + (b * d_inner + c0) * 3);
@@ -1375,21 +1411,30 @@ hipError_t launch_split_xdbl(int dtype, const float *xdbl, int n_slices, int64_t
   return hipGetLastError();
 }
 
+template <typename T, int kRun>
+static hipError_t conv_dispatch(const void *xz, int64_t ld_xz, const float *conv_w, const float *conv_b, const float *state_in,
+                                float *state_out, void *u, int64_t B, int64_t L, int d_inner, hipStream_t s) {
+  const int64_t threads = d_inner / kConvCh * ceil_div(L, kRun);
+  if (threads >= (1ll << 31)) return hipErrorInvalidValue;           // (a thread finds its place with 32 bits)
+  hipLaunchKernelGGL((conv_silu_kernel<T, kRun>), dim3(static_cast<unsigned>(ceil_div(threads, 256)), 1, static_cast<unsigned>(B)),
+                     dim3(256), 0, s, static_cast<const T *>(xz), ld_xz, conv_w, conv_b, state_in, state_out, static_cast<T *>(u),
+                     L, d_inner);
+  return hipGetLastError();
+}
+
 hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const float *conv_w,
                             const float *conv_b, const float *state_in, float *state_out, void *u,
                             int64_t B, int64_t L, int d_inner, hipStream_t s) {
-  const int V = dtype == ROM_DTYPE_BF16 ? 8 : 4;
-  const int groups = d_inner / V;
-  const dim3 grid(static_cast<unsigned>(ceil_div(groups, 256)),
-                  static_cast<unsigned>(ceil_div(L, kConvRun)), static_cast<unsigned>(B));
-  if (dtype == ROM_DTYPE_BF16)
-    hipLaunchKernelGGL(conv_silu_kernel<bf16_t>, grid, dim3(256), 0, s,
-                       static_cast<const bf16_t *>(xz), ld_xz, conv_w, conv_b, state_in, state_out,
-                       static_cast<bf16_t *>(u), L, d_inner);
-  else
-    hipLaunchKernelGGL(conv_silu_kernel<float>, grid, dim3(256), 0, s, static_cast<const float *>(xz),
-                       ld_xz, conv_w, conv_b, state_in, state_out, static_cast<float *>(u), L, d_inner);
-  return hipGetLastError();
+  // Runs of one batch where runs of kConvInPlaceMaxLen leave fewer than eight wavefronts a CU (us, short / long runs): 256 x 2048
+  // 7.0 / 8.2, 3 x 1021 x 3072 10.2 / 13.2, 4096 x 4096 (just eight) 15.1 / 15.3, 4 x 4096 x 2048 26.0 / 24.8, 16384 x 6144
+  // 101 / 81.  A state that is updated in place needs one run for the whole sequence, which reads it before it writes it.
+  const int64_t n_state = B * d_inner * 3;
+  const bool in_place = state_in && state_out && state_in < state_out + n_state && state_out < state_in + n_state;
+  const bool long_runs = (in_place && L > kConvBatch) || B * (d_inner / kConvCh) * ceil_div(L, kConvInPlaceMaxLen) >= 131072;
+#define ROM_CONV(T, R) conv_dispatch<T, R>(xz, ld_xz, conv_w, conv_b, state_in, state_out, u, B, L, d_inner, s)
+  if (dtype == ROM_DTYPE_BF16) return long_runs ? ROM_CONV(bf16_t, kConvInPlaceMaxLen) : ROM_CONV(bf16_t, kConvBatch);
+  return long_runs ? ROM_CONV(float, kConvInPlaceMaxLen) : ROM_CONV(float, kConvBatch);
+#undef ROM_CONV
 }
 
 int scan_lane_chunks(int64_t B, int64_t L, int d_inner) {
