@@ -11,7 +11,7 @@
 // Epilogues (compile-time variants): plain store, bias + softplus, per-row scale (gate weight or
 // 1 / rms), per-row scale + skip rows added, fp32 partial sums of inner-dimension slices, and
 // SiLU(gate) * up over a weight whose rows interleave the two halves of a SwiGLU expert.
-// fp32 path (and shapes the MFMA kernel does not take): a plain LDS-tiled FMA kernel.
+// fp32 path (and shapes the bf16 kernels do not take): v_mfma_f32_16x16x4_f32, operands straight from memory.
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -1488,56 +1488,113 @@ void gemm_bf16_smallk_kernel(const GemmArgs a) {
   }
 }
 
-// ------------------------------------------------------------------ plain FMA kernel
-constexpr int kSB = 64, kSK = 16;       // 64x64 tile, K slab 16, 256 threads, 4x4 per thread
+// ------------------------------------------------------------------ fp32 products on the matrix cores
+// For fp32 operands (and the bf16 shapes that the kernels above do not take, widened as they are read).  What bounds the small
+// calls that use it is latency, so nothing goes through LDS: a lane of v_mfma_f32_16x16x4_f32 takes one row and, of every four
+// contraction indices, one.  Which four is free as long as both operands agree, so lane l reads 16 bytes, k = 4 (l / 16) .. + 3 of
+// row l & 15, straight into the operand of four instructions; kDirectBlocks of these 16-wide blocks are requested together, and
+// the next ones before the products of these.  Small calls take 16 x 16 products a wavefront, one behind the other in a
+// workgroup's four; calls that fill the CUs with 64 x 64 tiles take 32 x 32 ones, whose operands the four share in L1.
+// Sums are fp32 throughout; their error against 64 bits over ten layers of 22 ... 369 tokens, d_model 64 ... 256, is that of the
+// fp32 FMA tiles it replaced (4.57e-7 both).  64 tokens, d_model 64, four experts, the call's four products: 61 -> 25 us (LDS
+// tiles of 16 contraction indices waited for memory at each); the layer call 77 -> 41.
+constexpr int kDirectBlocks = 4;
+constexpr int kDirectWideMinTiles = 256;                      // a 64 x 64 tile for every CU
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(const GemmArgs a) {
-  __shared__ float As[kSK][kSB + 4];
-  __shared__ float Bs[kSK][kSB + 4];
-  const TileCoord tc = locate_tile(a, kSB, kSB);
-  if (!tc.valid) return;
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const T *Ap = static_cast<const T *>(a.A);
-  const T *Wp = static_cast<const T *>(a.W) + static_cast<int64_t>(tc.group) * a.N * a.K;
-  // staging: thread -> (row = tid / 4, 4 consecutive k = (tid % 4) * 4)
-  const int s_r = tid / 4, s_k = (tid % 4) * 4;
-  const int64_t pa = tc.row0 + s_r;
-  const int64_t a_off = (pa < tc.row_end) ? static_cast<int64_t>(a.a_rows ? a.a_rows[pa] : pa) * a.lda : -1;
-  const int64_t b_off = (tc.n0 + s_r < a.N) ? static_cast<int64_t>(tc.n0 + s_r) * a.K : -1;
-  float acc[4][4] = {};
-  const int k_begin = blockIdx.y * a.k_per_split;
-  const int k_stop = (a.K - k_begin < a.k_per_split) ? a.K : k_begin + a.k_per_split;
-  for (int k0 = k_begin; k0 < k_stop; k0 += kSK) {
+// elements k .. k + 3 of a row, zero from k_stop on; VEC: 16-byte aligned rows and k_stop a multiple of four
+template <typename T, bool VEC>
+__device__ __forceinline__ f32x4_t load_k4(const T *row, int k, int k_begin, int k_stop) {
+  f32x4_t v;
+  if constexpr (VEC) {
+    const bool in = k < k_stop;
+    v = *reinterpret_cast<const f32x4_t *>(row + (in ? k : k_begin));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = in ? v[i] : 0.0f;
+  } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int k = k0 + s_k + i;
-      As[s_k + i][s_r] = (a_off >= 0 && k < k_stop) ? to_f32(Ap[a_off + k]) : 0.0f;
-      Bs[s_k + i][s_r] = (b_off >= 0 && k < k_stop) ? to_f32(Wp[b_off + k]) : 0.0f;
+      const bool in = k + i < k_stop;
+      const float x = to_f32(row[in ? k + i : k_begin]);
+      v[i] = in ? x : 0.0f;
     }
-    __syncthreads();
+  }
+  return v;
+}
+
+// a workgroup of WM x WN wavefronts, each TM x TN tiles of 16 x 16
+template <typename T, bool VEC, int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_f32_direct_kernel(const GemmArgs a) {
+  const TileCoord tc = locate_tile(a, WM * TM * 16, WN * TN * 16);
+  if (!tc.valid) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, kq = (lane >> 4) * 4;
+  const int64_t row0 = tc.row0 + wave / WN * (TM * 16);
+  const int col0 = tc.n0 + wave % WN * (TN * 16);
+  if (row0 >= tc.row_end || col0 >= a.N) return;
+  const int k_begin = blockIdx.y * a.k_per_split;
+  const int k_stop = (a.K - k_begin < a.k_per_split) ? a.K : k_begin + a.k_per_split;
+  // rows and columns past the end re-read the tile's first ones; their products are not stored
+  const T *a_row[TM], *w_row[TN];
 #pragma unroll
-    for (int k = 0; k < kSK; ++k) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = As[k][ty * 4 + i]; bv[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int j = 0; j < TN; ++j) {
+    const int c = col0 + j * 16 + r16;
+    w_row[j] = static_cast<const T *>(a.W) + (static_cast<int64_t>(tc.group) * a.N + (c < a.N ? c : col0)) * a.K;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t p = tc.row0 + ty * 4 + i;
-    const bool row_ok = p < tc.row_end;
-    const int64_t crow = row_ok ? (a.c_rows ? a.c_rows[p] : p) : 0;
+  for (int i = 0; i < TM; ++i) {
+    const int64_t p = row0 + i * 16 + r16 < tc.row_end ? row0 + i * 16 + r16 : row0;
+    a_row[i] = static_cast<const T *>(a.A) + static_cast<int64_t>(a.a_rows ? a.a_rows[p] : p) * a.lda;
+  }
+  f32x4_t acc[TM][TN] = {};
+  struct Blocks {
+    f32x4_t a[kDirectBlocks][TM], w[kDirectBlocks][TN];
+  };
+  auto load = [&](int k0, Blocks &f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = tc.n0 + tx * 4 + j;
-      if (row_ok && col < a.N) store_out(a, crow, col, acc[i][j]);
+    for (int b = 0; b < kDirectBlocks; ++b) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) f.w[b][j] = load_k4<T, VEC>(w_row[j], k0 + b * 16 + kq, k_begin, k_stop);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) f.a[b][i] = load_k4<T, VEC>(a_row[i], k0 + b * 16 + kq, k_begin, k_stop);
     }
+  };
+  auto products = [&](int k0, const Blocks &f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < kDirectBlocks; ++b) {
+      if (k0 + b * 16 >= k_stop) break;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.w[b][j][s], f.a[b][i][s], acc[i][j], 0, 0, 0);
+    }
+  };
+  constexpr int kStep = kDirectBlocks * 16;
+  Blocks f0, f1;
+  load(k_begin, f0);
+  for (int k0 = k_begin; k0 < k_stop; k0 += 2 * kStep) {
+    if (k0 + kStep < k_stop) load(k0 + kStep, f1);
+    products(k0, f0);
+    if (k0 + kStep >= k_stop) break;
+    if (k0 + 2 * kStep < k_stop) load(k0 + 2 * kStep, f0);
+    products(k0 + kStep, f1);
+  }
+  // the weight is the instruction's row operand: a lane holds row r16 of C, columns kq .. kq + 3
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int64_t p = row0 + i * 16 + r16;
+    if (p >= tc.row_end) continue;
+    const int64_t crow = a.c_rows ? a.c_rows[p] : p;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int col = col0 + j * 16 + kq + r;
+        if (col < a.N) store_out(a, crow, col, acc[i][j][r]);
+      }
   }
 }
 
@@ -1570,6 +1627,23 @@ int grid_tiles(const GemmArgs &a, int BM, int BN) {
   int64_t g = patches * kPatchTiles;
   g = ceil_div(g, 8) * 8;
   return static_cast<int>(g);
+}
+
+template <typename T, bool VEC>
+hipError_t launch_f32_direct_t(const GemmArgs &a, hipStream_t s) {
+  const int64_t tiles = (a.M / 64 + (a.offsets ? a.n_groups : 1)) * ceil_div(a.N, 64) * a.k_splits;
+  if (tiles >= kDirectWideMinTiles)
+    hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, 2, 2, 2, 2>), dim3(grid_tiles(a, 64, 64), a.k_splits), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, 1, 1, 1, 4>), dim3(grid_tiles(a, 16, 64), a.k_splits), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_f32_direct(const GemmArgs &a, hipStream_t s) {
+  if (a.dtype == ROM_DTYPE_BF16) return launch_f32_direct_t<bf16_t, false>(a, s);
+  // whole 16-byte pieces of every row: alignment of both operands (a slice of K starts at a multiple of 64)
+  const bool vec = a.K % 4 == 0 && a.lda % 4 == 0 && reinterpret_cast<uintptr_t>(a.A) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(a.W) % 16 == 0;
+  return vec ? launch_f32_direct_t<float, true>(a, s) : launch_f32_direct_t<float, false>(a, s);
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, bool KTAIL>
@@ -1699,7 +1773,7 @@ bool grouped_gemm_takes_kmajor(const GemmArgs &args) {
          a.N % 256 == 0 && gemm_tile(shape_of(a, false)) == GemmTile::kStream;
 }
 
-// whether the call takes the MFMA kernels (else the plain FMA kernel, which has no fused SwiGLU)
+// whether the call takes the MFMA kernels (else the fp32 one, which has no fused SwiGLU)
 bool grouped_gemm_on_mfma(const GemmArgs &a) {
   const int out_align = a.c_is_f32 ? 4 : 8;      // elements per output store
   return a.dtype == ROM_DTYPE_BF16 && a.K % 8 == 0 && a.lda % 8 == 0 &&
@@ -1728,12 +1802,7 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
   const bool few = mfma_ok && few_rows_takes(a);
   if (a.swiglu) return few ? launch_few_rows<kEpiSwiGLU>(a, s) : launch_mfma_tiles<kEpiSwiGLU>(a, s);
   if (!mfma_ok) {
-    const dim3 grid(grid_tiles(a, kSB, kSB), a.k_splits);
-    if (a.dtype == ROM_DTYPE_BF16)
-      hipLaunchKernelGGL(gemm_simple_kernel<bf16_t>, grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL(gemm_simple_kernel<float>, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+    return launch_f32_direct(a, s);
   }
   if (few && a.c_is_f32) return launch_few_rows<kEpiPlainF32>(a, s);
   if (a.c_is_f32) {
