@@ -1194,21 +1194,40 @@ __global__ __launch_bounds__(512) void wgrad_bf16_big_kernel(const bf16_t *__res
 // rows of 16 columns, lane i receives column i of the four rows).  No register transposes, no LDS
 // writes and no load -> park dependency are left in the loop.  A slab is 64 positions; LDS is a
 // ring of five half-slab slots of 32 KiB (A rows of slab m, B rows of slab m, A rows of slab m + 1, ...)
-// filled in ring order, four DMA instructions per wave and half slab, so that "vmcnt(4)" means
+// filled in ring order, eight DMA instructions per wave and half slab, so that "vmcnt(8)" means
 // "everything but the newest half slab I asked for has landed".  The 16-byte chunk c of row r lies
 // at position c ^ 4 (r & 3) of its row (the swizzle is applied where the global address is formed):
 // the four rows x 64 bytes that 32 lanes read at a time then cover all 64 banks once.
-// Row indices (positions -> rows of the operand) are uniform per wave and instruction half: they
-// are read through the scalar cache one slab before the DMA that uses them is issued.
-// Positions past the group's end are fetched from whatever valid row follows and zeroed in LDS
-// before the last slab is multiplied.
-constexpr bool kUseWgradDma = true;
+//
+// One workgroup of four wavefronts per CU (128 x 128 each: a third less LDS traffic per product than
+// eight of 64 x 128, which kept the LDS port busy all the time) walks its share of the tiles, and the ring runs
+// on across tile boundaries.  Every XCD has an eighth of every expert's tiles, so that experts of uneven
+// size load all of them alike; consecutive tiles form patches four tile rows high, whose operands meet in
+// the XCD's L2.  A tile of 256 KiB of sums is dear to store, all CUs at once and nothing multiplied meanwhile:
+// half of it goes out at once behind requests for the next two slabs (loads and stores retire in order; the
+// first wait that includes these stores is the one at the end of the next tile's second slab), the other
+// half is kept in registers and goes out four stores a slab.  A store covers 64 bytes of each of 16 rows.
+// Row indices (positions -> rows of the operand) are uniform per wave and instruction half: they are read
+// sixteen at a time through the scalar cache, a 16-wide step of MFMAs ahead of the DMA that uses them.  Where a
+// wavefront's 16 positions would reach past the last one they are moved down to end there; what a slab
+// holds of positions that are not its own is zeroed in LDS before it is multiplied.
+// Bound by the power that the matrix pipe draws: without its stores a launch of 16384 rows x 8192 x 2048 in 8 experts takes
+// 450-470 us, with them 507-519 (601-574 with a tile per workgroup of eight wavefronts and both operands' stores at the
+// end); 2048 x 4096 329 -> 271 through row maps, 272 -> 263 without; 8192 rows, 4096 x 1024 100 -> 88, 1024 x 2048 53 -> 47.  Stores past
+// the caches: 549 us.  One held block instead of two makes no difference beyond 2 %.
 constexpr int kWdSlots = 5;
 constexpr int kWdSlotBytes = kWgSlab * kWgBig * 2;         // 64 positions x 256 columns x 2 bytes
 constexpr int kWdSmem = kWdSlots * kWdSlotBytes;           // 160 KiB
-constexpr int kWdInstr = 4;                                // DMA instructions per wave and half slab (2 rows each)
+constexpr int kWdInstr = 8;                                // DMA instructions per wave and half slab (2 rows each)
+constexpr int kWdRows = 2 * kWdInstr;                      // positions that a wave brings per half slab
+constexpr int kWdWgs = 256;                                // one workgroup per CU
+constexpr int kWdBand = 4;                                 // tile rows of a patch
+constexpr int kWdHeld = 2;                                 // 32-row blocks (of four) whose stores wait for the next tile
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef short i16x8_t __attribute__((ext_vector_type(8)));
+typedef int i32x16_t __attribute__((ext_vector_type(16)));
+typedef i32x16_t i32x16_word_t __attribute__((aligned(4)));
+typedef float f32x4_wd_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
 
 __device__ __forceinline__ void wd_dma_16(unsigned lds_addr, unsigned voff, const void *base) {
@@ -1225,179 +1244,359 @@ __device__ __forceinline__ bf16x8_t wd_frag(const lds_byte_t *p) {
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
+// an output tile; a place in the list of this workgroup's tiles (e == n_groups: behind the last one)
+struct WdTile {
+  int e, i;                       // expert, and place among the XCD's tiles of that expert
+  int m0, n0;
+  int p_lo, p_hi, slabs;          // positions; an expert without any has one slab of zeros
+};
+
 // MAP_A / MAP_B: the operand's rows are rows_x[position] (else the position itself)
 template <bool MAP_A, bool MAP_B>
-__global__ __launch_bounds__(512) void wgrad_bf16_dma_kernel(const bf16_t *__restrict__ A, int64_t lda, int M,
-                                                             const bf16_t *__restrict__ Bm, int64_t ldb, int N,
-                                                             const int32_t *__restrict__ rows_a,
-                                                             const int32_t *__restrict__ rows_b,
-                                                             const int32_t *__restrict__ offsets, int64_t n_pos,
-                                                             int n_groups, float *__restrict__ C) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void wgrad_bf16_dma_kernel(
+    const bf16_t *__restrict__ A, int64_t lda, int M, const bf16_t *__restrict__ Bm, int64_t ldb, int N,
+    const int32_t *__restrict__ rows_a, const int32_t *__restrict__ rows_b, const int32_t *__restrict__ offsets,
+    int n_pos, int n_groups, float *__restrict__ C) {
   extern __shared__ __attribute__((aligned(16))) unsigned char wd_smem[];
-  const int tn = N / kWgBig, tm = M / kWgBig;                      // (the launcher checks divisibility)
-  const int per_xcd = gridDim.x / 8;                             // tiles dealt to XCDs in contiguous runs
-  const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (t >= tn * tm * n_groups) return;
-  const int e = t / (tn * tm);
-  const int64_t p_lo = offsets ? offsets[e] : 0, p_hi = offsets ? offsets[e + 1] : n_pos;
-  const int m0 = ((t / tn) % tm) * kWgBig, n0 = (t % tn) * kWgBig;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 3, wn = wave >> 2;                       // 4 x 2 waves, 64 x 128 each
-  f32x16_t acc[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-  const int frag_row = lane & 31, frag_half = lane >> 5;
-  const int64_t n_grp = p_hi - p_lo;
-  const int KT = static_cast<int>((n_grp + kWgSlab - 1) / kWgSlab);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave & 1, wn = wave >> 1;                       // 2 x 2 waves, 128 x 128 each
+  const int xcd = blockIdx.x % 8, cu = blockIdx.x / 8, cus = gridDim.x / 8;
 
-  if (KT > 0) {
-    const lds_byte_t *lds = (const lds_byte_t *)wd_smem;
-    const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void *)wd_smem));
-    const unsigned lds_wave = __builtin_amdgcn_readfirstlane(lds_base + wave * (kWdInstr * 1024));
-
-    // DMA side: instruction j of a half slab fills rows 8 wave + 2 j and + 1 of the slot; this lane
-    // brings position lane & 31 of row 2 j + (lane >> 5), i.e. the chunk that belongs there
-    const int half = lane >> 5;
-    unsigned col_a[kWdInstr], col_b[kWdInstr];
-#pragma unroll
-    for (int j = 0; j < kWdInstr; ++j) {
-      const int r = 2 * j + half;                                 // (8 wave is a multiple of 4)
-      const unsigned c = static_cast<unsigned>((lane & 31) ^ (4 * (r & 3)));
-      col_a[j] = (static_cast<unsigned>(m0) + c * 8) * 2;
-      col_b[j] = (static_cast<unsigned>(n0) + c * 8) * 2;
+  // ---- this workgroup's tiles (the launcher checks divisibility, and that the numbers fit)
+  const int tn = N / kWgBig, tm = M / kWgBig, per_group = tn * tm;
+  // x / d for 0 <= x < 2^31 with inv = ceil(2^32 / d), d > 1: the product is less than half too large
+  auto inverse = [](int d) { return d > 1 ? 0xFFFFFFFFu / static_cast<unsigned>(d) + 1u : 0u; };
+  auto divide = [](int x, int d, unsigned inv) __attribute__((always_inline)) {
+    if (d == 1) return x;
+    const int q = static_cast<int>(__umulhi(static_cast<unsigned>(x), inv));
+    return q * d > x ? q - 1 : q;
+  };
+  const int band_tiles = kWdBand * tn, last_rows = tm % kWdBand;
+  const unsigned inv_band = inverse(band_tiles), inv_last = inverse(last_rows);
+  // an XCD's part of an expert's tiles: the eighths are dealt in turn, since they differ by a tile
+  auto share_lo = [&](int e) __attribute__((always_inline)) { return per_group * ((xcd + e) & 7) / 8; };
+  auto share = [&](int e) __attribute__((always_inline)) { return per_group * (((xcd + e) & 7) + 1) / 8 - share_lo(e); };
+  typedef const __attribute__((address_space(4))) int32_t const_i32_t;
+  auto tile_at = [&](int e, int i) __attribute__((always_inline)) {
+    while (e < n_groups && i >= share(e)) {
+      i -= share(e);
+      ++e;
     }
-    const unsigned lda2 = static_cast<unsigned>(lda) * 2, ldb2 = static_cast<unsigned>(ldb) * 2;
+    WdTile t;
+    t.e = e;
+    t.i = i;
+    t.m0 = t.n0 = t.p_lo = t.p_hi = 0;
+    t.slabs = 1;
+    if (e < n_groups) {
+      const int at = share_lo(e) + i, band = divide(at, band_tiles, inv_band), in = at - band * band_tiles;
+      const int rows = tm - band * kWdBand >= kWdBand ? kWdBand : last_rows;
+      const int col = rows == kWdBand ? in / kWdBand : divide(in, rows, inv_last);
+      t.m0 = (band * kWdBand + in - col * rows) * kWgBig;
+      t.n0 = col * kWgBig;
+      const_i32_t *off = (const_i32_t *)(reinterpret_cast<uintptr_t>(offsets));
+      t.p_lo = offsets ? off[e] : 0;
+      t.p_hi = offsets ? off[e + 1] : n_pos;
+      t.slabs = t.p_hi > t.p_lo ? (t.p_hi - t.p_lo + kWgSlab - 1) / kWgSlab : 1;
+    }
+    return t;
+  };
+  auto behind = [&](const WdTile &t) __attribute__((always_inline)) { return tile_at(t.e, t.i + cus); };
+  WdTile cur = tile_at(0, cu);
+  if (cur.e >= n_groups) return;
+  WdTile nxt = behind(cur);
 
-    // the eight operand rows a wave brings for half slab h (uniform: scalar loads; the index only - its
-    // first use, the multiply in issue(), is where the compiler waits for the load)
-    auto row_idx = [&](int h, unsigned (&row)[8]) __attribute__((always_inline)) {
-      const int m = h >> 1, sl = m < KT ? m : KT - 1;             // past the end: harmless reload
-      const int64_t pb = p_lo + static_cast<int64_t>(sl) * kWgSlab + wave * 8;
-      const int32_t *rows = (h & 1) ? rows_b : rows_a;
-      const bool mapped = (h & 1) ? MAP_B : MAP_A;
+  // ---- DMA side: instruction j of a half slab fills rows 16 wave + 2 j and + 1 of the slot; this lane brings 16 bytes
+  // lane & 31 of row 2 j + (lane >> 5), i.e. the chunk that belongs there
+  const lds_byte_t *lds = (const lds_byte_t *)wd_smem;
+  const unsigned lds_base =
+      static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void *)wd_smem));
+  const unsigned half_mask = lane >> 5 ? 0xFFFFFFFFu : 0u;
+  unsigned lane_col[2];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int64_t pp = pb + i < n_pos ? pb + i : n_pos - 1;
-        row[i] = mapped ? static_cast<unsigned>(rows[pp]) : static_cast<unsigned>(pp);
-      }
-    };
-    auto issue = [&](int h, const unsigned (&row)[8]) __attribute__((always_inline)) {
-      const unsigned slot = lds_wave + static_cast<unsigned>(h % kWdSlots) * kWdSlotBytes;
-      const void *base = (h & 1) ? static_cast<const void *>(Bm) : static_cast<const void *>(A);
-      const unsigned ld2 = (h & 1) ? ldb2 : lda2;
-#pragma unroll
-      for (int j = 0; j < kWdInstr; ++j) {
-        // (the launcher checks that row * ld2 fits 32 bits)
-        const unsigned voff = (half ? row[2 * j + 1] : row[2 * j]) * ld2 + ((h & 1) ? col_b[j] : col_a[j]);
-        wd_dma_16(slot + j * 1024, voff, base);
-      }
-    };
+  for (int j = 0; j < 2; ++j)
+    lane_col[j] = static_cast<unsigned>(((lane & 31) ^ (4 * ((2 * j + (lane >> 5)) & 3))) * 16);
+  const unsigned lda2 = static_cast<unsigned>(lda) * 2, ldb2 = static_cast<unsigned>(ldb) * 2;
+  // workgroups that share an operand tile start on different rows of it
+  const int wave_a = (wave + cu / kWdBand) & 3, wave_b = (wave + cu) & 3;
+  const unsigned lds_a = lds_base + wave_a * (kWdInstr * 1024), lds_b = lds_base + wave_b * (kWdInstr * 1024);
 
-    // fragment side: lane i of a 16-lane group names row i >> 2 (of four), columns 4 (i & 3) .. + 3 of
-    // its group's 16 columns and receives column i; groups 0/1 hold tile rows 0-15 / 16-31 of
-    // positions 0-7, groups 2/3 the same of positions 8-15
+  // where the requests are: a slab of a tile, and the tile behind it
+  WdTile rq = cur, rq_next = nxt;
+  int rq_slab = 0;
+  auto request_next = [&]() __attribute__((always_inline)) {
+    if (rq_slab + 1 < rq.slabs) {
+      ++rq_slab;
+    } else if (rq_next.e < n_groups) {
+      rq = rq_next;
+      rq_slab = 0;
+      rq_next = behind(rq);
+    }                                                          // behind the last tile: its last slab again, unused
+  };
+  // first of the 16 positions that a wave brings of a slab: moved down where they would reach past the last one
+  auto first_pos = [&](const WdTile &t, int slab, int w) __attribute__((always_inline)) {
+    const int p = t.p_lo + slab * kWgSlab + w * kWdRows;
+    return p < n_pos - kWdRows ? p : n_pos - kWdRows;
+  };
+  auto row_numbers = [](const int32_t *rows, int p) __attribute__((always_inline)) {
+    typedef const __attribute__((address_space(4))) i32x16_word_t const_i32x16_t;
+    return static_cast<i32x16_t>(*(const_i32x16_t *)(reinterpret_cast<uintptr_t>(rows + p)));
+  };
+  i32x16_t idx_a, idx_b;                                       // rows of the half slab under way
+  int pos_a = 0, pos_b = 0, col_a = 0, col_b = 0;
+  auto fetch_a = [&]() __attribute__((always_inline)) {
+    pos_a = first_pos(rq, rq_slab, wave_a);
+    col_a = rq.m0 * 2;
+    if constexpr (MAP_A) idx_a = row_numbers(rows_a, pos_a);
+  };
+  auto fetch_b = [&]() __attribute__((always_inline)) {
+    pos_b = first_pos(rq, rq_slab, wave_b);
+    col_b = rq.n0 * 2;
+    if constexpr (MAP_B) idx_b = row_numbers(rows_b, pos_b);
+  };
+  // (the launcher checks that row * ld2 fits 32 bits)
+  auto dma_a = [&](unsigned slot, int j) __attribute__((always_inline)) {
+    const unsigned s0 = (MAP_A ? static_cast<unsigned>(idx_a[2 * j]) : static_cast<unsigned>(pos_a + 2 * j)) * lda2;
+    const unsigned d = MAP_A ? static_cast<unsigned>(idx_a[2 * j + 1]) * lda2 - s0 : lda2;
+    wd_dma_16(lds_a + slot * kWdSlotBytes + j * 1024, (half_mask & d) + (s0 + col_a) + lane_col[j & 1], A);
+  };
+  auto dma_b = [&](unsigned slot, int j) __attribute__((always_inline)) {
+    const unsigned s0 = (MAP_B ? static_cast<unsigned>(idx_b[2 * j]) : static_cast<unsigned>(pos_b + 2 * j)) * ldb2;
+    const unsigned d = MAP_B ? static_cast<unsigned>(idx_b[2 * j + 1]) * ldb2 - s0 : ldb2;
+    wd_dma_16(lds_b + slot * kWdSlotBytes + j * 1024, (half_mask & d) + (s0 + col_b) + lane_col[j & 1], Bm);
+  };
+
+  // ---- MFMA side: lane i of a 16-lane group names row i >> 2 (of four), columns 4 (i & 3) .. + 3 of
+  // its group's 16 columns and receives column i; groups 0/1 hold tile rows 0-15 / 16-31 of
+  // positions 0-7, groups 2/3 the same of positions 8-15
+  unsigned frag_off[4];
+  {
     const int i16 = lane & 15, grp = lane >> 4;
-    const int row_l = 8 * (grp >> 1) + (i16 >> 2);
-    const int sw = 4 * (i16 >> 2);
-    unsigned a_off[2], b_off[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int chunk = (wm * 8 + i * 4 + 2 * (grp & 1) + ((i16 >> 1) & 1)) ^ sw;
-      a_off[i] = static_cast<unsigned>(row_l * (kWgBig * 2) + chunk * 16 + (i16 & 1) * 8);
+    for (int i = 0; i < 4; ++i) {
+      const int chunk = (i * 4 + 2 * (grp & 1) + ((i16 >> 1) & 1)) ^ (4 * (i16 >> 2));
+      frag_off[i] = static_cast<unsigned>((8 * (grp >> 1) + (i16 >> 2)) * (kWgBig * 2) + chunk * 16 + (i16 & 1) * 8);
     }
+  }
+  f32x16_t acc[4][4];
+  bf16x8_t fa0[4], fa1[4], fb0[4], fb1[4];
+  auto read_a = [&](unsigned slot, int kk, int i) __attribute__((always_inline)) {
+    return wd_frag(lds + (slot * kWdSlotBytes + wm * 256) + frag_off[i] + kk * (16 * kWgBig * 2));
+  };
+  auto read_b = [&](unsigned slot, int kk, int j) __attribute__((always_inline)) {
+    return wd_frag(lds + (slot * kWdSlotBytes + wn * 256) + frag_off[j] + kk * (16 * kWgBig * 2));
+  };
+  // one 16-wide step on (fa, fb); (na, nb) receive the fragments of step kn of the slab in slots (sa, sb); dma(q) runs
+  // behind MFMA q
+  auto step = [&](auto zero, const bf16x8_t(&fa)[4], const bf16x8_t(&fb)[4], bf16x8_t(&na)[4], bf16x8_t(&nb)[4],
+                  unsigned sa, unsigned sb, int kn, auto dma) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int chunk = (wn * 16 + j * 4 + 2 * (grp & 1) + ((i16 >> 1) & 1)) ^ sw;
-      b_off[j] = static_cast<unsigned>(row_l * (kWgBig * 2) + chunk * 16 + (i16 & 1) * 8);
-    }
-    bf16x8_t fa0[2], fa1[2], fb0[4], fb1[4];
-    auto load_frags = [&](int m, int kk, bf16x8_t(&af)[2], bf16x8_t(&bfr)[4]) __attribute__((always_inline)) {
-      const lds_byte_t *sa = lds + ((2 * m) % kWdSlots) * kWdSlotBytes + kk * (16 * kWgBig * 2);
-      const lds_byte_t *sb = lds + ((2 * m + 1) % kWdSlots) * kWdSlotBytes + kk * (16 * kWgBig * 2);
-      af[0] = wd_frag(sa + a_off[0]);
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bfr[j] = wd_frag(sb + b_off[j]);
-      af[1] = wd_frag(sa + a_off[1]);
-    };
-    auto mma = [&](const bf16x8_t(&af)[2], const bf16x8_t(&bfr)[4]) __attribute__((always_inline)) {
+      for (int j = 0; j < 4; ++j) {
+        const int q = i * 4 + j;
+        if constexpr (decltype(zero)::value) {
+          f32x16_t z;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-    };
-    // rows of slab m past the group's end, both operands; ends in a barrier
-    const int tail = static_cast<int>(n_grp % kWgSlab);
-    auto zero_tail = [&](int m) __attribute__((always_inline)) {
-      __attribute__((address_space(3))) unsigned char *sa =
-          (__attribute__((address_space(3))) unsigned char *)wd_smem + ((2 * m) % kWdSlots) * kWdSlotBytes;
-      __attribute__((address_space(3))) unsigned char *sb =
-          (__attribute__((address_space(3))) unsigned char *)wd_smem + ((2 * m + 1) % kWdSlots) * kWdSlotBytes;
-      const int first = tail * (kWgBig * 2), bytes = (kWgSlab - tail) * (kWgBig * 2);
-      for (int q = tid * 16; q < bytes; q += 512 * 16) {
-        *(__attribute__((address_space(3))) u32x4_t *)(sa + first + q) = u32x4_t{0u, 0u, 0u, 0u};
-        *(__attribute__((address_space(3))) u32x4_t *)(sb + first + q) = u32x4_t{0u, 0u, 0u, 0u};
+          for (int v = 0; v < 16; ++v) z[v] = 0.0f;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], z, 0, 0, 0);
+        } else {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+        }
+        // in the order of first use by the next step
+        if (q == 0) na[0] = read_a(sa, kn, 0);
+        else if (q <= 4) nb[q - 1] = read_b(sb, kn, q - 1);
+        else if (q < 8) na[q - 4] = read_a(sa, kn, q - 4);
+        dma(q);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __syncthreads();
-    };
+  };
+  const auto mod5 = [](unsigned s) { return s >= 5 ? s - 5 : s; };
+  using True = std::true_type;
+  using False = std::false_type;
+  const auto none = [](int) {};
 
+  // what slab `slab` of tile t holds of positions that are not its own, both operands; ends in a barrier
+  auto zero_rest = [&](const WdTile &t, int slab, unsigned sa, unsigned sb) __attribute__((always_inline)) {
+    if (t.p_hi - t.p_lo - slab * kWgSlab >= kWgSlab) return;   // (whole slabs end before p_hi <= n_pos: nothing was moved)
+    typedef __attribute__((address_space(3))) u32x4_t lds_u32x4_t;
+    __attribute__((address_space(3))) unsigned char *smem = (__attribute__((address_space(3))) unsigned char *)wd_smem;
+    for (int r = threadIdx.x >> 5; r < kWgSlab; r += 8) {
+      const int w = r / kWdRows, p = first_pos(t, slab, w) + r % kWdRows;
+      if (p < t.p_lo + slab * kWgSlab + w * kWdRows || p >= t.p_hi) {
+        const unsigned at = r * (kWgBig * 2) + (threadIdx.x & 31) * 16;
+        *(lds_u32x4_t *)(smem + sa * kWdSlotBytes + at) = u32x4_t{0u, 0u, 0u, 0u};
+        *(lds_u32x4_t *)(smem + sb * kWdSlotBytes + at) = u32x4_t{0u, 0u, 0u, 0u};
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
+
+  // ---- stores: a lane holds, for row lane & 31 of each 32-row block, columns 8 q + 4 (lane >> 5) + (0..3) of each
+  // 32-column block in elements 4 q ..; lanes l and l + 16 trade rows between two neighbouring q, so that a store covers
+  // 64 bytes of each of 16 rows
+  constexpr int kBlockStores = 16;                             // per 32-row block
+  const unsigned lane_out = ((wm * 128 + (lane & 15)) * static_cast<unsigned>(N) + wn * 128 + ((lane >> 4) & 1) * 8 + (lane >> 5) * 4) * 4;
+  f32x4_wd_t held[kWdHeld][kBlockStores];
+  float *held_at = nullptr;                                    // where the held blocks' tile starts (NULL: nothing held)
+  auto piece = [&](int i, int k) __attribute__((always_inline)) {   // k: column block k / 4, 16 columns k / 2 % 2, rows k % 2
+    const int j = k / 4, q = k / 2 % 2 * 2;
+    f32x4_wd_t o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][4 * q + r]),
+                                                         __float_as_uint(acc[i][j][4 * q + 4 + r]), false, false);
+      o[r] = __uint_as_float(rows[k % 2]);
+    }
+    return o;
+  };
+  auto store = [&](float *tile, int i, int k, f32x4_wd_t v) __attribute__((always_inline)) {
+    char *at = reinterpret_cast<char *>(tile + static_cast<int64_t>(i * 32 + k % 2 * 16) * N + k / 4 * 32 + k / 2 % 2 * 16);
+    unsigned l = lane_out;
+    asm volatile("" : "+v"(l));                                // (an address per block and tile in registers otherwise: they spill)
+    *reinterpret_cast<f32x4_wd_t *>(at + l) = v;
+  };
+  constexpr int kHeldStores = kWdHeld * kBlockStores, kHeldSlabs = kHeldStores / 4;
+  auto store_held = [&](int k) __attribute__((always_inline)) {
+    store(held_at, 4 - kWdHeld + k / kBlockStores, k % kBlockStores, held[k / kBlockStores][k % kBlockStores]);
+  };
+
+  // Scalar loads answer in any order: while one is on its way, every wait for a fragment is a wait for everything.  So they
+  // go out behind a step's fragment reads, once these have arrived, and are used behind the fragment reads of the next step.
+  auto lds_landed = []() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0xC07F); };   // lgkmcnt(0)
+
+  // ---- fill the ring: A(0) B(0) A(1) B(1) A(2)
+  fetch_a();
+  fetch_b();
+#pragma unroll
+  for (unsigned m = 0; m < 3; ++m) {
+#pragma unroll
+    for (int j = 0; j < kWdInstr; ++j) dma_a(2 * m, j);
+    if (m < 2) {
+#pragma unroll
+      for (int j = 0; j < kWdInstr; ++j) dma_b(2 * m + 1, j);
+      request_next();
+      fetch_a();
+      if (m == 0) fetch_b();
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kWdInstr) : "memory");
+  unsigned ra = 0;                                            // slot of A(m); B(m) and the next slabs follow it in the ring
+  zero_rest(cur, 0, 0, 1);
+  fa0[0] = read_a(0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) fb0[j] = read_b(1, 0, j);
+#pragma unroll
+  for (int i = 1; i < 4; ++i) fa0[i] = read_a(0, 0, i);
+
+  bool stored = false;                                        // the wait below has a tile's stores to let pass
+  for (;;) {
+    // slab 0: what it would request went out ahead of the previous tile's stores
     {
-      unsigned off[kWdSlots][8];                                  // all index loads first: one round trip, not five
-#pragma unroll
-      for (int h = 0; h < kWdSlots; ++h) row_idx(h, off[h]);
-#pragma unroll
-      for (int h = 0; h < kWdSlots; ++h) issue(h, off[h]);
+      const unsigned rb = mod5(ra + 1);
+      step(True{}, fa0, fb0, fa1, fb1, ra, rb, 1, none);
+      step(False{}, fa1, fb1, fa0, fb0, ra, rb, 2, none);
+      step(False{}, fa0, fb0, fa1, fb1, ra, rb, 3, [&](int q) __attribute__((always_inline)) {
+        if (q == 11) {
+          lds_landed();
+          fetch_b();
+        }
+      });
+      lds_landed();
+      // slab 1 has landed once only A(2), and the stores behind it, are outstanding
+      if (stored)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kWdInstr + (4 - kWdHeld) * kBlockStores) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kWdInstr) : "memory");
+      asm volatile("s_barrier" ::: "memory");
     }
-    // slab 0 is in LDS once only A(1), B(1), A(2) are outstanding
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * kWdInstr) : "memory");
-    if (tail != 0 && KT == 1) zero_tail(0);
-    load_frags(0, 0, fa0, fb0);
-
-    for (int m = 0; m < KT; ++m) {
-      unsigned off_b[8], off_a[8];
-      row_idx(2 * m + kWdSlots, off_b);                           // B(m+2) and A(m+3), issued after this slab
-      row_idx(2 * m + kWdSlots + 1, off_a);
-      // the index loads leave now, a slab's worth of MFMAs before they are used (left to itself the
-      // scheduler sinks them to their use behind the barrier, a scalar-memory round trip per slab)
-      __builtin_amdgcn_sched_barrier(0);
-      load_frags(m, 1, fa1, fb1);
-      mma(fa0, fb0);
-      load_frags(m, 2, fa0, fb0);
-      mma(fa1, fb1);
-      load_frags(m, 3, fa1, fb1);
-      mma(fa0, fb0);
-      // slab m+1 has landed for everyone (only A(m+2) is outstanding) and nobody reads slab m any more
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kWdInstr) : "memory");
-      issue(2 * m + kWdSlots, off_b);                             // B(m+2) into the slot of A(m)
-      issue(2 * m + kWdSlots + 1, off_a);                         // A(m+3) into the slot of B(m)
-      if (tail != 0 && m + 2 == KT) zero_tail(m + 1);
-      load_frags(m + 1, 0, fa0, fb0);
-      mma(fa1, fb1);
-    }
-    // no DMA may be in flight into LDS that the next workgroup on this CU owns
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-  }
-
-  // the B fragment is the MFMA's row operand: this lane holds, for output row m = frag_row, the
-  // columns 8 q + 4 frag_half + r of each 32-wide tile in accumulator element 4 q + r
-  float *Ce = C + static_cast<int64_t>(e) * M * N;
+    const int slabs = cur.slabs;
+    for (int m = 0; m < slabs - 1; ++m) {
+      // slab m is in registers, slab m + 1 in LDS: the last step of m, then the first three of m + 1
+      zero_rest(cur, m + 1, mod5(ra + 2), mod5(ra + 3));
+      if (held_at != nullptr && m < kHeldSlabs) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m0 + wm * 64 + i * 32 + frag_row;
+        for (int h = 0; h < kHeldSlabs; ++h)
+          if (m == h) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int cc = n0 + wn * 128 + j * 32 + q * 8 + frag_half * 4;
-        *reinterpret_cast<float4 *>(Ce + static_cast<int64_t>(m) * N + cc) =
-            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+            for (int k = 0; k < 4; ++k) store_held(4 * h + k);
+          }
       }
+      {
+        const unsigned r0 = ra;
+        ra = mod5(ra + 2);
+        step(False{}, fa1, fb1, fa0, fb0, ra, mod5(ra + 1), 0, [&](int q) __attribute__((always_inline)) {
+          if (q % 4 == 3) dma_b(r0, q / 4);                   // B(m+2) into the slot of A(m)
+        });
+      }
+      const unsigned rb = mod5(ra + 1);
+      {
+        const unsigned r0 = mod5(ra + 3);
+        step(False{}, fa0, fb0, fa1, fb1, ra, rb, 1, [&](int q) __attribute__((always_inline)) {
+          if (q % 4 == 3) dma_b(r0, 4 + q / 4);
+          if (q == 11) {
+            lds_landed();
+            request_next();
+            fetch_a();
+          }
+        });
+      }
+      {
+        const unsigned r0 = mod5(ra + 4);
+        step(False{}, fa1, fb1, fa0, fb0, ra, rb, 2, [&](int q) __attribute__((always_inline)) {
+          if (q > 8 && q % 2 == 1) dma_a(r0, (q - 9) / 2);    // A(m+3) into the slot of B(m)
+        });
+        step(False{}, fa0, fb0, fa1, fb1, ra, rb, 3, [&](int q) __attribute__((always_inline)) {
+          if (q % 4 == 3) dma_a(r0, 4 + q / 4);
+          if (q == 11) {
+            lds_landed();
+            fetch_b();
+          }
+        });
+      }
+      lds_landed();
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kWdInstr) : "memory");
+    }
+    // the tile's last step: everything that slab 0 of the next tile would request goes before the stores
+    if (held_at != nullptr) {
+#pragma unroll
+      for (int h = 0; h < kHeldSlabs; ++h)                     // few slabs: what is left
+        if (slabs - 1 <= h) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) store_held(4 * h + k);
+        }
+    }
+    const bool last = nxt.e >= n_groups;
+    if (!last) zero_rest(nxt, 0, mod5(ra + 2), mod5(ra + 3));
+    request_next();
+    {
+      const unsigned r0 = ra, r1 = mod5(ra + 1);
+      ra = mod5(ra + 2);
+      step(False{}, fa1, fb1, fa0, fb0, ra, mod5(ra + 1), 0, [&](int q) __attribute__((always_inline)) {
+        if (q == 0) fetch_a();
+        if (q < 8) dma_b(r0, q); else dma_a(r1, q - 8);
+      });
+    }
+    float *tile = C + (static_cast<int64_t>(cur.e) * M + cur.m0) * N + cur.n0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < kBlockStores; ++k) {
+        const f32x4_wd_t v = piece(i, k);
+        if (i < 4 - kWdHeld) store(tile, i, k, v);
+        else held[i - (4 - kWdHeld)][k] = v;
+        if (k % 2) __builtin_amdgcn_sched_barrier(0);         // (registers: two pieces at a time)
+      }
+    held_at = tile;
+    stored = true;
+    if (last) break;
+    cur = nxt;
+    nxt = behind(cur);
   }
+#pragma unroll
+  for (int k = 0; k < kHeldStores; ++k) store_held(k);
+  // no DMA may be in flight into LDS that the next workgroup on this CU owns
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
 // rows scaled by a per-row factor (the gate weight of Eq. (12) on d_out):
@@ -1818,7 +2017,8 @@ hipError_t launch_wgrad(int dtype, const void *A, int64_t lda, int M, const void
                         int n_groups, int64_t n_pos, float *C, hipStream_t s) {
   const bool mfma = dtype == ROM_DTYPE_BF16 && M % 8 == 0 && N % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 &&
                     reinterpret_cast<uintptr_t>(A) % 16 == 0 && reinterpret_cast<uintptr_t>(Bm) % 16 == 0;
-  if (mfma && !row_scale && M % kWgBig == 0 && N % kWgBig == 0 && M > 0 && N > 0 && n_pos > 0 && kUseWgradDma &&
+  if (mfma && !row_scale && M % kWgBig == 0 && N % kWgBig == 0 && M > 0 && N > 0 && n_pos >= kWdRows &&
+      n_pos < (1 << 30) && N <= (1 << 21) && ceil_div(M, kWgBig) * ceil_div(N, kWgBig) < (1 << 24) &&
       static_cast<uint64_t>(n_pos) * static_cast<uint64_t>(lda) * 2 < (1ull << 32) &&
       static_cast<uint64_t>(n_pos) * static_cast<uint64_t>(ldb) * 2 < (1ull << 32)) {
     // (operand rows are rows_x[p] < n_pos or p itself: 32-bit byte offsets reach every one of them)
@@ -1842,12 +2042,10 @@ hipError_t launch_wgrad(int dtype, const void *A, int64_t lda, int M, const void
         done[dev].store(true, std::memory_order_release);
       }
     }
-    const int64_t tiles = static_cast<int64_t>(N / kWgBig) * (M / kWgBig) * n_groups;
-    const dim3 grid(static_cast<unsigned>(ceil_div(tiles, 8) * 8));
     auto kernel = rows_a ? (rows_b ? &wgrad_bf16_dma_kernel<true, true> : &wgrad_bf16_dma_kernel<true, false>)
                          : (rows_b ? &wgrad_bf16_dma_kernel<false, true> : &wgrad_bf16_dma_kernel<false, false>);
-    hipLaunchKernelGGL(kernel, grid, dim3(512), kWdSmem, s, static_cast<const bf16_t *>(A), lda, M,
-                       static_cast<const bf16_t *>(Bm), ldb, N, rows_a, rows_b, offsets, n_pos, n_groups, C);
+    hipLaunchKernelGGL(kernel, dim3(kWdWgs), dim3(256), kWdSmem, s, static_cast<const bf16_t *>(A), lda, M,
+                       static_cast<const bf16_t *>(Bm), ldb, N, rows_a, rows_b, offsets, static_cast<int>(n_pos), n_groups, C);
     return hipGetLastError();
   }
   if (mfma && !row_scale && M >= kWgBig && N >= kWgBig) {
