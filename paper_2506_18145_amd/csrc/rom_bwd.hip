@@ -644,20 +644,39 @@ __global__ __launch_bounds__(256) void router_bwd_kernel(const float *__restrict
   }
 }
 
+// two consecutive channels of a row (4- or 8-byte accesses)
+__device__ __forceinline__ void conv_ld2(const bf16_t *p, float (&f)[2]) {
+  const unsigned u = *reinterpret_cast<const unsigned *>(p);
+  f[0] = bf16_to_f32(static_cast<bf16_t>(u & 0xffffu));
+  f[1] = bf16_to_f32(static_cast<bf16_t>(u >> 16));
+}
+__device__ __forceinline__ void conv_ld2(const float *p, float (&f)[2]) {
+  const float2 v = *reinterpret_cast<const float2 *>(p);
+  f[0] = v.x; f[1] = v.y;
+}
+__device__ __forceinline__ void conv_st2(bf16_t *p, const float (&f)[2]) {
+  *reinterpret_cast<unsigned *>(p) = static_cast<unsigned>(f32_to_bf16(f[0])) | (static_cast<unsigned>(f32_to_bf16(f[1])) << 16);
+}
+__device__ __forceinline__ void conv_st2(float *p, const float (&f)[2]) { *reinterpret_cast<float2 *>(p) = make_float2(f[0], f[1]); }
+
 // partial[chunk][e][d] = sum over the chunk's tokens of d_logits[n, e] * x[n, d]  (d = d_model is the
-// bias column: x = 1).  grid (ceil((d_model + 1) / 256), n_chunks); a thread owns one column.
-constexpr int kRouterChunk = 128;    // (512: 288 blocks on 256 CUs, one wavefront per SIMD walking 512 dependent rows: 0.24 ms at 16K tokens)
+// bias column: x = 1).  grid (ceil((d_model + 1) / 512), n_chunks); a thread owns two columns (d_model is even) and asks for
+// kRouterAhead rows together: a row at a time it is a chain of memory round trips.
+constexpr int kRouterAhead = 16;
+// 8192 tokens x 1024 with 8 experts 48 -> 11 us, 16384 x 2048 52 -> 27 (a column and a row at a time; sixteen rows of one column with
+// their ends checked one by one 51 and 76).  Tokens per chunk: workgroups count, down to one round of 64 tokens.
+inline int router_chunk(int64_t n_tok) { return n_tok > 8192 ? 128 : 64; }
 template <typename T, int EMAX>
 __global__ __launch_bounds__(256) void router_wgrad_partial_kernel(const float *__restrict__ d_logits,
                                                                    const T *__restrict__ x, int64_t n_tok, int d_model,
-                                                                   int n_experts, float *__restrict__ partial) {
+                                                                   int n_experts, int chunk, float *__restrict__ partial) {
   __shared__ float dl[64][EMAX];                    // [token in round][expert]
-  const int d = blockIdx.x * 256 + threadIdx.x;
-  const int64_t n0 = static_cast<int64_t>(blockIdx.y) * kRouterChunk;
-  const int64_t n1 = n0 + kRouterChunk < n_tok ? n0 + kRouterChunk : n_tok;
-  float acc[EMAX];
+  const int d = (blockIdx.x * 256 + threadIdx.x) * 2;
+  const int64_t n0 = static_cast<int64_t>(blockIdx.y) * chunk;
+  const int64_t n1 = n0 + chunk < n_tok ? n0 + chunk : n_tok;
+  float acc[2][EMAX];
 #pragma unroll
-  for (int e = 0; e < EMAX; ++e) acc[e] = 0.0f;
+  for (int e = 0; e < EMAX; ++e) acc[0][e] = acc[1][e] = 0.0f;
   for (int64_t r0 = n0; r0 < n1; r0 += 64) {
     __syncthreads();
     for (int i = threadIdx.x; i < 64 * EMAX; i += 256) {
@@ -666,36 +685,67 @@ __global__ __launch_bounds__(256) void router_wgrad_partial_kernel(const float *
       dl[i / EMAX][e] = (n < n1 && e < n_experts) ? d_logits[n * n_experts + e] : 0.0f;
     }
     __syncthreads();
-    if (d <= d_model) {
-      for (int i = 0; i < 64 && r0 + i < n1; ++i) {
-        const float xv = d < d_model ? to_f32(x[(r0 + i) * d_model + d]) : 1.0f;
+    const int rows = static_cast<int>(n1 - r0 < 64 ? n1 - r0 : 64);
+    const T *xr = x + r0 * d_model + (d < d_model ? d : 0);
+    const auto add = [&](int i, float x0, float x1) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < EMAX; ++e) acc[e] = fmaf(dl[i][e], xv, acc[e]);
+      for (int e = 0; e < EMAX; ++e) {
+        acc[0][e] = fmaf(dl[i][e], x0, acc[0][e]);
+        acc[1][e] = fmaf(dl[i][e], x1, acc[1][e]);
       }
+    };
+    if (d < d_model) {
+      int i = 0;
+      for (; i + kRouterAhead <= rows; i += kRouterAhead) {
+        float xv[kRouterAhead][2];
+#pragma unroll
+        for (int k = 0; k < kRouterAhead; ++k) conv_ld2(xr + static_cast<int64_t>(k) * d_model, xv[k]);
+        xr += static_cast<int64_t>(kRouterAhead) * d_model;
+#pragma unroll
+        for (int k = 0; k < kRouterAhead; ++k) add(i + k, xv[k][0], xv[k][1]);
+      }
+      for (; i < rows; ++i, xr += d_model) {
+        float xv[2];
+        conv_ld2(xr, xv);
+        add(i, xv[0], xv[1]);
+      }
+    } else if (d == d_model) {
+      for (int i = 0; i < rows; ++i) add(i, 1.0f, 0.0f);
     }
   }
-  if (d <= d_model)
 #pragma unroll
-    for (int e = 0; e < EMAX; ++e)
-      if (e < n_experts) partial[(static_cast<int64_t>(blockIdx.y) * n_experts + e) * (d_model + 1) + d] = acc[e];
+  for (int v = 0; v < 2; ++v)
+    if (d + v <= d_model)
+#pragma unroll
+      for (int e = 0; e < EMAX; ++e)
+        if (e < n_experts) partial[(static_cast<int64_t>(blockIdx.y) * n_experts + e) * (d_model + 1) + d + v] = acc[v][e];
 }
 
-__global__ __launch_bounds__(256) void router_wgrad_finish_kernel(const float *__restrict__ partial, int n_chunks,
+// Waves per 64 outputs of the two kernels that add partial sums: each adds every sixteenth, then the wave sums are added in
+// wave order (one thread walking all partials is a chain of memory round trips).
+constexpr int kFinishWaves = 16;
+__device__ __forceinline__ float finish_total(float acc, float (&sums)[kFinishWaves][64], int lane, int wave) {
+  sums[wave][lane] = acc;
+  __syncthreads();
+  float tot = sums[0][lane];
+#pragma unroll
+  for (int w = 1; w < kFinishWaves; ++w) tot += sums[w][lane];
+  return tot;
+}
+
+__global__ __launch_bounds__(kFinishWaves * 64) void router_wgrad_finish_kernel(const float *__restrict__ partial, int n_chunks,
                                                                   int d_model, int n_experts,
                                                                   float *__restrict__ d_w_router,
                                                                   float *__restrict__ d_b_router) {
-  // (four waves per 64 outputs, as in conv_bwd_finish_kernel)
-  __shared__ float sums[4][64];
+  __shared__ float sums[kFinishWaves][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
   const bool live = i < n_experts * (d_model + 1);
   float acc = 0.0f;
   if (live)
-    for (int c = q; c < n_chunks; c += 4) acc += partial[static_cast<int64_t>(c) * n_experts * (d_model + 1) + i];
-  sums[q][lane] = acc;
-  __syncthreads();
+    for (int c = q; c < n_chunks; c += kFinishWaves) acc += partial[static_cast<int64_t>(c) * n_experts * (d_model + 1) + i];
+  const float tot = finish_total(acc, sums, lane, q);
   if (q != 0 || !live) return;
-  const float tot = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
   const int e = i / (d_model + 1), d = i % (d_model + 1);
   if (d < d_model) d_w_router[e * d_model + d] = tot;
   else if (d_b_router) d_b_router[e] = tot;
@@ -726,42 +776,34 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const T *__restrict__ dx
 }
 
 // ------------------------------------------------------------------ adjoint of conv + SiLU, Eq. (2)
-// A thread owns one channel and a run of kConvBwdRun steps of one sequence.  c_t = b + sum_j w_j x_{t-3+j}
+// A thread owns one channel (or two) and a run of steps of one sequence (conv_bwd_run).  c_t = b + sum_j w_j x_{t-3+j}
 // is recomputed, d_c_t = (du_a + du_b)_t * SiLU'(c_t); d_x_{t} = sum_j w_j d_c_{t+3-j} needs d_c of three
 // later steps (zero past the sequence end), so the thread runs three steps into the next run.
 // Per-run partial sums of d_w[i, j] = sum_t d_c_t x_{t-3+j} and d_b = sum_t d_c_t go to
 // partial[run][5][channel] and are added in run order by conv_bwd_finish_kernel.
-constexpr int kConvBwdRun = 128;
+// Steps per run: 128, and half of that as long as there are fewer than 4096 wavefronts (16 a CU).  A run reads six rows more than
+// its steps, and its partial sums are five rows.  4 x 2048 steps x 2048 channels: runs of 128 (1024 wavefronts) 94 us, 64 57, 32 40,
+// 16 46; 16384 x 4096 (4096 wavefronts of 128) 135, of 64 145.
+inline int conv_bwd_run(int64_t B, int64_t L, int d_inner) {
+  int run = 128;
+  while (run > 16 && B * ceil_div(L, run) * ceil_div(d_inner, 128) < 4096) run /= 2;
+  return run;
+}
 constexpr int kConvBwdAhead = 8;     // steps whose rows are requested together
-// two consecutive channels of a row (4- or 8-byte accesses; the launcher checks evenness and alignment)
-__device__ __forceinline__ void conv_ld2(const bf16_t *p, float (&f)[2]) {
-  const unsigned u = *reinterpret_cast<const unsigned *>(p);
-  f[0] = bf16_to_f32(static_cast<bf16_t>(u & 0xffffu));
-  f[1] = bf16_to_f32(static_cast<bf16_t>(u >> 16));
-}
-__device__ __forceinline__ void conv_ld2(const float *p, float (&f)[2]) {
-  const float2 v = *reinterpret_cast<const float2 *>(p);
-  f[0] = v.x; f[1] = v.y;
-}
-__device__ __forceinline__ void conv_st2(bf16_t *p, const float (&f)[2]) {
-  *reinterpret_cast<unsigned *>(p) = static_cast<unsigned>(f32_to_bf16(f[0])) | (static_cast<unsigned>(f32_to_bf16(f[1])) << 16);
-}
-__device__ __forceinline__ void conv_st2(float *p, const float (&f)[2]) { *reinterpret_cast<float2 *>(p) = make_float2(f[0], f[1]); }
-
 // V = 2: a thread owns two neighbouring channels (half the memory instructions, twice their width)
 template <typename T, int V>
 __global__ __launch_bounds__(256) void conv_bwd_kernel(const T *__restrict__ xz, int64_t ld_xz,
                                                        const float *__restrict__ conv_w,
                                                        const float *__restrict__ conv_b, const T *__restrict__ du_a,
                                                        const T *__restrict__ du_b, int64_t L, int d_inner,
-                                                       T *__restrict__ d_xpre, int64_t ld_dx,
+                                                       T *__restrict__ d_xpre, int64_t ld_dx, int run_steps,
                                                        float *__restrict__ partial) {
   static_assert(V == 1 || V == 2, "one or two channels per thread");
   const int ch = (blockIdx.x * blockDim.x + threadIdx.x) * V;
   if (ch >= d_inner) return;
   const int64_t b = blockIdx.z, run = blockIdx.y;
-  const int64_t t0 = run * kConvBwdRun;
-  const int64_t t1 = t0 + kConvBwdRun < L ? t0 + kConvBwdRun : L;
+  const int64_t t0 = run * run_steps;
+  const int64_t t1 = t0 + run_steps < L ? t0 + run_steps : L;
   float w[V][4], bias[V];
 #pragma unroll
   for (int v = 0; v < V; ++v) {
@@ -858,23 +900,19 @@ __global__ __launch_bounds__(256) void conv_bwd_kernel(const T *__restrict__ xz,
   }
 }
 
-__global__ __launch_bounds__(256) void conv_bwd_finish_kernel(const float *__restrict__ partial, int64_t n_parts,
+__global__ __launch_bounds__(kFinishWaves * 64) void conv_bwd_finish_kernel(const float *__restrict__ partial, int64_t n_parts,
                                                               int d_inner, float *__restrict__ d_conv_w,
                                                               float *__restrict__ d_conv_b) {
-  // a block owns 64 outputs; its four waves each add every fourth partial in order, then the four sums
-  // are added in wave order (one thread walking all partials is a chain of dependent memory round trips)
-  __shared__ float sums[4][64];
+  __shared__ float sums[kFinishWaves][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
   const bool live = i < 5 * d_inner;
   const int j = live ? i / d_inner : 0, ch = live ? i % d_inner : 0;
   float acc = 0.0f;
   if (live)
-    for (int64_t p = q; p < n_parts; p += 4) acc += partial[(p * 5 + j) * d_inner + ch];
-  sums[q][lane] = acc;
-  __syncthreads();
+    for (int64_t p = q; p < n_parts; p += kFinishWaves) acc += partial[(p * 5 + j) * d_inner + ch];
+  const float tot = finish_total(acc, sums, lane, q);
   if (q != 0 || !live) return;
-  const float tot = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
   if (j < 4) d_conv_w[ch * 4 + j] = tot;
   else if (d_conv_b) d_conv_b[ch] = tot;
 }
@@ -944,6 +982,9 @@ __global__ __launch_bounds__(256) void pack_dxdbl_kernel(const float *__restrict
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+// 64 x 64 tiles where 128 x 128 ones would not give every CU a workgroup (8192 rows in 8 experts, 96 x 2048 and 2048 x 64,
+// 128 workgroups: 41 and 43 us, 28 and 30; 16384 rows, 160 x 4096 and 4096 x 128, 512 and 256: 78 and 103, 102 and 142).
+constexpr int kWgTileMinWgs = 256;
 constexpr int kWgTile = 128, kWgSlab = 64, kWgPitch = kWgSlab + 8;     // halfs per LDS row (144 bytes: 16-byte aligned rows)
 
 // eight 16-byte pieces (eight consecutive columns of eight consecutive positions) -> for each of the
@@ -964,68 +1005,88 @@ __device__ __forceinline__ void wgrad_park8x8(const u32x4_t (&v)[8], bf16_t (*ds
   }
 }
 
-__global__ __launch_bounds__(256) void wgrad_bf16_kernel(const bf16_t *__restrict__ A, int64_t lda, int M,
+// TILE x TILE on TILE / 32 wavefronts (128: 2 x 2 of 64 x 64; 64: two of 32 x 64)
+template <int TILE>
+__global__ __launch_bounds__(2 * TILE) void wgrad_bf16_kernel(const bf16_t *__restrict__ A, int64_t lda, int M,
                                                          const bf16_t *__restrict__ Bm, int64_t ldb, int N,
                                                          const int32_t *__restrict__ rows_a,
                                                          const int32_t *__restrict__ rows_b,
                                                          const int32_t *__restrict__ offsets, int64_t n_pos,
                                                          float *__restrict__ C) {
-  __shared__ __attribute__((aligned(16))) bf16_t As[kWgTile][kWgPitch];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[kWgTile][kWgPitch];
+  constexpr int MB = TILE / 64;                                  // 32-row blocks of a wavefront
+  __shared__ __attribute__((aligned(16))) bf16_t As[TILE][kWgPitch];
+  __shared__ __attribute__((aligned(16))) bf16_t Bs[TILE][kWgPitch];
   const int e = blockIdx.z;
   const int64_t p_lo = offsets ? offsets[e] : 0, p_hi = offsets ? offsets[e + 1] : n_pos;
-  const int m0 = blockIdx.y * kWgTile, n0 = blockIdx.x * kWgTile;
+  const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;                       // 2 x 2 waves, 64 x 64 each
-  f32x16_t acc[2][2];
+  const int wm = wave & 1, wn = wave >> 1;
+  f32x16_t acc[MB][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
   const int frag_row = lane & 31, frag_half = lane >> 5;
-  // staging: a slab is 64 positions; threads 0..127 bring the A operand, 128..255 the B operand, each an
-  // 8-position x 8-column block: (position group pg = 0..7, column piece = 0..15)
-  const bool is_a = __builtin_amdgcn_readfirstlane(tid < 128 ? 1 : 0) != 0;      // wave-uniform
-  const int t2 = tid & 127, pg = t2 & 7, piece = t2 >> 3;       // 16 consecutive lanes park into 64 distinct banks
+  // staging: a slab is 64 positions; the first half of the threads brings the A operand, the second the B operand, each an
+  // 8-position x 8-column block: (position group pg = 0..7, column piece)
+  const bool is_a = __builtin_amdgcn_readfirstlane(tid < TILE ? 1 : 0) != 0;     // wave-uniform
+  const int t2 = tid & (TILE - 1), pg = t2 & 7, piece = t2 >> 3;       // 16 consecutive lanes park into 64 distinct banks
   const bf16_t *src = is_a ? A : Bm;
   const int32_t *rows = is_a ? rows_a : rows_b;      // position -> row of this operand (NULL: the position itself)
   const int64_t ld = is_a ? lda : ldb;
   const int col = (is_a ? m0 : n0) + piece * 8;
   const bool col_ok = col < (is_a ? M : N);
   bf16_t(*dst)[kWgPitch] = is_a ? As : Bs;
-  for (int64_t p0 = p_lo; p0 < p_hi; p0 += kWgSlab) {
-    // (branch-free, indices first: see the 256 x 256 kernel)
-    u32x4_t v[8];
-    int64_t r[8];
+  // Row numbers are asked for two slabs ahead of their use and rows one slab ahead: with one or two workgroups on a CU nothing
+  // else hides the two round trips (160 x 4096 of 16384 rows 84-87 -> 78 us).  (Branch-free, indices first: see the 256 x 256
+  // kernel.)
+  const auto numbers = [&](int64_t p0, int(&r)[8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int64_t p = p0 + pg * 8 + i;
-      r[i] = p < p_hi ? p : p_hi - 1;
+      r[i] = static_cast<int>(p < p_hi ? p : p_hi - 1);
     }
     if (rows) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) r[i] = rows[r[i]];
     }
+  };
+  u32x4_t v[8];
+  int r[8];
+  const auto fetch = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const u32x4_t *>(src + r[i] * ld + (col_ok ? col : 0));
+  };
+  if (p_lo < p_hi) {
+    numbers(p_lo, r);
+    fetch();
+    numbers(p_lo + kWgSlab, r);
+  }
+  for (int64_t p0 = p_lo; p0 < p_hi; p0 += kWgSlab) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (p0 + pg * 8 + i >= p_hi || !col_ok) v[i] = u32x4_t{0u, 0u, 0u, 0u};
     __syncthreads();                       // the slab before this one has been multiplied
     wgrad_park8x8(v, dst, piece * 8, pg * 8);
     __syncthreads();
+    if (p0 + kWgSlab < p_hi) {
+      fetch();
+      numbers(p0 + 2 * kWgSlab, r);
+      __builtin_amdgcn_sched_barrier(0);                         // the requests go out ahead of the products
+    }
 #pragma unroll
     for (int kk = 0; kk < kWgSlab / 16; ++kk) {
-      bf16x8_t fa[2], fb[2];
+      bf16x8_t fa[MB], fb[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[i] = *reinterpret_cast<const bf16x8_t *>(&As[wm * 64 + i * 32 + frag_row][kk * 16 + frag_half * 8]);
-        fb[i] = *reinterpret_cast<const bf16x8_t *>(&Bs[wn * 64 + i * 32 + frag_row][kk * 16 + frag_half * 8]);
-      }
+      for (int i = 0; i < MB; ++i)
+        fa[i] = *reinterpret_cast<const bf16x8_t *>(&As[(wm * MB + i) * 32 + frag_row][kk * 16 + frag_half * 8]);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
+        fb[i] = *reinterpret_cast<const bf16x8_t *>(&Bs[wn * 64 + i * 32 + frag_row][kk * 16 + frag_half * 8]);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
@@ -1035,8 +1096,8 @@ __global__ __launch_bounds__(256) void wgrad_bf16_kernel(const bf16_t *__restric
   // columns 8 q + 4 frag_half + r of each 32-wide tile in accumulator element 4 q + r
   float *Ce = C + static_cast<int64_t>(e) * M * N;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m0 + wm * 64 + i * 32 + frag_row;
+  for (int i = 0; i < MB; ++i) {
+    const int m = m0 + (wm * MB + i) * 32 + frag_row;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -1761,7 +1822,7 @@ hipError_t launch_gate_backward(int dtype, const void *a, const void *b, const i
 }
 
 size_t router_bwd_partial_bytes(int64_t n_tok, int d_model, int n_experts) {
-  return static_cast<size_t>(ceil_div(n_tok, kRouterChunk)) * n_experts * (d_model + 1) * sizeof(float);
+  return static_cast<size_t>(ceil_div(n_tok, router_chunk(n_tok))) * n_experts * (d_model + 1) * sizeof(float);
 }
 
 hipError_t launch_router_backward(int dtype, const float *logits, const int32_t *expert_idx, const float *d_gate,
@@ -1769,18 +1830,18 @@ hipError_t launch_router_backward(int dtype, const float *logits, const int32_t 
                                   float *d_logits, float *partial, float *d_w_router, float *d_b_router, hipStream_t s) {
   hipLaunchKernelGGL(router_bwd_kernel, grid1d(n_tok, 256), dim3(256), 0, s, logits, expert_idx, d_gate, n_tok, n_experts,
                      top_k, gate_mode, d_logits);
-  const int n_chunks = static_cast<int>(ceil_div(n_tok, kRouterChunk));
-  const dim3 grid(static_cast<unsigned>(ceil_div(d_model + 1, 256)), static_cast<unsigned>(n_chunks));
+  const int chunk = router_chunk(n_tok), n_chunks = static_cast<int>(ceil_div(n_tok, chunk));
+  const dim3 grid(static_cast<unsigned>(ceil_div(d_model + 1, 512)), static_cast<unsigned>(n_chunks));
 #define ROM_RW(T, EMAX)                                                                                       \
   hipLaunchKernelGGL((router_wgrad_partial_kernel<T, EMAX>), grid, dim3(256), 0, s, d_logits, static_cast<const T *>(x), \
-                     n_tok, d_model, n_experts, partial)
+                     n_tok, d_model, n_experts, chunk, partial)
   if (dtype == ROM_DTYPE_BF16) {
     if (n_experts <= 8) ROM_RW(bf16_t, 8); else if (n_experts <= 16) ROM_RW(bf16_t, 16); else ROM_RW(bf16_t, 64);
   } else {
     if (n_experts <= 8) ROM_RW(float, 8); else if (n_experts <= 16) ROM_RW(float, 16); else ROM_RW(float, 64);
   }
 #undef ROM_RW
-  hipLaunchKernelGGL(router_wgrad_finish_kernel, grid1d(static_cast<int64_t>(n_experts) * (d_model + 1), 64), dim3(256), 0,
+  hipLaunchKernelGGL(router_wgrad_finish_kernel, grid1d(static_cast<int64_t>(n_experts) * (d_model + 1), 64), dim3(kFinishWaves * 64), 0,
                      s, partial, n_chunks, d_model, n_experts, d_w_router, d_b_router);
   return hipGetLastError();
 }
@@ -1798,13 +1859,14 @@ hipError_t launch_dx_finish(int dtype, const void *dx_in, const float *d_logits,
 }
 
 size_t conv_bwd_partial_bytes(int64_t B, int64_t L, int d_inner) {
-  return static_cast<size_t>(B) * static_cast<size_t>(ceil_div(L, kConvBwdRun)) * 5 * d_inner * sizeof(float);
+  return static_cast<size_t>(B) * static_cast<size_t>(ceil_div(L, conv_bwd_run(B, L, d_inner))) * 5 * d_inner * sizeof(float);
 }
 
 hipError_t launch_conv_backward(int dtype, const void *xz, int64_t ld_xz, const float *conv_w, const float *conv_b,
                                 const void *du_a, const void *du_b, int64_t B, int64_t L, int d_inner, void *d_xpre,
                                 int64_t ld_dx, float *partial, float *d_conv_w, float *d_conv_b, hipStream_t s) {
-  const int64_t n_runs = ceil_div(L, kConvBwdRun);
+  const int run_steps = conv_bwd_run(B, L, d_inner);
+  const int64_t n_runs = ceil_div(L, run_steps);
   const size_t eb = dtype == ROM_DTYPE_BF16 ? 2 : 4;
   const auto al = [&](const void *p) { return reinterpret_cast<uintptr_t>(p) % (2 * eb) == 0; };
   const bool two = d_inner % 2 == 0 && ld_xz % 2 == 0 && ld_dx % 2 == 0 && al(xz) && al(du_a) && al(du_b) && al(d_xpre);
@@ -1813,14 +1875,14 @@ hipError_t launch_conv_backward(int dtype, const void *xz, int64_t ld_xz, const 
 #define ROM_CONV_BWD(T, V)                                                                                          \
   hipLaunchKernelGGL((conv_bwd_kernel<T, V>), grid, dim3(256), 0, s, static_cast<const T *>(xz), ld_xz, conv_w, conv_b, \
                      static_cast<const T *>(du_a), static_cast<const T *>(du_b), L, d_inner, static_cast<T *>(d_xpre),  \
-                     ld_dx, partial)
+                     ld_dx, run_steps, partial)
   if (dtype == ROM_DTYPE_BF16) {
     if (two) ROM_CONV_BWD(bf16_t, 2); else ROM_CONV_BWD(bf16_t, 1);
   } else {
     if (two) ROM_CONV_BWD(float, 2); else ROM_CONV_BWD(float, 1);
   }
 #undef ROM_CONV_BWD
-  hipLaunchKernelGGL(conv_bwd_finish_kernel, grid1d(5 * d_inner, 64), dim3(256), 0, s, partial, B * n_runs, d_inner,
+  hipLaunchKernelGGL(conv_bwd_finish_kernel, grid1d(5 * d_inner, 64), dim3(kFinishWaves * 64), 0, s, partial, B * n_runs, d_inner,
                      d_conv_w, d_conv_b);
   return hipGetLastError();
 }
@@ -2072,10 +2134,13 @@ hipError_t launch_wgrad(int dtype, const void *A, int64_t lda, int M, const void
     return hipGetLastError();
   }
   if (mfma && !row_scale) {
-    const dim3 grid(static_cast<unsigned>(ceil_div(N, kWgTile)), static_cast<unsigned>(ceil_div(M, kWgTile)),
+    const bool small = ceil_div(N, kWgTile) * ceil_div(M, kWgTile) * n_groups < kWgTileMinWgs;
+    const int tile = small ? kWgTile / 2 : kWgTile;
+    const dim3 grid(static_cast<unsigned>(ceil_div(N, tile)), static_cast<unsigned>(ceil_div(M, tile)),
                     static_cast<unsigned>(n_groups));
-    hipLaunchKernelGGL(wgrad_bf16_kernel, grid, dim3(256), 0, s, static_cast<const bf16_t *>(A), lda, M,
-                       static_cast<const bf16_t *>(Bm), ldb, N, rows_a, rows_b, offsets, n_pos, C);
+    hipLaunchKernelGGL(small ? &wgrad_bf16_kernel<kWgTile / 2> : &wgrad_bf16_kernel<kWgTile>, grid, dim3(2 * tile), 0, s,
+                       static_cast<const bf16_t *>(A), lda, M, static_cast<const bf16_t *>(Bm), ldb, N, rows_a, rows_b, offsets,
+                       n_pos, C);
     return hipGetLastError();
   }
   const dim3 grid(static_cast<unsigned>(ceil_div(N, 64)), static_cast<unsigned>(ceil_div(M, 64)),
