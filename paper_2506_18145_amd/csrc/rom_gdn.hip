@@ -622,8 +622,10 @@ __global__ __launch_bounds__(256) void gdn_fold_kernel(const float *__restrict__
   }
 }
 
-// One step per sequence (L == 1): grid (n_heads, B); thread = (value channel v, quarter of the key channels).
-// The state is read and written once, in rows of 64 consecutive value channels.
+// One step per sequence (L == 1): grid (n_heads, B); thread = (four value channels, every sixteenth key channel).  Bound by
+// reading and writing the state once: a wavefront's instruction moves four whole rows of 64 value channels (1 KiB), and all of
+// a thread's rows are asked for before the norms, sums and barriers that they wait for.  Step of 256 sequences, 12 heads of 128
+// keys 98.6 -> 92.6 us, 32 heads 262 -> 258, of 64 keys 175 -> 171, one sequence 37.3 -> 34.9, against a lane a channel.
 template <int NS>
 __global__ __launch_bounds__(256) void gdn_step_kernel(const bf16_t *__restrict__ qkv, int64_t ld_qkv, int q_col, int k_col,
                                                        int v_col, const bf16_t *__restrict__ proj, int64_t ld_p, int b_col,
@@ -631,14 +633,21 @@ __global__ __launch_bounds__(256) void gdn_step_kernel(const bf16_t *__restrict_
                                                        const float *__restrict__ A_log, const float *__restrict__ norm_w,
                                                        float eps, const float *s_in, float *s_out, bf16_t *__restrict__ y,
                                                        int64_t ld_y) {
+  constexpr int kPer = NS / 16;
   __shared__ float kq[2][NS];          // normalised key, normalised and scaled query
-  __shared__ float part[4][kV];
+  __shared__ __attribute__((aligned(16))) float part[2][4][kV];
   __shared__ float red[2][4];
-  const int tid = threadIdx.x, v = tid & 63, q4 = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, v = (tid & 15) * 4, n0 = tid >> 4;
   const int h = blockIdx.x, n_heads = gridDim.x;
   const int64_t b = blockIdx.y;
   const bf16_t *row = qkv + b * ld_qkv;
   const bf16_t *prow = proj + b * ld_p;
+  // this thread's state values: S^T[n][v .. v + 3]
+  const int64_t base = (b * n_heads + h) * static_cast<int64_t>(NS) * kV + v;
+  f32x4_t st[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    st[j] = s_in ? *reinterpret_cast<const f32x4_t *>(s_in + base + (n0 + 16 * j) * kV) : f32x4_t{0.f, 0.f, 0.f, 0.f};
   // L2 norms of q and k: threads [0, NS) square a key element, threads [128, 128 + NS) a query element
   float kval = 0.0f, qval = 0.0f;
   if (tid < NS) kval = bf16_to_f32(row[k_col + h * NS + tid]);
@@ -650,49 +659,62 @@ __global__ __launch_bounds__(256) void gdn_step_kernel(const bf16_t *__restrict_
     sq += __shfl_xor(sq, off);
   }
   if (lane == 0) {
-    red[0][q4] = sk;
-    red[1][q4] = sq;
+    red[0][wave] = sk;
+    red[1][wave] = sq;
   }
+  const float beta = fast_rcp(1.0f + __expf(-bf16_to_f32(prow[b_col + h])));
+  const float alpha = __expf(-__expf(A_log[h]) * softplus_f32(bf16_to_f32(prow[a_col + h]) + dt_bias[h]));
+  float val[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) val[i] = bf16_to_f32(row[v_col + h * kV + v + i]);
   __syncthreads();
   const float rk = rsqrtf(red[0][0] + red[0][1] + red[0][2] + red[0][3] + kL2Eps);
   const float rq = rsqrtf(red[1][0] + red[1][1] + red[1][2] + red[1][3] + kL2Eps) * rsqrtf(static_cast<float>(NS));
   if (tid < NS) kq[0][tid] = kval * rk;
   if (tid >= 128 && tid < 128 + NS) kq[1][tid - 128] = qval * rq;
   __syncthreads();
-  const float beta = fast_rcp(1.0f + __expf(-bf16_to_f32(prow[b_col + h])));
-  const float alpha = __expf(-__expf(A_log[h]) * softplus_f32(bf16_to_f32(prow[a_col + h]) + dt_bias[h]));
-  // this thread's state values: S^T[n][v] for its quarter of n
-  constexpr int kPer = NS / 4;
-  const int64_t base = (b * n_heads + h) * static_cast<int64_t>(NS) * kV + v;
-  float st[kPer];
-  float pred = 0.0f;
+  // sums over the key channels: a wavefront's four rows of lanes, then the four wavefronts
+  auto share = [&](float (&s)[4], float (&dst)[4][kV]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] += __shfl_xor(s[i], 16);
+      s[i] += __shfl_xor(s[i], 32);
+      if (lane < 16) dst[wave][v + i] = s[i];
+    }
+    __syncthreads();
+  };
+  float pred[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const int n = q4 * kPer + j;
-    st[j] = alpha * (s_in ? s_in[base + static_cast<int64_t>(n) * kV] : 0.0f);
-    pred = fmaf(st[j], kq[0][n], pred);
+    const float kn = kq[0][n0 + 16 * j];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      st[j][i] = alpha * st[j][i];
+      pred[i] = fmaf(st[j][i], kn, pred[i]);
+    }
   }
-  part[q4][v] = pred;
-  __syncthreads();
-  const float u = beta * (bf16_to_f32(row[v_col + h * kV + v]) - (part[0][v] + part[1][v] + part[2][v] + part[3][v]));
-  __syncthreads();
-  float o = 0.0f;
+  share(pred, part[0]);
+  float u[4], o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) u[i] = beta * (val[i] - (part[0][0][v + i] + part[0][1][v + i] + part[0][2][v + i] + part[0][3][v + i]));
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const int n = q4 * kPer + j;
-    st[j] = fmaf(u, kq[0][n], st[j]);
-    if (s_out) s_out[base + static_cast<int64_t>(n) * kV] = st[j];
-    o = fmaf(st[j], kq[1][n], o);
+    const float kn = kq[0][n0 + 16 * j], qn = kq[1][n0 + 16 * j];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      st[j][i] = fmaf(u[i], kn, st[j][i]);
+      o[i] = fmaf(st[j][i], qn, o[i]);
+    }
+    if (s_out) *reinterpret_cast<f32x4_t *>(s_out + base + (n0 + 16 * j) * kV) = st[j];
   }
-  part[q4][v] = o;
-  __syncthreads();
-  if (q4 == 0) {
-    const float ov = part[0][v] + part[1][v] + part[2][v] + part[3][v];
+  share(o, part[1]);
+  if (wave == 0) {
+    const float ov = part[1][0][lane] + part[1][1][lane] + part[1][2][lane] + part[1][3][lane];
     float ss = ov * ov;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
     const float rstd = rsqrtf(ss * (1.0f / kV) + eps);
-    y[b * ld_y + h * kV + v] = f32_to_bf16(ov * rstd * norm_w[v] * silu_f32(bf16_to_f32(prow[h * kV + v])));
+    y[b * ld_y + h * kV + lane] = f32_to_bf16(ov * rstd * norm_w[lane] * silu_f32(bf16_to_f32(prow[h * kV + lane])));
   }
 }
 
