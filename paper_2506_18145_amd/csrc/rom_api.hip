@@ -362,7 +362,8 @@ int forward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_t
     ga.n_groups = 1; ga.M = N;
   }
   ROM_TRY(launch_grouped_gemm(ga, s));
-  {
+  const bool tail = step_tail_takes(d->dtype, B, L, K, De, R);      // dt_low, B, C, dt and the scan in one launch
+  if (!tail) {
     const bool by_pos = routed_xdt && multi;      // xdbl rows in sorted-slot order, else in token order
     ROM_TRY(launch_split_xdbl(d->dtype, xdbl, ga.k_splits, ga.c_split_stride, by_pos ? inv_perm : nullptr, K, N, R,
                               at(p.dt_low), reinterpret_cast<float *>(at(p.bc)), s));
@@ -375,7 +376,9 @@ int forward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_t
   ga.dtype = d->dtype;
   ga.A = at(p.dt_low); ga.lda = R; ga.a_span = N * R;
   ga.W = w->w_dt; ga.N = De; ga.K = R; ga.ldc = De;
-  if (passes) {
+  if (tail) {
+    // (with the scan)
+  } else if (passes) {
     // dt[n] = softplus(sum_r W_dt[e_r(n)] dt_low[n] + bias): the sums accumulate in dt (without the
     // bias, so that what is stored in T between the passes is small), the last pass activates
     ga.C = at(p.dt);
@@ -407,9 +410,15 @@ int forward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_t
 
   // selective scan + D skip + SiLU(z) gate, Eq. (5), (6)
   mark.begin(ROM_STAGE_SCAN, s);
-  ROM_TRY(launch_scan_gate(d->dtype, at(p.u), at(p.dt), reinterpret_cast<const float *>(at(p.bc)),
-                           at(p.xz) + static_cast<size_t>(De) * eb, 2 * De, w->A_log, w->D, ssm_in, ssm_out, at(p.g), B,
-                           L, De, reinterpret_cast<float *>(at(p.scan_q)), reinterpret_cast<float *>(at(p.scan_p)), s));
+  if (tail)
+    ROM_TRY(launch_step_tail(xdbl, p.xproj_slices, (routed_xdt ? S : N) * (R + 32),
+                             routed_xdt ? reinterpret_cast<const int32_t *>(at(p.expert_idx)) : nullptr, w->w_dt, w->dt_bias, R,
+                             at(p.u), at(p.xz) + static_cast<size_t>(De) * eb, 2 * De, w->A_log, w->D, ssm_in, ssm_out,
+                             at(p.dt_low), reinterpret_cast<float *>(at(p.bc)), at(p.dt), at(p.g), B, De, s));
+  else
+    ROM_TRY(launch_scan_gate(d->dtype, at(p.u), at(p.dt), reinterpret_cast<const float *>(at(p.bc)),
+                             at(p.xz) + static_cast<size_t>(De) * eb, 2 * De, w->A_log, w->D, ssm_in, ssm_out, at(p.g), B,
+                             L, De, reinterpret_cast<float *>(at(p.scan_q)), reinterpret_cast<float *>(at(p.scan_p)), s));
   mark.end(ROM_STAGE_SCAN, s);
 
   // out projection, Eq. (13), and the gate-weighted combine, Eq. (12)

@@ -111,6 +111,13 @@ hipError_t launch_slot_sum(int src_is_f32, int dst_is_f32, const void *src, int6
 hipError_t launch_split_xdbl(int dtype, const float *xdbl, int n_slices, int64_t slice_stride,
                              const int32_t *inv_perm, int top_k, int64_t n_tokens, int dt_rank,
                              void *dt_low, float *bc, hipStream_t s);
+// the three launches behind the x projection of a bf16 step as one; expert: of each sequence, or NULL for a shared W_dt
+constexpr int kXprojMaxSlices = 8;
+bool step_tail_takes(int dtype, int64_t B, int64_t L, int top_k, int d_inner, int dt_rank);
+hipError_t launch_step_tail(const float *xdbl, int n_slices, int64_t slice_stride, const int32_t *expert, const void *w_dt,
+                            const float *dt_bias, int dt_rank, const void *u, const void *z, int64_t ld_z, const float *A_log,
+                            const float *D, const float *h_in, float *h_out, void *dt_low, float *bc, void *dt, void *g,
+                            int64_t B, int d_inner, hipStream_t s);
 // number of inner-dimension slices the x projection is cut into (small batches only)
 int xproj_k_splits(int64_t rows, int n_groups, int d_inner);
 // a sequence of at most this many steps is one run of one conv thread: its state may be updated in place

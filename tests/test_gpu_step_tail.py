@@ -1,0 +1,63 @@
+"""What stands behind the x projection of a bf16 step, one launch: ranks that leave lanes of a quad without a piece of the W_dt row,
+channels off the 64 of a workgroup, routed and shared x / dt projections, states from and to memory of their own, in place and not
+wanted; and, beside it, large batches, ranks and top-2 calls that the three launches keep.  Against the formulas on the layer's own u, xz and x
+projection."""
+import pytest
+import torch
+
+from paper_2506_18145_amd import RomLayer
+from paper_2506_18145_amd.binding import rom_layer_forward
+from rom_synth import RomConfig, make_input, make_weights
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,d_inner,rank,E,top_k,shared", [
+    (1, 16, 8, 1, 1, False), (1, 80, 16, 3, 1, False), (3, 1088, 24, 4, 1, True), (2, 64, 32, 2, 1, False), (5, 128, 40, 5, 1, False),
+    (1, 1536, 48, 8, 1, False), (9, 272, 64, 2, 1, True), (2, 144, 72, 2, 1, False), (4, 528, 96, 3, 1, False),
+    (7, 4096, 128, 8, 1, False), (40, 208, 104, 4, 1, False), (256, 512, 120, 8, 1, False),
+    (700, 1024, 128, 2, 1, False), (3, 80, 136, 2, 1, False), (3, 80, 20, 2, 1, False), (3, 80, 24, 3, 2, False),
+])
+def test_step_tail(B, d_inner, rank, E, top_k, shared):
+    cfg = RomConfig(f"tail_{rank}", 900 + rank, B, 1, 64, d_inner, 16, 4, rank, E, top_k, "bf16", int(top_k > 1),
+                    routed_xdt=not shared, weight_std=0.1)
+    layer = RomLayer(cfg, make_weights(cfg))
+    x = layer.to_device(make_input(cfg))
+    gen = torch.Generator(device="cuda").manual_seed(rank)
+    conv = torch.randn(B, d_inner, 3, generator=gen, device="cuda")
+    before = torch.randn(B, d_inner, 16, generator=gen, device="cuda")
+    _, _, after = layer.forward(x, conv, before, return_states=True)
+    after = after.clone()
+    view = {n: layer.ws_view(n, B, 1).reshape(B, -1).double() for n in ("dt_low", "bc", "dt", "u", "xz", "g")}
+    idx = layer.ws_view("expert_idx", B, 1).long()
+    u, z, w = view["u"], view["xz"][:, d_inner:], {k: v.double() for k, v in layer.weights.items() if v is not None}
+    if top_k == 1:
+        # the sums of the x projection round to dt_low once; a product of 1088 or so fp32 terms otherwise
+        w_x = w["w_x"][torch.zeros_like(idx[:, 0]) if shared else idx[:, 0]]
+        xdbl = (w_x * u[:, None]).sum(-1)
+        size = (w_x * u[:, None]).abs().sum(-1)
+        got = torch.cat([view["dt_low"], view["bc"]], 1)
+        assert bool(((got - xdbl).abs() <= size * d_inner * 2.0 ** -24 + 2.0 ** -8 * xdbl.abs() * (torch.arange(rank + 32, device="cuda") < rank)).all())
+        w_dt = w["w_dt"][torch.zeros_like(idx[:, 0]) if shared else idx[:, 0]]
+        pre = (w_dt * view["dt_low"][:, None]).sum(-1) + w["dt_bias"]
+        want = torch.nn.functional.softplus(pre)
+        # fp32 sums and softplus (some of the three launches' own form: 1.3e-4 of the value), then half an ulp of bf16
+        bound = (w_dt * view["dt_low"][:, None]).abs().sum(-1) * rank * 2.0 ** -24 + (2.0 ** -8 + 2e-4) * want + 1e-7
+        assert bool(((view["dt"] - want).abs() <= bound).all())
+    dt, b, c = view["dt"], view["bc"][:, :16], view["bc"][:, 16:]
+    a = -torch.exp(w["A_log"])
+    h = torch.exp(dt[..., None] * a) * before.double() + (dt * u)[..., None] * b[:, None]
+    scale = before.double().abs() + ((dt * u)[..., None] * b[:, None]).abs()
+    assert bool(((after - h).abs() <= 64 * 2.0 ** -23 * scale + 1e-7).all())
+    y = (h * c[:, None]).sum(-1) + w["D"] * u
+    want = y * z * torch.sigmoid(z)
+    terms = ((h * c[:, None]).abs().sum(-1) + (w["D"] * u).abs()) * z.abs()
+    assert bool(((view["g"] - want).abs() <= 64 * 2.0 ** -23 * terms + 2.0 ** -8 * want.abs() + 1e-7).all())
+
+    out, first = torch.empty_like(x), layer.ws_view("g", B, 1).clone()
+    state, cs = before.clone(), conv.clone()                     # in place
+    rom_layer_forward(layer.dims, layer.weights, x, B, 1, cs, state, out, cs, state, layer.workspace(B, 1))
+    assert torch.equal(state, after) and torch.equal(layer.ws_view("g", B, 1), first)
+    rom_layer_forward(layer.dims, layer.weights, x, B, 1, None, None, out, None, None, layer.workspace(B, 1))
+    zero = layer.forward(x, torch.zeros_like(conv), torch.zeros_like(before))
+    assert torch.equal(out, zero[0] if isinstance(zero, tuple) else zero)
