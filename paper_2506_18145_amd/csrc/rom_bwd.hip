@@ -1821,8 +1821,10 @@ hipError_t launch_gate_backward(int dtype, const void *a, const void *b, const i
   return hipGetLastError();
 }
 
+// (no less for fewer tokens: a workspace of the largest call serves the smaller ones)
 size_t router_bwd_partial_bytes(int64_t n_tok, int d_model, int n_experts) {
-  return static_cast<size_t>(ceil_div(n_tok, router_chunk(n_tok))) * n_experts * (d_model + 1) * sizeof(float);
+  const int64_t at_line = 8192 / router_chunk(8192), chunks = ceil_div(n_tok, router_chunk(n_tok));
+  return static_cast<size_t>(chunks > at_line || n_tok <= 8192 ? chunks : at_line) * n_experts * (d_model + 1) * sizeof(float);
 }
 
 hipError_t launch_router_backward(int dtype, const float *logits, const int32_t *expert_idx, const float *d_gate,
@@ -1859,7 +1861,11 @@ hipError_t launch_dx_finish(int dtype, const void *dx_in, const float *d_logits,
 }
 
 size_t conv_bwd_partial_bytes(int64_t B, int64_t L, int d_inner) {
-  return static_cast<size_t>(B) * static_cast<size_t>(ceil_div(L, conv_bwd_run(B, L, d_inner))) * 5 * d_inner * sizeof(float);
+  // a run is halved only while there are fewer than 4096 wavefronts, which leaves fewer than 8192: that bound grows with B and L
+  // where the runs themselves do not, so that a workspace of the largest call serves the smaller ones
+  const int64_t most = B * ceil_div(L, 16), cut = 8191 / ceil_div(d_inner, 128), whole = B * ceil_div(L, 128);
+  const int64_t parts = whole > cut ? whole : most < cut ? most : cut;
+  return static_cast<size_t>(parts) * 5 * d_inner * sizeof(float);
 }
 
 hipError_t launch_conv_backward(int dtype, const void *xz, int64_t ld_xz, const float *conv_w, const float *conv_b,
