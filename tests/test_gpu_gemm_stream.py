@@ -65,7 +65,7 @@ def test_stream_gemm_backward(L, E):
     (36000, 5, 832, 512, None),                  # out projection 4 column tiles, 64 in the last
     (48000, 4, 520, 512, (0.5, 0.0, 0.0, -9.0)), # 3 and 8
     (36000, 2, 320, 640, None), (36000, 3, 384, 528, None), (36000, 2, 448, 512, None),      # five, six and seven slabs
-    (40000, 64, 576, 520, None), (36000, 5, 640, 704, None),      # as many groups as there are lanes; nine to eleven slabs
+    (40000, 64, 576, 528, None), (36000, 5, 640, 704, None),      # as many groups as there are lanes; nine to eleven slabs
 ])
 def test_stream_gemm_rounds(N, E, d_model, d_inner, bias, block):
     cfg = RomConfig(f"rounds_{N}", 860 + d_model % 97, 8, N // 8, d_model, d_inner, 16, 4, 32, E, 1, "bf16", 0, weight_std=0.05,
