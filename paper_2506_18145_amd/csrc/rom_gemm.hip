@@ -734,7 +734,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
 // once), and their partial sums are added through LDS in wavefront order.  The weight is the MFMA's row operand: lane
 // (c, g) ends with columns 4 g .. 4 g + 3 of position c.  Positions past the group's end repeat its first row and are not
 // stored.  One sequence, d_model 2048: with 64 x 64 tiles the in and out projections take 30 us each of a step of 94 us;
-// the step now takes 55 us through twelve layers in turn, 47 (91) with one layer whose expert the last step has just read.
+// the step took 55 us through twelve layers in turn with this kernel, 47 (91) with one layer whose expert the last step has
+// just read; 36 since the launches behind the x projection are one (step_tail_kernel).
 constexpr int kFewWideCols = 4096;
 constexpr int kFewWaves = 8, kFewUnits = 4;
 typedef float f32x4_few_t __attribute__((ext_vector_type(4)));
