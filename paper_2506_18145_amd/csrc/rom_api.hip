@@ -468,8 +468,8 @@ FfnPlan make_ffn_plan(const rom_dims *d, int32_t d_ff, int64_t n_tok) {
   const size_t S = static_cast<size_t>(n_tok) * d->top_k, b = d->dtype == ROM_DTYPE_BF16 ? 2 : 4;
   p.tok_of_pos = take(S * 4);
   p.rstd = take(S * 4);
-  // gate | up pre-activations: only the plain FMA kernel (fp32, or operands beyond the MFMA
-  // kernels' 32-bit element offsets) writes them out; the MFMA kernels apply SwiGLU themselves
+  // gate | up pre-activations: only the fp32 kernels (fp32, or operands beyond the bf16
+  // kernels' 32-bit element offsets) write them out; the bf16 kernels apply SwiGLU themselves
   const bool fused = d->dtype == ROM_DTYPE_BF16 && static_cast<int64_t>(n_tok) * d->d_model < (1ll << 32) &&
                      static_cast<int64_t>(2) * d_ff * d->d_model < (1ll << 32);
   p.h = fused ? kNone : take(S * 2 * d_ff * b);

@@ -25,6 +25,7 @@ namespace {
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
@@ -104,17 +105,48 @@ __device__ __forceinline__ TileCoord locate_tile(const GemmArgs &a, int BM, int 
 enum { kEpiPlain = 0, kEpiBiasSoftplus = 1, kEpiRowScale = 2, kEpiPlainF32 = 3, kEpiRowScaleResidual = 4,
        kEpiSwiGLU = 5 };
 
-__device__ __forceinline__ void store_out(const GemmArgs &a, int64_t crow, int col, float v) {
+__device__ __forceinline__ float finish_out(const GemmArgs &a, int64_t crow, int col, float v) {
   if (a.bias) v += a.bias[col];
   if (a.softplus) v = softplus_f32(v);
   if (a.row_scale) v *= a.row_scale[crow];
   if (a.residual)
     v += a.dtype == ROM_DTYPE_F32 ? static_cast<const float *>(a.residual)[crow * a.ldc + col]
                                   : bf16_to_f32(static_cast<const bf16_t *>(a.residual)[crow * a.ldc + col]);
+  return v;
+}
+__device__ __forceinline__ void store_out(const GemmArgs &a, int64_t crow, int col, float v) {
+  v = finish_out(a, crow, col, v);
   if (a.c_is_f32 || a.dtype == ROM_DTYPE_F32)
     static_cast<float *>(a.C)[blockIdx.y * a.c_split_stride + crow * a.ldc + col] = v;
   else
     static_cast<bf16_t *>(a.C)[crow * a.ldc + col] = f32_to_bf16(v);
+}
+// whether C takes stores of four columns, from every fourth one on
+__device__ __forceinline__ bool out_in_fours(const GemmArgs &a) {
+  const uintptr_t bytes = a.c_is_f32 || a.dtype == ROM_DTYPE_F32 ? 16 : 8;
+  return a.N % 4 == 0 && a.ldc % 4 == 0 && a.c_split_stride % 4 == 0 && reinterpret_cast<uintptr_t>(a.C) % bytes == 0;
+}
+// columns col .. col + 3 of a row, those that exist; whole: out_in_fours
+__device__ __forceinline__ void store_out4(const GemmArgs &a, bool whole, int64_t crow, int col, f32x4_t v) {
+  if (col >= a.N) return;
+  const bool f32 = a.c_is_f32 || a.dtype == ROM_DTYPE_F32;
+  const int64_t at = (f32 ? blockIdx.y * a.c_split_stride : 0) + crow * a.ldc + col;
+  const int n = a.N - col < 4 ? a.N - col : 4;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (r < n) v[r] = finish_out(a, crow, col + r, v[r]);
+  if (whole && f32) {
+    *reinterpret_cast<f32x4_t *>(static_cast<float *>(a.C) + at) = v;
+  } else if (whole) {
+    *reinterpret_cast<u32x2_t *>(static_cast<bf16_t *>(a.C) + at) = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (r >= n) continue;
+      if (f32) static_cast<float *>(a.C)[at + r] = v[r];
+      else static_cast<bf16_t *>(a.C)[at + r] = f32_to_bf16(v[r]);
+    }
+  }
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel
@@ -1493,25 +1525,27 @@ void gemm_bf16_smallk_kernel(const GemmArgs a) {
 // For fp32 operands (and the bf16 shapes that the kernels above do not take, widened as they are read).  What bounds the small
 // calls that use it is latency, so nothing goes through LDS: a lane of v_mfma_f32_16x16x4_f32 takes one row and, of every four
 // contraction indices, one.  Which four is free as long as both operands agree, so lane l reads 16 bytes, k = 4 (l / 16) .. + 3 of
-// row l & 15, straight into the operand of four instructions; kDirectBlocks of these 16-wide blocks are requested together, and
-// the next ones before the products of these.  Small calls take 16 x 16 products a wavefront, one behind the other in a
-// workgroup's four; calls that fill the CUs with 64 x 64 tiles take 32 x 32 ones, whose operands the four share in L1.
+// row l & 15 (8 in bf16), straight into the operand of four instructions; kDirectBlocks of these 16-wide blocks are requested
+// together.  Small calls take 16 x 16 products a wavefront, side by side in a workgroup's four; calls that fill the CUs
+// with 64 x 64 tiles take 32 x 32 ones, whose operands the four share in L1 (gemm_f32_tile).  A lane's sums are four neighbouring
+// columns: one store.
 // Sums are fp32 throughout; their error against 64 bits over ten layers of 22 ... 369 tokens, d_model 64 ... 256, is that of the
 // fp32 FMA tiles it replaced (4.57e-7 both).  64 tokens, d_model 64, four experts, the call's four products: 61 -> 25 us (LDS
-// tiles of 16 contraction indices waited for memory at each); the layer call 77 -> 41.
+// tiles of 16 contraction indices waited for memory at each); the layer call 77 -> 41.  8192 rows in 8 experts, fp32 8192 x 2048
+// 7817 -> 5094, 2048 x 4096 4331 -> 2575, 4096 x 128 with softplus 322 -> 204; bf16 1680 x 52 74 -> 74, 94 x 2000 (an output that the
+// bf16 kernels' stores do not take) 177 -> 119.
 constexpr int kDirectBlocks = 4;
-constexpr int kDirectWideMinTiles = 256;                      // a 64 x 64 tile for every CU
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-// elements k .. k + 3 of a row, zero from k_stop on; VEC: 16-byte aligned rows and k_stop a multiple of four
+// elements k .. k + 3 of a row, zero from k_stop on; VEC: rows aligned to four elements and k_stop a multiple of four
 template <typename T, bool VEC>
 __device__ __forceinline__ f32x4_t load_k4(const T *row, int k, int k_begin, int k_stop) {
   f32x4_t v;
   if constexpr (VEC) {
+    typedef T t4_t __attribute__((ext_vector_type(4)));
     const bool in = k < k_stop;
-    v = *reinterpret_cast<const f32x4_t *>(row + (in ? k : k_begin));
+    const t4_t x = *reinterpret_cast<const t4_t *>(row + (in ? k : k_begin));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = in ? v[i] : 0.0f;
+    for (int i = 0; i < 4; ++i) v[i] = in ? to_f32(x[i]) : 0.0f;
   } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1523,8 +1557,8 @@ __device__ __forceinline__ f32x4_t load_k4(const T *row, int k, int k_begin, int
   return v;
 }
 
-// a workgroup of WM x WN wavefronts, each TM x TN tiles of 16 x 16
-template <typename T, bool VEC, int TM, int TN, int WM, int WN>
+// a workgroup of WM x WN wavefronts, each TM x TN tiles of 16 x 16; AHEAD: the next blocks' requests stand ahead of the products
+template <typename T, bool VEC, bool AHEAD, int TM, int TN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_direct_kernel(const GemmArgs a) {
   const TileCoord tc = locate_tile(a, WM * TM * 16, WN * TN * 16);
   if (!tc.valid) return;
@@ -1574,28 +1608,87 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f32_direct_kernel(const Gem
     }
   };
   constexpr int kStep = kDirectBlocks * 16;
-  Blocks f0, f1;
-  load(k_begin, f0);
-  for (int k0 = k_begin; k0 < k_stop; k0 += 2 * kStep) {
-    if (k0 + kStep < k_stop) load(k0 + kStep, f1);
-    products(k0, f0);
-    if (k0 + kStep >= k_stop) break;
-    if (k0 + 2 * kStep < k_stop) load(k0 + 2 * kStep, f0);
-    products(k0 + kStep, f1);
+  if constexpr (AHEAD) {
+    Blocks f0, f1;
+    load(k_begin, f0);
+    for (int k0 = k_begin; k0 < k_stop; k0 += 2 * kStep) {
+      if (k0 + kStep < k_stop) load(k0 + kStep, f1);
+      products(k0, f0);
+      if (k0 + kStep >= k_stop) break;
+      if (k0 + 2 * kStep < k_stop) load(k0 + 2 * kStep, f0);
+      products(k0 + kStep, f1);
+    }
+  } else {
+    for (int k0 = k_begin; k0 < k_stop; k0 += kStep) {
+      Blocks f;
+      load(k0, f);
+      products(k0, f);
+    }
   }
   // the weight is the instruction's row operand: a lane holds row r16 of C, columns kq .. kq + 3
+  const bool whole = out_in_fours(a);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t p = row0 + i * 16 + r16;
     if (p >= tc.row_end) continue;
     const int64_t crow = a.c_rows ? a.c_rows[p] : p;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) store_out4(a, whole, crow, col0 + j * 16 + kq, acc[i][j]);
+  }
+}
+
+// The same for many rows that cannot be read four elements at a time (an odd dt_rank): the 64 x 64 tile's operands go through LDS,
+// in slabs of 16 contraction indices, so that each element is asked for once in a workgroup where the kernel above asks for it
+// in two wavefronts.  Bound by these requests; 256 threads, 4 x 4 fp32 FMA sums each.
+constexpr int kSB = 64, kSK = 16;
+
+template <typename T>
+__global__ __launch_bounds__(256) void gemm_f32_staged_kernel(const GemmArgs a) {
+  __shared__ float As[kSK][kSB + 4];
+  __shared__ float Bs[kSK][kSB + 4];
+  const TileCoord tc = locate_tile(a, kSB, kSB);
+  if (!tc.valid) return;
+  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+  const T *Ap = static_cast<const T *>(a.A);
+  const T *Wp = static_cast<const T *>(a.W) + static_cast<int64_t>(tc.group) * a.N * a.K;
+  // staging: thread -> (row = tid / 4, 4 consecutive k = (tid % 4) * 4)
+  const int s_r = tid / 4, s_k = (tid % 4) * 4;
+  const int64_t pa = tc.row0 + s_r;
+  const int64_t a_off = (pa < tc.row_end) ? static_cast<int64_t>(a.a_rows ? a.a_rows[pa] : pa) * a.lda : -1;
+  const int64_t b_off = (tc.n0 + s_r < a.N) ? static_cast<int64_t>(tc.n0 + s_r) * a.K : -1;
+  float acc[4][4] = {};
+  const int k_begin = blockIdx.y * a.k_per_split;
+  const int k_stop = (a.K - k_begin < a.k_per_split) ? a.K : k_begin + a.k_per_split;
+  for (int k0 = k_begin; k0 < k_stop; k0 += kSK) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int col = col0 + j * 16 + kq + r;
-        if (col < a.N) store_out(a, crow, col, acc[i][j][r]);
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int k = k0 + s_k + i;
+      As[s_k + i][s_r] = (a_off >= 0 && k < k_stop) ? to_f32(Ap[a_off + k]) : 0.0f;
+      Bs[s_k + i][s_r] = (b_off >= 0 && k < k_stop) ? to_f32(Wp[b_off + k]) : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSK; ++k) {
+      float av[4], bv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { av[i] = As[k][ty * 4 + i]; bv[i] = Bs[k][tx * 4 + i]; }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t p = tc.row0 + ty * 4 + i;
+    const bool row_ok = p < tc.row_end;
+    const int64_t crow = row_ok ? (a.c_rows ? a.c_rows[p] : p) : 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int col = tc.n0 + tx * 4 + j;
+      if (row_ok && col < a.N) store_out(a, crow, col, acc[i][j]);
+    }
   }
 }
 
@@ -1631,20 +1724,30 @@ int grid_tiles(const GemmArgs &a, int BM, int BN) {
 }
 
 template <typename T, bool VEC>
-hipError_t launch_f32_direct_t(const GemmArgs &a, hipStream_t s) {
-  const int64_t tiles = (a.M / 64 + (a.offsets ? a.n_groups : 1)) * ceil_div(a.N, 64) * a.k_splits;
-  if (tiles >= kDirectWideMinTiles)
-    hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, 2, 2, 2, 2>), dim3(grid_tiles(a, 64, 64), a.k_splits), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, 1, 1, 1, 4>), dim3(grid_tiles(a, 16, 64), a.k_splits), dim3(256), 0, s, a);
+hipError_t launch_f32_t(const GemmArgs &a, hipStream_t s) {
+  const dim3 grid64(grid_tiles(a, 64, 64), a.k_splits);
+  switch (gemm_f32_tile(a.M, a.offsets ? a.n_groups : 1, a.N, a.k_per_split < a.K ? a.k_per_split : a.K, a.k_splits, VEC)) {
+    case GemmF32Tile::kStaged:
+      if constexpr (!VEC) hipLaunchKernelGGL(gemm_f32_staged_kernel<T>, grid64, dim3(256), 0, s, a);
+      break;
+    case GemmF32Tile::kWide:
+      if constexpr (VEC) hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, true, 2, 2, 2, 2>), grid64, dim3(256), 0, s, a);
+      break;
+    case GemmF32Tile::kWideShort:
+      if constexpr (VEC) hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, false, 2, 2, 2, 2>), grid64, dim3(256), 0, s, a);
+      break;
+    case GemmF32Tile::kSmall:
+      hipLaunchKernelGGL((gemm_f32_direct_kernel<T, VEC, true, 1, 1, 1, 4>), dim3(grid_tiles(a, 16, 64), a.k_splits), dim3(256), 0, s, a);
+      break;
+  }
   return hipGetLastError();
 }
-hipError_t launch_f32_direct(const GemmArgs &a, hipStream_t s) {
-  if (a.dtype == ROM_DTYPE_BF16) return launch_f32_direct_t<bf16_t, false>(a, s);
-  // whole 16-byte pieces of every row: alignment of both operands (a slice of K starts at a multiple of 64)
-  const bool vec = a.K % 4 == 0 && a.lda % 4 == 0 && reinterpret_cast<uintptr_t>(a.A) % 16 == 0 &&
-                   reinterpret_cast<uintptr_t>(a.W) % 16 == 0;
-  return vec ? launch_f32_direct_t<float, true>(a, s) : launch_f32_direct_t<float, false>(a, s);
+template <typename T>
+hipError_t launch_f32(const GemmArgs &a, hipStream_t s) {
+  // whole pieces of four elements in every row of both operands (a slice of K starts at a multiple of 64)
+  const bool vec = a.K % 4 == 0 && a.lda % 4 == 0 && reinterpret_cast<uintptr_t>(a.A) % (4 * sizeof(T)) == 0 &&
+                   reinterpret_cast<uintptr_t>(a.W) % (4 * sizeof(T)) == 0;
+  return vec ? launch_f32_t<T, true>(a, s) : launch_f32_t<T, false>(a, s);
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, bool KTAIL>
@@ -1803,7 +1906,7 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
   const bool few = mfma_ok && few_rows_takes(a);
   if (a.swiglu) return few ? launch_few_rows<kEpiSwiGLU>(a, s) : launch_mfma_tiles<kEpiSwiGLU>(a, s);
   if (!mfma_ok) {
-    return launch_f32_direct(a, s);
+    return a.dtype == ROM_DTYPE_BF16 ? launch_f32<bf16_t>(a, s) : launch_f32<float>(a, s);
   }
   if (few && a.c_is_f32) return launch_few_rows<kEpiPlainF32>(a, s);
   if (a.c_is_f32) {

@@ -1,4 +1,4 @@
-// Which tile kernel of the bf16 routed GEMM takes a call (host code, no HIP).  Kernels and their launches: rom_gemm.hip.
+// Which kernel of the routed GEMM takes a call (host code, no HIP).  Kernels and their launches: rom_gemm.hip.
 #pragma once
 
 #include <cstdint>
@@ -78,6 +78,32 @@ inline bool gemm_few_rows(int64_t M, int groups, int N, int K) {
   if (M > kGemmFewRows || K % 64 != 0 || groups > 64) return false;
   const int64_t used = M < groups ? M : groups;
   return K > 1024 || groups > 16 || used * ((N + 15) / 16) <= 512;
+}
+
+// Which fp32 kernel takes a call: fp32 operands, and bf16 shapes that the kernels above do not take.
+enum class GemmF32Tile {
+  kSmall,      // 16 x 64 tiles, 16 x 16 a wavefront
+  kWide,       // 64 x 64 tiles, 32 x 32 a wavefront, the next 64 contraction indices requested ahead of the products
+  kWideShort,  // the same with no requests ahead: a third of the registers, three times the wavefronts
+  kStaged,     // 64 x 64 tiles through LDS
+};
+// vec: rows of both operands can be read four elements at a time.  All times us on MI355X, 8 groups drawn at random, kernel alone.
+//   * A group with fewer rows than a wide tile leaves it mostly empty: small / wide 64 rows x 8192 x 2048 184 / 321, 256 x 8192 x
+//     2048 403 / 465, 500 x 4000 x 1000 128 / 149.
+//   * Otherwise 64 x 64 tiles share their operands, and 16 x 64 ones have four times the wavefronts.  Over a long K the sharing gains
+//     once there is a wide tile per CU (512 x 1000 x 2000, 256 tiles, 75.5 / 66.9; 8192 x 94 x 2000, 272, 90.4 / 80.9; at 192 tiles
+//     49.6 / 71.7), over a short one only the wavefronts count until there are some 640 (512 x 1680 x 52, 432 tiles, 10.2 /
+//     16.0, 1024 x 1680 x 52, 648, 19.9 / 21.0).
+//   * Up to 256 contraction indices there is next to nothing to request ahead, and the registers for it cost two of three wavefronts:
+//     4096 rows x 4864 x 152 214 / 147 without, x 8192 x 256 504 / 340.
+//   * Element by element the requests are the bound, and LDS halves them: small / staged 1024 x 2032 x 63 26.5 / 25.0, 500 x 6432
+//     x 201 147 / 77, but 512 tiles (512 x 2032 x 63) 17.3 / 21.4, and 64 x 4848 x 151 with eight rows a group 33 / 49.
+inline GemmF32Tile gemm_f32_tile(int64_t M, int groups, int N, int k_per_split, int k_splits, bool vec) {
+  const int64_t tiles = (M / 64 + groups) * ((N + 63) / 64) * k_splits;
+  if (!vec) return M < int64_t{16} * groups || tiles < 640 ? GemmF32Tile::kSmall : GemmF32Tile::kStaged;
+  const bool brief = k_per_split <= 256;
+  if (M < int64_t{64} * groups || tiles < (brief ? 640 : 256)) return GemmF32Tile::kSmall;
+  return brief ? GemmF32Tile::kWideShort : GemmF32Tile::kWide;
 }
 
 }  // namespace rom

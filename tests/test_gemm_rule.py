@@ -8,14 +8,15 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2506_18145_amd", "csrc")
 NAMES = ("stream", "dma256", "reg256", "t128", "skinny")
+F32_NAMES = ("small", "wide", "wide_short", "staged")
 MAIN = """
 #include <cstdio>
 #include "rom_gemm_rule.h"
 int main() {
   long long M; int g, N, K, dma, wide, km, ip, f;
   while (std::scanf("%lld %d %d %d %d %d %d %d %d", &M, &g, &N, &K, &dma, &wide, &km, &ip, &f) == 9)
-    std::printf("%d %d\\n", static_cast<int>(rom::gemm_tile({M, g, N, K, dma != 0, wide != 0, km != 0, ip != 0, f != 0})),
-                rom::gemm_few_rows(M, g, N, K));
+    std::printf("%d %d %d\\n", static_cast<int>(rom::gemm_tile({M, g, N, K, dma != 0, wide != 0, km != 0, ip != 0, f != 0})),
+                rom::gemm_few_rows(M, g, N, K), static_cast<int>(rom::gemm_f32_tile(M, g, N, K, 1, wide == 0)));
 }
 """
 
@@ -30,8 +31,8 @@ def rule(tmp_path_factory):
         dma = (K % 64 == 0 and not wide) if dma is None else dma
         line = " ".join(str(int(v)) for v in (M, groups, N, K, dma, wide, w_kmajor, in_place, f32_or_softplus))
         out = subprocess.run([str(d / "rule")], input=line + "\n", capture_output=True, text=True, check=True).stdout
-        which, few = out.split()
-        return NAMES[int(which)], few == "1"
+        which, few, f32 = out.split()
+        return NAMES[int(which)], few == "1", F32_NAMES[int(f32)]
 
     return ask
 
@@ -97,3 +98,16 @@ def test_what_the_stream_kernel_cannot_do(tile):
 ])
 def test_few_rows(rule, M, groups, N, K, want):
     assert rule(M, groups, N, K)[1] == want
+
+
+# fp32 operands and the bf16 shapes that no bf16 kernel takes: the form measured fastest on either side of each line
+@pytest.mark.parametrize("M,N,K,vec,want", [
+    (64, 8192, 2048, True, "small"), (256, 8192, 2048, True, "small"), (500, 4000, 1000, True, "small"),
+    (256, 4800, 152, True, "small"), (512, 1680, 52, True, "small"), (1024, 1680, 52, True, "wide_short"),
+    (8192, 4096, 256, True, "wide_short"), (8192, 4096, 260, True, "wide"),
+    (512, 960, 2000, True, "small"), (512, 1000, 2000, True, "wide"), (8192, 8192, 2048, True, "wide"),
+    (512, 2032, 63, False, "small"), (1024, 2032, 63, False, "staged"), (16384, 2032, 63, False, "staged"),
+    (500, 6432, 201, False, "staged"), (64, 4848, 151, False, "small"),
+])
+def test_f32_gemm(rule, M, N, K, vec, want):
+    assert rule(M, 8, N, K, wide=not vec)[2] == want
