@@ -165,6 +165,7 @@ ROM_API int rom_balance_stats(const rom_dims *dims, const float *logits, const i
  *   ssm_state_in   f32 [B, d_inner, d_state] or NULL (zeros)
  *   out            T   [B, L, d_model]; must not alias x
  *   conv_state_out / ssm_state_out: same shapes, written if not NULL (may alias the *_in)
+ * States should be 16-byte aligned, as x and out have to be: they are read and written 16 bytes at a time.
  * B == 0 or L == 0 is a successful no-op. */
 ROM_API int rom_layer_forward(const rom_dims *dims, const rom_weights *w, const void *x,
                       int64_t B, int64_t L,

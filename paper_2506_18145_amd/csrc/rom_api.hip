@@ -222,13 +222,6 @@ struct BlockOpts {
   float eps;
 };
 
-// conv_out may alias conv_in (rom_step): a sequence of up to kConvInPlaceMaxLen steps is one run of one thread, which
-// reads the old state before it writes the new one; longer sequences are cut into runs for different threads, so a
-// new state that shares memory with the old one goes beside it and is copied over.
-bool conv_state_beside(const float *conv_in, const float *conv_out, int64_t L, int64_t n) {
-  return conv_in && conv_out && L > kConvInPlaceMaxLen && conv_in < conv_out + n && conv_out < conv_in + n;
-}
-
 int route_into(const rom_dims *d, const rom_weights *w, const void *x, int64_t n_tok,
                int32_t *expert_idx, float *gate, int32_t *counts, int32_t *offsets, int32_t *perm,
                int32_t *inv_perm, int32_t *tok_of_pos, int32_t *block_counts, float *logits,

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "rom.h"
+#include "rom_conv_rule.h"
 
 namespace rom {
 
@@ -120,8 +121,6 @@ hipError_t launch_step_tail(const float *xdbl, int n_slices, int64_t slice_strid
                             int64_t B, int d_inner, hipStream_t s);
 // number of inner-dimension slices the x projection is cut into (small batches only)
 int xproj_k_splits(int64_t rows, int n_groups, int d_inner);
-// a sequence of at most this many steps is one run of one conv thread: its state may be updated in place
-constexpr int kConvInPlaceMaxLen = 32;
 hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const float *conv_w,
                             const float *conv_b, const float *state_in, float *state_out, void *u,
                             int64_t B, int64_t L, int d_inner, hipStream_t s);

@@ -3,9 +3,9 @@ in place, against the formula on the layer's own xz in fp32."""
 import pytest
 import torch
 
-from paper_2506_18145_amd import RomLayer
-from paper_2506_18145_amd.binding import rom_layer_forward
-from rom_synth import RomConfig, make_input, make_weights
+from paper_2506_18145_amd import RomLayer, RomMamba2Layer
+from paper_2506_18145_amd.binding import rom_layer_forward, rom_mamba2_forward
+from rom_synth import RomConfig, get_mamba2_config, make_input, make_mamba2_input, make_mamba2_weights, make_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +39,26 @@ def test_conv(B, L, d_inner, dtype):
     conv, state = before.clone(), ssm.clone()
     rom_layer_forward(layer.dims, layer.weights, x, B, L, conv, state, out, conv, state, layer.workspace(B, L))
     assert torch.equal(conv, after) and torch.equal(state, ssm_after) and torch.equal(layer.ws_view("u", B, L), u)
+
+
+@pytest.mark.parametrize("kind,shift", [("layer", 1), ("layer", 3), ("layer", 240), ("mamba2", 240)])
+def test_conv_state_places(kind, shift):
+    """A longer call's end state where the conv cannot write it directly: not aligned to its stores, or on part of the old one."""
+    B, L = 2, 70
+    if kind == "layer":
+        cfg = RomConfig("conv_places", 790, B, L, 64, 80, 16, 4, 8, 2, 1, "bf16", 0, weight_std=0.05)
+        layer, channels = RomLayer(cfg, make_weights(cfg)), 80
+        call = lambda x, before, out, after, ws: rom_layer_forward(layer.dims, layer.weights, x, B, L, before, None, out, after, None, ws)
+    else:
+        cfg = get_mamba2_config("m2_cfg2", batch=B, seq_len=L, d_model=256, d_inner=512)
+        layer, channels = RomMamba2Layer(cfg, make_mamba2_weights(cfg)), cfg.d_conv_ch
+        call = lambda x, before, out, after, ws: rom_mamba2_forward(layer.dims, layer.weights, x, B, L, 1e-5, before, None, out, after, None, ws)
+    x = layer.to_device((make_input if kind == "layer" else make_mamba2_input)(cfg)).view(B, L, -1)
+    n = B * channels * 3
+    buf = torch.randn(2 * n + 16, generator=torch.Generator(device="cuda").manual_seed(shift), device="cuda")
+    before, want, out, out2 = buf[:n].clone(), torch.empty(n, device="cuda"), torch.empty_like(x), torch.empty_like(x)
+    call(x, before, out, want, layer.workspace(B, L))
+    rest = buf.clone()
+    call(x, buf[:n] if shift > 16 else before, out2, buf[shift:shift + n], layer.workspace(B, L))
+    assert torch.equal(out, out2) and torch.equal(buf[shift:shift + n], want)
+    assert torch.equal(buf[:shift], rest[:shift]) and torch.equal(buf[shift + n:], rest[shift + n:])
