@@ -656,12 +656,15 @@ ROM_API const char *rom_strerror(int code);
 #define ROM_STAGE_PERMUTE   1  /* histogram, offsets, stable permutation              */
 #define ROM_STAGE_IN_PROJ   2  /* grouped GEMM, Eq. (10)/(11) (+ sum over k if K > 1)  */
 #define ROM_STAGE_CONV      3  /* causal depthwise conv + SiLU, Eq. (2)                */
-#define ROM_STAGE_X_PROJ    4  /* grouped GEMM dt_low | B | C                          */
-#define ROM_STAGE_DT_PROJ   5  /* grouped GEMM + bias + softplus                       */
+#define ROM_STAGE_X_PROJ    4  /* grouped GEMM dt_low | B | C (1)                      */
+#define ROM_STAGE_DT_PROJ   5  /* grouped GEMM + bias + softplus (1)                   */
 #define ROM_STAGE_SCAN      6  /* selective scan + D skip + SiLU(z) gating, Eq. (5)/(6) */
 #define ROM_STAGE_OUT_PROJ  7  /* grouped GEMM Eq. (13) (+ gate scaling if K == 1)     */
 #define ROM_STAGE_COMBINE   8  /* un-permute + gate-weighted sum, Eq. (12) (K > 1)     */
 #define ROM_STAGE_COUNT     9
+/* (1) bf16 calls of one step with K == 1, dt_rank a multiple of 8 up to 128 and B * d_inner * dt_rank <= 80 * 2^20 sum the x
+ *     projection's slices and form dt in the scan's launch: there the x projection is its products alone, the dt projection is a
+ *     stage that did not run, and both rests are part of ROM_STAGE_SCAN. */
 ROM_API int rom_profile_enable(int max_calls);
 /* Restricts the timing to the stages whose bit (1u << ROM_STAGE_*) is set; the default is all.  An
  * event between two kernels costs several microseconds of launch overlap, so a benchmark that

@@ -364,7 +364,7 @@ int forward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_t
   mark.end(ROM_STAGE_X_PROJ, s);
 
   // dt projection + bias + softplus
-  mark.begin(ROM_STAGE_DT_PROJ, s);
+  if (!tail) mark.begin(ROM_STAGE_DT_PROJ, s);
   memset(&ga, 0, sizeof(ga));
   ga.dtype = d->dtype;
   ga.A = at(p.dt_low); ga.lda = R; ga.a_span = N * R;
@@ -399,7 +399,7 @@ int forward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_t
     ga.bias = w->dt_bias; ga.softplus = 1;
     ROM_TRY(launch_grouped_gemm(ga, s));
   }
-  mark.end(ROM_STAGE_DT_PROJ, s);
+  if (!tail) mark.end(ROM_STAGE_DT_PROJ, s);
 
   // selective scan + D skip + SiLU(z) gate, Eq. (5), (6)
   mark.begin(ROM_STAGE_SCAN, s);

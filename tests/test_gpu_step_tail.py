@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2506_18145_amd import RomLayer
-from paper_2506_18145_amd.binding import rom_layer_forward
+from paper_2506_18145_amd.binding import STAGE_NAMES, rom_layer_forward, rom_profile_collect_calls, rom_profile_enable
 from rom_synth import RomConfig, make_input, make_weights
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +61,24 @@ def test_step_tail(B, d_inner, rank, E, top_k, shared):
     rom_layer_forward(layer.dims, layer.weights, x, B, 1, None, None, out, None, None, layer.workspace(B, 1))
     zero = layer.forward(x, torch.zeros_like(conv), torch.zeros_like(before))
     assert torch.equal(out, zero[0] if isinstance(zero, tuple) else zero)
+
+
+def test_stage_times():
+    """The dt projection is a stage that did not run where the scan's launch forms dt, and one that did elsewhere."""
+    cfg = RomConfig("tail_stages", 990, 4, 2, 64, 128, 16, 4, 32, 2, 1, "bf16", 0, weight_std=0.1)
+    layer = RomLayer(cfg, make_weights(cfg))
+    x = layer.to_device(make_input(cfg))
+    conv, ssm = torch.zeros(4, 128, 3, device="cuda"), torch.zeros(4, 128, 16, device="cuda")
+    layer.step(x[:, 0].contiguous(), conv, ssm)
+    layer.forward(x)
+    torch.cuda.synchronize()
+    rom_profile_enable(2)
+    try:
+        layer.step(x[:, 0].contiguous(), conv, ssm)
+        layer.forward(x)
+        step, two = rom_profile_collect_calls(2)
+    finally:
+        rom_profile_enable(0)
+    ran = [n for n in STAGE_NAMES if n != "combine"]           # K == 1
+    assert [n for n in STAGE_NAMES if two[n] > 0] == ran
+    assert [n for n in STAGE_NAMES if step[n] > 0] == [n for n in ran if n != "dt_proj"]
