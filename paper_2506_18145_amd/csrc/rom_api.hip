@@ -61,7 +61,7 @@ int check_dims(const rom_dims *d) {
   if (d->top_k < 1 || d->top_k > d->n_experts) return ROM_E_INVAL;
   if (d->n_experts_xdt != 1 && d->n_experts_xdt != d->n_experts) return ROM_E_INVAL;
   if (d->d_state != 16 || d->d_conv != 4) return ROM_E_UNSUPPORTED;
-  if (d->n_experts > 64 || d->top_k > 8) return ROM_E_UNSUPPORTED;
+  if (d->n_experts > kMaxExperts || d->top_k > 8) return ROM_E_UNSUPPORTED;
   if (d->d_inner % 16 != 0 || d->d_model % 8 != 0) return ROM_E_UNSUPPORTED;
   return ROM_OK;
 }
@@ -1202,7 +1202,7 @@ int check_mamba2_dims(const rom_mamba2_dims *d) {
   if (d->top_k < 1 || d->top_k > d->n_experts) return ROM_E_INVAL;
   if (d->d_inner % d->headdim != 0) return ROM_E_INVAL;
   if (d->dtype != ROM_DTYPE_BF16 || d->d_conv != 4 || !ssd_supported(d->d_state, d->headdim)) return ROM_E_UNSUPPORTED;
-  if (d->n_experts > 64 || d->top_k > 8) return ROM_E_UNSUPPORTED;
+  if (d->n_experts > kMaxExperts || d->top_k > 8) return ROM_E_UNSUPPORTED;
   if (d->d_inner % 512 != 0 || d->d_model % 8 != 0) return ROM_E_UNSUPPORTED;
   return ROM_OK;
 }
@@ -1359,7 +1359,7 @@ int check_gdn_dims(const rom_gdn_dims *d) {
   if (d->d_model <= 0 || d->n_heads <= 0 || d->d_k <= 0 || d->d_v <= 0 || d->n_experts <= 0) return ROM_E_INVAL;
   if (d->top_k < 1 || d->top_k > d->n_experts) return ROM_E_INVAL;
   if (d->dtype != ROM_DTYPE_BF16 || d->d_conv != 4 || !gdn_supported(d->d_k, d->d_v)) return ROM_E_UNSUPPORTED;
-  if (d->n_experts > 64 || d->top_k > 8) return ROM_E_UNSUPPORTED;
+  if (d->n_experts > kMaxExperts || d->top_k > 8) return ROM_E_UNSUPPORTED;
   if (d->n_heads % 4 != 0 || d->d_model % 8 != 0 || d->n_heads > 16384) return ROM_E_UNSUPPORTED;
   return ROM_OK;
 }

@@ -900,8 +900,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
   // ---- this workgroup's tiles
   // Lane e keeps where group e's tiles end, and the group's rows: finding a tile's group is a ballot, not a walk over the
-  // offsets in memory (at most 64 groups: gemm_tile).
+  // offsets in memory.
   const int n_tiles = (a.N + 255) / 256;
+  static_assert(kMaxExperts <= 64, "a group a lane");
   int m_tiles, grp_end, grp_lo, grp_hi;
   {
     const int e = threadIdx.x & 63;

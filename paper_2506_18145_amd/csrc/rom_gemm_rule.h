@@ -24,14 +24,12 @@ struct GemmShape {
 };
 
 constexpr int kStreamMinK = 320;          // its schedule needs five slabs
-constexpr int kStreamMaxGroups = 64;      // it keeps a group's rows in a lane (the entry points take up to 64 experts)
 
 // The times below are us on MI355X, plain or scaled bf16 output, experts drawn at random, kernel alone.
 inline GemmTile gemm_tile(const GemmShape &s) {
   const int groups = s.groups > 0 ? s.groups : 1;
   const int64_t rows = s.M / groups, cols = (s.N + 255) / 256;
   if (rows < 96) return GemmTile::kSkinny;
-  if (groups > kStreamMaxGroups && !s.f32_or_softplus) return GemmTile::k128;
   if (s.f32_or_softplus) {
     // fp32 output, 256 x 256 tiles against 128 x 128: too few to fill the CUs 16384 x 256 x 4096 (72 tiles) 77.7 / 65.0;
     // about one each 15373 x 1024 x 768 (256) 34.7 / 42.1; just above that, where the second round runs nearly empty,

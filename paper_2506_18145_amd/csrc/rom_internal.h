@@ -9,6 +9,7 @@
 
 namespace rom {
 
+constexpr int kMaxExperts = 64; // that the entry points take
 typedef unsigned short bf16_t;  // raw bf16 bit pattern
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) {

@@ -54,8 +54,8 @@ def tile(rule):
     (2720, 16, 3072, 768, "t128"), (2800, 16, 1536, 3072, "t128"), (2720, 16, 8192, 2048, "stream"),
     # no whole slabs
     (16384, 8, 4000, 1000, "t128"), (16384, 8, 2080, 520, "t128"),
-    # a group a lane
-    (40000, 64, 8192, 2048, "stream"), (40000, 65, 8192, 2048, "t128"),
+    # as many groups as there are lanes (the entry points take no more)
+    (40000, 64, 8192, 2048, "stream"),
     # the recurrent step
     (256, 8, 8192, 2048, "skinny"),
 ])
