@@ -1275,7 +1275,10 @@ __global__ __launch_bounds__(512) void wgrad_bf16_big_kernel(const bf16_t *__res
 // Bound by the power that the matrix pipe draws: without its stores a launch of 16384 rows x 8192 x 2048 in 8 experts takes
 // 450-470 us, with them 507-519 (601-574 with a tile per workgroup of eight wavefronts and both operands' stores at the
 // end); 2048 x 4096 329 -> 271 through row maps, 272 -> 263 without; 8192 rows, 4096 x 1024 100 -> 88, 1024 x 2048 53 -> 47.  Stores past
-// the caches: 549 us.  One held block instead of two makes no difference beyond 2 %.
+// the caches: 549 us.  One held block instead of two makes no difference beyond 2 %.  Matrix pipe busy 48-51 % (38-47 % before).
+// With half of 16384 rows on one of 8 experts 8192 x 2048 takes 510 us (even 525, a tile per workgroup 1966 and 672), but
+// 2048 x 4096 329 (even 275, 1047 and 355): its 128 tiles an expert are dealt to half of each XCD's CUs, and the large expert's
+// stay there.  With half of the slots on one of 16 experts 629 and 377 us (2453 and 1113).
 constexpr int kWdSlots = 5;
 constexpr int kWdSlotBytes = kWgSlab * kWgBig * 2;         // 64 positions x 256 columns x 2 bytes
 constexpr int kWdSmem = kWdSlots * kWdSlotBytes;           // 160 KiB

@@ -865,8 +865,9 @@ __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(cons
 // tile (32 slabs of 2420 cycles): a wavefront alone on its SIMD issues an instruction every five cycles, the L2 of an XCD
 // takes about 16 bytes a cycle from each of its CUs when all store at once, and a wait for a register that came from memory
 // drains the ring.  Hence: the stores spread over eight slabs, each covering 64 bytes of a row; everything else that a tile
-// needs (row numbers, scales, the place of a later tile, offsets) between MFMAs; nothing spilled.  91.9 k cycles a tile
-// (14.5 k more than its slabs) -> 84 k.  16384 rows in 8 even groups, against the same kernel without this: 8192 x 512
+// needs (row numbers, scales, the place of a later tile, offsets) between MFMAs; nothing spilled, but for one register with row
+// scale and skip.  91.9 k cycles a tile (14.5 k more than its slabs) -> 84 k; the matrix pipe is busy for 65 % of a launch of
+// 8192 columns x 2048 (56 % before) and 58 % of 2048 x 4096 (54 %).  16384 rows in 8 even groups, against the same kernel without this: 8192 x 512
 // 167 -> 139 us, x 1024 276 -> 248, x 2048 467 -> 445, 2048 x 4096 217 -> 209; SwiGLU 4096 x 1024 144 -> 131; contraction-major
 // 4096 x 2048 257 -> 245.
 // One workgroup of four wavefronts per CU (2 x 2, 128 x 128 each: 256 accumulator

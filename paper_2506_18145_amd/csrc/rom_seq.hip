@@ -137,9 +137,11 @@ template <> struct Quad<float> {
 // A thread owns four neighbouring channels and walks kRun consecutive time steps with the last three inputs in registers, so
 // every input row is read once (plus a 3-row halo per run); kConvBatch rows are requested before the first is used.
 // Bound by HBM where it is long (2 reads and writes of T per element: 16384 x 4096 bf16 50 us, 5.4 TB/s), else by one chain
-// of weights, history and rows, and launch.  Eight channels a thread, a row requested a step (us, before / now): 16384 x
-// 4096 55 / 50, 16384 x 6144 110 / 81, 3 x 1021 x 3072 20 / 10, 256 x 1 x 4096 11.2 / 7.8; with eight channels in batches
-// 54 / 93 / 15 / 11.8 (twice the registers, and the 48 bytes of state a lane has apart cost L1 half as many lines as 96).
+// of weights, history and rows, and launch.  Eight channels a thread, a row requested a step (us, before / now, the same buffers
+// again and again): 16384 x 4096 55 / 50, 16384 x 6144 110 / 81, 3 x 1021 x 3072 20 / 10, 256 x 1 x 4096 in runs of 32 11.2 / 7.8;
+// with eight channels in batches 54 / 93 / 15 / 11.8 (twice the registers, and the 48 bytes of state a lane has apart cost L1
+// half as many lines as 96).  Within a step over four layers' states in turn 256 x 1 x 4096 14.2 / 11.3, and 256 x 1 x 4352 of a
+// Mamba2 step, whose state comes from HBM, 14.5 / 14.5.
 constexpr int kConvBatch = 8;
 
 template <typename T, int kRun>
