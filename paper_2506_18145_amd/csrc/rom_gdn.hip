@@ -53,8 +53,8 @@ struct GdnPrepSmem {
 template <int NS, bool CARRY>
 struct GdnSmem {
   bf16_t kn[kQ][NS + 8];                  // normalised keys, step-major
-  bf16_t vt[kQ][kV + 8];                  // values, step-major
-  bf16_t kw_t[NS][kQ + 8];                // exp(cum_64 - cum_s) k_s, channel-major, 16-byte pieces swizzled
+  bf16_t vt[kQ][kV + 16];                 // values, step-major
+  bf16_t kw[kQ][NS + 16];                 // exp(cum_64 - cum_s) k_s, step-major
   bf16_t qr[CARRY ? 1 : kQ][NS + 8];      // raw queries, step-major
   float y[CARRY ? 1 : kQ][kV + 4];        // the output tile
   float ecum[kQ], beta[kQ], rq[kQ];
@@ -71,6 +71,13 @@ struct GdnOneSmem {
   GdnPrepSmem<NS> prep;
   u32x4_t frags[2 * kFrags * 64];
 };
+// Four rows x 16 columns of a step-major array in LDS per 16 lanes: lane i names row i / 4, columns 4 (i % 4) .. +3, and receives column
+// i of the four rows.  Rows of 32 bytes more than a multiple of 256 or 128 keep 32 lanes' pieces in different banks.
+__device__ __forceinline__ u32x2_t read_transposed(const bf16_t *at) {
+  typedef short i16x4_t __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+  return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)at));
+}
 __device__ __forceinline__ constexpr int frag_id(int tb, int k2) { return k2 == 0 ? tb : 2 + tb; }
 
 __device__ __forceinline__ float sum_sq8(const u32x4_t &v) {
@@ -309,39 +316,30 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
     }
   }
 
-  // roles while a chunk is parked: threads [0, NS) keys (8 x 8 blocks), the next 64 values; all: queries
-  const bool is_k = tid < NS;
-  const bool is_v = tid >= NS && tid < NS + 64;
-  const int lt = is_k ? tid : tid - NS;
-  const int n_co = is_k ? NS / 8 : kV / 8;
-  const int so = lt / n_co, co = lt % n_co;
-  const int t_col = is_k ? k_col + h * NS + 8 * co : v_col + h * kV + 8 * co;
   const int e_row = tid >> 3, e_po = tid & 7;
 
   // A chunk's inputs are requested one chunk ahead (rows beyond the end: the last valid row, zeroed
   // when parked): what the parking needs right after the chunk before has been parked, the gate rows
   // after the chunk before has been stored.
-  u32x4_t pv[8], pq[NS / 32], ez[2];
+  u32x4_t pk[NS / 32], pv[2], pq[NS / 32], ez[2];
   unsigned short p_b = 0, p_a = 0;
   auto fetch_main = [&](int64_t t0) {
     if (t0 >= te) return;
     const bf16_t *row = proj_b + (t0 + lane < te ? t0 + lane : te - 1) * ld_p;
     p_b = row[b_col + h];
     p_a = row[a_col + h];
-    if (is_k || is_v) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int64_t t = t0 + 8 * so + i;
-        pv[i] = *reinterpret_cast<const u32x4_t *>(qkv_b + (t < te ? t : te - 1) * ld_qkv + t_col);
-      }
+    for (int i = 0; i < NS / 32; ++i) {
+      const int piece = tid + 256 * i;
+      const int64_t t = t0 + piece / (NS / 8);
+      const bf16_t *src = qkv_b + (t < te ? t : te - 1) * ld_qkv + h * NS + 8 * (piece % (NS / 8));
+      pk[i] = *reinterpret_cast<const u32x4_t *>(src + k_col);
+      if (!CARRY) pq[i] = *reinterpret_cast<const u32x4_t *>(src + q_col);
     }
-    if (!CARRY) {
 #pragma unroll
-      for (int i = 0; i < NS / 32; ++i) {
-        const int piece = tid + 256 * i;
-        const int64_t t = t0 + piece / (NS / 8);
-        pq[i] = *reinterpret_cast<const u32x4_t *>(qkv_b + (t < te ? t : te - 1) * ld_qkv + q_col + h * NS + 8 * (piece % (NS / 8)));
-      }
+    for (int i = 0; i < 2; ++i) {
+      const int64_t t = t0 + e_row + 32 * i;
+      pv[i] = *reinterpret_cast<const u32x4_t *>(qkv_b + (t < te ? t : te - 1) * ld_qkv + v_col + h * kV + 8 * e_po);
     }
   };
   auto fetch_out = [&](int64_t t0) {
@@ -360,7 +358,7 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
     // The lane's coordinates go through an opaque copy every chunk: with them loop-invariant the compiler
     // hoists some two hundred addresses and mask predicates out of the loop and spills them.
     const int gq = opaque(g), cq = opaque(c);
-    const int soq = opaque(so), coq = opaque(co), sopq = soq ^ (coq & 7), erq = opaque(e_row), epq = opaque(e_po);
+    const int tq = opaque(tid), erq = opaque(e_row), epq = opaque(e_po);
     // per step: beta, log decay, cumulative log decay (every wavefront for itself, one step per lane)
     float beta = 0.0f, gl = 0.0f;
     if (t0 + lane < te) {
@@ -371,39 +369,31 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
     const float cum_last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cum), 63));
 
     __syncthreads();                // the chunk before this one is done with the LDS
-    if (is_k || is_v) {
+    // Pieces of 16 bytes, NS / 32 (keys, queries) and two (values) a thread: the NS / 8 lanes that hold a row sum its squares.  With
+    // a wavefront each for the keys and the values, a lane eight rows, this stood for half of a chunk's time.
+    const float w_lane = fast_exp2((cum_last - cum) * kLog2e);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (t0 + 8 * soq + i >= te) pv[i] = u32x4_t{0u, 0u, 0u, 0u};
-      if (is_k) {
-        // row norms: the n_co lanes with this `soq` hold the eight steps' other column blocks
-        const float w_lane = fast_exp2((cum_last - cum) * kLog2e);
-        // a row at a time (normalised copy out, decay-weighted copy kept packed), then the packed rows are
-        // transposed by byte permutes: few values live at once
-        u32x4_t kw[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float rk = rsqrtf(group_sum<NS / 8>(sum_sq8(pv[i])) + kL2Eps);
-          *reinterpret_cast<u32x4_t *>(&sm.kn[8 * soq + i][8 * coq]) = scale8(pv[i], rk);
-          kw[i] = scale8(pv[i], rk * __shfl(w_lane, 8 * soq + i));
-        }
-        park_8x8<kQ + 8>(kw, sm.kw_t, 8 * coq, 8 * sopq);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t *>(&sm.vt[8 * soq + i][8 * coq]) = pv[i];
-      }
-    }
-    if (!CARRY) {
-#pragma unroll
-      for (int i = 0; i < NS / 32; ++i) {           // queries: 64 rows of NS / 8 pieces, raw; their norms
-        const int piece = tid + 256 * i;
-        const int row = piece / (NS / 8), oc = piece % (NS / 8);
-        u32x4_t v = pq[i];
-        if (t0 + row >= te) v = u32x4_t{0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4_t *>(&sm.qr[row][8 * oc]) = v;
-        const float ss = group_sum<NS / 8>(sum_sq8(v));
+    for (int i = 0; i < NS / 32; ++i) {
+      const int piece = tq + 256 * i;
+      const int row = piece / (NS / 8), oc = piece % (NS / 8);
+      u32x4_t v = pk[i];
+      if (t0 + row >= te) v = u32x4_t{0u, 0u, 0u, 0u};
+      const float rk = rsqrtf(group_sum<NS / 8>(sum_sq8(v)) + kL2Eps);
+      *reinterpret_cast<u32x4_t *>(&sm.kn[row][8 * oc]) = scale8(v, rk);
+      *reinterpret_cast<u32x4_t *>(&sm.kw[row][8 * oc]) = scale8(v, rk * __shfl(w_lane, row));
+      if (!CARRY) {                                 // queries: raw, and their norms
+        u32x4_t q = pq[i];
+        if (t0 + row >= te) q = u32x4_t{0u, 0u, 0u, 0u};
+        *reinterpret_cast<u32x4_t *>(&sm.qr[row][8 * oc]) = q;
+        const float ss = group_sum<NS / 8>(sum_sq8(q));
         if (oc == 0) sm.rq[row] = rsqrtf(ss + kL2Eps) * q_scale;
       }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      u32x4_t v = pv[i];
+      if (t0 + erq + 32 * i >= te) v = u32x4_t{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4_t *>(&sm.vt[erq + 32 * i][8 * epq]) = v;
     }
     if (wave == 3) {
       sm.ecum[lane] = fast_exp2(cum * kLog2e);
@@ -443,9 +433,10 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
       }
       const f32x4_t e = *reinterpret_cast<const f32x4_t *>(&sm.ecum[16 * tb + 4 * gq]);
       const f32x4_t bt = *reinterpret_cast<const f32x4_t *>(&sm.beta[16 * tb + 4 * gq]);
+      const u32x2_t v4 = read_transposed(&sm.vt[16 * tb + 4 * gq + (cq >> 2)][16 * wave + 4 * (cq & 3)]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float vv = bf16_to_f32(sm.vt[16 * tb + 4 * gq + r][16 * wave + cq]);
+        const float vv = __uint_as_float(r & 1 ? v4[r / 2] & 0xFFFF0000u : v4[r / 2] << 16);
         rhs[0][tb][r] = bt[r] * (vv - e[r] * pacc[0][r]);    // beta_t (v_t - gamma_t S_0 k_t)
 #pragma unroll
         for (int grp = 1; grp < kG; ++grp) rhs[grp][tb][r] = -bt[r] * e[r] * pacc[grp][r];      // the same with v = 0
@@ -498,13 +489,11 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
         for (int grp = 0; grp < kG; ++grp)
 #pragma unroll
           for (int r = 0; r < 4; ++r) sacc[grp][nb][r] *= dec;
-        const int row = 16 * nb + cq, sw = (row >> 3) & 7;
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2) {
-          // steps 32 k2 + 4 gq .. +3 and 32 k2 + 16 + 4 gq .. +3 of the swizzled channel-major array
-          const int p_lo = (4 * k2 + (gq >> 1)) ^ sw, p_hi = (4 * k2 + 2 + (gq >> 1)) ^ sw;
-          const u32x2_t lo = *reinterpret_cast<const u32x2_t *>(&sm.kw_t[row][8 * p_lo + 4 * (gq & 1)]);
-          const u32x2_t hi = *reinterpret_cast<const u32x2_t *>(&sm.kw_t[row][8 * p_hi + 4 * (gq & 1)]);
+          // channel 16 nb + cq of steps 32 k2 + 4 gq .. +3 and 32 k2 + 16 + 4 gq .. +3
+          const bf16_t *at = &sm.kw[32 * k2 + 4 * gq + (cq >> 2)][16 * nb + 4 * (cq & 3)];
+          const u32x2_t lo = read_transposed(at), hi = read_transposed(at + 16 * (NS + 16));
           const bf16x8_t fw = frag_from_halves(lo, hi);
 #pragma unroll
           for (int grp = 0; grp < kG; ++grp)
