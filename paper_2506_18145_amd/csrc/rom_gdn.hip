@@ -64,12 +64,14 @@ struct GdnSmem {
 // lower triangular.  Fragment (tb, k2) covers rows 16 tb .. +15 and columns 32 k2 .. +31; the two that lie
 // above the diagonal do not exist.  Lane (g, c) owns row 16 tb + c, columns 32 k2 + 4 g .. +3 and 32 k2 + 16 + 4 g .. +3.
 constexpr int kFrags = 6;
-constexpr size_t kFragFloats = 2 * kFrags * 64 * 4;       // of one chunk, in floats
+// Behind them cum_t and beta_t of its 64 steps, fp32.
+constexpr int kChunkWords = 2 * kFrags * 64 + 2 * kQ / 4;  // of one chunk, in 16-byte words
+constexpr size_t kFragFloats = kChunkWords * 4;
 template <int NS>
 struct GdnOneSmem {
   GdnSmem<NS, false> main;
   GdnPrepSmem<NS> prep;
-  u32x4_t frags[2 * kFrags * 64];
+  u32x4_t frags[kChunkWords];
 };
 // Four rows x 16 columns of a step-major array in LDS per 16 lanes: lane i names row i / 4, columns 4 (i % 4) .. +3, and receives column
 // i of the four rows.  Rows of 32 bytes more than a multiple of 256 or 128 keep 32 lanes' pieces in different banks.
@@ -90,10 +92,17 @@ __device__ __forceinline__ float sum_sq8(const u32x4_t &v) {
   return s;
 }
 // sum over the WIDTH (8 or 16) consecutive lanes that share a row
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
 template <int WIDTH>
 __device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-  for (int off = 1; off < WIDTH; off <<= 1) v += __shfl_xor(v, off);
+  static_assert(WIDTH == 8 || WIDTH == 16, "mirrors of 8 and of 16 lanes");
+  v += dpp_of<0xB1>(v);                          // lane ^ 1
+  v += dpp_of<0x4E>(v);                          // lane ^ 2
+  v += dpp_of<0x141>(v);                         // lane 7 - i of its eight: from here on all of a half hold its sum
+  if constexpr (WIDTH == 16) v += dpp_of<0x140>(v);       // lane 15 - i
   return v;
 }
 
@@ -180,8 +189,12 @@ __device__ __forceinline__ void gdn_prep_chunk(GdnPrepSmem<NS> &sm, const bf16_t
     const float pb = bf16_to_f32(row[b_col + h]), pa = bf16_to_f32(row[a_col + h]);
     const float beta = live ? fast_rcp(1.0f + __expf(-pb)) : 0.0f;
     const float gl = live ? -__expf(A_log[h]) * softplus_f32(pa + dt_bias[h]) : 0.0f;
-    sm.cum[lane] = wave_inclusive_sum(gl);
+    const float cum = wave_inclusive_sum(gl);
+    sm.cum[lane] = cum;
     sm.beta[lane] = beta;
+    float *const tail = reinterpret_cast<float *>(out - lane + 2 * kFrags * 64);
+    tail[lane] = cum;
+    tail[kQ + lane] = beta;
   }
 #pragma unroll
   for (int i = 0; i < NS / 32; ++i) {
@@ -252,7 +265,7 @@ __global__ __launch_bounds__(256, NS == 64 ? 4 : 3) void gdn_prep_kernel(
   const int64_t bc = blockIdx.x / n_heads;
   const int64_t b = bc / n_chunks, chunk = bc % n_chunks;
   gdn_prep_chunk<NS>(sm, qkv + b * L * ld_qkv, ld_qkv, q_col, k_col, proj + b * L * ld_p, ld_p, b_col, a_col, dt_bias, A_log, L,
-                     chunk * kQ, h, frags + ((b * n_heads + h) * n_chunks + chunk) * (2 * kFrags * 64) + (threadIdx.x & 63));
+                     chunk * kQ, h, frags + ((b * n_heads + h) * n_chunks + chunk) * kChunkWords + (threadIdx.x & 63));
 }
 
 //   qkv   bf16 [B*L, ld_qkv] after conv + SiLU: q of head h at q_col + NS h, k at k_col + NS h, v at v_col + 64 h
@@ -285,7 +298,6 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
   const int seg = static_cast<int>(blockIdx.y % n_seg);
   if (CARRY && seg == n_seg - 1) return;            // nobody needs the last segment's carry
   const int64_t ts = seg * seg_len, te = ts + seg_len < L ? ts + seg_len : L;
-  const float rate = __expf(A_log[h]), bias = dt_bias[h];
   const bf16_t *qkv_b = qkv + b * L * ld_qkv;
   const bf16_t *proj_b = proj + b * L * ld_p;
   const float q_scale = rsqrtf(static_cast<float>(NS));
@@ -298,6 +310,7 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
   GdnOneSmem<NS> &one = *reinterpret_cast<GdnOneSmem<NS> *>(smem_raw);
   if constexpr (ONE)
     gdn_prep_chunk<NS>(one.prep, qkv_b, ld_qkv, q_col, k_col, proj_b, ld_p, b_col, a_col, dt_bias, A_log, L, 0, h, one.frags + lane);
+  if constexpr (ONE) __syncthreads();             // cum and beta are read before the loop's first barrier
 #pragma unroll
   for (int grp = 0; grp < kG; ++grp)
 #pragma unroll
@@ -322,12 +335,13 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
   // when parked): what the parking needs right after the chunk before has been parked, the gate rows
   // after the chunk before has been stored.
   u32x4_t pk[NS / 32], pv[2], pq[NS / 32], ez[2];
-  unsigned short p_b = 0, p_a = 0;
+  const u32x4_t *frag_ptr = ONE ? one.frags + lane : frags + ((b * n_heads + h) * n_chunks + ts / kQ) * kChunkWords + lane;
+  float p_cum = 0.0f, p_beta = 0.0f;
   auto fetch_main = [&](int64_t t0) {
     if (t0 >= te) return;
-    const bf16_t *row = proj_b + (t0 + lane < te ? t0 + lane : te - 1) * ld_p;
-    p_b = row[b_col + h];
-    p_a = row[a_col + h];
+    const float *const tail = reinterpret_cast<const float *>(frag_ptr - lane + 2 * kFrags * 64);     // frag_ptr: this chunk's
+    p_cum = tail[lane];
+    p_beta = tail[kQ + lane];
 #pragma unroll
     for (int i = 0; i < NS / 32; ++i) {
       const int piece = tid + 256 * i;
@@ -352,49 +366,55 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
   };
   fetch_main(ts);
   fetch_out(ts);
-  const u32x4_t *frag_ptr = ONE ? one.frags + lane : frags + ((b * n_heads + h) * n_chunks + ts / kQ) * (2 * kFrags * 64) + lane;
 
   for (int64_t t0 = ts; t0 < te; t0 += kQ) {
     // The lane's coordinates go through an opaque copy every chunk: with them loop-invariant the compiler
     // hoists some two hundred addresses and mask predicates out of the loop and spills them.
     const int gq = opaque(g), cq = opaque(c);
     const int tq = opaque(tid), erq = opaque(e_row), epq = opaque(e_po);
-    // per step: beta, log decay, cumulative log decay (every wavefront for itself, one step per lane)
-    float beta = 0.0f, gl = 0.0f;
-    if (t0 + lane < te) {
-      beta = fast_rcp(1.0f + __expf(-bf16_to_f32(p_b)));
-      gl = -rate * softplus_f32(bf16_to_f32(p_a) + bias);
-    }
-    const float cum = wave_inclusive_sum(gl);
+    // cumulative log decay and beta, one step per lane
+    const float cum = p_cum, beta = p_beta;
     const float cum_last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cum), 63));
 
+    // this chunk's T and G, wanted after the products with the state the chunk starts from: ahead of the next chunk's inputs, whose
+    // arrival the wait for them would include
+    u32x4_t tfr[kFrags], gfr[kFrags];
+#pragma unroll
+    for (int i = 0; i < kFrags; ++i) {
+      tfr[i] = frag_ptr[i * 64];
+      if (!CARRY) gfr[i] = frag_ptr[(kFrags + i) * 64];
+    }
+    frag_ptr += kChunkWords;
     __syncthreads();                // the chunk before this one is done with the LDS
     // Pieces of 16 bytes, NS / 32 (keys, queries) and two (values) a thread: the NS / 8 lanes that hold a row sum its squares.  With
     // a wavefront each for the keys and the values, a lane eight rows, this stood for half of a chunk's time.
     const float w_lane = fast_exp2((cum_last - cum) * kLog2e);
+    if (t0 + kQ > te) {
+      const int live = static_cast<int>(te - t0);
+#pragma unroll
+      for (int i = 0; i < NS / 32; ++i)
+        if ((tq + 256 * i) / (NS / 8) >= live) pk[i] = pq[i] = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (erq + 32 * i >= live) pv[i] = u32x4_t{0u, 0u, 0u, 0u};
+    }
 #pragma unroll
     for (int i = 0; i < NS / 32; ++i) {
       const int piece = tq + 256 * i;
       const int row = piece / (NS / 8), oc = piece % (NS / 8);
-      u32x4_t v = pk[i];
-      if (t0 + row >= te) v = u32x4_t{0u, 0u, 0u, 0u};
+      const u32x4_t v = pk[i];
       const float rk = rsqrtf(group_sum<NS / 8>(sum_sq8(v)) + kL2Eps);
       *reinterpret_cast<u32x4_t *>(&sm.kn[row][8 * oc]) = scale8(v, rk);
       *reinterpret_cast<u32x4_t *>(&sm.kw[row][8 * oc]) = scale8(v, rk * __shfl(w_lane, row));
       if (!CARRY) {                                 // queries: raw, and their norms
-        u32x4_t q = pq[i];
-        if (t0 + row >= te) q = u32x4_t{0u, 0u, 0u, 0u};
+        const u32x4_t q = pq[i];
         *reinterpret_cast<u32x4_t *>(&sm.qr[row][8 * oc]) = q;
         const float ss = group_sum<NS / 8>(sum_sq8(q));
         if (oc == 0) sm.rq[row] = rsqrtf(ss + kL2Eps) * q_scale;
       }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      u32x4_t v = pv[i];
-      if (t0 + erq + 32 * i >= te) v = u32x4_t{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4_t *>(&sm.vt[erq + 32 * i][8 * epq]) = v;
-    }
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4_t *>(&sm.vt[erq + 32 * i][8 * epq]) = pv[i];
     if (wave == 3) {
       sm.ecum[lane] = fast_exp2(cum * kLog2e);
       sm.beta[lane] = beta;
@@ -402,14 +422,6 @@ __global__ __launch_bounds__(256, CARRY && NS == 128 ? 1 : 2) void gdn_kernel(co
     __syncthreads();
     fetch_main(t0 + kQ);
 
-    // this chunk's T and G, wanted after the products with the state the chunk starts from
-    u32x4_t tfr[kFrags], gfr[kFrags];
-#pragma unroll
-    for (int i = 0; i < kFrags; ++i) {
-      tfr[i] = frag_ptr[i * 64];
-      if (!CARRY) gfr[i] = frag_ptr[(kFrags + i) * 64];
-    }
-    frag_ptr += 2 * kFrags * 64;
     bf16x8_t sop[kG][kKS];
 #pragma unroll
     for (int grp = 0; grp < kG; ++grp)
