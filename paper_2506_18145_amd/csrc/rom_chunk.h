@@ -1,5 +1,5 @@
 // Device helpers shared by the chunked recurrences on the matrix cores (rom_mamba2.hip, rom_gdn.hip):
-// packed-bf16 access, the wavefront prefix sum, 8 x 8 block transposes into LDS, MFMA operand fragments.
+// packed-bf16 access, the wavefront prefix sum, MFMA operand fragments.
 // gfx950 only.
 #pragma once
 
@@ -51,37 +51,11 @@ __device__ __forceinline__ u32x4_t scale8(const u32x4_t &v, float f) {
   for (int a = 0; a < 4; ++a) o[a] = pack_bf16x2(f * bf16_elem(v, 2 * a), f * bf16_elem(v, 2 * a + 1));
   return o;
 }
-// Eight 16-byte pieces (eight consecutive columns of eight consecutive steps), step i scaled by f[i],
-// to LDS column-major: for each of the eight columns the eight steps as one 16-byte row segment.
-template <int PITCH>
-__device__ __forceinline__ void park_scaled_8x8(const u32x4_t (&v)[8], const float (&f)[8], bf16_t (*dst)[PITCH], int col0,
-                                                int step0) {
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    u32x4_t seg;
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-      seg[a] = pack_bf16x2(f[2 * a] * bf16_elem(v[2 * a], m), f[2 * a + 1] * bf16_elem(v[2 * a + 1], m));
-    *reinterpret_cast<u32x4_t *>(&dst[col0 + m][step0]) = seg;
-  }
-}
-
-// eight 16-byte pieces (8 columns of 8 steps) -> column-major 16-byte segments: word a of column m's
-// segment holds steps 2a, 2a+1, which v_perm_b32 picks out of word m/2 of the two step rows
-template <int PITCH>
-__device__ __forceinline__ void park_8x8(const u32x4_t (&v)[8], bf16_t (*dst)[PITCH], int col0, int step0) {
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {          // word w of a piece = columns 2w, 2w+1
-    u32x4_t lo, hi;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const unsigned int p0 = v[2 * a][w], p1 = v[2 * a + 1][w];
-      lo[a] = __builtin_amdgcn_perm(p1, p0, 0x05040100u);      // (p0.lo16, p1.lo16)
-      hi[a] = __builtin_amdgcn_perm(p1, p0, 0x07060302u);      // (p0.hi16, p1.hi16)
-    }
-    *reinterpret_cast<u32x4_t *>(&dst[col0 + 2 * w][step0]) = lo;
-    *reinterpret_cast<u32x4_t *>(&dst[col0 + 2 * w + 1][step0]) = hi;
-  }
+// 2^v, formed here and now: a value that only some lanes keep would otherwise get a branch around it, four of them a block of scores
+__device__ __forceinline__ float exp2_here(float v) {
+  float e = fast_exp2(v);
+  asm volatile("" : "+v"(e));
+  return e;
 }
 
 __device__ __forceinline__ bf16x8_t as_frag(const u32x4_t &v) { return __builtin_bit_cast(bf16x8_t, v); }

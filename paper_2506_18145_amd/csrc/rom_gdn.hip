@@ -231,7 +231,7 @@ __device__ __forceinline__ void gdn_prep_chunk(GdnPrepSmem<NS> &sm, const bf16_t
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int s = 16 * sb + 4 * g + r, t = 16 * wave + c;
-        const float dec = s <= t ? fast_exp2((cum_t - cum_s[r]) * kLog2e) : 0.0f;
+        const float e = exp2_here(s <= t ? (cum_t - cum_s[r]) * kLog2e : 0.0f), dec = s <= t ? e : 0.0f;
         av[r] = s < t ? beta_t * dec * kk[r] : 0.0f;
         gv[r] = dec * qk[r];
       }

@@ -37,11 +37,26 @@ struct SsdSmem {
     float y[kQ][kP + 4];        // later in the chunk: the output tile, for row-wise stores
   } u;
   bf16_t c[kQ][NS + 8];         // C, step-major
-  bf16_t bw_t[NS][kQ + 8];      // exp(cum_Q - cum_s) dt_s B_s, state-major (operand of the state update)
-  bf16_t xd_t[kP][kQ + 8];      // x, channel-major
+  bf16_t bw[kQ][NS + 16];       // exp(cum_Q - cum_s) dt_s B_s, step-major, columns as read_steps wants them
+  bf16_t x[kQ][kP + 16];        // x, likewise
   bf16_t g[kQ][kQ + 8];         // masked, decayed, dt-weighted scores [t][s]
   float cum[kQ], ecum[kQ], dt[kQ];   // cum_t, exp(cum_t), dt_t
 };
+
+// The operands that are contracted over steps are step-major in LDS and come out of it through the transposing read: the 16 lanes
+// of group g name four rows of 32 bytes, lane c receives column c of them.  Groups 1 and 3 read rows 8 and 24 behind those of groups 0 and
+// 2: their columns are exchanged in blocks of `flip`, so that 32 lanes meet 64 different banks.
+template <int NC>
+__device__ __forceinline__ int flip_of(int row) { return ((row >> 3) & 1) * (NC == 128 ? 64 : 16); }
+template <int NC>
+__device__ __forceinline__ bf16x8_t read_steps(const bf16_t (*arr)[NC + 16], int k2, int block, int g, int c) {
+  typedef short i16x4_t __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+  const int row = 32 * k2 + 8 * g + (c >> 2), col = ((16 * block) ^ flip_of<NC>(8 * g)) + 4 * (c & 3);
+  const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)&arr[row][col]);
+  const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)&arr[row + 4][col]);
+  return frag_from_halves(__builtin_bit_cast(u32x2_t, lo), __builtin_bit_cast(u32x2_t, hi));
+}
 
 // Grid (n_heads, B * n_seg).  CARRY: the state-only pass (segments before the last one).
 //   xbc   bf16 [B*L, ld_xbc]: x of head h at columns x_col + 64 h, B at b_col, C at c_col (after conv + SiLU)
@@ -102,94 +117,77 @@ __global__ __launch_bounds__(256, 2) void ssd_kernel(const bf16_t *__restrict__ 
   }
   float log_decay_total = 0.0f;
 
-  // roles while a chunk is parked: threads [0, NS) transpose B, the next 64 transpose x
-  const bool is_b = tid < NS;
-  const bool is_x = tid >= NS && tid < NS + 64;
-  const int lt = is_b ? tid : tid - NS;
-  // eight steps 8 so .., eight columns 8 co ..; consecutive lanes take consecutive column blocks of
-  // the same steps (whole rows per request, and the step-major copy of B lands in distinct banks)
-  const int n_co = is_b ? NS / 8 : kP / 8;
-  const int so = lt / n_co, co = lt % n_co;
-  // The channel-major arrays keep their 16-byte step pieces in swizzled order: piece j of row r
-  // sits at position j ^ ((r >> 3) & 7), so that the eight lanes that write the same steps of eight
-  // different column blocks (rows 8 apart: the same banks otherwise) hit distinct banks.
-  const int so_phys = so ^ (co & 7);
-  const int t_col = is_b ? b_col + 8 * co : xc + 8 * co;
+  // While a chunk is parked a thread has pieces of 16 bytes: NS / 32 of B and of C, in rows p_row + i 256 / (NS / 8), and two of x, in rows
+  // x_row + 32 i.  (With two wavefronts for B, one for x, which transposed 8 x 8 blocks in registers, the fourth waited: 16384 steps,
+  // 64 heads of 128 states: main pass 220 us, carry 78.)
+  constexpr int kPer = NS / 32, kRows = 256 / (NS / 8);
+  const int p_row = tid / (NS / 8), p_col = tid % (NS / 8) * 8;
+  const int x_row = tid >> 3, x_piece = tid & 7;
   // output rows: a wavefront stores the 16 channels it computed, two 8-channel pieces per step
   const int e_row = lane >> 1, e_po = 2 * wave + (lane & 1);
 
   // A chunk's inputs are requested one chunk ahead (rows beyond the segment's end: the last valid
   // row, zeroed when parked - no branch around a load, so that the requests go out back to back):
   // what the parking needs right after the chunk before has been parked, what the output rows need
-  // (x for the D skip, z) after the chunk before has been stored.
-  u32x4_t pv[8], pc[NS / 32], ex[2], ez[2];
+  // (z) after the chunk before has been stored.  A row is a uniform base and one lane offset.
+  u32x4_t pb[kPer], pc[kPer], px[2], ez[2];
   unsigned short p_dt = 0;
-  // this thread's rows in the chunk to fetch next; the pointers advance by a chunk per fetch (no
-  // 64-bit multiplies per row), and only the segment's last, ragged chunk takes the clamped path
-  const bf16_t *dt_ptr = dt_b + (ts + lane) * ld_dt;
-  const bf16_t *pv_ptr = xbc_b + (ts + 8 * so) * ld_xbc + t_col;
-  const bf16_t *pc_ptr[NS / 32];
-#pragma unroll
-  for (int i = 0; i < NS / 32; ++i) {               // C: 64 rows of NS / 8 pieces
-    const int piece = tid + 256 * i;
-    pc_ptr[i] = xbc_b + (ts + piece / (NS / 8)) * ld_xbc + c_col + 8 * (piece % (NS / 8));
-  }
-  const bf16_t *ex_ptr = xbc_b + (ts + e_row) * ld_xbc + xc + 8 * e_po;
-  const bf16_t *ez_ptr = z + (b * L + ts + e_row) * ld_z + h * kP + 8 * e_po;
+  auto load16 = [](const bf16_t *base, unsigned off) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4_t *>(reinterpret_cast<const char *>(base) + off);
+  };
+  const auto bytes = [](int64_t row, int64_t ld, int col) { return static_cast<unsigned>((row * ld + col) * 2); };
+  const unsigned b_off = bytes(p_row, ld_xbc, p_col), x_off = bytes(x_row, ld_xbc, 8 * x_piece), z_off = bytes(e_row, ld_z, 8 * e_po);
+  const unsigned dt_off = bytes(lane, ld_dt, 0);
   auto fetch_main = [&](int64_t t0) {
     if (t0 >= te) return;
+    const bf16_t *const rows = xbc_b + t0 * ld_xbc;
+    const char *const dts = reinterpret_cast<const char *>(dt_b + t0 * ld_dt);
     if (t0 + kQ <= te) {
-      p_dt = *dt_ptr;
-      if (is_b || is_x) {
-        const bf16_t *row = pv_ptr;
+      p_dt = *reinterpret_cast<const unsigned short *>(dts + dt_off);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          pv[i] = *reinterpret_cast<const u32x4_t *>(row);
-          row += ld_xbc;
-        }
+      for (int i = 0; i < kPer; ++i) {
+        pb[i] = load16(rows + b_col + i * kRows * ld_xbc, b_off);
+        if (!CARRY) pc[i] = load16(rows + c_col + i * kRows * ld_xbc, b_off);
       }
-      if (!CARRY) {
 #pragma unroll
-        for (int i = 0; i < NS / 32; ++i) pc[i] = *reinterpret_cast<const u32x4_t *>(pc_ptr[i]);
-      }
+      for (int i = 0; i < 2; ++i) px[i] = load16(rows + xc + 32 * i * ld_xbc, x_off);
     } else {
-      const int64_t last = te - 1 - t0;               // last valid row of the chunk
-      p_dt = dt_ptr[(lane <= last ? 0 : last - lane) * ld_dt];
-      if (is_b || is_x) {
+      const int last = static_cast<int>(te - 1 - t0);               // last valid row of the chunk
+      const auto upto = [&](int r) { return r <= last ? r : last; };
+      p_dt = *reinterpret_cast<const unsigned short *>(dts + bytes(upto(lane), ld_dt, 0));
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int64_t r = 8 * so + i;
-          pv[i] = *reinterpret_cast<const u32x4_t *>(pv_ptr + (r <= last ? i : last - 8 * so) * ld_xbc);
-        }
+      for (int i = 0; i < kPer; ++i) {
+        const unsigned off = bytes(upto(p_row + i * kRows), ld_xbc, p_col);
+        pb[i] = load16(rows + b_col, off);
+        if (!CARRY) pc[i] = load16(rows + c_col, off);
       }
-      if (!CARRY) {
 #pragma unroll
-        for (int i = 0; i < NS / 32; ++i) {
-          const int64_t r = (tid + 256 * i) / (NS / 8);
-          pc[i] = *reinterpret_cast<const u32x4_t *>(pc_ptr[i] + (r <= last ? 0 : last - r) * ld_xbc);
-        }
-      }
+      for (int i = 0; i < 2; ++i) px[i] = load16(rows + xc, bytes(upto(x_row + 32 * i), ld_xbc, 8 * x_piece));
     }
-    dt_ptr += kQ * ld_dt;
-    pv_ptr += kQ * ld_xbc;
-#pragma unroll
-    for (int i = 0; i < NS / 32; ++i) pc_ptr[i] += kQ * ld_xbc;
   };
   auto fetch_out = [&](int64_t t0) {
     if (CARRY || t0 >= te) return;
-    const int64_t last = te - 1 - t0;
+    const bf16_t *const rows = z + (b * L + t0) * ld_z + h * kP;
+    if (t0 + kQ <= te) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int64_t r = e_row + 32 * i;
-      const int64_t back = r <= last ? r - e_row : last - e_row;      // rows relative to this thread's first
-      ex[i] = *reinterpret_cast<const u32x4_t *>(ex_ptr + back * ld_xbc);
-      ez[i] = *reinterpret_cast<const u32x4_t *>(ez_ptr + back * ld_z);
+      for (int i = 0; i < 2; ++i) ez[i] = load16(rows + 32 * i * ld_z, z_off);
+    } else {
+      const int last = static_cast<int>(te - 1 - t0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) ez[i] = load16(rows, bytes(e_row + 32 * i <= last ? e_row + 32 * i : last, ld_z, 8 * e_po));
     }
-    ex_ptr += kQ * ld_xbc;
-    ez_ptr += kQ * ld_z;
   };
   fetch_main(ts);
   fetch_out(ts);
+  // Scores on and below the diagonal, in blocks of 16 x 16 (row block 4 t + column block s a nibble), three for wavefronts 0 and 1, two for 2
+  // and 3.  Of the others the products read (0, 1) and (2, 3) only: zero for good.
+  constexpr uint64_t kBlocks = 0x0FA098E54DC0ull;
+  const int n_blocks = wave < 2 ? 3 : 2;
+  if (!CARRY) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (wave < 2) sm.g[32 * wave + c][32 * wave + 16 + 4 * g + r] = 0;
+  }
 
   for (int64_t t0 = ts; t0 < te; t0 += kQ) {
     // time steps of the chunk, one per lane (every wavefront computes them for itself)
@@ -200,34 +198,35 @@ __global__ __launch_bounds__(256, 2) void ssd_kernel(const bf16_t *__restrict__ 
     log_decay_total += cum_last;
 
     __syncthreads();                // the chunk before this one is done with the LDS
-    if (is_b || is_x) {
+    if (t0 + kQ > te) {
+      const int live = static_cast<int>(te - t0);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (t0 + 8 * so + i >= te) pv[i] = u32x4_t{0u, 0u, 0u, 0u};
-      if (is_b) {
-        // this lane's weight w_s = exp(cum_Q - cum_s) dt_s; the eight steps of the block come from their lanes
-        const float w_lane = fast_exp2((cum_last - cum) * kLog2e) * dtv;
-        float f[8];
+      for (int i = 0; i < kPer; ++i)
+        if (p_row + i * kRows >= live) pb[i] = pc[i] = u32x4_t{0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = __shfl(w_lane, 8 * so + i);
+      for (int i = 0; i < 2; ++i)
+        if (x_row + 32 * i >= live) px[i] = u32x4_t{0u, 0u, 0u, 0u};
+    }
+    {
+      // weight w_s = exp(cum_Q - cum_s) dt_s of step `lane`; the pieces' steps come from their lanes
+      const float w_lane = fast_exp2((cum_last - cum) * kLog2e) * dtv;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int row = p_row + i * kRows;
+        *reinterpret_cast<u32x4_t *>(&sm.bw[row][p_col ^ flip_of<NS>(row)]) = scale8(pb[i], __shfl(w_lane, row));
         if (!CARRY) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t *>(&sm.u.b[8 * so + i][8 * co]) = pv[i];
+          *reinterpret_cast<u32x4_t *>(&sm.u.b[row][p_col]) = pb[i];
+          *reinterpret_cast<u32x4_t *>(&sm.c[row][p_col]) = pc[i];
         }
-        park_scaled_8x8<kQ + 8>(pv, f, sm.bw_t, 8 * co, 8 * so_phys);
-      } else {
-        park_8x8<kQ + 8>(pv, sm.xd_t, 8 * co, 8 * so_phys);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = x_row + 32 * i;
+        *reinterpret_cast<u32x4_t *>(&sm.x[row][(8 * x_piece) ^ flip_of<kP>(row)]) = px[i];
       }
     }
     if (!CARRY) {
-#pragma unroll
-      for (int i = 0; i < NS / 32; ++i) {
-        const int piece = tid + 256 * i;
-        const int row = piece / (NS / 8);
-        if (t0 + row >= te) pc[i] = u32x4_t{0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4_t *>(&sm.c[row][8 * (piece % (NS / 8))]) = pc[i];
-      }
-      if (wave == 3) {                // the wavefront with no block to transpose
+      if (wave == 3) {
         sm.cum[lane] = cum;
         sm.ecum[lane] = fast_exp2(cum * kLog2e);
         sm.dt[lane] = dtv;
@@ -238,30 +237,31 @@ __global__ __launch_bounds__(256, 2) void ssd_kernel(const bf16_t *__restrict__ 
 
     f32x4_t yacc[4];
     if (!CARRY) {
-      // scores, this wavefront's 16 steps t = 16 wave + c against all s: G^T[s][t] = B_s . C_t, then the
+      // scores, steps t = 16 tb + c against s = 16 sb + 4 g ..: G^T[s][t] = B_s . C_t, then the
       // causal mask, the decay exp(cum_t - cum_s) and the step size dt_s; stored [t][s]
-      const float cum_t = sm.cum[16 * wave + c];
 #pragma unroll
-      for (int sb = 0; sb < 4; ++sb) {
+      for (int j = 0; j < 3; ++j) {
+        if (j >= n_blocks) break;
+        const int block = static_cast<int>(kBlocks >> (4 * (3 * wave + j))) & 15, tb = block >> 2, sb = block & 3;
         f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (sb <= wave) {
 #pragma unroll
-          for (int ks = 0; ks < kKS; ++ks) {
-            const bf16x8_t fa = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.b[16 * sb + c][32 * ks + 8 * g]));
-            const bf16x8_t fb = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.c[16 * wave + c][32 * ks + 8 * g]));
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
-          }
+        for (int ks = 0; ks < kKS; ++ks) {
+          const bf16x8_t fa = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.u.b[16 * sb + c][32 * ks + 8 * g]));
+          const bf16x8_t fb = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.c[16 * tb + c][32 * ks + 8 * g]));
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
         }
+        const float cum_t = sm.cum[16 * tb + c];
         const f32x4_t cum_s = *reinterpret_cast<const f32x4_t *>(&sm.cum[16 * sb + 4 * g]);
         const f32x4_t dt_s = *reinterpret_cast<const f32x4_t *>(&sm.dt[16 * sb + 4 * g]);
         float val[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int s = 16 * sb + 4 * g + r, t = 16 * wave + c;
-          val[r] = s <= t ? acc[r] * dt_s[r] * fast_exp2((cum_t - cum_s[r]) * kLog2e) : 0.0f;
+          const int s = 16 * sb + 4 * g + r, t = 16 * tb + c;
+          const float dec = exp2_here(s <= t ? (cum_t - cum_s[r]) * kLog2e : 0.0f);
+          val[r] = s <= t ? acc[r] * dt_s[r] * dec : 0.0f;
         }
         const u32x2_t packed = {pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])};
-        *reinterpret_cast<u32x2_t *>(&sm.g[16 * wave + c][16 * sb + 4 * g]) = packed;
+        *reinterpret_cast<u32x2_t *>(&sm.g[16 * tb + c][16 * sb + 4 * g]) = packed;
       }
       // contribution of the state the chunk starts from: Y[t][p] = exp(cum_t) sum_n C[t][n] H[n][p].
       // The accumulators are the B operand as they are: slot (g, e) of a 32-wide step holds
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(256, 2) void ssd_kernel(const bf16_t *__restrict__ 
     bf16x8_t xop[2];
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2)
-      xop[k2] = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.xd_t[16 * wave + c][8 * ((4 * k2 + g) ^ ((2 * wave + (c >> 3)) & 7))]));
+      xop[k2] = read_steps<kP>(sm.x, k2, wave, g, c);
     if (!CARRY) {
       // inside the chunk: Y[t][p] += sum_{s <= t} G[t][s] x_s[p]; steps 32.. only reach t >= 32
 #pragma unroll
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256, 2) void ssd_kernel(const bf16_t *__restrict__ 
         for (int r = 0; r < 4; ++r) hacc[nb][r] *= dec;
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2) {
-          const bf16x8_t fa = as_frag(*reinterpret_cast<const u32x4_t *>(&sm.bw_t[16 * nb + c][8 * ((4 * k2 + g) ^ ((2 * nb + (c >> 3)) & 7))]));
+          const bf16x8_t fa = read_steps<NS>(sm.bw, k2, nb, g, c);
           hacc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, xop[k2], hacc[nb], 0, 0, 0);
         }
       }
@@ -335,10 +335,11 @@ __global__ __launch_bounds__(256, 2) void ssd_kernel(const bf16_t *__restrict__ 
         const int64_t t = t0 + row;
         const f32x4_t y0 = *reinterpret_cast<const f32x4_t *>(&sm.u.y[row][8 * e_po]);
         const f32x4_t y1 = *reinterpret_cast<const f32x4_t *>(&sm.u.y[row][8 * e_po + 4]);
+        const u32x4_t xv = *reinterpret_cast<const u32x4_t *>(&sm.x[row][(8 * e_po) ^ flip_of<kP>(row)]);
         float o[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
-          const float yv = (m < 4 ? y0[m & 3] : y1[m & 3]) + d_skip * bf16_elem(ex[i], m);
+          const float yv = (m < 4 ? y0[m & 3] : y1[m & 3]) + d_skip * bf16_elem(xv, m);
           o[m] = yv * silu_f32(bf16_elem(ez[i], m));
         }
         const u32x4_t ov = {pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
