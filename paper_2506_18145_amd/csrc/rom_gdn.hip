@@ -192,9 +192,6 @@ __device__ __forceinline__ void gdn_prep_chunk(GdnPrepSmem<NS> &sm, const bf16_t
     const float cum = wave_inclusive_sum(gl);
     sm.cum[lane] = cum;
     sm.beta[lane] = beta;
-    float *const tail = reinterpret_cast<float *>(out - lane + 2 * kFrags * 64);
-    tail[lane] = cum;
-    tail[kQ + lane] = beta;
   }
 #pragma unroll
   for (int i = 0; i < NS / 32; ++i) {
@@ -209,9 +206,9 @@ __device__ __forceinline__ void gdn_prep_chunk(GdnPrepSmem<NS> &sm, const bf16_t
 
   // scores of this wavefront's 16 steps t = 16 wave + c against all s <= t, computed transposed: a lane's
   // values of G are the row segment that its fragments hold
+  u32x2_t gpk[4];
   {
     const float cum_t = sm.cum[16 * wave + c], beta_t = sm.beta[16 * wave + c];
-    u32x2_t gpk[4];
 #pragma unroll
     for (int sb = 0; sb < 4; ++sb) {
       f32x4_t kk = {0.0f, 0.0f, 0.0f, 0.0f}, qk = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -238,12 +235,17 @@ __device__ __forceinline__ void gdn_prep_chunk(GdnPrepSmem<NS> &sm, const bf16_t
       *reinterpret_cast<f32x4_t *>(&sm.am[16 * wave + c][16 * sb + 4 * g]) = av;
       gpk[sb] = u32x2_t{pack_bf16x2(gv[0], gv[1]), pack_bf16x2(gv[2], gv[3])};
     }
-    out[(kFrags + frag_id(wave, 0)) * 64] = u32x4_t{gpk[0][0], gpk[0][1], gpk[1][0], gpk[1][1]};
-    if (wave >= 2) out[(kFrags + frag_id(wave, 1)) * 64] = u32x4_t{gpk[2][0], gpk[2][1], gpk[3][0], gpk[3][1]};
   }
   __syncthreads();                // A is complete; the step-major keys and queries are no longer read
   invert_unit_lower(sm.am, sm.u.tm, lane, wave);
 
+  out[(kFrags + frag_id(wave, 0)) * 64] = u32x4_t{gpk[0][0], gpk[0][1], gpk[1][0], gpk[1][1]};
+  if (wave >= 2) out[(kFrags + frag_id(wave, 1)) * 64] = u32x4_t{gpk[2][0], gpk[2][1], gpk[3][0], gpk[3][1]};
+  if (wave == 3) {
+    float *const tail = reinterpret_cast<float *>(out - lane + 2 * kFrags * 64);
+    tail[lane] = sm.cum[lane];
+    tail[kQ + lane] = sm.beta[lane];
+  }
 #pragma unroll
   for (int k2 = 0; k2 < 2; ++k2) {
     if (k2 == 1 && wave < 2) break;
