@@ -769,10 +769,11 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_dma_kernel(const GemmAr
 // the step took 55 us through twelve layers in turn with this kernel, 47 (91) with one layer whose expert the last step has
 // just read; 36 since the launches behind the x projection are one (step_tail_kernel).
 constexpr int kFewWideCols = 4096;
-constexpr int kFewWaves = 8, kFewUnits = 4;
+constexpr int kFewWaves = 8;
 typedef float f32x4_few_t __attribute__((ext_vector_type(4)));
 
-template <int CT, int EPI>
+// UNITS: 64-wide units that a wavefront requests together.
+template <int CT, int EPI, int UNITS>
 __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(const GemmArgs a) {
   __shared__ float red[kFewWaves][CT][16][20];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -804,10 +805,10 @@ __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(cons
   f32x4_few_t acc[CT];
 #pragma unroll
   for (int t = 0; t < CT; ++t) acc[t] = f32x4_few_t{0.0f, 0.0f, 0.0f, 0.0f};
-  for (int u0 = wave; u0 < units; u0 += kFewWaves * kFewUnits) {
-    bf16x8_t fw[kFewUnits][CT][2], fx[kFewUnits][2];
+  for (int u0 = wave; u0 < units; u0 += kFewWaves * UNITS) {
+    bf16x8_t fw[UNITS][CT][2], fx[UNITS][2];
 #pragma unroll
-    for (int i = 0; i < kFewUnits; ++i) {
+    for (int i = 0; i < UNITS; ++i) {
       const int u = u0 + i * kFewWaves < units ? u0 + i * kFewWaves : u0;      // past the end: re-read, not multiplied
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -818,7 +819,7 @@ __global__ __launch_bounds__(kFewWaves * 64) void gemm_bf16_few_rows_kernel(cons
     }
     __builtin_amdgcn_sched_barrier(0);                         // all requests ahead of the first wait
 #pragma unroll
-    for (int i = 0; i < kFewUnits; ++i) {
+    for (int i = 0; i < UNITS; ++i) {
       if (u0 + i * kFewWaves < units) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -1828,16 +1829,18 @@ inline bool few_rows_takes(const GemmArgs &a) {
   return !a.w_kmajor && gemm_few_rows(a.M, a.offsets ? a.n_groups : 1, a.N, a.K);
 }
 
+template <int CT, int EPI>
+hipError_t launch_few_rows_cols(const GemmArgs &a, hipStream_t s) {
+  const unsigned gz = static_cast<unsigned>(!a.offsets ? 1 : a.M < a.n_groups ? a.M : a.n_groups);
+  const dim3 grid(static_cast<unsigned>(ceil_div(a.N, 16 * CT)), a.k_splits, gz), block(kFewWaves * 64);
+  // a wavefront's whole share of K at once where that is up to eight units
+  if (a.k_per_split > kFewWaves * 4 * 64) hipLaunchKernelGGL((gemm_bf16_few_rows_kernel<CT, EPI, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_bf16_few_rows_kernel<CT, EPI, 4>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
 template <int EPI>
 hipError_t launch_few_rows(const GemmArgs &a, hipStream_t s) {
-  const unsigned gz = static_cast<unsigned>(!a.offsets ? 1 : a.M < a.n_groups ? a.M : a.n_groups);
-  if (a.N >= kFewWideCols)
-    hipLaunchKernelGGL((gemm_bf16_few_rows_kernel<2, EPI>), dim3(static_cast<unsigned>(ceil_div(a.N, 32)), a.k_splits, gz),
-                       dim3(kFewWaves * 64), 0, s, a);
-  else
-    hipLaunchKernelGGL((gemm_bf16_few_rows_kernel<1, EPI>), dim3(static_cast<unsigned>(ceil_div(a.N, 16)), a.k_splits, gz),
-                       dim3(kFewWaves * 64), 0, s, a);
-  return hipGetLastError();
+  return a.N >= kFewWideCols ? launch_few_rows_cols<2, EPI>(a, s) : launch_few_rows_cols<1, EPI>(a, s);
 }
 
 template <int EPI>

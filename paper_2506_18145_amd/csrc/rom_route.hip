@@ -16,28 +16,36 @@ constexpr int kWave = 64;
 
 // Wave-wide reductions that leave the result in every lane: the four steps inside a row of 16
 // lanes are DPP operands of the add / max itself (no LDS crossbar, no extra instruction), the two
-// steps across rows go through the permute network.  Any lane order gives the same maximum; the
+// steps across rows exchange rows between two copies (permlane swaps: a vector instruction where a shuffle is an LDS round trip).  Any lane order gives the same maximum; the
 // sum is the same in every lane because every step adds the same two partial sums in both partners.
 template <int CTRL> __device__ __forceinline__ float dpp_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float swap_sum16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_sum32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<0xB1>(v);      // quad_perm [1,0,3,2]
   v += dpp_f<0x4E>(v);      // quad_perm [2,3,0,1]
   v += dpp_f<0x141>(v);     // row_half_mirror: quads 0 <-> 1, 2 <-> 3
   v += dpp_f<0x140>(v);     // row_mirror: halves of the row
-  v += __shfl_xor(v, 16, kWave);
-  v += __shfl_xor(v, 32, kWave);
-  return v;
+  v = swap_sum16(v);
+  return swap_sum32(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp_f<0xB1>(v));
   v = fmaxf(v, dpp_f<0x4E>(v));
   v = fmaxf(v, dpp_f<0x141>(v));
   v = fmaxf(v, dpp_f<0x140>(v));
-  v = fmaxf(v, __shfl_xor(v, 16, kWave));
-  v = fmaxf(v, __shfl_xor(v, 32, kWave));
-  return v;
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 template <typename T> struct Vec8;  // 8 consecutive elements
@@ -238,7 +246,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(
       unsigned long long hit = __ballot(cand && mine == best);
       if (hit == 0ull) hit = __ballot(cand);
       const int e_sel = __ffsll(static_cast<long long>(hit)) - 1;   // lowest index wins ties
-      const float p_sel = __shfl(p_un, e_sel, kWave);
+      const float p_sel = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p_un), e_sel));
       picked_sum += p_sel;
       if (lane == k) { my_pick = e_sel; my_gate = p_sel; }
       if (lane == e_sel) picked = true;
@@ -580,8 +588,46 @@ __global__ __launch_bounds__(kSortBlock) void scatter_kernel(
   tok_of_pos[static_cast<int64_t>(blockIdx.y) * n_items + pos] = static_cast<int32_t>(s / tok_div);
 }
 
-// Whole grouping in one workgroup for small slot counts (decode steps): three passes over the
-// slots in rounds of 256, counts and running bases in LDS.
+// Whole grouping in one workgroup for at most as many slots as it has threads (decode steps): one barrier, after which lane e of every
+// wavefront has expert e's counts, place and the rank its wavefront's slots start from.  256 slots 4.7 us in the rounds below.
+__global__ __launch_bounds__(kSortBlock) void permutation_round_kernel(
+    const int32_t *__restrict__ expert_idx, int n_slots, int n_experts, int top_k,
+    int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ perm,
+    int32_t *__restrict__ inv_perm, int32_t *__restrict__ tok_of_pos) {
+  __shared__ int cnt[kSortWaves][64];
+  const int s = threadIdx.x, lane = s & (kWave - 1), wave = s / kWave;
+  const int key = s < n_slots ? expert_idx[s] : -1;
+  const unsigned long long same = match_expert(key, n_experts, lane, cnt[wave]);
+  __syncthreads();
+  int total = 0, before = 0;
+  if (lane < n_experts) {
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+      const int c = cnt[w][lane];
+      total += c;
+      if (w < wave) before += c;
+    }
+  }
+  int end = total;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int up = __shfl_up(end, d, kWave);
+    if (lane >= d) end += up;
+  }
+  const int first = __shfl(end - total + before, key >= 0 && key < n_experts ? key : 0, kWave);
+  if (wave == 0 && lane < n_experts) {
+    counts[lane] = total;
+    offsets[lane] = end - total;
+    if (lane == n_experts - 1) offsets[n_experts] = end;
+  }
+  if (key < 0 || key >= n_experts) return;
+  const int pos = first + __popcll(same & ((1ull << lane) - 1ull));
+  inv_perm[s] = pos;
+  perm[pos] = s;
+  tok_of_pos[pos] = s / top_k;
+}
+
+// The same for some more slots: three passes over them in rounds of 256, counts and running bases in LDS.
 __global__ __launch_bounds__(kSortBlock) void permutation_small_kernel(
     const int32_t *__restrict__ expert_idx, int n_slots, int n_experts, int top_k,
     int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ perm,
@@ -821,6 +867,11 @@ hipError_t launch_balance_stats(const float *logits, const int32_t *counts, int6
 hipError_t launch_permutation(const int32_t *expert_idx, int64_t n_slots, int n_experts, int top_k,
                               int32_t *block_counts, int32_t *counts, int32_t *offsets,
                               int32_t *perm, int32_t *inv_perm, int32_t *tok_of_pos, hipStream_t s) {
+  if (n_slots <= kSortBlock) {
+    hipLaunchKernelGGL(permutation_round_kernel, dim3(1), dim3(kSortBlock), 0, s, expert_idx, static_cast<int>(n_slots), n_experts,
+                       top_k, counts, offsets, perm, inv_perm, tok_of_pos);
+    return hipGetLastError();
+  }
   if (n_slots <= 2048) {
     hipLaunchKernelGGL(permutation_small_kernel, dim3(1), dim3(kSortBlock), 0, s, expert_idx,
                        static_cast<int>(n_slots), n_experts, top_k, counts, offsets, perm, inv_perm, tok_of_pos);
