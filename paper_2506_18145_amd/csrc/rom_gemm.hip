@@ -1404,16 +1404,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, short inner dimension
-// For K <= 128 (the dt projection: K = dt_rank) there is no K loop to pipeline: a tile of the
-// general kernel is one load, a few MFMAs and a long epilogue in sequence, and the epilogue
+// For a K of up to ten 16-wide steps (the dt projection, K = dt_rank, and its input gradient, dt_rank + 32) there is no K loop to
+// pipeline: a tile of the general kernel is one load, a few MFMAs and a long epilogue in sequence, and the epilogue
 // (bias + softplus, two transcendentals per element) is bound by plain ALU issue, which needs
 // about four wavefronts per SIMD to run at full rate.  Here a workgroup of eight waves keeps its
 // 128-column slice of W (all of K) and of the bias in LDS and the waves stream 32-row sub-tiles of
 // A past it: A fragments come straight from global memory into registers, each 32x64 half of the
 // result goes through bias + softplus into the wave's own LDS patch and leaves as whole 128-byte
 // row segments.  No workgroup barrier after the W load; registers are capped at 128 so that two
-// workgroups (16 waves) share a CU.
-constexpr int kSkBM = 512, kSkBN = 128, kSkWaves = 8;
+// workgroups (16 waves) share a CU.  There are just two workgroups a CU, each with an equal run of the rows for its slice: with one per 512
+// rows, two sub-tiles a wave paid for each load of W and the last of 2.5 rounds left the chip half empty (16384 x 4096 x 128 in 8
+// groups 58 -> 50 us, without softplus 50 -> 37, 2048 x 64 32 -> 26).  RES reads whole row pieces ahead of the products (113 -> 67; eight
+// bytes a lane where the sums lie had every line of the output asked for eight times).
+// What a group costs a workgroup besides its rows (weights, a fresh start), in sub-tiles: 15 of 16 groups with 64 of 16384 rows, one
+// with the rest, 16384 x 4096 x 128 in us at 0 / 1 / 3 / 8: 71 / 61 / 52 / 55; even groups 48 at each.
+constexpr int kSkGroup = 3;
+constexpr int kSkBN = 128, kSkWaves = 8, kSkWgs = 512;     // two workgroups a CU
+__host__ __device__ inline int64_t smallk_most(int64_t rows, int groups) { return rows / 32 + (groups > 0 ? groups : 1); }   // sub-tiles, at most
 
 // PLAIN: no bias, no softplus.  RES: the rows of a.residual (the output's layout and row map) are
 // added to the sums before bias and activation: the passes of K > 1 accumulate into the output,
@@ -1422,50 +1429,92 @@ template <int KSTEPS, bool PLAIN, bool RES = false>
 __global__ __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void gemm_bf16_smallk_kernel(const GemmArgs a) {
   constexpr int KC = KSTEPS * 2;                       // 16-byte chunks per row of A / W
-  static_assert(KC == 4 || KC == 8 || KC == 16, "K must be 32, 64 or 128");
-  constexpr int kSwzShift = KC == 16 ? 0 : (KC == 8 ? 1 : 2);   // 16 consecutive rows -> 16 distinct 16-byte banks
+  static_assert(KSTEPS >= 2 && KSTEPS <= 10, "W and two workgroups' patches in 160 KiB, A in 128 registers");
+  constexpr int kWPitch = KC + 1;                      // an odd number of chunks: 16 consecutive rows -> 16 distinct 16-byte banks
   constexpr int kHalf = kSkBN / 2;                     // columns per pass over the accumulators
   constexpr int kPitch = kHalf * 2 + 16;               // bytes per staged output row; the pad holds its C row index
 
   extern __shared__ __attribute__((aligned(16))) uint4 smem[];
-  const TileCoord tc = locate_tile(a, kSkBM, kSkBN);
-  if (!tc.valid) return;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bf16_t *Ap = static_cast<const bf16_t *>(a.A);
-  const bf16_t *Wp = static_cast<const bf16_t *>(a.W) + static_cast<int64_t>(tc.group) * a.N * a.K;
-  uint4 *Ws = smem;                                                        // [128][KC], swizzled
-  float *bias_s = reinterpret_cast<float *>(smem + kSkBN * KC);            // [128]
-  char *stage = reinterpret_cast<char *>(bias_s + kSkBN) + wave * (32 * kPitch);
-
-  for (int q = tid; q < kSkBN * KC; q += kSkWaves * 64) {
-    const int r = q / KC, c = q % KC;
-    const int n = (tc.n0 + r < a.N) ? tc.n0 + r : a.N - 1;
-    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(Wp + static_cast<int64_t>(n) * a.K + c * 8);
-    Ws[r * KC + (c ^ ((r >> kSwzShift) & (KC - 1)))] = make_uint4(v.x, v.y, v.z, v.w);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // this workgroup's column slice and its run of the sub-tiles (32 rows of one group); an XCD has neighbouring runs for all slices
+  const int n_slices = (a.N + kSkBN - 1) / kSkBN, runs = gridDim.x / n_slices;
+  int t = blockIdx.x;
+  if (gridDim.x % 8 == 0) t = (t % 8) * (gridDim.x / 8) + t / 8;
+  const int n0 = t % n_slices * kSkBN, run = t / n_slices;
+  const int per_group = runs < smallk_most(a.M, a.n_groups) ? kSkGroup : 0;         // (else each sub-tile has a workgroup)
+  int grp_lo, grp_hi, grp_end;       // lane e: group e's rows, and where it ends in sub-tiles, per_group more for each group that has rows
+  {
+    const bool have = a.offsets != nullptr && lane < a.n_groups;
+    grp_lo = have ? a.offsets[lane] : 0;
+    grp_hi = have ? a.offsets[lane + 1] : a.offsets == nullptr && lane == 0 ? static_cast<int>(a.M) : 0;
+    grp_end = grp_hi > grp_lo ? (grp_hi - grp_lo + 31) / 32 + per_group : 0;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int below = __shfl_up(grp_end, d);
+      if (lane >= d) grp_end += below;
+    }
   }
-  if (tid < kSkBN) bias_s[tid] = PLAIN ? 0.0f : a.bias[(tc.n0 + tid < a.N) ? tc.n0 + tid : a.N - 1];
-  __syncthreads();
+  const int64_t total = __builtin_amdgcn_readlane(grp_end, 63);
+  int at = static_cast<int>(total * run / runs);
+  const int at_end = static_cast<int>(total * (run + 1) / runs);
+
+  const bf16_t *Ap = static_cast<const bf16_t *>(a.A);
+  uint4 *Ws = smem;                                                        // [128][KC], rows kWPitch apart
+  float *bias_s = reinterpret_cast<float *>(smem + kSkBN * kWPitch);            // [128]
+  char *stage = reinterpret_cast<char *>(bias_s + kSkBN) + wave * (32 * kPitch);
+  if (tid < kSkBN) bias_s[tid] = PLAIN ? 0.0f : a.bias[(n0 + tid < a.N) ? n0 + tid : a.N - 1];
 
   const int frag_row = lane & 31, frag_half = lane >> 5;
-  const int swz = (frag_row >> kSwzShift) & (KC - 1);
-  const int n_sub = static_cast<int>((tc.row_end - tc.row0 + 31) / 32);
   const int chunk = lane & 7, sub_row = lane >> 3;     // store phase: 8 rows x 128 bytes per instruction
 
-  for (int sub = wave; sub < n_sub; sub += kSkWaves) {
+  while (at < at_end) {                                // one group after the other
+    const int group = __builtin_popcountll(__ballot(grp_end <= at));
+    const int lo = __builtin_amdgcn_readlane(grp_lo, group), hi = __builtin_amdgcn_readlane(grp_hi, group);
+    const int end = __builtin_amdgcn_readlane(grp_end, group), first = end - (hi - lo + 31) / 32;
+    const int sub0 = at > first ? at - first : 0, stop = (end < at_end ? end : at_end) - first;
+    at = end;
+    if (sub0 >= stop) continue;
+    const bf16_t *Wp = static_cast<const bf16_t *>(a.W) + static_cast<int64_t>(group) * a.N * a.K;
+    for (int q = tid; q < kSkBN * KC; q += kSkWaves * 64) {
+      const int r = q / KC, c = q % KC;
+      const int n = (n0 + r < a.N) ? n0 + r : a.N - 1;
+      const u32x4_t v = *reinterpret_cast<const u32x4_t *>(Wp + static_cast<int64_t>(n) * a.K + c * 8);
+      Ws[r * kWPitch + c] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+    // rows of A and C of this lane's position, a sub-tile ahead; positions past the group's end: computed, never stored
+    auto position = [&](int sub) __attribute__((always_inline)) {
+      const int p = lo + sub * 32 + frag_row;
+      return sub < stop && p < hi ? p : lo;
+    };
+    int p_next = position(sub0 + wave);
+    int ar_next = a.a_rows ? a.a_rows[p_next] : p_next, cr_next = a.c_rows ? a.c_rows[p_next] : p_next;
+    __syncthreads();
+
+  for (int sub = sub0 + wave; sub < stop; sub += kSkWaves) {
+    const int ar = ar_next, crow = cr_next, row0 = lo + sub * 32;
     // A fragment: row frag_row of the sub-tile, 8 elements at K offset 16 kk + 8 frag_half
-    int64_t p = tc.row0 + sub * 32 + frag_row;
-    if (p >= tc.row_end) p = tc.row0;                 // rows past the tile: computed, never stored
-    const int64_t ar = a.a_rows ? a.a_rows[p] : p;
-    const int crow = static_cast<int>(a.c_rows ? a.c_rows[p] : p);
-    const bf16_t *src = Ap + ar * a.lda + frag_half * 8;
+    const bf16_t *src = Ap + static_cast<int64_t>(ar) * a.lda + frag_half * 8;
     bf16x8_t af[KSTEPS];
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) af[kk] = *reinterpret_cast<const bf16x8_t *>(src + kk * 16);
     if (frag_half == 0) *reinterpret_cast<int *>(stage + frag_row * kPitch + kHalf * 2) = crow;
+    p_next = position(sub + kSkWaves);
+    ar_next = a.a_rows ? a.a_rows[p_next] : p_next;
+    cr_next = a.c_rows ? a.c_rows[p_next] : p_next;
 
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
+      // RES: whole row pieces, in the layout of the stores, ahead of the products; through the wave's patch to the lanes that add them
+      const int col = n0 + h * kHalf + chunk * 8;
+      u32x4_t res[RES ? 4 : 1];
+      if constexpr (RES) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int cr = *reinterpret_cast<const int *>(stage + (i * 8 + sub_row) * kPitch + kHalf * 2);
+          res[i] = *reinterpret_cast<const u32x4_t *>(static_cast<const bf16_t *>(a.residual) + static_cast<int64_t>(cr) * a.ldc +
+                                                      (col < a.N ? col : 0));
+        }
+      }
       f32x16_t acc[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -1473,12 +1522,16 @@ void gemm_bf16_smallk_kernel(const GemmArgs a) {
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) {
-        const int c = (kk * 2 + frag_half) ^ swz;
+        const int c = kk * 2 + frag_half;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          const uint4 w = Ws[(h * kHalf + j * 32 + frag_row) * KC + c];
+          const uint4 w = Ws[(h * kHalf + j * 32 + frag_row) * kWPitch + c];
           acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t *>(&w), af[kk], acc[j], 0, 0, 0);
         }
+      }
+      if constexpr (RES) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4_t *>(stage + (i * 8 + sub_row) * kPitch + chunk * 16) = res[i];
       }
       // W is the MFMA's row operand: this lane holds, for A row frag_row, the output columns
       // 32 j + 8 q + 4 frag_half + r of this half in acc[j][4 q + r]
@@ -1490,13 +1543,9 @@ void gemm_bf16_smallk_kernel(const GemmArgs a) {
           const float4 b4 = *reinterpret_cast<const float4 *>(bias_s + h * kHalf + lcol);
           float v0 = acc[j][4 * q], v1 = acc[j][4 * q + 1], v2 = acc[j][4 * q + 2], v3 = acc[j][4 * q + 3];
           if constexpr (RES) {
-            const int gcol = tc.n0 + h * kHalf + lcol;
-            if (gcol < a.N) {
-              const u32x2_t o = *reinterpret_cast<const u32x2_t *>(static_cast<const bf16_t *>(a.residual) +
-                                                                   static_cast<int64_t>(crow) * a.ldc + gcol);
-              v0 += __uint_as_float(o.x << 16); v1 += __uint_as_float(o.x & 0xFFFF0000u);
-              v2 += __uint_as_float(o.y << 16); v3 += __uint_as_float(o.y & 0xFFFF0000u);
-            }
+            const u32x2_t o = *reinterpret_cast<const u32x2_t *>(stage + frag_row * kPitch + lcol * 2);
+            v0 += __uint_as_float(o.x << 16); v1 += __uint_as_float(o.x & 0xFFFF0000u);
+            v2 += __uint_as_float(o.y << 16); v3 += __uint_as_float(o.y & 0xFFFF0000u);
           }
           uint2 pk;
           if constexpr (PLAIN) {
@@ -1510,17 +1559,17 @@ void gemm_bf16_smallk_kernel(const GemmArgs a) {
         }
       }
       // the wave's own patch: LDS serves one wave's accesses in program order, no barrier needed
-      const int col = tc.n0 + h * kHalf + chunk * 8;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = i * 8 + sub_row;
-        const int64_t pr = tc.row0 + sub * 32 + row;
         const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * kPitch + chunk * 16);
         const int cr = *reinterpret_cast<const int *>(stage + row * kPitch + kHalf * 2);
-        if (pr < tc.row_end && col < a.N)
+        if (row0 + row < hi && col < a.N)
           *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.C) + static_cast<int64_t>(cr) * a.ldc + col) = v;
       }
     }
+  }
+    if (at < at_end) __syncthreads();                  // the next group's weights go over these
   }
 }
 
@@ -1774,21 +1823,47 @@ hipError_t launch_mfma(const GemmArgs &a, hipStream_t s) {
 
 template <int KSTEPS, bool PLAIN, bool RES>
 hipError_t launch_smallk_t(const GemmArgs &a, hipStream_t s) {
-  constexpr int kSmem = kSkBN * KSTEPS * 2 * 16 + kSkBN * 4 + kSkWaves * 32 * (kSkBN + 16);
+  constexpr int kSmem = kSkBN * (KSTEPS * 2 + 1) * 16 + kSkBN * 4 + kSkWaves * 32 * (kSkBN + 16);
   static LdsAttrOnce attr;
   const hipError_t e = attr.ensure(reinterpret_cast<const void *>(&gemm_bf16_smallk_kernel<KSTEPS, PLAIN, RES>), kSmem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gemm_bf16_smallk_kernel<KSTEPS, PLAIN, RES>), dim3(grid_tiles(a, kSkBM, kSkBN)), dim3(kSkWaves * 64), kSmem, s, a);
+  const int64_t slices = ceil_div(a.N, kSkBN), most = smallk_most(a.M, a.n_groups);
+  const int64_t fill = kSkWgs / slices > 0 ? kSkWgs / slices : 1, runs = fill < most ? fill : most;
+  hipLaunchKernelGGL((gemm_bf16_smallk_kernel<KSTEPS, PLAIN, RES>), dim3(static_cast<unsigned>(slices * runs)), dim3(kSkWaves * 64), kSmem,
+                     s, a);
   return hipGetLastError();
 }
-template <int KSTEPS, bool PLAIN>
+// the accumulating form goes with the activation (the last pass of K > 1), the plain one without
+template <bool PLAIN>
 hipError_t launch_smallk(const GemmArgs &a, hipStream_t s) {
-  return a.residual ? launch_smallk_t<KSTEPS, PLAIN, true>(a, s) : launch_smallk_t<KSTEPS, PLAIN, false>(a, s);
+  const auto steps = [&](auto k) -> hipError_t {
+    constexpr int KS = decltype(k)::value;
+    if constexpr (!PLAIN && (KS == 2 || KS == 4 || KS == 8))
+      if (a.residual) return launch_smallk_t<KS, false, true>(a, s);
+    return launch_smallk_t<KS, PLAIN, false>(a, s);
+  };
+  switch (a.K / 16) {
+    case 2: return steps(std::integral_constant<int, 2>{});
+    case 3: return steps(std::integral_constant<int, 3>{});
+    case 4: return steps(std::integral_constant<int, 4>{});
+    case 6: return steps(std::integral_constant<int, 6>{});
+    case 8: return steps(std::integral_constant<int, 8>{});
+  }
+  if constexpr (PLAIN) {
+    if (a.K == 80) return steps(std::integral_constant<int, 5>{});
+    if (a.K == 160) return steps(std::integral_constant<int, 10>{});
+  }
+  return hipErrorInvalidValue;
 }
-// whether the streaming small-K kernel takes the call (inner dimension 32, 64 or 128, dense rows of A)
-bool smallk_takes(const GemmArgs &a) {
-  return kUseSmallK && a.lda >= a.K && a.M < (1ll << 31) && (a.K == 128 || a.K == 64 || a.K == 32) &&
-         !a.row_scale && !a.c_is_f32;
+// whether the streaming small-K kernel takes the call (dense rows of A; with the activation 32, 48, 64, 96 or 128 contraction indices, the
+// ranks of the workloads' dt projections; without it also those + 32, 80 and 160).  The general kernel runs a K that is no multiple of 64
+// in whole slabs: 3063 x 3072 x 96, one group, 22.0 us against 13.5, 16384 x 4096 x 160 74 / 36; its 64-row tiles have the shorter start where
+// most groups have less than one of them (700 x 1536 x 48 in 8 groups 6.1 / 6.9, 1000 rows 10.3 / 7.1).
+bool smallk_takes(const GemmArgs &a, bool plain) {
+  if (!kUseSmallK || a.lda < a.K || a.M >= (1ll << 31) || a.row_scale || a.c_is_f32 || (plain && a.residual)) return false;
+  if (a.K == 32 || a.K == 64 || a.K == 128) return true;
+  if (a.M < int64_t{96} * a.n_groups) return false;
+  return ((a.K == 48 || a.K == 96) && !a.residual) || (plain && (a.K == 80 || a.K == 160));
 }
 
 template <int BN, int WM, int WN, int EPI>
@@ -1939,20 +2014,12 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
     return launch_mfma_tiles<kEpiPlainF32>(a, s);
   }
   if (a.bias) {
-    if (smallk_takes(a)) {
-      if (a.K == 128) return launch_smallk<8, false>(a, s);
-      if (a.K == 64) return launch_smallk<4, false>(a, s);
-      return launch_smallk<2, false>(a, s);
-    }
+    if (smallk_takes(a, false)) return launch_smallk<false>(a, s);
     if (a.residual) return hipErrorInvalidValue;       // bias + activation on top of an accumulated output: small-K kernel only
     return launch_mfma_tiles<kEpiBiasSoftplus>(a, s);
   }
   // short inner dimension, many rows, wide output: the streaming kernel without its activation
-  if (smallk_takes(a) && a.M >= 4096 && a.N >= 1024) {
-    if (a.K == 128) return launch_smallk<8, true>(a, s);
-    if (a.K == 64) return launch_smallk<4, true>(a, s);
-    return launch_smallk<2, true>(a, s);
-  }
+  if (smallk_takes(a, true) && a.M >= 4096 && a.N >= 1024) return launch_smallk<true>(a, s);
   if (few) return a.residual ? launch_few_rows<kEpiRowScaleResidual>(a, s)
                 : a.row_scale ? launch_few_rows<kEpiRowScale>(a, s) : launch_few_rows<kEpiPlain>(a, s);
   if (a.residual) return launch_mfma_tiles<kEpiRowScaleResidual>(a, s);
