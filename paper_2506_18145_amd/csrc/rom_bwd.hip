@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256) void scan_bwd_fold_kernel(const float *__restr
   float *x = (rev ? carry_r : carry_q) + b * n_chunks * per_seq + w;
   const float *s = carry_s + b * n_chunks * d_inner + ch;
   float v = 0.0f;
-  constexpr int kAhead = 8;
+  constexpr int kAhead = 16;
   float xv[kAhead], sv[kAhead];
   for (int k0 = 0; k0 < n_chunks; k0 += kAhead) {
 #pragma unroll

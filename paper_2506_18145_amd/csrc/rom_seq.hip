@@ -261,7 +261,6 @@ __global__ __launch_bounds__(256) void conv_silu_kernel(
 constexpr int kScanTile = 64;
 constexpr bool kScanDouble = true;
 constexpr int kScanGroups = kScanTile / 16;
-constexpr int kScanCh = 16;
 constexpr int kBcPitch = kScanTile + 4;     // floats; keeps 16-byte alignment of the row reads
 
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
@@ -802,8 +801,6 @@ __global__ __launch_bounds__(HELPERS ? 512 : 256) void scan_pipe_kernel(
 // different wavefronts take 5.5 together).  16384 x 4096 bf16, launches alone: 351 us, lane = (channel, state) 385; within
 // a layer, behind a GEMM, the full pass takes 201 us, the state-only pass 150 and the fold 13.
 constexpr int kLaneRun = 8;
-constexpr int kLaneWaves = 4096;
-constexpr int kLaneMinLen = 64;
 typedef float f32x16s_t __attribute__((ext_vector_type(16)));
 typedef const __attribute__((address_space(4))) f32x16s_t const_f32x16_t;
 typedef __attribute__((address_space(1))) char global_char_t;
@@ -976,7 +973,7 @@ __global__ __launch_bounds__(256) void scan_fold_kernel(const float *__restrict_
   float *q = chunk_q + b * n_chunks * per_seq + r;
   const float *s = chunk_s + b * n_chunks * d_inner + ch;
   float h = q[(n_chunks - 1) * per_seq];
-  constexpr int kAhead = 8;
+  constexpr int kAhead = 16;
   float qv[kAhead], sv[kAhead];
   for (int k0 = 0; k0 < n_chunks - 1; k0 += kAhead) {
 #pragma unroll
@@ -1551,32 +1548,8 @@ hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const floa
 #undef ROM_CONV
 }
 
-int scan_lane_chunks(int64_t B, int64_t L, int d_inner) {
-  const int64_t waves = B * ceil_div(d_inner, 64);
-  if (waves >= 2048) return 1;
-  int64_t nc = kLaneWaves / (waves > 0 ? waves : 1);
-  const int64_t by_len = L / kLaneMinLen;
-  if (nc > by_len) nc = by_len;
-  if (nc < 1) nc = 1;
-  return static_cast<int>(nc);
-}
-
-int scan_chunks(int64_t B, int64_t L, int d_inner) {
-  // chunk only when there are fewer workgroups than CUs (256): the state-only pass costs about as
-  // much as the better occupancy of the full pass gains once every SIMD has a wavefront; chunks are whole tiles and at least 256 steps long
-  const int64_t blocks = B * (d_inner / kScanCh);
-  int64_t nc = ceil_div(256, blocks > 0 ? blocks : 1);
-  const int64_t by_len = L / 256;
-  if (nc > by_len) nc = by_len;
-  if (nc > 8) nc = 8;
-  if (nc < 1) nc = 1;
-  return static_cast<int>(nc);
-}
-
 size_t scan_chunk_state_bytes(int64_t B, int64_t L, int d_inner) {
-  const int a = scan_chunks(B, L, d_inner), b = scan_by_lane(B, L, d_inner) ? scan_lane_chunks(B, L, d_inner) : 1;
-  const int nc = a > b ? a : b;
-  return static_cast<size_t>(B) * (nc > 1 ? nc : 0) * d_inner * 16 * sizeof(float);
+  return static_cast<size_t>(scan_most_chunks(B, L, d_inner)) * d_inner * 16 * sizeof(float);
 }
 
 template <typename T>
@@ -1590,7 +1563,7 @@ static hipError_t scan_dispatch(const T *u, const T *dt, const float *bc, const 
                        0, s, u, dt, bc, z, ld_z, A_log, D, h_in, h_out, g, B, d_inner);
     return hipGetLastError();
   }
-  if (scan_by_lane(B, L, d_inner)) {
+  if (scan_by_lane(B, L, d_inner, sizeof(T) == 4)) {
     const int64_t chunk_len = ceil_div(ceil_div(L, scan_lane_chunks(B, L, d_inner)), kLaneRun) * kLaneRun;
     const int nc = static_cast<int>(ceil_div(L, chunk_len));      // no empty chunk after rounding
     // the kernel addresses a chunk's rows with 32-bit byte offsets; grid.y and grid.z are 16-bit

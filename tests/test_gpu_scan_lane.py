@@ -19,3 +19,13 @@ def test_scan_lane(B, L, d_inner, dtype):
     _, gpu, x, w = run_layer(cfg, cs, ss)
     assert np.isfinite(gpu["ssm_state"]).all()
     compare_layer(cfg, gpu, x, w, cs, ss)
+
+
+@pytest.mark.parametrize("B,L,d_inner", [(1, 4500, 784), (2, 1500, 1296), (1, 2999, 1040)])
+def test_scan_lane_short_chunks(B, L, d_inner):
+    """Calls below 7 Mi (step, channel) pairs, whose chunks may be 32 steps long: remainders of chunks and of channel groups."""
+    cfg = RomConfig(f"lane_short_{B}_{L}", 950 + L % 89, B, L, 64, d_inner, 16, 4, 8, 4, 1, "bf16", 0)
+    cs, ss = make_states(cfg)
+    _, gpu, x, w = run_layer(cfg, cs, ss)
+    assert np.isfinite(gpu["ssm_state"]).all()
+    compare_layer(cfg, gpu, x, w, cs, ss)

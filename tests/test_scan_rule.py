@@ -46,3 +46,37 @@ def test_adjoint_scan_chunks(rules, B, L, d_inner, want):
 ])
 def test_lane_scan(rules, B, L, d_inner, want):
     assert rules(B, L, d_inner)[1] == want
+
+
+@pytest.mark.parametrize("B,L,d_inner,want", [
+    (1, 8192, 768, 1), (1, 3900, 768, 0), (1, 2048, 1536, 1), (1, 1536, 1536, 0), (1, 3072, 2048, 1), (2, 1536, 1280, 1), (2, 1024, 1536, 0),
+    (2, 3072, 2048, 0), (4, 1536, 1280, 1), (4, 1024, 1536, 0), (4, 3072, 1792, 1), (4, 3200, 2048, 1), (4, 1536, 2304, 1), (4, 1024, 2304, 0),
+    (8, 2048, 1536, 0), (1, 6500, 4096, 1), (1, 600, 4096, 0), (1, 8192, 16, 0),
+])
+def test_lane_scan_of_few_blocks(rules, B, L, d_inner, want):
+    """Both sides of the line for up to three workgroups per CU, where each was measured faster."""
+    assert rules(B, L, d_inner)[1] == want
+
+
+CHUNKS = r"""
+#include <cstdio>
+#include "rom_scan_rule.h"
+int main() {
+  for (long long B = 1; B < 40; B += 1 + B / 5)
+    for (long long L = 1; L < 40000; L += 1 + L / 9)
+      for (int d = 16; d < 6000; d += 16 * (1 + d / 100)) {
+        const long long most = rom::scan_most_chunks(B, L, d), a = rom::scan_chunks(B, L, d), b = rom::scan_lane_chunks(B, L, d);
+        if ((a > 1 && B * a > most) || (B * ((d + 63) / 64) < 2048 && b > 1 && B * b > most) || rom::scan_most_chunks(B + 1, L, d) < most ||
+            rom::scan_most_chunks(B, L + 7, d) < most)
+          return std::printf("%lld %lld %d\n", B, L, d), 1;
+      }
+  return 0;
+}
+"""
+
+
+def test_chunk_states_fit_and_serve_smaller_calls(tmp_path):
+    (tmp_path / "main.cpp").write_text(CHUNKS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(tmp_path / "main.cpp"), "-o", str(tmp_path / "chunks")], check=True)
+    r = subprocess.run([str(tmp_path / "chunks")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
