@@ -596,8 +596,8 @@ __device__ __forceinline__ void dma_load_16(unsigned lds_addr, unsigned voff, co
 // BN < 256 or BM < 256 keep the five 32 KiB ring slots; the half slabs just fill less of theirs.
 // grid.y slices the inner dimension (fp32 partial sums, plain epilogue only).
 // WT: the weight is stored contraction-major, [group][K][N] (a forward weight used for the input
-// gradient without a transposed copy; BN = 256, N a multiple of 256).  Its half slab is then 64
-// contraction rows x 256 output columns as they lie in memory, two rows per DMA instruction, chunk c
+// gradient without a transposed copy; BN = 128 or 256, N a multiple of 256).  Its half slab is then 64
+// contraction rows x BN output columns as they lie in memory, 512 / BN rows per DMA instruction, chunk c
 // of row r at position c ^ 4 (r & 3), and the MFMA fragments - eight consecutive contraction indices of
 // one output column per lane - come out of it through the transposing LDS read (ds_read_b64_tr_b16:
 // the 16 lanes of a group name four rows x 16 columns, lane i receives column i of the four rows).
@@ -611,7 +611,8 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
   constexpr int kSlotBytes = kSlotChunks * 16;                // 32 KiB
   constexpr int kAInstr = BM / (8 * NW);                      // DMA instructions per wave and half slab: 8 rows each
   constexpr int kWInstr = (BN + 8 * NW - 1) / (8 * NW);       // (rows past BN are clamped re-reads into unused slot space)
-  static_assert(!WT || BN == 256, "contraction-major weights: whole 256-column slabs");
+  static_assert(!WT || BN == 256 || BN == 128, "contraction-major weights: a row's chunks cover the banks in whole rounds");
+  constexpr int kWtChunks = BN / 8;                           // 16-byte chunks per contraction row of a contraction-major W
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM;
@@ -634,8 +635,8 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
 #pragma unroll
   for (int j = 0; j < kWInstr; ++j) {
     if constexpr (WT) {
-      const int r = (wave * kWInstr + j) * 2 + (lane >> 5);    // contraction row within the slab
-      const int c = (lane & 31) ^ (4 * (r & 3));
+      const int r = (wave * kWInstr + j) * (64 / kWtChunks) + lane / kWtChunks;    // contraction row within the slab
+      const int c = (lane % kWtChunks) ^ (4 * (r & 3));
       b_voff[j] = static_cast<unsigned>((static_cast<int64_t>(r) * a.N + tc.n0 + c * 8) * 2);
     } else {
       const int r = (wave * kWInstr + j) * 8 + (lane >> 3);
@@ -677,7 +678,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int chunk = (wn * (WTN / 8) + j * 4 + 2 * (grp & 1) + ((i16 >> 1) & 1)) ^ (4 * (i16 >> 2));
-      wt_off[j] = static_cast<unsigned>((8 * (grp >> 1) + (i16 >> 2)) * 512 + chunk * 16 + (i16 & 1) * 8);
+      wt_off[j] = static_cast<unsigned>((8 * (grp >> 1) + (i16 >> 2)) * (2 * BN) + chunk * 16 + (i16 & 1) * 8);
     }
   }
   bf16x8_t fa0[TM], fa1[TM], fb0[TN], fb1[TN];
@@ -692,9 +693,9 @@ __device__ __forceinline__ void dma_tile(const GemmArgs &a, const TileCoord &tc,
       typedef short i16x8_t __attribute__((ext_vector_type(8)));
       typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
       const __attribute__((address_space(3))) unsigned char *pb =
-          (const __attribute__((address_space(3))) unsigned char *)sb + kk * (16 * 512) + wt_off[j];
+          (const __attribute__((address_space(3))) unsigned char *)sb + kk * (16 * 2 * BN) + wt_off[j];
       const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)pb);
-      const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(pb + 4 * 512));
+      const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(pb + 4 * 2 * BN));
       return __builtin_bit_cast(bf16x8_t, (i16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     } else {
       const uint4 v = sb[b_base + j * 32 * kDmaRC + ((kk * 2 + frag_half) ^ swz)];
@@ -1383,24 +1384,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const StreamTile tl = locate(tile_end + cu / cut);
   TileCoord tc;
   const int piece = cu % cut;
-  // rows x columns of a piece: 128 x 256, 128 x 128, 64 x 128 (a contraction-major weight comes in whole 256-column
-  // slabs: 64 x 256, 32 x 256); fewest lines of both operands per product
-  const int col_cuts = WT || cut == 2 ? 1 : 2, rows = 256 * col_cuts / cut;
+  // rows x columns of a piece: 128 x 256, 128 x 128, 64 x 128; fewest lines of both operands per product, which bound a piece
+  // (contraction-major weights in pieces of 64 x 256 and 32 x 256: 2000 x 768 x 3072 in 4 groups 36 us, so 33; 8192 x 2048 x 1024 in 8 49.5 / 47.7)
+  const int col_cuts = cut == 2 ? 1 : 2, rows = 256 * col_cuts / cut;
   tc.group = tl.group;
   tc.n0 = tl.n0 + piece % col_cuts * 128;
   tc.row0 = tl.row0 + piece / col_cuts * rows;
   tc.row_end = tl.row_end < tc.row0 + rows ? tl.row_end : tc.row0 + rows;
   tc.valid = true;
   if (tc.row0 >= tc.row_end || tc.n0 >= a.N) return;
-  if (cut == 2) {
-    dma_tile<256, 1, 4, EPI, WT, 128>(a, tc, smem);
-  } else if constexpr (WT) {
-    if (cut == 4) dma_tile<256, 1, 4, EPI, WT, 64>(a, tc, smem);
-    else dma_tile<256, 1, 4, EPI, WT, 32>(a, tc, smem);
-  } else {
-    if (cut == 4) dma_tile<128, 2, 2, EPI, WT, 128>(a, tc, smem);
-    else dma_tile<128, 2, 2, EPI, WT, 64>(a, tc, smem);
-  }
+  if (cut == 2) dma_tile<256, 1, 4, EPI, WT, 128>(a, tc, smem);
+  else if (cut == 4) dma_tile<128, 2, 2, EPI, WT, 128>(a, tc, smem);
+  else dma_tile<128, 2, 2, EPI, WT, 64>(a, tc, smem);
 }
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, short inner dimension
