@@ -627,60 +627,66 @@ __global__ __launch_bounds__(kSortBlock) void permutation_round_kernel(
   tok_of_pos[pos] = s / top_k;
 }
 
-// The same for some more slots: three passes over them in rounds of 256, counts and running bases in LDS.
-__global__ __launch_bounds__(kSortBlock) void permutation_small_kernel(
+// The same for more slots: sixteen wavefronts, each with a run of R times 64 consecutive ones, their keys in registers.  Lane e of a wavefront
+// counts expert e; after the one barrier it knows where the wavefront's first slot of that expert goes, and moves on by
+// the round's count.  Bound by the scattered stores of one CU, about an address a clock: 8 experts, 1000 slots 3.1 us, 2048 4.2 (with four
+// wavefronts and four barriers for every 256 slots 10.1 and 16.2), 4096 6.5 (three launches 13.1).
+constexpr int kRunWaves = 16;
+template <int R>
+__global__ __launch_bounds__(kRunWaves *kWave) void permutation_run_kernel(
     const int32_t *__restrict__ expert_idx, int n_slots, int n_experts, int top_k,
     int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ perm,
     int32_t *__restrict__ inv_perm, int32_t *__restrict__ tok_of_pos) {
-  __shared__ int cnt[kSortWaves][64];
-  __shared__ int base[64];          // running position of every expert
-  __shared__ int total[64];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (threadIdx.x < 64) total[threadIdx.x] = 0;
-  __syncthreads();
-  for (int s0 = 0; s0 < n_slots; s0 += kSortBlock) {      // histogram
-    const int s = s0 + threadIdx.x;
-    match_expert(s < n_slots ? expert_idx[s] : -1, n_experts, lane, cnt[wave]);
-    __syncthreads();
-    if (threadIdx.x < n_experts) {
-      int t = 0;
+  __shared__ int cnt[kRunWaves][kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, s0 = wave * (R * kWave) + lane;
+  int key[R], mine[R];                                  // mine: this round's slots of expert `lane`
 #pragma unroll
-      for (int w = 0; w < kSortWaves; ++w) t += cnt[w][threadIdx.x];
-      total[threadIdx.x] += t;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int e = 0; e < n_experts; ++e) {
-      offsets[e] = run;
-      base[e] = run;
-      counts[e] = total[e];
-      run += total[e];
-    }
-    offsets[n_experts] = run;
-  }
-  __syncthreads();
-  for (int s0 = 0; s0 < n_slots; s0 += kSortBlock) {      // stable scatter
-    const int s = s0 + threadIdx.x;
-    const int key = s < n_slots ? expert_idx[s] : -1;
-    const unsigned long long same = match_expert(key, n_experts, lane, cnt[wave]);
-    __syncthreads();
-    if (s < n_slots && key >= 0 && key < n_experts) {
-      int pos = base[key] + __popcll(same & ((1ull << lane) - 1ull));
-      for (int w = 0; w < wave; ++w) pos += cnt[w][key];
-      inv_perm[s] = pos;
-      perm[pos] = s;
-      tok_of_pos[pos] = s / top_k;
-    }
-    __syncthreads();
-    if (threadIdx.x < n_experts) {
-      int t = 0;
+  for (int r = 0; r < R; ++r) key[r] = s0 + r * kWave < n_slots ? expert_idx[s0 + r * kWave] : -1;
+  unsigned long long same[R];
+  int run = 0;
 #pragma unroll
-      for (int w = 0; w < kSortWaves; ++w) t += cnt[w][threadIdx.x];
-      base[threadIdx.x] += t;
+  for (int r = 0; r < R; ++r) same[r] = 0ull, mine[r] = 0;
+  for (int e = 0; e < n_experts; ++e) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const unsigned long long m = __ballot(key[r] == e);
+      if (key[r] == e) same[r] = m;
+      if (lane == e) mine[r] = __popcll(m);
     }
-    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) run += mine[r];
+  cnt[wave][lane] = run;
+  __syncthreads();
+  int total = 0, before = 0;
+#pragma unroll
+  for (int w = 0; w < kRunWaves; ++w) {
+    const int c = cnt[w][lane];
+    total += c;
+    if (w < wave) before += c;
+  }
+  int end = total;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int up = __shfl_up(end, d, kWave);
+    if (lane >= d) end += up;
+  }
+  if (wave == 0 && lane < n_experts) {
+    counts[lane] = total;
+    offsets[lane] = end - total;
+    if (lane == n_experts - 1) offsets[n_experts] = end;
+  }
+  int at = end - total + before;                        // of expert `lane`, for this wavefront's next round
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool valid = key[r] >= 0 && key[r] < n_experts;
+    const int pos = __shfl(at, valid ? key[r] : 0, kWave) + __popcll(same[r] & ((1ull << lane) - 1ull));
+    at += mine[r];
+    if (!valid) continue;
+    const int s = s0 + r * kWave;
+    inv_perm[s] = pos;
+    perm[pos] = s;
+    tok_of_pos[pos] = s / top_k;
   }
 }
 
@@ -872,11 +878,17 @@ hipError_t launch_permutation(const int32_t *expert_idx, int64_t n_slots, int n_
                        top_k, counts, offsets, perm, inv_perm, tok_of_pos);
     return hipGetLastError();
   }
-  if (n_slots <= 2048) {
-    hipLaunchKernelGGL(permutation_small_kernel, dim3(1), dim3(kSortBlock), 0, s, expert_idx,
-                       static_cast<int>(n_slots), n_experts, top_k, counts, offsets, perm, inv_perm, tok_of_pos);
-    return hipGetLastError();
+  // One workgroup or three launches (us, three / one): 3063 slots, 8 experts 13.0 / 5.3, 16 12.2 / 7.8; 6000 12.7 / 9.4,
+  // 13.1 / 13.4; 8192 12.9 / 11.2, 13.7 / 15.3; 12000, 8 experts 12.8 / 15.8
+  const bool one = n_slots <= (n_experts <= 8 ? 8192 : n_experts <= 16 ? 4096 : 2048);
+#define ROM_RUN(R)                                                                                                                  \
+  if (one && n_slots <= R * kRunWaves * kWave) {                                                                                           \
+    hipLaunchKernelGGL(permutation_run_kernel<R>, dim3(1), dim3(kRunWaves * kWave), 0, s, expert_idx, static_cast<int>(n_slots),     \
+                       n_experts, top_k, counts, offsets, perm, inv_perm, tok_of_pos);                                              \
+    return hipGetLastError();                                                                                                       \
   }
+  ROM_RUN(1) ROM_RUN(2) ROM_RUN(4) ROM_RUN(8)
+#undef ROM_RUN
   const int64_t blocks = route_blocks(n_slots);
   hipLaunchKernelGGL(hist_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kSortBlock), 0, s,
                      expert_idx, n_slots, n_experts, 1, block_counts);

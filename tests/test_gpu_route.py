@@ -1,0 +1,33 @@
+"""Grouping: the edges of a workgroup's rounds and of one workgroup against three launches (stable order, exact)."""
+import numpy as np
+import pytest
+
+from oracle import rom_oracle as O
+from paper_2506_18145_amd import RomLayer
+from rom_synth import RomConfig, make_weights
+from gpu_util import to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def layer_of(n, d_model, E, K, dtype="bf16", bias=None):
+    cfg = RomConfig(f"route_{n}", 900 + n % 89, 1, n, d_model, 64, 16, 4, 8, E, K, dtype, K > 1, router_bias=bias)
+    w = make_weights(cfg)
+    return cfg, w, RomLayer(cfg, w)
+
+
+@pytest.mark.parametrize("E,K,tokens", [
+    (8, 1, (1, 64, 255, 256, 257, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192, 8193)),
+    (16, 1, (257, 2049, 4096, 4097)), (17, 1, (1025, 2048, 2049)), (64, 1, (257, 1024, 2048, 2049)),
+    (1, 1, (1000, 8192)), (5, 3, (86, 342, 683, 2730, 2731)), (64, 8, (33, 128, 256, 257)),
+])
+@pytest.mark.parametrize("skewed", [False, True])
+def test_grouping_edges(E, K, tokens, skewed):
+    bias = None if not skewed else tuple(9.0 if e == E - 1 else -9.0 if e == 0 and E > K else 0.0 for e in range(E))
+    _, _, layer = layer_of(max(tokens), 64, E, K, bias=bias)
+    x = layer.to_device(np.random.default_rng(E).standard_normal((max(tokens), 64)).astype(np.float32))
+    for n in tokens:
+        r = {k: to_np(v) for k, v in layer.route(x[:n]).items()}
+        want = O.expert_permutation(r["expert_idx"], E)
+        for name, ref in zip(("counts", "offsets", "perm", "inv_perm"), want):
+            assert np.array_equal(r[name], ref), (n, name)
