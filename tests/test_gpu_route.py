@@ -1,11 +1,14 @@
-"""Grouping: the edges of a workgroup's rounds and of one workgroup against three launches (stable order, exact)."""
+"""Grouping and router at the lines of their rules: the edges of a workgroup's rounds and of one workgroup against three
+launches (stable order, exact), and four wavefronts, one wavefront or the matrix pipe for a token (logits and gates against
+the oracle; the router of a block reads the normalised input)."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import rom_oracle as O
 from paper_2506_18145_amd import RomLayer
-from rom_synth import RomConfig, make_weights
-from gpu_util import to_np
+from rom_synth import RomConfig, make_input, make_weights
+from gpu_util import BLOCK_EPS, check_routing, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +34,22 @@ def test_grouping_edges(E, K, tokens, skewed):
         want = O.expert_permutation(r["expert_idx"], E)
         for name, ref in zip(("counts", "offsets", "perm", "inv_perm"), want):
             assert np.array_equal(r[name], ref), (n, name)
+
+
+@pytest.mark.parametrize("n,d_model,E,K,dtype", [
+    (1024, 512, 8, 1, "bf16"), (1025, 512, 8, 1, "bf16"), (3072, 544, 8, 1, "bf16"), (3073, 544, 8, 2, "bf16"),
+    (4096, 1024, 8, 1, "bf16"), (4097, 1024, 5, 1, "bf16"), (4097, 1032, 8, 1, "bf16"), (4097, 1024, 8, 1, "fp32"),
+    (3072, 768, 16, 2, "bf16"), (3073, 768, 16, 1, "bf16"), (3073, 776, 12, 1, "bf16"), (3072, 1024, 16, 1, "fp32"),
+])
+@pytest.mark.parametrize("block", [False, True])
+def test_router_rule(n, d_model, E, K, dtype, block):
+    cfg, w, layer = layer_of(n, d_model, E, K, dtype)
+    x_np = make_input(cfg)
+    x = layer.to_device(x_np)
+    if block:
+        layer.block_forward(x, eps=BLOCK_EPS)
+    else:
+        layer.forward(x)
+    torch.cuda.synchronize()
+    names = ("expert_idx", "gate", "counts", "offsets", "perm", "inv_perm", "logits")
+    check_routing(cfg, {k: to_np(layer.ws_view(k, 1, n)) for k in names}, x_np, w, block)
