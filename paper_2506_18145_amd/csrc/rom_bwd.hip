@@ -989,8 +989,8 @@ __global__ __launch_bounds__(256) void pack_dxdbl_kernel(const float *__restrict
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-// 64 x 64 tiles where 128 x 128 ones would not give every CU a workgroup (8192 rows in 8 experts, 96 x 2048 and 2048 x 64,
-// 128 workgroups: 41 and 43 us, 28 and 30; 16384 rows, 160 x 4096 and 4096 x 128, 512 and 256: 78 and 103, 102 and 142).
+// 64 x 64 tiles where 128 x 128 ones would not give every CU a workgroup (8192 rows in 8 experts, 128 workgroups of 96 x 2048: 41 us, 28;
+// 16384 rows, 512 of 160 x 4096: 78, 102).  Operands of at most 160 columns have a kernel of their own further down.
 constexpr int kWgTileMinWgs = 256;
 constexpr int kWgTile = 128, kWgSlab = 64, kWgPitch = kWgSlab + 8;     // halfs per LDS row (144 bytes: 16-byte aligned rows)
 
@@ -1047,7 +1047,7 @@ __global__ __launch_bounds__(2 * TILE) void wgrad_bf16_kernel(const bf16_t *__re
   const bool col_ok = col < (is_a ? M : N);
   bf16_t(*dst)[kWgPitch] = is_a ? As : Bs;
   // Row numbers are asked for two slabs ahead of their use and rows one slab ahead: with one or two workgroups on a CU nothing
-  // else hides the two round trips (160 x 4096 of 16384 rows 84-87 -> 78 us).  (Branch-free, indices first: see the 256 x 256
+  // else hides the two round trips (a tenth of the kernel at 16384 rows).  (Branch-free, indices first: see the 256 x 256
   // kernel.)
   const auto numbers = [&](int64_t p0, int(&r)[8]) __attribute__((always_inline)) {
 #pragma unroll
@@ -1303,6 +1303,11 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
 
 __device__ __forceinline__ void wd_dma_16(unsigned lds_addr, unsigned voff, const void *base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n"
+               :: "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
+}
+
+__device__ __forceinline__ void wt_dma_4(unsigned lds_addr, unsigned voff, const void *base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2\n"
                :: "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
 }
 
@@ -1668,6 +1673,170 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   for (int k = 0; k < kHeldStores; ++k) store_held(k);
   // no DMA may be in flight into LDS that the next workgroup on this CU owns
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+// The contraction where one operand has at most 160 columns (the routed x and dt projections: dt_rank + 32 and dt_rank): all of
+// them and TW columns of the wide one to a workgroup of TW / 32 wavefronts, which hold 32 wide columns each and every column of the
+// thin operand, so that the wide operand is read once.  Bound by what a CU brings in.  Rows go into LDS as in the 256 x 256 kernel,
+// three slabs of 64 positions under way and one being multiplied; the row numbers of a slab are on their way three slabs earlier still, into a
+// copy per wavefront (its own count of requests covers them).  A row's chunks are permuted where its length would put four consecutive
+// rows on the same banks (lengths of an odd number of 64 bytes need none).  The products are summed in the order of the kernels above.
+// 16384 rows in 8 experts, 160 x 4096 80 -> 43 us and 4096 x 128 105 -> 36 (128 x 128 tiles, rows through registers); 8192 rows, 80 x 1536 29 -> 17.5
+// and 1536 x 48 29 -> 14 (64 x 64 tiles).
+constexpr int kWtSlots = 4, kWtMaxBlocks = 5;                // slabs in LDS; 32-column blocks of the thin operand
+template <int CHUNKS>
+__device__ __forceinline__ int wt_swizzle(int chunk, int row) {
+  return CHUNKS % 16 == 0 ? chunk ^ (4 * (row & 3)) : CHUNKS % 8 == 0 ? chunk ^ (4 * ((row >> 1) & 1)) : chunk;
+}
+template <int PITCH>
+__device__ __forceinline__ bf16x8_t wt_frag(const lds_byte_t *p) {
+  typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+  const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(p));
+  const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(p + 4 * PITCH));
+  const i16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+constexpr int wt_slab_bytes(int tw, int nb) { return kWgSlab * (tw + 32 * nb) * 2; }
+constexpr int wt_smem(int tw, int nb) { return kWtSlots * (wt_slab_bytes(tw, nb) + tw / 32 * 2 * kWgSlab * 4); }
+
+// grid: x tiles of TW wide columns, y groups.  THIN_A: C [n_groups][T][W], else [n_groups][W][T].
+template <int TW, int NB, bool THIN_A>
+__global__ __launch_bounds__(2 * TW) void wgrad_bf16_thin_kernel(
+    const bf16_t *__restrict__ wide, int64_t ldw, int W, const int32_t *__restrict__ rows_w, const bf16_t *__restrict__ thin,
+    int64_t ldt, int T, const int32_t *__restrict__ rows_t, const int32_t *__restrict__ offsets, int n_pos, float *__restrict__ C) {
+  constexpr int NW = TW / 32, kThin = 32 * NB;
+  constexpr int kWideInstr = 4, kThinInstr = 4 * NB / NW, kInstr = kWideInstr + kThinInstr;      // per wavefront and slab
+  constexpr int kWidePitch = TW * 2, kThinPitch = kThin * 2, kWideBytes = kWgSlab * kWidePitch, kSlab = wt_slab_bytes(TW, NB);
+  static_assert(4 * NB % NW == 0 && (kWtSlots & (kWtSlots - 1)) == 0, "whole instructions; slots are masked");
+  extern __shared__ __attribute__((aligned(16))) unsigned char wt_smem_bytes[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e = blockIdx.y, w0 = blockIdx.x * TW;
+  const int p_lo = offsets ? offsets[e] : 0, p_hi = offsets ? offsets[e + 1] : n_pos;
+  const int slabs = (p_hi - p_lo + kWgSlab - 1) / kWgSlab;
+  lds_byte_t *lds = (lds_byte_t *)wt_smem_bytes;
+  const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void *)wt_smem_bytes));
+  constexpr int kNumbers = kWtSlots * kSlab;                   // then [wave][slot][operand][64] row numbers
+  auto numbers_at = [&](int slab, int op) __attribute__((always_inline)) {
+    return kNumbers + ((wave * kWtSlots + (slab & (kWtSlots - 1))) * 2 + op) * (kWgSlab * 4);
+  };
+
+  // ---- requests: lane l of instruction k of an operand brings chunk 64 k + l of its slab in LDS
+  unsigned col_w[kWideInstr], col_t[kThinInstr];
+  int row_w[kWideInstr], row_t[kThinInstr];
+#pragma unroll
+  for (int k = 0; k < kWideInstr; ++k) {
+    const int g = (wave * kWideInstr + k) * 64 + lane, r = g / (TW / 8), c = w0 + wt_swizzle<TW / 8>(g % (TW / 8), r) * 8;
+    row_w[k] = r;
+    col_w[k] = static_cast<unsigned>(c < W ? c : 0) * 2;       // (columns past the end: some others, not stored)
+  }
+#pragma unroll
+  for (int k = 0; k < kThinInstr; ++k) {
+    const int g = (wave * kThinInstr + k) * 64 + lane, r = g / (kThin / 8), c = wt_swizzle<kThin / 8>(g % (kThin / 8), r) * 8;
+    row_t[k] = r;
+    col_t[k] = static_cast<unsigned>(c < T ? c : 0) * 2;
+  }
+  const unsigned ldw2 = static_cast<unsigned>(ldw) * 2, ldt2 = static_cast<unsigned>(ldt) * 2;
+  auto position = [&](int slab, int r) __attribute__((always_inline)) {
+    const int p = p_lo + slab * kWgSlab + r;
+    return p < p_hi ? p : p_hi - 1;
+  };
+  auto request_numbers = [&](int slab) __attribute__((always_inline)) {
+    const unsigned off = static_cast<unsigned>(position(slab, lane)) * 4;
+    if (rows_w) wt_dma_4(lds_base + numbers_at(slab, 0), off, rows_w);
+    if (rows_t) wt_dma_4(lds_base + numbers_at(slab, 1), off, rows_t);
+  };
+  typedef const __attribute__((address_space(3))) int lds_int_t;
+  auto rows_of = [&](const int32_t *rows, int slab, int op, const auto &r, auto &out) __attribute__((always_inline)) {
+    constexpr int kN = sizeof(out) / sizeof(out[0]);
+    if (rows) {
+#pragma unroll
+      for (int k = 0; k < kN; ++k) out[k] = static_cast<unsigned>(*(lds_int_t *)(lds + numbers_at(slab, op) + r[k] * 4));
+    } else {
+#pragma unroll
+      for (int k = 0; k < kN; ++k) out[k] = static_cast<unsigned>(position(slab, r[k]));
+    }
+  };
+  // (the launcher checks that row * ld2 fits 32 bits)
+  auto request = [&](int slab) __attribute__((always_inline)) {
+    const unsigned at = lds_base + (slab & (kWtSlots - 1)) * kSlab;
+    unsigned rw[kWideInstr], rt[kThinInstr];
+    rows_of(rows_w, slab, 0, row_w, rw);
+    rows_of(rows_t, slab, 1, row_t, rt);
+#pragma unroll
+    for (int k = 0; k < kWideInstr; ++k) wd_dma_16(at + (wave * kWideInstr + k) * 1024, rw[k] * ldw2 + col_w[k], wide);
+#pragma unroll
+    for (int k = 0; k < kThinInstr; ++k) wd_dma_16(at + kWideBytes + (wave * kThinInstr + k) * 1024, rt[k] * ldt2 + col_t[k], thin);
+  };
+
+  // ---- products: fragments as in the 256 x 256 kernel
+  const int i16 = lane & 15, grp = lane >> 4, frow = 8 * (grp >> 1) + (i16 >> 2);
+  const int fchunk = 2 * (grp & 1) + ((i16 >> 1) & 1), fbyte = (i16 & 1) * 8;
+  const int off_w = frow * kWidePitch + wt_swizzle<TW / 8>(wave * 4 + fchunk, frow) * 16 + fbyte;
+  int off_t[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) off_t[i] = kWideBytes + frow * kThinPitch + wt_swizzle<kThin / 8>(i * 4 + fchunk, frow) * 16 + fbyte;
+  f32x16_t acc[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+
+  if (slabs > 0) {
+#pragma unroll
+    for (int t = 0; t < kWtSlots; ++t) request_numbers(t);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int t = 0; t < kWtSlots - 1; ++t) {
+      if (t < slabs) request(t);
+      if (t < kWtSlots - 2) request_numbers(t + kWtSlots);
+    }
+  }
+  for (int t = 0; t < slabs; ++t) {
+    // this slab has landed (requested two slabs and their row numbers ago), and with it the row numbers of slab t + 3;
+    // every wavefront has multiplied the one before
+    if (t + kWtSlots - 2 < slabs) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kWtSlots - 2) * kInstr) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const int slot = (t & (kWtSlots - 1)) * kSlab;
+    if (t == slabs - 1) {                                      // positions that are another group's, or nobody's
+      const int valid = p_hi - p_lo - t * kWgSlab;
+      typedef __attribute__((address_space(3))) u32x4_t lds_u32x4_t;
+      for (int at = valid * kWidePitch + threadIdx.x * 16; at < kWideBytes; at += 2 * TW * 16)
+        *(lds_u32x4_t *)(lds + slot + at) = u32x4_t{0u, 0u, 0u, 0u};
+      for (int at = kWideBytes + valid * kThinPitch + threadIdx.x * 16; at < kSlab; at += 2 * TW * 16)
+        *(lds_u32x4_t *)(lds + slot + at) = u32x4_t{0u, 0u, 0u, 0u};
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    if (t + kWtSlots - 1 < slabs) {
+      request_numbers(t + 2 * kWtSlots - 2);
+      request(t + kWtSlots - 1);
+    }
+#pragma unroll
+    for (int kk = 0; kk < kWgSlab / 16; ++kk) {
+      const bf16x8_t fw = wt_frag<kWidePitch>(lds + slot + off_w + kk * (16 * kWidePitch));
+      bf16x8_t ft[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) ft[i] = wt_frag<kThinPitch>(lds + slot + off_t[i] + kk * (16 * kThinPitch));
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        acc[i] = THIN_A ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, ft[i], acc[i], 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f32_32x32x16_bf16(ft[i], fw, acc[i], 0, 0, 0);
+    }
+  }
+  // this lane holds, of output row lane & 31 of a block, the columns 8 q + 4 (lane / 32) + 0 .. 3 in elements 4 q ..
+  // (both operands are whole pieces of eight columns)
+  const int M = THIN_A ? T : W, N = THIN_A ? W : T;
+  float *Ce = C + static_cast<int64_t>(e) * M * N;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int m = (THIN_A ? i * 32 : w0 + wave * 32) + (lane & 31);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int cc = (THIN_A ? w0 + wave * 32 : i * 32) + q * 8 + (lane >> 5) * 4;
+      if (m < M && cc < N)
+        *reinterpret_cast<float4 *>(Ce + static_cast<int64_t>(m) * N + cc) =
+            make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
+    }
+  }
 }
 
 // rows scaled by a per-row factor (the gate weight of Eq. (12) on d_out):
@@ -2090,6 +2259,30 @@ hipError_t launch_rmsnorm_backward(int dtype, const void *x, const float *norm_w
   return hipGetLastError();
 }
 
+template <int TW, int NB, bool THIN_A>
+hipError_t launch_wgrad_thin(const bf16_t *wide, int64_t ldw, int W, const int32_t *rows_w, const bf16_t *thin, int64_t ldt, int T,
+                             const int32_t *rows_t, const int32_t *offsets, int n_groups, int n_pos, float *C, hipStream_t s) {
+  // more than 64 KiB of dynamic LDS: a function attribute, set once per device
+  static std::mutex mu;
+  static std::atomic<bool> done[64] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!done[dev].load(std::memory_order_acquire)) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (!done[dev].load(std::memory_order_relaxed)) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_bf16_thin_kernel<TW, NB, THIN_A>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, wt_smem(TW, NB));
+      if (e != hipSuccess) return e;
+      done[dev].store(true, std::memory_order_release);
+    }
+  }
+  hipLaunchKernelGGL((wgrad_bf16_thin_kernel<TW, NB, THIN_A>), dim3(static_cast<unsigned>(ceil_div(W, TW)), static_cast<unsigned>(n_groups)),
+                     dim3(2 * TW), wt_smem(TW, NB), s, wide, ldw, W, rows_w, thin, ldt, T, rows_t, offsets, n_pos, C);
+  return hipGetLastError();
+}
+
 hipError_t launch_wgrad(int dtype, const void *A, int64_t lda, int M, const void *Bm, int64_t ldb, int N,
                         const int32_t *rows_a, const int32_t *rows_b, const float *row_scale, const int32_t *offsets,
                         int n_groups, int64_t n_pos, float *C, hipStream_t s) {
@@ -2125,6 +2318,28 @@ hipError_t launch_wgrad(int dtype, const void *A, int64_t lda, int M, const void
     hipLaunchKernelGGL(kernel, dim3(kWdWgs), dim3(256), kWdSmem, s, static_cast<const bf16_t *>(A), lda, M,
                        static_cast<const bf16_t *>(Bm), ldb, N, rows_a, rows_b, offsets, static_cast<int>(n_pos), n_groups, C);
     return hipGetLastError();
+  }
+  const bool thin_a = M <= N;
+  const int T = thin_a ? M : N, W = thin_a ? N : M;
+  if (mfma && !row_scale && T > 0 && T <= 32 * kWtMaxBlocks && n_pos > 0 && n_pos < (1 << 30) &&
+      static_cast<uint64_t>(n_pos) * static_cast<uint64_t>(lda) * 2 < (1ull << 32) &&
+      static_cast<uint64_t>(n_pos) * static_cast<uint64_t>(ldb) * 2 < (1ull << 32)) {
+    const bf16_t *const a = static_cast<const bf16_t *>(A), *const b = static_cast<const bf16_t *>(Bm);
+    const bool half = ceil_div(W, 128) * n_groups < kWgTileMinWgs;       // 64 wide columns where 128 would leave CUs without a workgroup
+#define ROM_WT(TW, NB)                                                                                                                     \
+  return thin_a ? launch_wgrad_thin<TW, NB, true>(b, ldb, W, rows_b, a, lda, T, rows_a, offsets, n_groups, static_cast<int>(n_pos), C, s)   \
+                : launch_wgrad_thin<TW, NB, false>(a, lda, W, rows_a, b, ldb, T, rows_b, offsets, n_groups, static_cast<int>(n_pos), C, s)
+#define ROM_WT_BLOCKS(NB)     \
+  do {                        \
+    if (half) ROM_WT(64, NB); \
+    ROM_WT(128, NB);          \
+  } while (0)
+    if (T <= 64) ROM_WT_BLOCKS(2);
+    if (T <= 96) ROM_WT_BLOCKS(3);
+    if (T <= 128) ROM_WT_BLOCKS(4);
+    ROM_WT_BLOCKS(5);
+#undef ROM_WT_BLOCKS
+#undef ROM_WT
   }
   if (mfma && !row_scale && M >= kWgBig && N >= kWgBig) {
     // more than 64 KiB of dynamic LDS: a function attribute, set once per device

@@ -36,3 +36,29 @@ def test_weight_gradients(L, d_model, d_inner, E, top_k, bias):
         for e in range(E):                                      # an expert without tokens: zeros, not what was there
             if not (idx == e).any():
                 assert not to_np(grads[name])[e].any()
+
+
+@pytest.mark.parametrize("L,d_inner,rank,E,top_k,bias", [
+    # dt_rank + 32 and dt_rank thin columns: two to five blocks of 32, whole and ragged, and past the last (136 + 32)
+    (130, 144, 8, 2, 1, None), (320, 80, 32, 1, 1, None), (65, 272, 40, 1, 1, None), (193, 208, 64, 3, 1, (9.0, 0.0, -50.0)),
+    (400, 64, 72, 2, 2, None), (257, 336, 96, 1, 1, None), (90, 144, 104, 4, 2, (0.0, 9.0, 9.0, -50.0)), (600, 400, 128, 2, 1, None),
+    (1, 48, 136, 3, 1, None),
+    # 128 wide columns a workgroup: one slab, and more than the ring holds
+    (100, 4096, 24, 8, 1, None), (520, 4112, 128, 8, 1, (9.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, -50.0)),
+])
+def test_thin_weight_gradients(L, d_inner, rank, E, top_k, bias):
+    cfg = RomConfig(f"wgt_{L}", 800 + L % 97, 1, L, 64, d_inner, 16, 4, rank, E, top_k, "bf16", int(top_k > 1), weight_std=0.05,
+                    router_bias=bias)
+    w, x = make_weights(cfg), make_input(cfg)
+    layer = RomLayer(cfg, w)
+    layer.forward(layer.to_device(x))
+    idx = to_np(layer.ws_view("expert_idx", 1, L))
+    d_out = layer.to_device(np.random.default_rng(L).standard_normal((1, L, 64)).astype(np.float32))
+    _, grads = layer.backward(layer.to_device(x), d_out)
+    torch.cuda.synchronize()
+    ref = O.rom_layer_backward(x, w, cfg.top_k, cfg.gate_mode, to_np(d_out), expert_idx=idx)
+    for name in ("d_w_x", "d_w_dt"):
+        assert rel_err(to_np(grads[name]), ref[name]) <= TOL["bf16"], name
+        for e in range(E):
+            if not (idx == e).any():
+                assert not to_np(grads[name])[e].any()
