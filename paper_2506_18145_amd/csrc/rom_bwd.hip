@@ -789,8 +789,9 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const T *__restrict__ dx
 // Per-run partial sums of d_w[i, j] = sum_t d_c_t x_{t-3+j} and d_b = sum_t d_c_t go to
 // partial[run][5][channel] and are added in run order by conv_bwd_finish_kernel.
 // Steps per run: 128, and half of that as long as there are fewer than 4096 wavefronts (16 a CU).  A run reads six rows more than
-// its steps, and its partial sums are five rows.  4 x 2048 steps x 2048 channels: runs of 128 (1024 wavefronts) 94 us, 64 57, 32 40,
-// 16 46; 16384 x 4096 (4096 wavefronts of 128) 135, of 64 145.
+// its steps, and its partial sums are five rows.  4 x 2048 steps x 2048 channels: runs of 64 29 us, 32 30, 16 33; 16384 x 4096 (4096 wavefronts of
+// 128) 114, of 64 118.  Bound by memory (three rows in, one out: 537 MB, 4.7 TB/s); with the rows of eight steps requested in one go
+// and converted where they were requested, 8192 x 2048 took 41 and 16384 x 4096 139.
 inline int conv_bwd_run(int64_t B, int64_t L, int d_inner) {
   int run = 128;
   while (run > 16 && B * ceil_div(L, run) * ceil_div(d_inner, 128) < 4096) run /= 2;
@@ -820,18 +821,31 @@ __global__ __launch_bounds__(256) void conv_bwd_kernel(const T *__restrict__ xz,
   }
   const T *xr = xz + b * L * ld_xz + ch;
   const int64_t tok0 = b * L;
-  auto load = [&](const T *p, float (&f)[V]) __attribute__((always_inline)) {
-    if constexpr (V == 2) conv_ld2(p, f); else f[0] = to_f32(*p);
+  // the rows a step needs from memory, as they lie there: x_{t+3} and the two d u rows of step t+3 (zeros outside the sequence,
+  // put in place of the values of its ends - the same number of requests for every step, and none that waits for a conversion)
+  using Raw = std::conditional_t<V == 1, T, std::conditional_t<sizeof(T) == 2, uint32_t, float2>>;
+  struct Rows {
+    Raw x, ua, ub;
   };
-  // the rows a step needs from memory: x_{t+3} and the two d u rows of step t+3 (zeros outside the sequence)
-  auto fetch = [&](int64_t t, float (&x)[V], float (&ua)[V], float (&ub)[V]) __attribute__((always_inline)) {
-    if (t >= 0 && t < L) {
-      load(xr + t * ld_xz, x);
-      load(du_a + (tok0 + t) * d_inner + ch, ua);
-      load(du_b + (tok0 + t) * d_inner + ch, ub);
+  auto fetch = [&](int64_t t) __attribute__((always_inline)) {
+    const int64_t tc = t < 0 ? 0 : t < L ? t : L - 1;
+    Rows r;
+    r.x = *reinterpret_cast<const Raw *>(xr + tc * ld_xz);
+    r.ua = *reinterpret_cast<const Raw *>(du_a + (tok0 + tc) * d_inner + ch);
+    r.ub = *reinterpret_cast<const Raw *>(du_b + (tok0 + tc) * d_inner + ch);
+    return r;
+  };
+  auto value = [&](int64_t t, const Raw &raw, float (&f)[V]) __attribute__((always_inline)) {
+    const bool in = t >= 0 && t < L;
+    if constexpr (V == 1) {
+      f[0] = in ? to_f32(raw) : 0.0f;
+    } else if constexpr (sizeof(T) == 2) {
+      const uint32_t w2 = in ? raw : 0u;
+      f[0] = __uint_as_float(w2 << 16);
+      f[1] = __uint_as_float(w2 & 0xFFFF0000u);
     } else {
-#pragma unroll
-      for (int v = 0; v < V; ++v) x[v] = ua[v] = ub[v] = 0.0f;
+      f[0] = in ? raw.x : 0.0f;
+      f[1] = in ? raw.y : 0.0f;
     }
   };
   // d loss / d c_t from the four inputs x_{t-3..t} of c_t and d u_t (d u = 0 outside the sequence gives 0)
@@ -852,51 +866,62 @@ __global__ __launch_bounds__(256) void conv_bwd_kernel(const T *__restrict__ xz,
     for (int j = 0; j < 4; ++j) acc_w[v][j] = 0.0f;
   }
   // the inputs x_{t-3} .. x_{t+3} and d_c of t .. t+3 slide along the run: one new x row, one new pair
-  // of d u rows and one output row per step.  The rows of kConvBwdAhead steps are requested together
-  // before any of them is used: a thread's loop is otherwise one memory round trip per step.
+  // of d u rows and one output row per step.  The rows of kConvBwdAhead steps are under way at any time: a thread's loop
+  // is otherwise one memory round trip per step.
   float xs[7][V], d0[V], d1[V], d2[V], d3[V];
+  Rows ring[kConvBwdAhead];
   {
-    float ua[3][V], ub[3][V], unused_a[V], unused_b[V];
+    Rows first[6];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) fetch(t0 - 3 + k, xs[k], unused_a, unused_b);
+    for (int k = 0; k < 6; ++k) first[k] = fetch(t0 - 3 + k);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) fetch(t0 + k, xs[3 + k], ua[k], ub[k]);
+    for (int k = 0; k < kConvBwdAhead; ++k) ring[k] = fetch(t0 + 3 + k);
+    float ua[3][V], ub[3][V];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) value(t0 - 3 + k, first[k].x, xs[k]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) value(t0 + k, first[3 + k].ua, ua[k]), value(t0 + k, first[3 + k].ub, ub[k]);
     dc_of(xs[0], xs[1], xs[2], xs[3], ua[0], ub[0], d0);
     dc_of(xs[1], xs[2], xs[3], xs[4], ua[1], ub[1], d1);
     dc_of(xs[2], xs[3], xs[4], xs[5], ua[2], ub[2], d2);
   }
-  for (int64_t tb = t0; tb < t1; tb += kConvBwdAhead) {
-    float xn[kConvBwdAhead][V], una[kConvBwdAhead][V], unb[kConvBwdAhead][V];
+  auto step = [&](int64_t t, int k) __attribute__((always_inline)) {
+    float una[V], unb[V];
+    value(t + 3, ring[k].x, xs[6]);
+    value(t + 3, ring[k].ua, una);
+    value(t + 3, ring[k].ub, unb);
+    ring[k] = fetch(t + kConvBwdAhead < t1 ? t + 3 + kConvBwdAhead : t1 + 2);          // (past the run's end: its last rows again)
+    dc_of(xs[3], xs[4], xs[5], xs[6], una, unb, d3);
+    // x_t feeds c_t (tap 3), c_{t+1} (tap 2), c_{t+2} (tap 1), c_{t+3} (tap 0)
+    float o[V];
 #pragma unroll
-    for (int k = 0; k < kConvBwdAhead; ++k) fetch(tb + 3 + k, xn[k], una[k], unb[k]);
-#pragma unroll
-    for (int k = 0; k < kConvBwdAhead; ++k) {
-      const int64_t t = tb + k;
-      if (t < t1) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) xs[6][v] = xn[k][v];
-        dc_of(xs[3], xs[4], xs[5], xs[6], una[k], unb[k], d3);
-        // x_t feeds c_t (tap 3), c_{t+1} (tap 2), c_{t+2} (tap 1), c_{t+3} (tap 0)
-        float o[V];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          o[v] = w[v][3] * d0[v] + w[v][2] * d1[v] + w[v][1] * d2[v] + w[v][0] * d3[v];
-          acc_b[v] += d0[v];
-          acc_w[v][0] = fmaf(d0[v], xs[0][v], acc_w[v][0]);
-          acc_w[v][1] = fmaf(d0[v], xs[1][v], acc_w[v][1]);
-          acc_w[v][2] = fmaf(d0[v], xs[2][v], acc_w[v][2]);
-          acc_w[v][3] = fmaf(d0[v], xs[3][v], acc_w[v][3]);
-          d0[v] = d1[v]; d1[v] = d2[v]; d2[v] = d3[v];
-        }
-        if constexpr (V == 2) conv_st2(d_xpre + (tok0 + t) * ld_dx + ch, o);
-        else d_xpre[(tok0 + t) * ld_dx + ch] = from_f32<T>(o[0]);
-#pragma unroll
-        for (int j = 0; j < 6; ++j)
-#pragma unroll
-          for (int v = 0; v < V; ++v) xs[j][v] = xs[j + 1][v];
+    for (int v = 0; v < V; ++v) {
+      o[v] = w[v][3] * d0[v] + w[v][2] * d1[v] + w[v][1] * d2[v] + w[v][0] * d3[v];
+      {
+#pragma clang fp contract(off)                                // (the rounded d_c, as everywhere else)
+        acc_b[v] += d0[v];
       }
+      acc_w[v][0] = fmaf(d0[v], xs[0][v], acc_w[v][0]);
+      acc_w[v][1] = fmaf(d0[v], xs[1][v], acc_w[v][1]);
+      acc_w[v][2] = fmaf(d0[v], xs[2][v], acc_w[v][2]);
+      acc_w[v][3] = fmaf(d0[v], xs[3][v], acc_w[v][3]);
+      d0[v] = d1[v]; d1[v] = d2[v]; d2[v] = d3[v];
     }
+    if constexpr (V == 2) conv_st2(d_xpre + (tok0 + t) * ld_dx + ch, o);
+    else d_xpre[(tok0 + t) * ld_dx + ch] = from_f32<T>(o[0]);
+#pragma unroll
+    for (int j = 0; j < 6; ++j)
+#pragma unroll
+      for (int v = 0; v < V; ++v) xs[j][v] = xs[j + 1][v];
+  };
+  int64_t t = t0;
+  for (; t + kConvBwdAhead <= t1; t += kConvBwdAhead) {
+#pragma unroll
+    for (int k = 0; k < kConvBwdAhead; ++k) step(t + k, k);
   }
+#pragma unroll
+  for (int k = 0; k < kConvBwdAhead - 1; ++k)
+    if (t + k < t1) step(t + k, k);
   const int64_t n_runs = gridDim.y;
 #pragma unroll
   for (int v = 0; v < V; ++v) {
