@@ -6,6 +6,7 @@
 
 #include <mutex>
 
+#include "rom_gemm_rule.h"
 #include "rom_internal.h"
 
 // Scratch of rom_step_static: one copy per GPU the library is loaded on, held until the process
@@ -78,10 +79,13 @@ int check_weights(const rom_dims *d, const rom_weights *w) {
   return ROM_OK;
 }
 
-// slices of the x projection's inner dimension for a launch over `rows` rows
+// whether the x projection takes the narrow-output kernel, and the slices of its inner dimension, for a launch over `rows` rows
+bool xproj_is_thin(const rom_dims *d, int64_t rows) {
+  return d->dtype == ROM_DTYPE_BF16 && rows >= kThinMinRows && d->dt_rank + 32 <= kThinMaxCols && d->d_inner % 64 == 0;
+}
 int xproj_slices_for(const rom_dims *d, int64_t rows) {
-  const bool routed_xdt = d->n_experts_xdt > 1;
-  int n = xproj_k_splits(rows, routed_xdt ? d->n_experts : 1, d->d_inner);
+  const int groups = d->n_experts_xdt > 1 ? d->n_experts : 1;
+  const int n = xproj_is_thin(d, rows) ? thin_k_splits(rows, groups, d->dt_rank + 32, d->d_inner) : xproj_k_splits(rows, groups, d->d_inner);
   const int64_t per = ceil_div(ceil_div(d->d_inner, n), 64) * 64;   // whole 64-wide slabs
   return static_cast<int>(ceil_div(d->d_inner, per));
 }
@@ -115,7 +119,8 @@ Plan make_plan(const rom_dims *d, int64_t n_seq, int64_t seq_len) {
   p.xz = take(N * 2 * De * b);
   p.xz_sorted = multi ? take(S * 2 * De * b) : kNone;
   p.u = take(N * De * b);
-  p.xdbl = take((routed_xdt ? S : N) * (R + 32) * 4 * p.xproj_slices);
+  const size_t xproj_rows = routed_xdt ? S : N;
+  p.xdbl = take((xproj_is_thin(d, xproj_rows) ? thin_scratch_rows(xproj_rows) : xproj_rows * p.xproj_slices) * (R + 32) * 4);
   p.dt_low = take(N * R * b);
   p.bc = take(N * 32 * 4);
   p.dt = take(N * De * b);

@@ -580,7 +580,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_bf16_mfma_kernel(const GemmA
 // 128-byte rows.  The compiler does not see these loads (inline asm), so the waits are explicit:
 // every wave issues the same number of loads per half slab, in ring order, and a vmcnt of that number
 // therefore means "everything but the newest half slab I asked for has landed".
-// dma_tile is one tile of that kind: the x projection's (256 rows, one narrow column tile), a whole 256 x 256 one for the
+// dma_tile is one tile of that kind: 256 rows of one narrow column tile (fp32, 161 to 192 columns), a whole 256 x 256 one for the
 // epilogues that the stream kernel has not, and the pieces of the stream kernel's last round.
 constexpr int kDmaBK = 64, kDmaRC = kDmaBK / 8, kDmaSlots = 5;
 constexpr bool kUseDma = true;
@@ -1398,6 +1398,123 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   else dma_tile<128, 2, 2, EPI, WT, 64>(a, tc, smem);
 }
 
+// ------------------------------------------------------------------ bf16 MFMA kernel, narrow fp32 output
+// At most 160 columns (the x projection, and what comes back through the dt projection): a workgroup of four wavefronts owns RB blocks of
+// 32 rows and every column, and a quarter of each 64-wide slab's contraction belongs to each wavefront, so that a fragment is read once per
+// workgroup; the four sums are added through LDS at the end.  Bound by what a CU brings in, a row's share of A and all of its group's W:
+// rows straight into a ring of four slabs in LDS, three under way, and a row count that makes one workgroup per CU (thin_row_blocks); with
+// many rows by memory: rows that the launch before wrote come in at 2.4 TB/s, whoever reads them, while that launch's lines are written back.
+// In 8 experts, in place: 16384 x 160 x 4096 67 us and 10.6 to add two slices, now 62 and 8.7 for one; 16384 x 128 x 4096 62 -> 50; 16384 x
+// 96 x 2048 30.3 + 6.6 -> 23.7 + 5.5; 8192 x 96 x 2048 19.6 -> 15.8, x 64 20.9 -> 18 (256- or 128-row tiles of eight or four wavefronts,
+// of which 72 to 144 workgroups had work).  Requests ahead of the products instead of between them, and every workgroup from
+// the first slab on: 30.2 and 24.2 for the last two but one.
+constexpr int kThinSlots = 4;
+constexpr int thin_slab_bytes(int rb, int nb) { return (rb + nb) * 32 * kDmaBK * 2; }
+template <int RB, int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void gemm_bf16_thin_kernel(const GemmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint4 thin_smem[];
+  constexpr int BM = RB * 32, kSlab = thin_slab_bytes(RB, NB), kInstr = RB + NB;       // requests per wavefront and slab, 8 rows each
+  constexpr int kPitch = NB * 32 + 4;                          // floats: sixteen rows' 16-byte pieces cover the banks
+  static_assert(4 * 32 * kPitch * 4 <= kThinSlots * kSlab, "the sums of 32 rows fit the ring");
+  const TileCoord tc = locate_tile(a, BM, kThinMaxCols);
+  if (!tc.valid) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int split = blockIdx.y, k0 = split * a.k_per_split;
+  const int k_len = (a.K - k0 < a.k_per_split ? a.K - k0 : a.k_per_split), slabs = k_len / kDmaBK;
+  typedef __attribute__((address_space(3))) unsigned char lds_char_t;
+  lds_char_t *lds = (lds_char_t *)thin_smem;
+  const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void *)thin_smem));
+
+  // lane l of an instruction brings 16-byte place l & 7 of row l >> 3 (of eight): chunk place ^ ((row >> 1) & 7)
+  unsigned voff[kInstr];
+#pragma unroll
+  for (int j = 0; j < kInstr; ++j) {
+    const int r = (wave * kInstr + j) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+    if (r < BM) {
+      const int64_t pos = tc.row0 + r < tc.row_end ? tc.row0 + r : tc.row_end - 1;
+      const int64_t row = a.a_rows ? a.a_rows[pos] : pos;
+      voff[j] = static_cast<unsigned>((row * a.lda + k0 + chunk * 8) * 2);
+    } else {
+      const int n = r - BM < a.N ? r - BM : a.N - 1;
+      voff[j] = static_cast<unsigned>((static_cast<int64_t>(n) * a.K + k0 + chunk * 8) * 2);
+    }
+  }
+  const char *const a_base = static_cast<const char *>(a.A);
+  const char *const w_base = static_cast<const char *>(a.W) + static_cast<int64_t>(tc.group) * a.N * a.K * 2;
+  // (workgroups start on different slabs: rows lie a power of two apart, and the same columns of all of them in few channels)
+  const int first = static_cast<int>((static_cast<unsigned>(tc.row0 / BM) * 5) % static_cast<unsigned>(slabs));
+  auto request = [&](int t, int j) __attribute__((always_inline)) {
+    const unsigned at = lds_base + (t & (kThinSlots - 1)) * kSlab + wave * (kInstr * 1024);
+    const int tt = t < slabs ? t : slabs - 1, slab = tt + first < slabs ? tt + first : tt + first - slabs;
+    dma_load_16(at + j * 1024, voff[j], ((wave * kInstr + j) * 8 < BM ? a_base : w_base) + static_cast<int64_t>(slab) * (kDmaBK * 2));
+  };
+
+  const int frag_row = lane & 31, place = ((wave * 2 + (lane >> 5)) ^ ((frag_row >> 1) & 7)) * 16;      // this wavefront's 16 of 64
+  const int frag = frag_row * (kDmaBK * 2) + place;
+  f32x16_t acc[RB][NB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+#pragma unroll
+  for (int t = 0; t < kThinSlots - 1; ++t)
+#pragma unroll
+    for (int j = 0; j < kInstr; ++j) request(t, j);
+  for (int t = 0; t < slabs; ++t) {
+    // this slab has landed (two more are under way), and every wavefront has multiplied the one before
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kThinSlots - 2) * kInstr) : "memory");
+    typedef const __attribute__((address_space(3))) bf16x8_t lds_frag_t;
+    const lds_char_t *sl = lds + (t & (kThinSlots - 1)) * kSlab + frag;
+    bf16x8_t fa[RB], fw[NB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) fa[i] = *(lds_frag_t *)(sl + i * (32 * kDmaBK * 2));
+#pragma unroll
+    for (int j = 0; j < NB; ++j) fw[j] = *(lds_frag_t *)(sl + (RB + j) * (32 * kDmaBK * 2));
+    // the requests go out between the products (past the end: the last slab once more, into a slot that nobody reads)
+    const int ahead = t + kThinSlots - 1;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[j], fa[i], acc[i][j], 0, 0, 0);
+        const int q = i * NB + j;
+#pragma unroll
+        for (int d = q * kInstr / (RB * NB); d < (q + 1) * kInstr / (RB * NB); ++d) request(ahead, d);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // (the slabs asked for past the end: the sums take their place)
+  // lane: row frag_row of a block, columns 8 q + 4 (lane / 32) + 0 .. 3 of a block in elements 4 q ..
+  float *const sums = reinterpret_cast<float *>(thin_smem);
+  float *const C = static_cast<float *>(a.C) + split * a.c_split_stride;
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4 *>(sums + (wave * 32 + frag_row) * kPitch + j * 32 + q * 8 + (lane >> 5) * 4) =
+            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int item = k * 256 + threadIdx.x, r = item / (NB * 8), c = item % (NB * 8) * 4;
+      const int64_t pos = tc.row0 + i * 32 + r;
+      if (pos >= tc.row_end || c >= a.N) continue;
+      float4 v[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[w] = *reinterpret_cast<const float4 *>(sums + (w * 32 + r) * kPitch + c);
+      const int64_t row = a.c_rows ? a.c_rows[pos] : pos;
+      *reinterpret_cast<float4 *>(C + row * a.ldc + c) =
+          make_float4((v[0].x + v[1].x) + (v[2].x + v[3].x), (v[0].y + v[1].y) + (v[2].y + v[3].y),
+                      (v[0].z + v[1].z) + (v[2].z + v[3].z), (v[0].w + v[1].w) + (v[2].w + v[3].w));
+    }
+  }
+}
+
 // ------------------------------------------------------------------ bf16 MFMA kernel, short inner dimension
 // For a K of up to ten 16-wide steps (the dt projection, K = dt_rank, and its input gradient, dt_rank + 32) there is no K loop to
 // pipeline: a tile of the general kernel is one load, a few MFMAs and a long epilogue in sequence, and the epilogue
@@ -1871,6 +1988,35 @@ hipError_t launch_dma(const GemmArgs &a, hipStream_t s) {
                      dim3(WM * WN * 64), kSmem, s, a);
   return hipGetLastError();
 }
+template <int RB, int NB>
+hipError_t launch_thin_t(const GemmArgs &a, hipStream_t s) {
+  constexpr int kSmem = kThinSlots * thin_slab_bytes(RB, NB);
+  static LdsAttrOnce attr;
+  const hipError_t e = attr.ensure(reinterpret_cast<const void *>(&gemm_bf16_thin_kernel<RB, NB>), kSmem);
+  if (e != hipSuccess) return e;
+  const int64_t tiles = a.offsets ? a.M / (RB * 32) + a.n_groups : ceil_div(a.M, RB * 32);
+  hipLaunchKernelGGL((gemm_bf16_thin_kernel<RB, NB>), dim3(static_cast<unsigned>(ceil_div(tiles, 8) * 8), a.k_splits), dim3(256), kSmem, s, a);
+  return hipGetLastError();
+}
+template <int NB>
+hipError_t launch_thin_nb(const GemmArgs &a, hipStream_t s) {
+  switch (thin_row_blocks(a.M, a.offsets ? a.n_groups : 1, a.N, a.k_splits)) {
+    case 1: return launch_thin_t<1, NB>(a, s);
+    case 2: return launch_thin_t<2, NB>(a, s);
+    case 3: return launch_thin_t<3, NB>(a, s);
+    case 4: return launch_thin_t<4, NB>(a, s);
+    default: return launch_thin_t<NB < 5 ? 5 : 4, NB>(a, s);
+  }
+}
+hipError_t launch_thin(const GemmArgs &a, hipStream_t s) {
+  switch ((a.N + 31) / 32) {
+    case 1: return launch_thin_nb<1>(a, s);
+    case 2: return launch_thin_nb<2>(a, s);
+    case 3: return launch_thin_nb<3>(a, s);
+    case 4: return launch_thin_nb<4>(a, s);
+    default: return launch_thin_nb<5>(a, s);
+  }
+}
 constexpr int kStreamWgs = 256;      // one workgroup per CU
 template <int EPI, bool WT = false>
 hipError_t launch_stream(const GemmArgs &a, hipStream_t s) {
@@ -1985,15 +2131,15 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
   }
   if (few && a.c_is_f32) return launch_few_rows<kEpiPlainF32>(a, s);
   if (a.c_is_f32) {
+    // one column tile: every workgroup re-reads the whole weight slice of its group, so take the
+    // tallest row tile (256 rows, 128 on four waves, 64 on two) that still puts a workgroup on
+    // a good part of the CUs, counting the inner-dimension slices
+    const auto wgs = [&](int rows) { return (a.M / rows + a.n_groups) * a.k_splits; };
+    if (a.N <= kThinMaxCols && (a.M >= kThinMinRows || wgs(256) >= kSkinnyMinWgs) && dma_ok(a)) return launch_thin(a, s);
     if (a.N <= 192) {
-      // one column tile: every workgroup re-reads the whole weight slice of its group, so take the
-      // tallest row tile (256 rows, 128 on four waves, 64 on two) that still puts a workgroup on
-      // a good part of the CUs, counting the inner-dimension slices
-      const auto wgs = [&](int rows) { return (a.M / rows + a.n_groups) * a.k_splits; };
       const int tile_rows = wgs(256) >= kSkinnyMinWgs ? 256 : (wgs(128) >= kSkinnyMinWgs ? 128 : 64);
       switch ((a.N + 31) / 32) {
 #define ROM_SKINNY(NN)                                                               \
-  if (tile_rows == 256 && dma_ok(a)) return launch_dma<NN, 8, 1, kEpiPlainF32>(a, s); \
   return tile_rows == 256 ? launch_mfma<256, NN, 4, 1, kEpiPlainF32>(a, s)           \
        : tile_rows == 128 ? launch_mfma<128, NN, 4, 1, kEpiPlainF32>(a, s)           \
                           : launch_mfma<64, NN, 2, 1, kEpiPlainF32>(a, s)
@@ -2002,7 +2148,9 @@ hipError_t launch_grouped_gemm(const GemmArgs &args, hipStream_t s) {
         case 3: ROM_SKINNY(96);
         case 4: ROM_SKINNY(128);
         case 5: ROM_SKINNY(160);
-        default: ROM_SKINNY(192);
+        default:
+          if (tile_rows == 256 && dma_ok(a)) return launch_dma<192, 8, 1, kEpiPlainF32>(a, s);
+          ROM_SKINNY(192);
 #undef ROM_SKINNY
       }
     }

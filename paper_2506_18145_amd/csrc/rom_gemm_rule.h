@@ -65,6 +65,42 @@ inline GemmTile gemm_tile(const GemmShape &s) {
   return stream ? GemmTile::kStream : GemmTile::k128;
 }
 
+// Blocks of 32 rows per workgroup of the narrow-output kernel: fewest bytes into a CU (its rows of A and every row of W), for as many
+// rounds as there are more workgroups than CUs.  (Five blocks of rows by five of columns do not fit the registers.)
+constexpr int kThinMinRows = 1024, kThinMaxCols = 160;
+inline int64_t thin_blocks_per_cu(int64_t M, int groups, int nb, int k_splits, int rb) {
+  const int64_t wgs = (groups > 1 ? M / (rb * 32) + groups : (M + rb * 32 - 1) / (rb * 32)) * k_splits;
+  return (wgs + 255) / 256 * (rb + nb);
+}
+inline int thin_row_blocks(int64_t M, int groups, int N, int k_splits) {
+  const int nb = (N + 31) / 32;
+  int best = 1;
+  for (int rb = 2; rb <= (nb < 5 ? 5 : 4); ++rb)
+    if (thin_blocks_per_cu(M, groups, nb, k_splits, rb) < thin_blocks_per_cu(M, groups, nb, k_splits, best)) best = rb;
+  return best;
+}
+// Slices of its contraction, in us: what a CU brings in at 45 KB/us, or all rows once at 2.6 TB/s (they were written just before, and what
+// that pushed out of the caches is still on its way to memory), and partial sums written and read at 4 TB/s.
+// 3063 x 128 x 3072 in 8 groups, GEMM alone: one slice 19.9 us, two 13.3; 16384 x 160 x 4096 one 65, two 75 (partial sums not counted).
+// Slices times rows stay below a limit, so that scratch that is large enough for a call is so for every smaller one (thin_scratch_rows).
+constexpr int64_t kThinSliceRows = 16384;
+inline int64_t thin_scratch_rows(int64_t M) {
+  const int64_t most = 8 * M < kThinSliceRows ? 8 * M : kThinSliceRows;
+  return M > most ? M : most;
+}
+inline int thin_k_splits(int64_t M, int groups, int N, int K) {
+  const int nb = (N + 31) / 32;
+  int best = 1;
+  double best_us = 0.0;
+  for (int s = 1; s <= 8 && s * 256 <= K && (s == 1 || s * M <= kThinSliceRows); ++s) {
+    const double fill = static_cast<double>(thin_blocks_per_cu(M, groups, nb, s, thin_row_blocks(M, groups, N, s))) * (K / s) * 64.0 / 45e3;
+    const double rows = static_cast<double>(M) * K * 2.0 / 2.6e6;
+    const double us = (fill > rows ? fill : rows) + s * (static_cast<double>(M) * N * 8.0 / 4e6);
+    if (s == 1 || us < best_us) best = s, best_us = us;
+  }
+  return best;
+}
+
 // Which calls take the few-rows kernel: it gains while most experts have no row and few workgroups stream the weights.  Kernel
 // alone, us, against the tiled kernels' (weights not read just before): one row, 8 groups, 8192 x 2048 8.7 / 27.9, 8 rows
 // 33 / 47, 2048 x 4096 19.7 / 30.2, 3072 x 1536 13.7 / 13.5.  Over a short K, with more workgroups than the CUs hold at

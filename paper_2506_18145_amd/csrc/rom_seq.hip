@@ -1457,6 +1457,7 @@ hipError_t launch_ffn_prep(int dtype, const int32_t *perm, int top_k, int64_t n_
 }
 
 int xproj_k_splits(int64_t rows, int n_groups, int d_inner) {
+  // (fp32, and bf16 calls that the narrow-output kernel does not take: thin_k_splits.)
   // The x projection has a single column tile, so its grid is the number of 256-row tiles: far
   // fewer than CUs.  Slicing the long inner dimension shortens every workgroup's slab loop but
   // each slice writes fp32 partial sums that split_xdbl has to read back.  Pick the slice count

@@ -288,3 +288,15 @@ def test_gdn_segments_fill_256_cus_once(lib, d_k, n_heads, batch):
     units = batch * n_heads * segments if segments > 1 else 0
     want = up(frags + units * (2 * d_k * 64 + d_k * d_k) * 4) - up(frags)
     assert total(batch) - conv(batch) - (total(256) - conv(256)) == want
+
+
+@pytest.mark.parametrize("d_model,d_inner,dt_rank,n_experts", [(768, 1536, 48, 8), (2048, 4096, 128, 8), (64, 512, 128, 1)])
+def test_workspace_serves_smaller_calls(d_model, d_inner, dt_rank, n_experts):
+    """Slices of the x projection, like the scan's chunks, depend on the number of rows: room for a call is room for a smaller one."""
+    from paper_2506_18145_amd import binding
+    d = _dims(d_model=d_model, d_inner=d_inner, dt_rank=dt_rank, n_experts=n_experts, n_experts_xdt=n_experts, top_k=1, dtype=1)
+    most = 0
+    for n in (*range(1, 3000), *range(3000, 40000, 61)):
+        need = binding.rom_workspace_bytes(d, 1, n)
+        assert need >= most, n
+        most = need
