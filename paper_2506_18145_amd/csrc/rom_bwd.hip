@@ -2224,24 +2224,116 @@ __global__ __launch_bounds__(256) void rmsnorm_wgrad_partial_kernel(const T *__r
   part[static_cast<int64_t>(blockIdx.y) * d_model + c] = acc;
 }
 
-// out[c] = sum over parts: a block owns 64 columns, its four waves each add every fourth part in part
-// order, then the four sums are added in wave order (a fixed order either way)
-__global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ part, int n_parts, int n_cols,
-                                                     float *__restrict__ out) {
-  __shared__ float sums[4][64];
+// Both in one pass over x, d_xn and d_skip, for rows of up to 256 NP columns: a wavefront keeps a row in registers, with the next one on its
+// way, and its columns' sums for d_norm_w over its rows (every fourth of the block's).  Bound by memory (268 MB, 5 TB/s): 16384 x 2048 51-54 us
+// and 5 to add the parts up, in two passes 65-68, 26-31 and 21 (256 parts, four wavefronts for 64 columns).
+template <typename T, int NP>
+__global__ __launch_bounds__(256) void rmsnorm_bwd_rows_kernel(const T *__restrict__ x, const float *__restrict__ norm_w,
+                                                               const float *__restrict__ rstd, const T *__restrict__ d_xn,
+                                                               const T *__restrict__ d_skip, int64_t n_rows, int d_model,
+                                                               int rows_per_block, T *__restrict__ d_x, float *__restrict__ part) {
+  __shared__ float sums[4][NP * 256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rows_per_block;
+  const int64_t r1 = r0 + rows_per_block < n_rows ? r0 + rows_per_block : n_rows;
+  using Raw = std::conditional_t<sizeof(T) == 2, bwd_u32x2, bwd_f32x4>;
+  struct Row {
+    Raw x[NP], d[NP], s[NP];
+    float r;
+  };
+  bool in[NP];
+  float g[NP][4], acc[NP][4];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int c = p * 256 + lane * 4;
+    in[p] = c < d_model;
+    const float4 w = *reinterpret_cast<const float4 *>(norm_w + (in[p] ? c : 0));
+    g[p][0] = w.x; g[p][1] = w.y; g[p][2] = w.z; g[p][3] = w.w;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[p][q] = 0.0f;
+  }
+  auto fetch = [&](int64_t row) __attribute__((always_inline)) {
+    Row v;
+    const int64_t at = (row < r1 ? row : r1 - 1) * d_model;
+    v.r = rstd[row < r1 ? row : r1 - 1];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int64_t c = at + (in[p] ? p * 256 + lane * 4 : 0);
+      v.x[p] = *reinterpret_cast<const Raw *>(x + c);
+      v.d[p] = *reinterpret_cast<const Raw *>(d_xn + c);
+      if (d_skip) v.s[p] = *reinterpret_cast<const Raw *>(d_skip + c);
+    }
+    return v;
+  };
+  auto unpack = [](const Raw &w, float (&f)[4]) __attribute__((always_inline)) {
+    if constexpr (sizeof(T) == 2) {
+      f[0] = __uint_as_float(w.x << 16); f[1] = __uint_as_float(w.x & 0xFFFF0000u);
+      f[2] = __uint_as_float(w.y << 16); f[3] = __uint_as_float(w.y & 0xFFFF0000u);
+    } else {
+      f[0] = w.x; f[1] = w.y; f[2] = w.z; f[3] = w.w;
+    }
+  };
+  Row next = fetch(r0 + wave);
+  for (int64_t row = r0 + wave; row < r1; row += 4) {
+    const Row cur = next;
+    next = fetch(row + 4);
+    const float r = cur.r;
+    float dot = 0.0f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      float v[4], dv[4];
+      unpack(cur.x[p], v);
+      unpack(cur.d[p], dv);
+      if (in[p]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          dot = fmaf(dv[q] * g[p][q], v[q] * r, dot);
+          acc[p][q] = fmaf(dv[q] * v[q], r, acc[p][q]);
+        }
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off);
+    const float m = dot / static_cast<float>(d_model);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (!in[p]) continue;
+      float v[4], dv[4], sk[4] = {0.f, 0.f, 0.f, 0.f}, o[4];
+      unpack(cur.x[p], v);
+      unpack(cur.d[p], dv);
+      if (d_skip) unpack(cur.s[p], sk);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = sk[q] + r * (dv[q] * g[p][q] - v[q] * r * m);
+      bwd_store4(d_x + row * d_model + p * 256 + lane * 4, o);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+    *reinterpret_cast<float4 *>(&sums[wave][p * 256 + lane * 4]) = make_float4(acc[p][0], acc[p][1], acc[p][2], acc[p][3]);
+  __syncthreads();
+  for (int c = threadIdx.x; c < d_model; c += 256)
+    part[static_cast<int64_t>(blockIdx.x) * d_model + c] = (sums[0][c] + sums[1][c]) + (sums[2][c] + sums[3][c]);
+}
+
+// out[c] = sum over parts, 64 columns a workgroup (see kFinishWaves); a fixed order
+__global__ __launch_bounds__(kFinishWaves * 64) void colsum_kernel(const float *__restrict__ part, int n_parts, int n_cols,
+                                                                   float *__restrict__ out) {
+  __shared__ float sums[kFinishWaves][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
   float acc = 0.0f;
-  if (c < n_cols)
-    for (int p = q; p < n_parts; p += 4) acc += part[static_cast<int64_t>(p) * n_cols + c];
-  sums[q][lane] = acc;
-  __syncthreads();
-  if (q == 0 && c < n_cols) out[c] = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
+  if (c < n_cols) {
+#pragma unroll 8
+    for (int p = q; p < n_parts; p += kFinishWaves) acc += part[static_cast<int64_t>(p) * n_cols + c];
+  }
+  const float tot = finish_total(acc, sums, lane, q);
+  if (q == 0 && c < n_cols) out[c] = tot;
 }
 }  // namespace
 
+// at least 16 rows a part; two workgroups of the one-pass kernel per CU
 int rmsnorm_wgrad_parts(int64_t n_rows) {
-  const int64_t parts = (n_rows + 63) / 64;
+  const int64_t parts = (n_rows + 15) / 16;
   return static_cast<int>(parts < 512 ? (parts < 1 ? 1 : parts) : 512);
 }
 
@@ -2258,30 +2350,39 @@ hipError_t launch_rmsnorm_forward(int dtype, const void *x, const float *norm_w,
   return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_rmsnorm_backward_t(const T *x, const float *norm_w, const float *rstd, const T *d_xn, const T *d_skip, int64_t n_rows,
+                                     int d_model, T *d_x, float *part, float *d_norm_w, hipStream_t s) {
+  const int parts = rmsnorm_wgrad_parts(n_rows);
+  const int rows_per_block = static_cast<int>(ceil_div(n_rows, parts));
+#define ROM_RMS_ROWS(NP)                                                                                                               \
+  hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<T, NP>), dim3(static_cast<unsigned>(parts)), dim3(256), 0, s, x, norm_w, rstd, d_xn, d_skip, \
+                     n_rows, d_model, rows_per_block, d_x, part)
+  if (d_model <= 512) ROM_RMS_ROWS(2);
+  else if (d_model <= 1024) ROM_RMS_ROWS(4);
+  else if (d_model <= 1536) ROM_RMS_ROWS(6);
+  else if (d_model <= 2048) ROM_RMS_ROWS(8);
+#undef ROM_RMS_ROWS
+  else {                                                       // a row does not fit the registers: two passes
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<T>), dim3(static_cast<unsigned>(ceil_div(n_rows, 4))), dim3(256), 0, s, x, norm_w, rstd, d_xn,
+                       d_skip, n_rows, d_model, d_x);
+    hipLaunchKernelGGL((rmsnorm_wgrad_partial_kernel<T>), dim3(static_cast<unsigned>(ceil_div(d_model, 256)), static_cast<unsigned>(parts)),
+                       dim3(256), 0, s, x, rstd, d_xn, n_rows, d_model, rows_per_block, part);
+  }
+  hipLaunchKernelGGL(colsum_kernel, dim3(static_cast<unsigned>(ceil_div(d_model, 64))), dim3(kFinishWaves * 64), 0, s, part, parts,
+                     d_model, d_norm_w);
+  return hipGetLastError();
+}
+
 hipError_t launch_rmsnorm_backward(int dtype, const void *x, const float *norm_w, const float *rstd, const void *d_xn,
                                    const void *d_skip, int64_t n_rows, int d_model, void *d_x, float *part,
                                    float *d_norm_w, hipStream_t s) {
   if (d_model % 4 != 0) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(ceil_div(n_rows, 4)));
-  const int parts = rmsnorm_wgrad_parts(n_rows);
-  const int rows_per_block = static_cast<int>(ceil_div(n_rows, parts));
-  const dim3 grid_w(static_cast<unsigned>(ceil_div(d_model, 256)), static_cast<unsigned>(parts));
-  if (dtype == ROM_DTYPE_BF16) {
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(x), norm_w, rstd,
-                       static_cast<const bf16_t *>(d_xn), static_cast<const bf16_t *>(d_skip), n_rows, d_model,
-                       static_cast<bf16_t *>(d_x));
-    hipLaunchKernelGGL((rmsnorm_wgrad_partial_kernel<bf16_t>), grid_w, dim3(256), 0, s, static_cast<const bf16_t *>(x),
-                       rstd, static_cast<const bf16_t *>(d_xn), n_rows, d_model, rows_per_block, part);
-  } else {
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<float>), grid, dim3(256), 0, s, static_cast<const float *>(x), norm_w, rstd,
-                       static_cast<const float *>(d_xn), static_cast<const float *>(d_skip), n_rows, d_model,
-                       static_cast<float *>(d_x));
-    hipLaunchKernelGGL((rmsnorm_wgrad_partial_kernel<float>), grid_w, dim3(256), 0, s, static_cast<const float *>(x),
-                       rstd, static_cast<const float *>(d_xn), n_rows, d_model, rows_per_block, part);
-  }
-  hipLaunchKernelGGL(colsum_kernel, dim3(static_cast<unsigned>(ceil_div(d_model, 64))), dim3(256), 0, s, part, parts,
-                     d_model, d_norm_w);
-  return hipGetLastError();
+  if (dtype == ROM_DTYPE_BF16)
+    return launch_rmsnorm_backward_t(static_cast<const bf16_t *>(x), norm_w, rstd, static_cast<const bf16_t *>(d_xn),
+                                     static_cast<const bf16_t *>(d_skip), n_rows, d_model, static_cast<bf16_t *>(d_x), part, d_norm_w, s);
+  return launch_rmsnorm_backward_t(static_cast<const float *>(x), norm_w, rstd, static_cast<const float *>(d_xn),
+                                   static_cast<const float *>(d_skip), n_rows, d_model, static_cast<float *>(d_x), part, d_norm_w, s);
 }
 
 template <int TW, int NB, bool THIN_A>
