@@ -758,28 +758,46 @@ __global__ __launch_bounds__(kFinishWaves * 64) void router_wgrad_finish_kernel(
   else if (d_b_router) d_b_router[e] = tot;
 }
 
-// d_x[n, d] = dx_in[n, d] + sum_e d_logits[n, e] * W_r[e, d]; a thread owns four consecutive columns
+// d_x[n, d] = dx_in[n, d] + sum_e d_logits[n, e] * W_r[e, d].  A wavefront owns 512 columns, eight consecutive ones a lane (d_model is
+// a multiple of 8), of kDxRows tokens: their router weights are loaded once for all of them, and d_logits, uniform, through the scalar cache.
+// Bound by memory: 16384 x 2048 with 8 experts 47 us a token at a time and an index division per thread, now 33-34; 8192 x 1024 13 -> 12.
+constexpr int kDxRows = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void dx_finish_kernel(const T *__restrict__ dx_in, const float *__restrict__ d_logits,
                                                         const T *__restrict__ w_router, int64_t n_tok, int d_model,
                                                         int n_experts, T *__restrict__ d_x) {
-  // eight consecutive columns of one token per thread (d_model is a multiple of 8)
-  const int64_t i = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * 8;
-  if (i >= n_tok * d_model) return;
-  const int64_t n = i / d_model;
-  const int d = static_cast<int>(i % d_model);
-  float v[8], wv[8];
-  bwd_load4(dx_in + i, v);
-  bwd_load4(dx_in + i + 4, v + 4);
+  const int col_waves = (d_model + 511) / 512, lane = threadIdx.x & 63;
+  const int64_t wv_id = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t n0 = wv_id / col_waves * kDxRows;
+  const int d = static_cast<int>(wv_id % col_waves) * 512 + lane * 8;
+  if (n0 >= n_tok || d >= d_model) return;
+  const int rows = static_cast<int>(n_tok - n0 < kDxRows ? n_tok - n0 : kDxRows);
+  typedef const __attribute__((address_space(4))) float const_f32_t;
+  const uintptr_t dl = reinterpret_cast<uintptr_t>(d_logits + n0 * n_experts);
+  float v[kDxRows][8];
+#pragma unroll
+  for (int r = 0; r < kDxRows; ++r) {
+    const int64_t at = (n0 + (r < rows ? r : rows - 1)) * d_model + d;
+    bwd_load4(dx_in + at, v[r]);
+    bwd_load4(dx_in + at + 4, v[r] + 4);
+  }
   for (int e = 0; e < n_experts; ++e) {
-    const float dl = d_logits[n * n_experts + e];
+    float wv[8];
     bwd_load4(w_router + static_cast<int64_t>(e) * d_model + d, wv);
     bwd_load4(w_router + static_cast<int64_t>(e) * d_model + d + 4, wv + 4);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = fmaf(dl, wv[q], v[q]);
+    for (int r = 0; r < kDxRows; ++r) {
+      const float g = *reinterpret_cast<const_f32_t *>(dl + static_cast<uint32_t>((r < rows ? r : rows - 1) * n_experts + e) * 4u);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[r][q] = fmaf(g, wv[q], v[r][q]);
+    }
   }
-  bwd_store4(d_x + i, v);
-  bwd_store4(d_x + i + 4, v + 4);
+#pragma unroll
+  for (int r = 0; r < kDxRows; ++r) {
+    if (r >= rows) break;
+    bwd_store4(d_x + (n0 + r) * d_model + d, v[r]);
+    bwd_store4(d_x + (n0 + r) * d_model + d + 4, v[r] + 4);
+  }
 }
 
 // ------------------------------------------------------------------ adjoint of conv + SiLU, Eq. (2)
@@ -1867,21 +1885,27 @@ __global__ __launch_bounds__(2 * TW) void wgrad_bf16_thin_kernel(
 // rows scaled by a per-row factor (the gate weight of Eq. (12) on d_out):
 // dst[r, :] = scale[scale_idx ? scale_idx[r] : r] * src[src_idx ? src_idx[r] : r, :]
 // (top-K: r is a sorted position, src_idx its token, scale_idx its slot)
+// A wavefront per row, eight consecutive columns a lane and step: 16384 x 2048 30-36 us with four columns a thread and two index divisions, now
+// 22-23; 8192 x 1024 8.4 -> 6.5.
 template <typename T>
 __global__ __launch_bounds__(256) void scale_rows_kernel(const T *__restrict__ src, const float *__restrict__ scale,
                                                          const int32_t *__restrict__ src_idx,
                                                          const int32_t *__restrict__ scale_idx, int64_t n_rows,
                                                          int n_cols, T *__restrict__ dst) {
-  const int64_t i = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * 4;   // four consecutive columns
-  if (i >= n_rows * n_cols) return;
-  const int64_t r = i / n_cols, c = i % n_cols;
+  const int64_t r = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (r >= n_rows) return;
   const int64_t rs = src_idx ? src_idx[r] : r, rg = scale_idx ? scale_idx[r] : r;
   const float g = scale[rg];
-  float v[4];
-  bwd_load4(src + rs * n_cols + c, v);
+#pragma unroll 4
+  for (int c = (threadIdx.x & 63) * 8; c < n_cols; c += 512) {
+    float v[8];
+    bwd_load4(src + rs * n_cols + c, v);
+    bwd_load4(src + rs * n_cols + c + 4, v + 4);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] *= g;
-  bwd_store4(dst + i, v);
+    for (int q = 0; q < 8; ++q) v[q] *= g;
+    bwd_store4(dst + r * n_cols + c, v);
+    bwd_store4(dst + r * n_cols + c + 4, v + 4);
+  }
 }
 
 // the same contraction on the plain ALUs (fp32, or bf16 shapes the MFMA kernel does not take): 64 x 64 tiles
@@ -2054,7 +2078,7 @@ hipError_t launch_router_backward(int dtype, const float *logits, const int32_t 
 
 hipError_t launch_dx_finish(int dtype, const void *dx_in, const float *d_logits, const void *w_router, int64_t n_tok,
                             int d_model, int n_experts, void *d_x, hipStream_t s) {
-  const dim3 grid = grid1d(n_tok * d_model / 8, 256);      // d_model is a multiple of 8
+  const dim3 grid = grid1d(ceil_div(n_tok, kDxRows) * ceil_div(d_model, 512), 4);
   if (dtype == ROM_DTYPE_BF16)
     hipLaunchKernelGGL((dx_finish_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(dx_in), d_logits,
                        static_cast<const bf16_t *>(w_router), n_tok, d_model, n_experts, static_cast<bf16_t *>(d_x));
@@ -2125,8 +2149,8 @@ hipError_t launch_pack_dxdbl(int dtype, const float *d_dt_low, const float *d_bc
 
 hipError_t launch_scale_rows(int dtype, const void *src, const float *scale, const int32_t *src_idx,
                              const int32_t *scale_idx, int64_t n_rows, int n_cols, void *dst, hipStream_t s) {
-  if (n_cols % 4 != 0) return hipErrorInvalidValue;       // (d_model is a multiple of 8)
-  const dim3 grid = grid1d(n_rows * n_cols / 4, 256);
+  if (n_cols % 8 != 0) return hipErrorInvalidValue;       // (d_model is a multiple of 8)
+  const dim3 grid = grid1d(n_rows, 4);
   if (dtype == ROM_DTYPE_BF16)
     hipLaunchKernelGGL((scale_rows_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(src), scale,
                        src_idx, scale_idx, n_rows, n_cols, static_cast<bf16_t *>(dst));
