@@ -759,9 +759,9 @@ __global__ __launch_bounds__(kFinishWaves * 64) void router_wgrad_finish_kernel(
 }
 
 // d_x[n, d] = dx_in[n, d] + sum_e d_logits[n, e] * W_r[e, d].  A wavefront owns 512 columns, eight consecutive ones a lane (d_model is
-// a multiple of 8), of kDxRows tokens: their router weights are loaded once for all of them, and d_logits, uniform, through the scalar cache.
-// Bound by memory: 16384 x 2048 with 8 experts 47 us a token at a time and an index division per thread, now 33-34; 8192 x 1024 13 -> 12.
-constexpr int kDxRows = 8;
+// a multiple of 8), of kDxRows tokens: the router weights are loaded once for all of them, and d_logits, uniform, through the scalar cache.
+// Bound by memory: 16384 x 2048 with 8 experts 47 us a token at a time and an index division per thread, now 31; 8192 x 1024 12.7 -> 9.8.
+constexpr int kDxRows = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void dx_finish_kernel(const T *__restrict__ dx_in, const float *__restrict__ d_logits,
                                                         const T *__restrict__ w_router, int64_t n_tok, int d_model,
@@ -781,6 +781,7 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const T *__restrict__ dx
     bwd_load4(dx_in + at, v[r]);
     bwd_load4(dx_in + at + 4, v[r] + 4);
   }
+#pragma unroll 4
   for (int e = 0; e < n_experts; ++e) {
     float wv[8];
     bwd_load4(w_router + static_cast<int64_t>(e) * d_model + d, wv);
@@ -1885,27 +1886,27 @@ __global__ __launch_bounds__(2 * TW) void wgrad_bf16_thin_kernel(
 // rows scaled by a per-row factor (the gate weight of Eq. (12) on d_out):
 // dst[r, :] = scale[scale_idx ? scale_idx[r] : r] * src[src_idx ? src_idx[r] : r, :]
 // (top-K: r is a sorted position, src_idx its token, scale_idx its slot)
-// A wavefront per row, eight consecutive columns a lane and step: 16384 x 2048 30-36 us with four columns a thread and two index divisions, now
+// A wavefront per 512 columns of a row, eight consecutive ones a lane: 16384 x 2048 30-36 us with four columns a thread and two index divisions, now
 // 22-23; 8192 x 1024 8.4 -> 6.5.
 template <typename T>
 __global__ __launch_bounds__(256) void scale_rows_kernel(const T *__restrict__ src, const float *__restrict__ scale,
                                                          const int32_t *__restrict__ src_idx,
                                                          const int32_t *__restrict__ scale_idx, int64_t n_rows,
                                                          int n_cols, T *__restrict__ dst) {
-  const int64_t r = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (r >= n_rows) return;
+  const int col_waves = (n_cols + 511) / 512;
+  const int64_t wv_id = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r = wv_id / col_waves;
+  const int c = static_cast<int>(wv_id % col_waves) * 512 + (threadIdx.x & 63) * 8;
+  if (r >= n_rows || c >= n_cols) return;
   const int64_t rs = src_idx ? src_idx[r] : r, rg = scale_idx ? scale_idx[r] : r;
   const float g = scale[rg];
-#pragma unroll 4
-  for (int c = (threadIdx.x & 63) * 8; c < n_cols; c += 512) {
-    float v[8];
-    bwd_load4(src + rs * n_cols + c, v);
-    bwd_load4(src + rs * n_cols + c + 4, v + 4);
+  float v[8];
+  bwd_load4(src + rs * n_cols + c, v);
+  bwd_load4(src + rs * n_cols + c + 4, v + 4);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] *= g;
-    bwd_store4(dst + r * n_cols + c, v);
-    bwd_store4(dst + r * n_cols + c + 4, v + 4);
-  }
+  for (int q = 0; q < 8; ++q) v[q] *= g;
+  bwd_store4(dst + r * n_cols + c, v);
+  bwd_store4(dst + r * n_cols + c + 4, v + 4);
 }
 
 // the same contraction on the plain ALUs (fp32, or bf16 shapes the MFMA kernel does not take): 64 x 64 tiles
@@ -2150,7 +2151,7 @@ hipError_t launch_pack_dxdbl(int dtype, const float *d_dt_low, const float *d_bc
 hipError_t launch_scale_rows(int dtype, const void *src, const float *scale, const int32_t *src_idx,
                              const int32_t *scale_idx, int64_t n_rows, int n_cols, void *dst, hipStream_t s) {
   if (n_cols % 8 != 0) return hipErrorInvalidValue;       // (d_model is a multiple of 8)
-  const dim3 grid = grid1d(n_rows, 4);
+  const dim3 grid = grid1d(n_rows * ceil_div(n_cols, 512), 4);
   if (dtype == ROM_DTYPE_BF16)
     hipLaunchKernelGGL((scale_rows_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(src), scale,
                        src_idx, scale_idx, n_rows, n_cols, static_cast<bf16_t *>(dst));
