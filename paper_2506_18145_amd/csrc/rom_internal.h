@@ -207,8 +207,8 @@ hipError_t launch_rms_rows(const void *in, const float *w, float eps, int64_t n_
 //   qkv bf16 [B*L, ld_qkv] after conv + SiLU: q of head h at q_col + d_k h, k at k_col + d_k h, v at v_col + 64 h;
 //   proj bf16 [B*L, ld_p]: z of head h at columns 64 h, the beta logit at b_col + h, the decay logit at a_col + h;
 //   dt_bias, A_log f32 [n_heads]; norm_w f32 [64]; s_in / s_out f32 [B, n_heads, d_k, 64] or NULL;
-//   y bf16 [B*L, ld_y]; carry: f32 scratch of gdn_carry_bytes() (operand fragments of
-//   every chunk, then the segment carries of long, few sequences)
+//   y bf16 [B*L, ld_y]; carry: f32 scratch of gdn_carry_bytes() (operand fragments, decay sums
+//   and betas of every chunk, then the segment carries of long, few sequences)
 bool gdn_supported(int d_k, int d_v);
 size_t gdn_carry_bytes(int64_t B, int64_t L, int n_heads, int d_k);
 hipError_t launch_gdn_scan(const void *qkv, int64_t ld_qkv, int q_col, int k_col, int v_col, const void *proj, int64_t ld_p,

@@ -5,6 +5,7 @@
 //   1 / rms per routed row, SwiGLU for fp32).  All of this is bandwidth / plain-ALU work: no MFMA here.
 #include <type_traits>
 
+#include "rom_dpp.h"
 #include "rom_internal.h"
 #include "rom_scan_rule.h"
 
@@ -263,9 +264,6 @@ constexpr bool kScanDouble = true;
 constexpr int kScanGroups = kScanTile / 16;
 constexpr int kBcPitch = kScanTile + 4;     // floats; keeps 16-byte alignment of the row reads
 
-template <int CTRL> __device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
 constexpr int kDppQuadXor1 = 0xB1;      // quad_perm [1,0,3,2]
 constexpr int kDppQuadRev = 0x1B;       // quad_perm [3,2,1,0]
 constexpr int kDppHalfMirror = 0x141;   // lane i <-> 7 - i inside each 8
@@ -300,33 +298,12 @@ template <> struct StepSeq<-1> {
 };
 
 // p[j] = hs[j] * cv[j]; sum p[j] over the 16 lanes of a row for every j; lane i returns the
-// total of p[i].  Contraction is off so that every "x + dpp(x)" stays one DPP add.
+// total of p[i].
 __device__ __forceinline__ float transpose_reduce16(const float *hs, const float *cv, int n) {
-#pragma clang fp contract(off)
-  float a[8], b[4], c[2];
-  const bool hi8 = (n & 8) != 0, hi4 = (n & 4) != 0, hi2 = (n & 2) != 0, hi1 = (n & 1) != 0;
+  float p[16];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float pl = hs[j] * cv[j], ph = hs[j + 8] * cv[j + 8];
-    const float lo = dpp<kDppRowMirror>(pl) + pl;
-    const float hi = dpp<kDppRowMirror>(ph) + ph;
-    a[j] = hi8 ? hi : lo;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float lo = dpp<kDppHalfMirror>(a[j]) + a[j];
-    const float hi = dpp<kDppHalfMirror>(a[j + 4]) + a[j + 4];
-    b[j] = hi4 ? hi : lo;
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const float lo = dpp<kDppQuadRev>(b[j]) + b[j];
-    const float hi = dpp<kDppQuadRev>(b[j + 2]) + b[j + 2];
-    c[j] = hi2 ? hi : lo;
-  }
-  const float lo = dpp<kDppQuadXor1>(c[0]) + c[0];
-  const float hi = dpp<kDppQuadXor1>(c[1]) + c[1];
-  return hi1 ? hi : lo;
+  for (int j = 0; j < 16; ++j) p[j] = hs[j] * cv[j];
+  return transpose_sum16(p, n);
 }
 
 // sum of v over the 16 lanes of a row, in every lane
@@ -793,13 +770,13 @@ __global__ __launch_bounds__(HELPERS ? 512 : 256) void scan_pipe_kernel(
 // is, per state, v_mul, v_exp, v_mul, v_fma and (outputs) v_fma: five instructions for 64 (channel, state) pairs
 // where the lane = (channel, state) layout pays nine, four of them for the sum over the states.
 // The price is parallelism (d_inner / 64 wavefronts per sequence), so time is cut into chunks until the chip has
-// kLaneWaves wavefronts: a state-only pass leaves every chunk's end state from zero (chunk_q [B][chunk][16][d_inner])
+// kLaneWaves wavefronts (scan_lane_chunks; chunks of 64 steps or more, of 32 in small calls): a state-only pass leaves every chunk's end state from zero (chunk_q [B][chunk][16][d_inner])
 // and its sum of dt (chunk_s [B][chunk][d_inner]); scan_fold_kernel walks h <- exp(A sum dt_k) h + q_k over them and
 // leaves every chunk's start state in place of its end state, from which the full pass runs.
 // Bound by ALU issue, which is busy all of the time: 96 vector instructions per step of the full pass, 70 of the state-only
 // one, at 4.7 and 4.9 clocks each (v_exp takes 8; an instruction with an SGPR operand takes 4.4 where two register-only ones of
 // different wavefronts take 5.5 together).  16384 x 4096 bf16, launches alone: 351 us, lane = (channel, state) 385; within
-// a layer, behind a GEMM, the full pass takes 201 us, the state-only pass 150 and the fold 13.
+// a layer, behind a GEMM, the full pass takes 210 us, the state-only pass 160 and the fold 11.
 constexpr int kLaneRun = 8;
 typedef float f32x16s_t __attribute__((ext_vector_type(16)));
 typedef const __attribute__((address_space(4))) f32x16s_t const_f32x16_t;
