@@ -14,9 +14,10 @@ template <int CTRL> __device__ __forceinline__ float dpp(float v) {
 // Sixteen values per lane, each to be summed over the 16 lanes of a row: a butterfly that halves
 // the number of live values at every stage (the lanes with bit 3 / 2 / 1 / 0 of n set keep the upper
 // half) leaves the row total of p[n] in lane n - 30 DPP adds and 3 selects instead of 64 adds.  In the first two stages
-// the upper half's adds are written by their lanes' banks alone (with selects, 12 more instructions, the adjoint scan's main kernel on
-// 16384 x 4096 took 1064 us against 1016, the scan of 3 x 1021 x 3072 73.5 against 70.7; the compiler has no form for an add whose other lanes keep their value).  A DPP read wants two instructions between it and the
-// write of its source: the block starts with a wait for what its caller wrote, and within it a source is five and more instructions old.
+// the upper half's adds are written by their lanes' banks alone; with selects, 12 more instructions, the adjoint scan's main kernel took 1064 us on
+// 16384 x 4096 (now 1016), the scan of 3 x 1021 x 3072 73.5 (70.7).  The compiler has no form for an add whose other lanes keep their
+// value, hence the asm.  A DPP read wants two instructions between it and the write of its source: the block starts with a wait
+// for what its caller wrote, and within it a source is five and more instructions old.
 __device__ __forceinline__ float transpose_sum16(const float *p, int n) {
 #pragma clang fp contract(off)
   float a[8], c[2];
