@@ -1672,8 +1672,7 @@ int backward_impl(const rom_dims *d, const rom_weights *w, const void *x, int64_
 
   // transposed weights: d_inp = d_out W contracts over the row index of W (the two big projections
   // are transposed only where the GEMM cannot read them contraction-major, see dgrad)
-  ROM_TRY(launch_transpose(d->dtype, w->w_dt, at(bp.wt_dt), Ex, De, R, s));            // -> [Ex][R][De]
-  ROM_TRY(launch_transpose(d->dtype, w->w_x, at(bp.wt_x), Ex, R + 32, De, s));         // -> [Ex][De][R+32]
+  ROM_TRY(launch_transpose2(d->dtype, w->w_dt, at(bp.wt_dt), De, R, w->w_x, at(bp.wt_x), R + 32, De, Ex, s));   // -> [Ex][R][De], [Ex][De][R+32]
 
   // Input gradient of a routed projection, d_inp[n] = sum_k W[e_k(n)]^T d_outp[n]: the forward's grouped
   // GEMM on the transposed weights.  top-1: rows gathered from and scattered to token order, C is the

@@ -163,6 +163,8 @@ hipError_t launch_conv_backward(int dtype, const void *xz, int64_t ld_xz, const 
                                 int64_t ld_dx, float *partial, float *d_conv_w, float *d_conv_b, hipStream_t s);
 // dst[m][c][r] = src[m][r][c] for n_mats matrices
 hipError_t launch_transpose(int dtype, const void *src, void *dst, int n_mats, int rows, int cols, hipStream_t s);
+hipError_t launch_transpose2(int dtype, const void *src0, void *dst0, int rows0, int cols0, const void *src1, void *dst1, int rows1,
+                             int cols1, int n_mats, hipStream_t s);            // both in one launch
 hipError_t launch_pack_dxdbl(int dtype, const float *d_dt_low, const float *d_bc, int64_t n_tok, int dt_rank,
                              void *d_xdbl, hipStream_t s);
 // dst[r, :] = scale[scale_idx ? scale_idx[r] : r] * src[src_idx ? src_idx[r] : r, :]
