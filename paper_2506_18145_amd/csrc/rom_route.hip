@@ -2,6 +2,7 @@
 // gates, then a stable counting sort of the (token, k) slots by expert built from wavefront
 // ballots and prefix sums (no atomics, so the permutation is reproducible bit for bit).
 #include "rom_internal.h"
+#include "rom_route_rule.h"
 
 #include <atomic>
 #include <cstdint>
@@ -782,19 +783,12 @@ hipError_t route_dispatch(const void *x, const void *w_router, const float *b_ro
                        n_tokens, d_model, n_experts, top_k, gate_mode, expert_idx, gate, logits, \
                        norm_w, norm_eps, rstd);                                                  \
   } while (0)
-  // Few tokens: one token per block of four wavefronts, a quarter of d_model each, so that the launch spreads over the chip and no
-  // wavefront walks all of d_model for all experts alone; from some thousand tokens on the matrix pipe, whose workgroups hold 64 tokens (us,
-  // four wavefronts / one / matrix pipe: 8 experts, 3063 tokens x 1536 10.8 / 14.5 / 14.5, 4096 x 2048 13.7 / 19.7 / 19.0, 4096 x 768 9.6 / 8.7 / 9.3,
-  // 6000 x 2048 18.8 / 21.5 / 19.0; 16 experts, 3063 x 2048 18.8 / 33.8 / 27.6, 4096 x 768 19.5 / 18.4 / 14.7, 6000 x 1536 28.7 / 29.2 / 21.3).
-  const bool mfma = std::is_same<T, bf16_t>::value && n_experts <= 16 && d_model % 32 == 0 &&
-                    route_mfma_lds_bytes(n_experts <= 8 ? 8 : 16, d_model, NORM) <= kRouteMfmaLdsMax &&
-                    (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(w_router) & 15) == 0 &&
-                    (!NORM || (reinterpret_cast<uintptr_t>(norm_w) & 15) == 0);
-  const int64_t four = d_model <= 512 ? 1024 : n_experts <= 8 && d_model >= 1024 ? 4096 : 3072;
+  // a block of four wavefronts for a token, or a wavefront (rom_route_rule.h)
+  const int64_t four = route_four_most(d_model, n_experts);
   if (n_tokens <= four && n_experts <= 8) ROM_ROUTE_LAUNCH(8, 1, 4);
   else if (n_tokens <= four && n_experts <= 16) ROM_ROUTE_LAUNCH(16, 1, 4);
-  else if (n_tokens <= 8192 && n_experts <= 8 && !(mfma && n_tokens > 4096)) ROM_ROUTE_LAUNCH(8, 1, 1);
-  else if (n_tokens <= 8192 && n_experts <= 16 && !(mfma && n_tokens > 3072)) ROM_ROUTE_LAUNCH(16, 1, 1);
+  else if (n_tokens <= kRouteFewMost && n_experts <= 8) ROM_ROUTE_LAUNCH(8, 1, 1);
+  else if (n_tokens <= kRouteFewMost && n_experts <= 16) ROM_ROUTE_LAUNCH(16, 1, 1);
   // many tokens: router weights in LDS when they fit 48 KiB
 #define ROM_ROUTE_LAUNCH_LDS(EMAX, TOK, ROUNDS)                                                   \
   do {                                                                                           \
@@ -820,7 +814,10 @@ hipError_t route_dispatch(const void *x, const void *w_router, const float *b_ro
                        n_experts, top_k, gate_mode, expert_idx, gate, logits, norm_w, norm_eps,  \
                        rstd);                                                                    \
   } while (0)
-  else if (mfma) {
+  else if (std::is_same<T, bf16_t>::value && n_experts <= 16 && d_model % 32 == 0 &&
+           route_mfma_lds_bytes(n_experts <= 8 ? 8 : 16, d_model, NORM) <= kRouteMfmaLdsMax &&
+           (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (reinterpret_cast<uintptr_t>(w_router) & 15) == 0 &&
+           (!NORM || (reinterpret_cast<uintptr_t>(norm_w) & 15) == 0)) {
     if (n_experts <= 8) ROM_ROUTE_LAUNCH_MFMA(8);
     else ROM_ROUTE_LAUNCH_MFMA(16);
   }

@@ -1,6 +1,6 @@
 """Grouping and router at the lines of their rules: the edges of a workgroup's rounds and of one workgroup against three
-launches (stable order, exact), and four wavefronts, one wavefront or the matrix pipe for a token (logits and gates against
-the oracle; the router of a block reads the normalised input)."""
+launches (stable order, exact), and four wavefronts or one for a token (logits and gates against the oracle, the logits of up to
+8192 tokens against 64 bits; the router of a block reads the normalised input)."""
 import numpy as np
 import pytest
 import torch
@@ -53,3 +53,20 @@ def test_router_rule(n, d_model, E, K, dtype, block):
     torch.cuda.synchronize()
     names = ("expert_idx", "gate", "counts", "offsets", "perm", "inv_perm", "logits")
     check_routing(cfg, {k: to_np(layer.ws_view(k, 1, n)) for k in names}, x_np, w, block)
+
+
+@pytest.mark.parametrize("n,d_model,E", [(8192, 1024, 8), (5000, 2048, 8), (4097, 768, 5), (6000, 1536, 16), (3073, 768, 16)])
+@pytest.mark.parametrize("block", [False, True])
+def test_router_precision(n, d_model, E, block):
+    """Up to 8192 tokens a logit is at most d_model / 64 additions in a lane and six over the lanes.  An addition is off by up to
+    2^-24 of what it leaves, evenly spread (2^-24 / sqrt(3) rms), so the logits by that times the root of (d_model / 64 + 1) / 2 + 6 (sums
+    of part of the terms are smaller by the root of their part); a block adds two roundings a term and some four of 1 / rms."""
+    cfg, w, layer = layer_of(n, d_model, E, 1)
+    x_np = make_input(cfg)
+    x = layer.to_device(x_np)
+    layer.block_forward(x, eps=BLOCK_EPS) if block else layer.forward(x)
+    torch.cuda.synchronize()
+    x_r = (O.rms_norm(x_np, w["norm_w"], BLOCK_EPS) if block else x_np).reshape(n, -1)
+    ref = O.router_logits(x_r, w["w_router"], w.get("b_router"))
+    err = np.linalg.norm(to_np(layer.ws_view("logits", 1, n)).astype(np.float64) - ref) / np.linalg.norm(ref)
+    assert err <= 2.0 ** -24 / 3 ** 0.5 * ((d_model / 64 + 1) / 2 + 6 + (6 if block else 0)) ** 0.5

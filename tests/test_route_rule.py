@@ -1,0 +1,36 @@
+"""Which kernel routes a call's tokens (rom_route_rule.h, host code)."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_18145_amd", "csrc")
+MAIN = """
+#include <cstdio>
+#include "rom_route_rule.h"
+int main() {
+  int d, e;
+  while (std::scanf("%d %d", &d, &e) == 2) std::printf("%lld %lld\\n", (long long)rom::route_four_most(d, e), (long long)rom::kRouteFewMost);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rule")
+    (d / "main.cpp").write_text(MAIN)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "main.cpp"), "-o", str(d / "rule")], check=True)
+    return lambda *a: [int(v) for v in subprocess.run([str(d / "rule")], input=" ".join(map(str, a)) + "\n", capture_output=True,
+                                                      text=True, check=True).stdout.split()]
+
+
+@pytest.mark.parametrize("d_model,n_experts,four", [
+    (64, 8, 1024), (512, 16, 1024), (576, 8, 3072), (768, 8, 3072), (1024, 8, 4096), (2048, 8, 4096), (640, 16, 3072), (2048, 16, 3072),
+])
+def test_four_wavefronts_for_a_token(rule, d_model, n_experts, four):
+    assert rule(d_model, n_experts)[0] == four
+
+
+def test_matrix_pipe_line(rule):
+    """Its sums are less exact than the other kernels' (test_gpu_route.py holds theirs to a bound that it does not keep)."""
+    assert rule(2048, 8)[1] == 8192
