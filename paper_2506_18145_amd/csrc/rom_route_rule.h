@@ -1,4 +1,4 @@
-// Which kernel routes a call's tokens (host code, no HIP).  Kernels: rom_route.hip.
+// Which kernels route a call's tokens and group its slots by expert (host code, no HIP).  Kernels: rom_route.hip.
 #pragma once
 
 #include <cstdint>
@@ -6,10 +6,16 @@
 namespace rom {
 
 // Four wavefronts for a token, a quarter of d_model each, so that the launch spreads over the chip and no wavefront walks all of d_model
-// for all experts alone; from some thousand tokens on one wavefront a token (us, four / one: 8 experts, 3063 tokens x 1536 10.8 / 14.5,
-// 4096 x 2048 13.7 / 19.7, 4096 x 768 9.6 / 8.7; 16 experts, 3063 x 2048 18.8 / 33.8, 4096 x 768 19.5 / 18.4, 6000 x 1536 28.7 / 29.2).
+// for all experts alone; from a line that lies the higher the more a token has to multiply, one wavefront a token.  Layer calls in us, one /
+// four: 8 experts, 1200 tokens x 576 92.0 / 90.1, 3072 x 768 154.7 / 153.6, 4096 x 1024 204.8 / 204.5, 4096 x 2048 420 / 414;
+// 16 experts, 2000 x 1536 282 / 271; 6 experts, 3000 x 768 153.7 / 153.9, x 1024 149.1 / 149.8, x 2048 335 / 331; 2 experts,
+// 2000 x 768 105.9 / 105.4, 3000 x 768 133.3 / 134.1; one expert, 2000 x 1024 102.8 / 103.7, 3000 x 768 131.2 / 132.2.  fp32
+// likewise: 16 experts, 2000 x 1536 1974 / 1967, one, 3000 x 1024 814 / 816.
+// (The router alone: 16 experts, 4096 x 768 18.4 / 19.5, 6000 x 1536 29.2 / 28.7.)
 inline int64_t route_four_most(int d_model, int n_experts) {
-  return d_model <= 512 ? 1024 : n_experts <= 8 && d_model >= 1024 ? 4096 : 3072;
+  if (d_model <= 512) return 1024;
+  const int64_t least = n_experts == 1 ? 1024 : 2048, most = n_experts <= 8 ? 4096 : 3072, line = static_cast<int64_t>(d_model) * n_experts / 2;
+  return line < least ? least : line < most ? line : most;
 }
 
 // More tokens than this take the kernels with 64 and more tokens a workgroup: the matrix pipe (bf16, up to 16 experts) or router weights in

@@ -1,4 +1,4 @@
-"""Which kernel routes a call's tokens (rom_route_rule.h, host code)."""
+"""Which kernels route a call's tokens and group its slots (rom_route_rule.h, host code)."""
 import os
 import subprocess
 
@@ -10,7 +10,8 @@ MAIN = """
 #include "rom_route_rule.h"
 int main() {
   int d, e;
-  while (std::scanf("%d %d", &d, &e) == 2) std::printf("%lld %lld\\n", (long long)rom::route_four_most(d, e), (long long)rom::kRouteFewMost);
+  while (std::scanf("%d %d", &d, &e) == 2)
+    std::printf("%lld %lld \\n", (long long)rom::route_four_most(d, e), (long long)rom::kRouteFewMost);
 }
 """
 
@@ -25,9 +26,11 @@ def rule(tmp_path_factory):
 
 
 @pytest.mark.parametrize("d_model,n_experts,four", [
-    (64, 8, 1024), (512, 16, 1024), (576, 8, 3072), (768, 8, 3072), (1024, 8, 4096), (2048, 8, 4096), (640, 16, 3072), (2048, 16, 3072),
+    (64, 8, 1024), (512, 16, 1024), (576, 8, 2304), (768, 8, 3072), (768, 4, 2048), (1024, 8, 4096), (1024, 6, 3072), (2048, 8, 4096),
+    (1024, 1, 1024), (1024, 2, 2048), (2048, 2, 2048), (8192, 1, 4096), (640, 16, 3072), (2048, 16, 3072),
 ])
 def test_four_wavefronts_for_a_token(rule, d_model, n_experts, four):
+    """Both sides of the line as measured; never below what is too few for anything else."""
     assert rule(d_model, n_experts)[0] == four
 
 
