@@ -631,7 +631,7 @@ __global__ __launch_bounds__(kSortBlock) void permutation_round_kernel(
 // The same for more slots: sixteen wavefronts, each with a run of R times 64 consecutive ones, their keys in registers.  Lane e of a wavefront
 // counts expert e; after the one barrier it knows where the wavefront's first slot of that expert goes, and moves on by
 // the round's count.  Bound by the scattered stores of one CU, about an address a clock: 8 experts, 1000 slots 3.1 us, 2048 4.2 (with four
-// wavefronts and four barriers for every 256 slots 10.1 and 16.2), 4096 6.5 (three launches 13.1).
+// wavefronts and four barriers for every 256 slots 10.1 and 16.2), 4096 6.5 (grouping_in_one).
 constexpr int kRunWaves = 16;
 template <int R>
 __global__ __launch_bounds__(kRunWaves *kWave) void permutation_run_kernel(
@@ -880,16 +880,14 @@ hipError_t launch_permutation(const int32_t *expert_idx, int64_t n_slots, int n_
                        top_k, counts, offsets, perm, inv_perm, tok_of_pos);
     return hipGetLastError();
   }
-  // One workgroup or three launches (us, three / one): 3063 slots, 8 experts 13.0 / 5.3, 16 12.2 / 7.8; 6000 12.7 / 9.4,
-  // 13.1 / 13.4; 8192 12.9 / 11.2, 13.7 / 15.3; 12000, 8 experts 12.8 / 15.8
-  const bool one = n_slots <= (n_experts <= 8 ? 8192 : n_experts <= 16 ? 4096 : 2048);
+  const bool one = grouping_in_one(n_slots, n_experts);
 #define ROM_RUN(R)                                                                                                                  \
   if (one && n_slots <= R * kRunWaves * kWave) {                                                                                           \
     hipLaunchKernelGGL(permutation_run_kernel<R>, dim3(1), dim3(kRunWaves * kWave), 0, s, expert_idx, static_cast<int>(n_slots),     \
                        n_experts, top_k, counts, offsets, perm, inv_perm, tok_of_pos);                                              \
     return hipGetLastError();                                                                                                       \
   }
-  ROM_RUN(1) ROM_RUN(2) ROM_RUN(4) ROM_RUN(8)
+  ROM_RUN(1) ROM_RUN(2) ROM_RUN(4)
 #undef ROM_RUN
   const int64_t blocks = route_blocks(n_slots);
   hipLaunchKernelGGL(hist_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kSortBlock), 0, s,

@@ -25,4 +25,10 @@ inline int64_t route_four_most(int d_model, int n_experts) {
 // 21.5 / 19.0 us, 16 experts, 6000 x 1536 29.2 / 21.3), and is not taken there.
 constexpr int64_t kRouteFewMost = 8192;
 
+// Whether one workgroup groups a call's slots, else three launches.  One workgroup is bound by its scattered stores, about an address a
+// clock.  Layer calls in us, three launches / one: 8 experts, 1024 slots 67.7 / 64.8, 2048 75.6 / 73.6, 4096 93.7 / 93.2, 5000 95.0 / 97.1,
+// 8192 129.9 / 133.7; 4 experts, 4096 90.5 / 89.3, 8192 125.7 / 127.3; 16 experts, 2048 82.4 / 80.1, 3000 93.9 / 93.8, 4096 98.4 / 99.1;
+// 64 experts, 2048 129.5 / 125.9.
+inline bool grouping_in_one(int64_t n_slots, int n_experts) { return n_slots <= (n_experts <= 8 ? 4096 : 2048); }
+
 }  // namespace rom

@@ -11,7 +11,7 @@ MAIN = """
 int main() {
   int d, e;
   while (std::scanf("%d %d", &d, &e) == 2)
-    std::printf("%lld %lld \\n", (long long)rom::route_four_most(d, e), (long long)rom::kRouteFewMost);
+    std::printf("%lld %lld %d\\n", (long long)rom::route_four_most(d, e), (long long)rom::kRouteFewMost, rom::grouping_in_one(d, e));
 }
 """
 
@@ -37,3 +37,11 @@ def test_four_wavefronts_for_a_token(rule, d_model, n_experts, four):
 def test_matrix_pipe_line(rule):
     """Its sums are less exact than the other kernels' (test_gpu_route.py holds theirs to a bound that it does not keep)."""
     assert rule(2048, 8)[1] == 8192
+
+
+@pytest.mark.parametrize("n_slots,n_experts,one", [
+    (1, 8, 1), (4096, 8, 1), (4097, 8, 0), (8192, 8, 0), (4096, 1, 1), (8192, 4, 0), (2048, 9, 1), (2049, 9, 0), (4096, 16, 0), (2048, 64, 1),
+])
+def test_grouping_in_one_workgroup(rule, n_slots, n_experts, one):
+    """Up to where three launches are faster in a call."""
+    assert rule(n_slots, n_experts)[2] == one
