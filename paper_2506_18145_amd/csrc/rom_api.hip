@@ -79,15 +79,29 @@ int check_weights(const rom_dims *d, const rom_weights *w) {
   return ROM_OK;
 }
 
-// whether the x projection takes the narrow-output kernel, and the slices of its inner dimension, for a launch over `rows` rows
+// whether the x projection takes the narrow-output kernel for a launch over `rows` rows; slices of its inner dimension
 bool xproj_is_thin(const rom_dims *d, int64_t rows) {
   return d->dtype == ROM_DTYPE_BF16 && rows >= kThinMinRows && d->dt_rank + 32 <= kThinMaxCols && d->d_inner % 64 == 0;
 }
-int xproj_slices_for(const rom_dims *d, int64_t rows) {
-  const int groups = d->n_experts_xdt > 1 ? d->n_experts : 1;
-  const int n = xproj_is_thin(d, rows) ? thin_k_splits(rows, groups, d->dt_rank + 32, d->d_inner) : xproj_k_splits(rows, groups, d->d_inner);
-  const int64_t per = ceil_div(ceil_div(d->d_inner, n), 64) * 64;   // whole 64-wide slabs
+int whole_slabs(const rom_dims *d, int slices) {
+  const int64_t per = ceil_div(ceil_div(d->d_inner, slices), 64) * 64;   // whole 64-wide slabs
   return static_cast<int>(ceil_div(d->d_inner, per));
+}
+int tiled_slices(const rom_dims *d, int64_t rows, int groups) { return whole_slabs(d, xproj_k_splits(rows, groups, d->d_inner)); }
+// rows times tiled_slices, the most of any call of up to so many rows (more rows have fewer slices): room for a step is room for a smaller one
+int64_t tiled_room_rows(const rom_dims *d, int64_t rows, int groups) {
+  int64_t most = 0;
+  for (;;) {
+    const int s = tiled_slices(d, rows, groups);
+    if (rows * s > most) most = rows * s;
+    int64_t more = 1, same = rows;               // the last number of rows with more slices lies in [more, same)
+    if (tiled_slices(d, more, groups) == s) return most;
+    while (same - more > 1) {
+      const int64_t mid = (more + same) / 2;
+      (tiled_slices(d, mid, groups) > s ? more : same) = mid;
+    }
+    rows = more;
+  }
 }
 
 Plan make_plan(const rom_dims *d, int64_t n_seq, int64_t seq_len) {
@@ -105,7 +119,12 @@ Plan make_plan(const rom_dims *d, int64_t n_seq, int64_t seq_len) {
   const bool multi = K > 1;
   const bool routed_xdt = d->n_experts_xdt > 1;
   p.rank_passes = use_rank_passes(d, n_tok);
-  p.xproj_slices = xproj_slices_for(d, n_tok * (routed_xdt ? d->top_k : 1));
+  const int64_t xproj_rows = static_cast<int64_t>(routed_xdt ? S : N);
+  const int xproj_groups = routed_xdt ? d->n_experts : 1, tiled = tiled_slices(d, xproj_rows, xproj_groups);
+  const bool thin = xproj_is_thin(d, xproj_rows), step = seq_len == 1;
+  p.xproj_slices = thin ? whole_slabs(d, thin_k_splits(xproj_rows, xproj_groups, d->dt_rank + 32, d->d_inner)) : tiled;
+  // a step slices no finer than by the tiled kernels' rule (which matters for 1024 to 2000 rows): rom_step_static's array has a fixed size
+  if (step && p.xproj_slices > tiled) p.xproj_slices = tiled;
   p.expert_idx = take(S * 4);
   p.gate = take(S * 4);
   p.counts = take(E * 4);
@@ -119,8 +138,8 @@ Plan make_plan(const rom_dims *d, int64_t n_seq, int64_t seq_len) {
   p.xz = take(N * 2 * De * b);
   p.xz_sorted = multi ? take(S * 2 * De * b) : kNone;
   p.u = take(N * De * b);
-  const size_t xproj_rows = routed_xdt ? S : N;
-  p.xdbl = take((xproj_is_thin(d, xproj_rows) ? thin_scratch_rows(xproj_rows) : xproj_rows * p.xproj_slices) * (R + 32) * 4);
+  const int64_t xdbl_rows = step ? tiled_room_rows(d, xproj_rows, xproj_groups) : thin ? thin_scratch_rows(xproj_rows) : xproj_rows * tiled;
+  p.xdbl = take(static_cast<size_t>(xdbl_rows) * (R + 32) * 4);
   p.dt_low = take(N * R * b);
   p.bc = take(N * 32 * 4);
   p.dt = take(N * De * b);

@@ -300,3 +300,27 @@ def test_workspace_serves_smaller_calls(d_model, d_inner, dt_rank, n_experts):
         need = binding.rom_workspace_bytes(d, 1, n)
         assert need >= most, n
         most = need
+
+
+@pytest.mark.parametrize("d_model,top_k,n_experts_xdt,dtype,most", [
+    (256, 1, 8, 1, 6068), (512, 1, 8, 1, 3049), (768, 1, 8, 1, 2020), (1024, 1, 8, 1, 1502), (1024, 1, 1, 1, 1502), (1280, 1, 8, 1, 1190),
+    (2048, 1, 8, 1, 721), (256, 2, 8, 1, 2598), (768, 2, 8, 1, 858), (1024, 2, 8, 1, 638), (384, 4, 1, 1, 1424), (1024, 1, 8, 0, 781),
+    (768, 2, 8, 0, 441),
+])
+def test_sequences_of_a_static_step(lib, d_model, top_k, n_experts_xdt, dtype, most):
+    """rom_step_static takes what fits its 32 MiB: every one of these counts, and not one more."""
+    from paper_2506_18145_amd import binding
+    d = _dims(d_model=d_model, d_inner=2 * d_model, dt_rank=d_model // 16, n_experts=8, n_experts_xdt=n_experts_xdt, top_k=top_k, dtype=dtype,
+              gate_mode=int(top_k > 1))
+    need = [binding.rom_workspace_bytes(d, b, 1) for b in range(1, most + 2)]
+    assert max(need[:-1]) <= 32 << 20 < need[-1]
+
+
+@pytest.mark.parametrize("d_model,n_experts", [(768, 8), (1024, 64), (1536, 8), (2048, 1), (2048, 64)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_step_workspace_serves_smaller_steps(lib, d_model, n_experts, dtype):
+    """Top-1: the slices of the x projection get fewer with the rows, the room does not."""
+    from paper_2506_18145_amd import binding
+    d = _dims(d_model=d_model, d_inner=2 * d_model, dt_rank=d_model // 16, n_experts=n_experts, n_experts_xdt=n_experts, dtype=dtype)
+    need = [binding.rom_workspace_bytes(d, b, 1) for b in range(1, 4500)]
+    assert need == sorted(need)

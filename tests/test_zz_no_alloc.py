@@ -20,7 +20,8 @@ def _cfg(**kw):
 
 @pytest.mark.parametrize("kw", [dict(), dict(dtype="fp32", top_k=1, gate_mode=0, n_experts=4),
                                 dict(batch=256, d_model=2048, d_inner=4096, dt_rank=128, top_k=1, gate_mode=0,
-                                     weight_std=0.02)])
+                                     weight_std=0.02),
+                                dict(batch=1500, d_model=1024, d_inner=2048, dt_rank=64, top_k=1, gate_mode=0)])
 def test_step_static_matches_step_on_two_calls_the_second_smaller(kw):
     cfg = _cfg(**kw)
     layer = RomLayer(cfg, make_weights(cfg))
