@@ -88,7 +88,7 @@ int whole_slabs(const rom_dims *d, int slices) {
   return static_cast<int>(ceil_div(d->d_inner, per));
 }
 int tiled_slices(const rom_dims *d, int64_t rows, int groups) { return whole_slabs(d, xproj_k_splits(rows, groups, d->d_inner)); }
-// rows times tiled_slices, the most of any call of up to so many rows (more rows have fewer slices): room for a step is room for a smaller one
+// rows times tiled_slices, the most of any call of up to so many rows (more rows have fewer slices): room for a call is room for a smaller one
 int64_t tiled_room_rows(const rom_dims *d, int64_t rows, int groups) {
   int64_t most = 0;
   for (;;) {
@@ -138,7 +138,7 @@ Plan make_plan(const rom_dims *d, int64_t n_seq, int64_t seq_len) {
   p.xz = take(N * 2 * De * b);
   p.xz_sorted = multi ? take(S * 2 * De * b) : kNone;
   p.u = take(N * De * b);
-  const int64_t xdbl_rows = step ? tiled_room_rows(d, xproj_rows, xproj_groups) : thin ? thin_scratch_rows(xproj_rows) : xproj_rows * tiled;
+  const int64_t xdbl_rows = thin && !step ? thin_scratch_rows(xproj_rows, d->d_inner) : tiled_room_rows(d, xproj_rows, xproj_groups);
   p.xdbl = take(static_cast<size_t>(xdbl_rows) * (R + 32) * 4);
   p.dt_low = take(N * R * b);
   p.bc = take(N * 32 * 4);
@@ -148,7 +148,7 @@ Plan make_plan(const rom_dims *d, int64_t n_seq, int64_t seq_len) {
   p.op_sorted = multi ? take(S * Dm * b) : kNone;
   // the conv writes its end state beside the old one only when a sequence is cut into runs
   p.conv_tmp = take(seq_len > kConvInPlaceMaxLen ? static_cast<size_t>(n_seq) * De * 3 * 4 : 0);
-  const size_t chunk_bytes = scan_chunk_state_bytes(n_seq, seq_len, d->d_inner);
+  const size_t chunk_bytes = scan_chunk_state_bytes(d->dtype, n_seq, seq_len, d->d_inner);
   p.scan_q = take(chunk_bytes);
   p.scan_p = take(chunk_bytes);
   p.rstd = take(N * 4);

@@ -84,15 +84,16 @@ inline int thin_row_blocks(int64_t M, int groups, int N, int k_splits) {
 // 3063 x 128 x 3072 in 8 groups, GEMM alone: one slice 19.9 us, two 13.3; 16384 x 160 x 4096 one 65, two 75 (partial sums not counted).
 // Slices times rows stay below a limit, so that scratch that is large enough for a call is so for every smaller one (thin_scratch_rows).
 constexpr int64_t kThinSliceRows = 16384;
-inline int64_t thin_scratch_rows(int64_t M) {
-  const int64_t most = 8 * M < kThinSliceRows ? 8 * M : kThinSliceRows;
-  return M > most ? M : most;
+inline int thin_most_splits(int K) { return K < 512 ? 1 : K < 2048 ? K / 256 : 8; }
+inline int64_t thin_scratch_rows(int64_t M, int K) {
+  const int64_t most = thin_most_splits(K) * M < kThinSliceRows ? thin_most_splits(K) * M : kThinSliceRows;
+  return M > most || thin_most_splits(K) == 1 ? M : most;
 }
 inline int thin_k_splits(int64_t M, int groups, int N, int K) {
   const int nb = (N + 31) / 32;
   int best = 1;
   double best_us = 0.0;
-  for (int s = 1; s <= 8 && s * 256 <= K && (s == 1 || s * M <= kThinSliceRows); ++s) {
+  for (int s = 1; s <= thin_most_splits(K) && (s == 1 || s * M <= kThinSliceRows); ++s) {
     const double fill = static_cast<double>(thin_blocks_per_cu(M, groups, nb, s, thin_row_blocks(M, groups, N, s))) * (K / s) * 64.0 / 45e3;
     const double rows = static_cast<double>(M) * K * 2.0 / 2.6e6;
     const double us = (fill > rows ? fill : rows) + s * (static_cast<double>(M) * N * 8.0 / 4e6);

@@ -126,7 +126,7 @@ hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const floa
                             const float *conv_b, const float *state_in, float *state_out, void *u,
                             int64_t B, int64_t L, int d_inner, hipStream_t s);
 // chunk_q / chunk_p: f32 scratch of scan_chunk_state_bytes() each (chunk end states and decays)
-size_t scan_chunk_state_bytes(int64_t B, int64_t L, int d_inner);
+size_t scan_chunk_state_bytes(int dtype, int64_t B, int64_t L, int d_inner);
 hipError_t launch_scan_gate(int dtype, const void *u, const void *dt, const float *bc, const void *z,
                             int64_t ld_z, const float *A_log, const float *D, const float *h_in,
                             float *h_out, void *g, int64_t B, int64_t L, int d_inner, float *chunk_q,

@@ -62,6 +62,20 @@ inline int64_t scan_most_chunks(int64_t B, int64_t L, int d_inner) {
   return L < 64 ? 0 : by_len < by_waves ? by_len : by_waves;
 }
 
+// The same where a call or one of fewer or shorter sequences is cut, else none: 64 sequences of 64 steps keep no states.  (No call of fewer
+// than 512 steps is cut, and one that a shorter one of as many sequences is cut like is cut itself.)
+inline int64_t scan_room_chunks(int64_t B, int64_t L, int d_inner, bool f32) {
+  if (L < 512 || d_inner < kScanCh) return 0;
+  int64_t most = 0, by_lane = 0;
+  for (int64_t b = 1; b <= B && b * (d_inner / kScanCh) <= 768; ++b) {         // beyond that only calls without chunks
+    const int64_t n = scan_chunks(b, L, d_inner) > 1 ? b * scan_chunks(b, L, d_inner) : 0;
+    if (n > most) most = n;
+    if (scan_by_lane(b, L, d_inner, f32)) by_lane = b;
+  }
+  const int64_t lane = by_lane > 0 ? scan_most_chunks(by_lane, L, d_inner) : 0;
+  return lane > most ? lane : most;
+}
+
 // Steps per chunk of the adjoint scan (kernels in rom_bwd.hip), a multiple of 16.  A unit is one chunk of 64 channels, a
 // workgroup of its own; its kernels walk their chunk step by step, some 0.3 us each.
 //   * two units per CU and more: 128 steps.  2048 steps x 2048 channels (512 units) 126 us, in 32-step chunks 106, but

@@ -1526,8 +1526,8 @@ hipError_t launch_conv_silu(int dtype, const void *xz, int64_t ld_xz, const floa
 #undef ROM_CONV
 }
 
-size_t scan_chunk_state_bytes(int64_t B, int64_t L, int d_inner) {
-  return static_cast<size_t>(scan_most_chunks(B, L, d_inner)) * d_inner * 16 * sizeof(float);
+size_t scan_chunk_state_bytes(int dtype, int64_t B, int64_t L, int d_inner) {
+  return static_cast<size_t>(scan_room_chunks(B, L, d_inner, dtype != ROM_DTYPE_BF16)) * d_inner * 16 * sizeof(float);
 }
 
 template <typename T>

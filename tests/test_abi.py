@@ -292,7 +292,8 @@ def test_gdn_segments_fill_256_cus_once(lib, d_k, n_heads, batch):
 
 @pytest.mark.parametrize("d_model,d_inner,dt_rank,n_experts", [(768, 1536, 48, 8), (2048, 4096, 128, 8), (64, 512, 128, 1)])
 def test_workspace_serves_smaller_calls(d_model, d_inner, dt_rank, n_experts):
-    """Slices of the x projection, like the scan's chunks, depend on the number of rows: room for a call is room for a smaller one."""
+    """bf16, top-1, a sequence of any length: slices of the x projection, like the scan's chunks, depend on the number of rows, and room
+    for a call is room for a smaller one.  (Top-2 calls have no room for single slots' dt from 2048 tokens on.)"""
     from paper_2506_18145_amd import binding
     d = _dims(d_model=d_model, d_inner=d_inner, dt_rank=dt_rank, n_experts=n_experts, n_experts_xdt=n_experts, top_k=1, dtype=1)
     most = 0
@@ -324,3 +325,27 @@ def test_step_workspace_serves_smaller_steps(lib, d_model, n_experts, dtype):
     d = _dims(d_model=d_model, d_inner=2 * d_model, dt_rank=d_model // 16, n_experts=n_experts, n_experts_xdt=n_experts, dtype=dtype)
     need = [binding.rom_workspace_bytes(d, b, 1) for b in range(1, 4500)]
     assert need == sorted(need)
+
+
+@pytest.mark.parametrize("d_model,n_experts,dtype", [(64, 8, 1), (768, 8, 0), (1024, 8, 0), (1024, 64, 1), (2048, 1, 0), (2048, 8, 1)])
+def test_workspace_serves_fewer_and_shorter_sequences(lib, d_model, n_experts, dtype):
+    """Top-1, several sequences, both types."""
+    from paper_2506_18145_amd import binding
+    d = _dims(d_model=d_model, d_inner=2 * d_model, dt_rank=d_model // 16, n_experts=n_experts, n_experts_xdt=n_experts, dtype=dtype)
+    for length in (2, 16, 64, 300, 512, 2048, 5000):
+        need = [binding.rom_workspace_bytes(d, b, length) for b in range(1, 200)]
+        assert need == sorted(need), length
+    for b in (1, 3, 40):
+        need = [binding.rom_workspace_bytes(d, b, length) for length in range(2, 9000, 7)]
+        assert need == sorted(need), b
+
+
+def test_workspace_holds_no_room_that_nothing_uses(lib):
+    """64 sequences of 64 steps are not cut in time, nor are fewer or shorter ones; an inner width of 128 is not sliced."""
+    from paper_2506_18145_amd import binding
+    def rest(d, b, length):      # beside the activations that every call has
+        n = b * length
+        return binding.rom_workspace_bytes(d, b, length) - n * (2 * (5 * d.d_inner + d.dt_rank) + 4 * 32)
+    wide, narrow = (_dims(d_model=m, d_inner=2 * m, dt_rank=m // 16, n_experts=8, n_experts_xdt=8, dtype=1) for m in (2048, 64))
+    assert rest(wide, 64, 64) < 16384 * 160 * 4 + (4 << 20)                 # slices, states of the conv, routing
+    assert rest(narrow, 4, 511) < 2044 * 36 * 4 + (1 << 20)

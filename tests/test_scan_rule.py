@@ -80,3 +80,35 @@ def test_chunk_states_fit_and_serve_smaller_calls(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(tmp_path / "main.cpp"), "-o", str(tmp_path / "chunks")], check=True)
     r = subprocess.run([str(tmp_path / "chunks")], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+ROOM = r"""
+#include <cstdio>
+#include "rom_scan_rule.h"
+int main() {
+  for (int f32 = 0; f32 < 2; ++f32)
+    for (int d = 16; d < 6000; d += 16 * (1 + d / 60))
+      for (long long B = 1; B < 900; B += 1 + B / 3) {
+        long long shorter = 0;
+        for (long long L = 1; L < 40000; L += 1 + L / 11) {
+          const long long room = rom::scan_room_chunks(B, L, d, f32), a = rom::scan_chunks(B, L, d), lane = rom::scan_lane_chunks(B, L, d);
+          const long long used = rom::scan_by_lane(B, L, d, f32) && lane > 1 ? B * lane : a > 1 ? B * a : 0;
+          if (used > room || room < shorter || rom::scan_room_chunks(B + 1, L, d, f32) < room || (L < 512 && room))
+            return std::printf("%d %lld %lld %d\n", f32, B, L, d), 1;
+          shorter = room;
+        }
+      }
+  // calls that are not cut, and no smaller one is
+  for (auto c : {std::array<int, 3>{64, 64, 4096}, {4, 511, 128}, {1, 2048, 4096}, {8, 1024, 4096}, {512, 500, 2048}})
+    if (rom::scan_room_chunks(c[0], c[1], c[2], false)) return std::printf("room %d %d %d\n", c[0], c[1], c[2]), 1;
+  return 0;
+}
+"""
+
+
+def test_room_for_chunk_states(tmp_path):
+    """What a call uses, no less for more or longer sequences, none where nothing is cut."""
+    (tmp_path / "main.cpp").write_text("#include <array>\n#include <initializer_list>\n" + ROOM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(tmp_path / "main.cpp"), "-o", str(tmp_path / "room")], check=True)
+    r = subprocess.run([str(tmp_path / "room")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
