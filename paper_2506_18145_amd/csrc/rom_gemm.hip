@@ -1406,9 +1406,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // many rows by memory: rows that the launch before wrote come in at 2.4 TB/s, whoever reads them, while that launch's lines are written back.
 // In 8 experts, in place: 16384 x 160 x 4096 67 us and 10.6 to add two slices, now 62 and 8.7 for one; 16384 x 128 x 4096 62 -> 50; 16384 x
 // 96 x 2048 30.3 + 6.6 -> 23.7 + 5.5; 8192 x 96 x 2048 19.6 -> 15.8, x 64 20.9 -> 18 (256- or 128-row tiles of eight or four wavefronts,
-// of which 72 to 144 workgroups had work).  Requests ahead of the products instead of between them, and every workgroup from
-// the first slab on: 30.2 and 24.2 for the last two but one.
-constexpr int kThinSlots = 4;
+// of which 72 to 144 workgroups had work).  Requests ahead of the products instead of between them: 30.2 and 24.2 for the last two but one.
+// A row's products are added in one order wherever it lies in its group: the other rows of a call don't show in its sums.  (Workgroups
+// starting on different slabs are no faster than with W's lines asked for ahead: layer calls of 12000 x 1536 723 / 726 us, 8192 x 1024 322 / 322,
+// 3063 x 1536 271.5 / 271.7; without either 733, 326 and 272.)
+constexpr int kThinSlots = 4, kThinWShare = 4;
 constexpr int thin_slab_bytes(int rb, int nb) { return (rb + nb) * 32 * kDmaBK * 2; }
 template <int RB, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void gemm_bf16_thin_kernel(const GemmArgs a) {
@@ -1425,6 +1427,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void g
   lds_char_t *lds = (lds_char_t *)thin_smem;
   const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) void *)thin_smem));
 
+  const char *const a_base = static_cast<const char *>(a.A);
+  const char *const w_base = static_cast<const char *>(a.W) + static_cast<int64_t>(tc.group) * a.N * a.K * 2;
+
+  // An XCD's workgroups multiply the same slab of W at the same time, and each would wait for it to come from memory.  So each asks for
+  // a share of its group's lines ahead of everything else, one access a line, into the slot that is requested last.
+  {
+    const int lines = a.N * slabs, neighbours = static_cast<int>(gridDim.x >> 3), share = neighbours < kThinWShare ? neighbours : kThinWShare;
+    for (int l = (static_cast<int>(blockIdx.x >> 3) % share * 4 + wave) * 64; l < lines; l += share * 256) {
+      const int line = l + lane < lines ? l + lane : lines - 1, n = line / slabs, slab = line - n * slabs;
+      dma_load_16(lds_base + (kThinSlots - 1) * kSlab + wave * (kInstr * 1024),
+                  static_cast<unsigned>((static_cast<int64_t>(n) * a.K + k0 + slab * kDmaBK) * 2), w_base);
+    }
+  }
+
   // lane l of an instruction brings 16-byte place l & 7 of row l >> 3 (of eight): chunk place ^ ((row >> 1) & 7)
   unsigned voff[kInstr];
 #pragma unroll
@@ -1439,13 +1455,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void g
       voff[j] = static_cast<unsigned>((static_cast<int64_t>(n) * a.K + k0 + chunk * 8) * 2);
     }
   }
-  const char *const a_base = static_cast<const char *>(a.A);
-  const char *const w_base = static_cast<const char *>(a.W) + static_cast<int64_t>(tc.group) * a.N * a.K * 2;
-  // (workgroups start on different slabs: rows lie a power of two apart, and the same columns of all of them in few channels)
-  const int first = static_cast<int>((static_cast<unsigned>(tc.row0 / BM) * 5) % static_cast<unsigned>(slabs));
   auto request = [&](int t, int j) __attribute__((always_inline)) {
     const unsigned at = lds_base + (t & (kThinSlots - 1)) * kSlab + wave * (kInstr * 1024);
-    const int tt = t < slabs ? t : slabs - 1, slab = tt + first < slabs ? tt + first : tt + first - slabs;
+    const int slab = t < slabs ? t : slabs - 1;
     dma_load_16(at + j * 1024, voff[j], ((wave * kInstr + j) * 8 < BM ? a_base : w_base) + static_cast<int64_t>(slab) * (kDmaBK * 2));
   };
 
