@@ -1967,27 +1967,25 @@ hipError_t launch_smallk(const GemmArgs &a, hipStream_t s) {
     return launch_smallk_t<KS, PLAIN, false>(a, s);
   };
   switch (a.K / 16) {
-    case 2: return steps(std::integral_constant<int, 2>{});
-    case 3: return steps(std::integral_constant<int, 3>{});
-    case 4: return steps(std::integral_constant<int, 4>{});
-    case 6: return steps(std::integral_constant<int, 6>{});
-    case 8: return steps(std::integral_constant<int, 8>{});
-  }
-  if constexpr (PLAIN) {
-    if (a.K == 80) return steps(std::integral_constant<int, 5>{});
-    if (a.K == 160) return steps(std::integral_constant<int, 10>{});
+#define ROM_STEPS(KS) \
+  case KS: return steps(std::integral_constant<int, KS>{})
+    ROM_STEPS(2);
+    ROM_STEPS(3);
+    ROM_STEPS(4);
+    ROM_STEPS(5);
+    ROM_STEPS(6);
+    ROM_STEPS(7);
+    ROM_STEPS(8);
+    ROM_STEPS(9);
+    ROM_STEPS(10);
+#undef ROM_STEPS
   }
   return hipErrorInvalidValue;
 }
-// whether the streaming small-K kernel takes the call (dense rows of A; with the activation 32, 48, 64, 96 or 128 contraction indices, the
-// ranks of the workloads' dt projections; without it also those + 32, 80 and 160).  The general kernel runs a K that is no multiple of 64
-// in whole slabs: 3063 x 3072 x 96, one group, 22.0 us against 13.5, 16384 x 4096 x 160 74 / 36; its 64-row tiles have the shorter start where
-// most groups have less than one of them (700 x 1536 x 48 in 8 groups 6.1 / 6.9, 1000 rows 10.3 / 7.1).
+// whether the streaming small-K kernel takes the call (dense rows of A)
 bool smallk_takes(const GemmArgs &a, bool plain) {
-  if (!kUseSmallK || a.lda < a.K || a.M >= (1ll << 31) || a.row_scale || a.c_is_f32 || (plain && a.residual)) return false;
-  if (a.K == 32 || a.K == 64 || a.K == 128) return true;
-  if (a.M < int64_t{96} * a.n_groups) return false;
-  return ((a.K == 48 || a.K == 96) && !a.residual) || (plain && (a.K == 80 || a.K == 160));
+  return kUseSmallK && a.lda >= a.K && a.M < (1ll << 31) && !a.row_scale && !a.c_is_f32 && !(plain && a.residual) &&
+         gemm_smallk(a.M, a.n_groups, a.K, a.residual != nullptr);
 }
 
 template <int BN, int WM, int WN, int EPI>

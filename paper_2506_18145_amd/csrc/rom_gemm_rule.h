@@ -65,6 +65,17 @@ inline GemmTile gemm_tile(const GemmShape &s) {
   return stream ? GemmTile::kStream : GemmTile::k128;
 }
 
+// Which short contractions (32 to 160 in whole 16-wide steps) take the streaming small-K kernel.  The general kernel runs a K that is no multiple
+// of 64 in whole slabs: 3063 x 3072 x 96, one group, 22.0 us against 13.5, 16384 x 4096 x 160 without activation 74 / 36; layer calls with a
+// rank of 80, 800 x 1280 165 / 161, 16000 x 1280 699 / 670, of 112, 4096 x 1792 402 / 389, of 144, 16000 x 2048 1310 / 1267, of 160
+// 1314 / 1270, training ones 8000 x 1280 1415 / 1396, 16000 x 1792 3799 / 3746.  Its 64-row tiles have the shorter start where most groups have
+// less than one of them (700 x 1536 x 48 in 8 groups 6.1 / 6.9, 1000 rows 10.3 / 7.1).  The form that accumulates is asked for
+// with a K of 32, 64 and 128 only (use_rank_passes).
+inline bool gemm_smallk(int64_t M, int groups, int K, bool accumulates) {
+  if (K == 32 || K == 64 || K == 128) return true;
+  return K % 16 == 0 && K >= 32 && K <= 160 && !accumulates && M >= int64_t{96} * groups;
+}
+
 // Blocks of 32 rows per workgroup of the narrow-output kernel: fewest bytes into a CU (its rows of A and every row of W), for as many
 // rounds as there are more workgroups than CUs.  (Five blocks of rows by five of columns do not fit the registers.)
 constexpr int kThinMinRows = 1024, kThinMaxCols = 160;

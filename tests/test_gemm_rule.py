@@ -111,3 +111,27 @@ def test_few_rows(rule, M, groups, N, K, want):
 ])
 def test_f32_gemm(rule, M, N, K, vec, want):
     assert rule(M, 8, N, K, wide=not vec)[2] == want
+
+
+SMALLK = r"""
+#include <initializer_list>
+#include <cstdio>
+#include "rom_gemm_rule.h"
+int main() {
+  for (int K = 1; K <= 200; ++K) {
+    const bool step = K % 16 == 0 && K >= 32 && K <= 160, power = K == 32 || K == 64 || K == 128;
+    for (long long M : {1ll, 767ll, 768ll, 100000ll})
+      if (rom::gemm_smallk(M, 8, K, false) != (power || (step && M >= 768)) || rom::gemm_smallk(M, 8, K, true) != power)
+        return std::printf("%d %lld\n", K, M), 1;
+  }
+  return 0;
+}
+"""
+
+
+def test_short_contractions(tmp_path):
+    """Every whole number of 16-wide steps from 32 to 160, not only the widths of some models."""
+    (tmp_path / "main.cpp").write_text(SMALLK)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(tmp_path / "main.cpp"), "-o", str(tmp_path / "smallk")], check=True)
+    r = subprocess.run([str(tmp_path / "smallk")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
