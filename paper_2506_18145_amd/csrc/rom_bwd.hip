@@ -730,46 +730,77 @@ __global__ __launch_bounds__(kFinishWaves * 64) void router_wgrad_finish_kernel(
   else if (d_b_router) d_b_router[e] = tot;
 }
 
-// d_x[n, d] = dx_in[n, d] + sum_e d_logits[n, e] * W_r[e, d].  A wavefront owns 512 columns, eight consecutive ones a lane (d_model is
-// a multiple of 8), of kDxRows tokens: the router weights are loaded once for all of them, and d_logits, uniform, through the scalar cache.
-// Bound by memory: 16384 x 2048 with 8 experts 47 us a token at a time and an index division per thread, now 31; 8192 x 1024 12.7 -> 9.8.
-constexpr int kDxRows = 4;
+// Row passes: 16 bytes of a row a lane, so a wavefront has 512 columns of it (fp32 256), or, NARROW, as many lanes as a shorter row fills
+// (2^lanes_log2) and several rows.
+template <typename T> constexpr int kRowCols = 16 / static_cast<int>(sizeof(T));
 template <typename T>
+inline int row_lanes_log2(int n_cols) {
+  int lg = 0;
+  while (lg < 6 && (kRowCols<T> << lg) < n_cols) ++lg;
+  return lg;
+}
+template <typename T>
+inline dim3 row_grid(int64_t n_rows, int n_cols) {
+  return grid1d(ceil_div(n_rows, 64 >> row_lanes_log2<T>(n_cols)) * ceil_div(n_cols, 64 * kRowCols<T>), 4);
+}
+// this lane's row and first column
+template <typename T, bool NARROW>
+__device__ __forceinline__ void row_place(int n_cols, int lanes_log2, int64_t &row, int &col) {
+  const int lane = threadIdx.x & 63;
+  const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (NARROW) {
+    row = wave * (64 >> lanes_log2) + (lane >> lanes_log2);
+    col = (lane & ((1 << lanes_log2) - 1)) * kRowCols<T>;
+  } else {
+    const int col_waves = (n_cols + 64 * kRowCols<T> - 1) / (64 * kRowCols<T>);
+    row = wave / col_waves;
+    col = (static_cast<int>(wave % col_waves) * 64 + lane) * kRowCols<T>;
+  }
+}
+
+// d_x[n, d] = dx_in[n, d] + sum_e d_logits[n, e] * W_r[e, d].  A lane has kDxRows tokens: the router weights are loaded once for all of them,
+// and d_logits, uniform, through the scalar cache; in short rows one (four leave 8192 x 128 too few wavefronts, 5.9 us, one 4.2).
+// Bound by memory: 16384 x 2048 with 8 experts 47 us a token at a time and an index division per thread, now 31; 8192 x 1024 12.2 -> 9.8,
+// fp32 21.7 -> 15.6; 32768 x 64 5.5 -> 5.0, fp32 7.8 -> 6.2 (10.0 and 19.9 with a row a wavefront).
+template <bool NARROW> constexpr int kDxRows = NARROW ? 1 : 4;
+template <typename T, bool NARROW>
 __global__ __launch_bounds__(256) void dx_finish_kernel(const T *__restrict__ dx_in, const float *__restrict__ d_logits,
-                                                        const T *__restrict__ w_router, int64_t n_tok, int d_model,
-                                                        int n_experts, T *__restrict__ d_x) {
-  const int col_waves = (d_model + 511) / 512, lane = threadIdx.x & 63;
-  const int64_t wv_id = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t n0 = wv_id / col_waves * kDxRows;
-  const int d = static_cast<int>(wv_id % col_waves) * 512 + lane * 8;
+                                                        const T *__restrict__ w_router, int64_t n_tok, int d_model, int n_experts,
+                                                        int lanes_log2, T *__restrict__ d_x) {
+  constexpr int kCols = kRowCols<T>, kRows = kDxRows<NARROW>;
+  int64_t n0;
+  int d;
+  row_place<T, NARROW>(d_model, lanes_log2, n0, d);
+  n0 *= kRows;
   if (n0 >= n_tok || d >= d_model) return;
-  const int rows = static_cast<int>(n_tok - n0 < kDxRows ? n_tok - n0 : kDxRows);
+  const int rows = static_cast<int>(n_tok - n0 < kRows ? n_tok - n0 : kRows);
   typedef const __attribute__((address_space(4))) float const_f32_t;
   const uintptr_t dl = reinterpret_cast<uintptr_t>(d_logits + n0 * n_experts);
-  float v[kDxRows][8];
+  float v[kRows][kCols];
 #pragma unroll
-  for (int r = 0; r < kDxRows; ++r) {
-    const int64_t at = (n0 + (r < rows ? r : rows - 1)) * d_model + d;
-    bwd_load4(dx_in + at, v[r]);
-    bwd_load4(dx_in + at + 4, v[r] + 4);
-  }
+  for (int r = 0; r < kRows; ++r)
+#pragma unroll
+    for (int q = 0; q < kCols; q += 4) bwd_load4(dx_in + (n0 + (r < rows ? r : rows - 1)) * d_model + d + q, v[r] + q);
 #pragma unroll 4
   for (int e = 0; e < n_experts; ++e) {
-    float wv[8];
-    bwd_load4(w_router + static_cast<int64_t>(e) * d_model + d, wv);
-    bwd_load4(w_router + static_cast<int64_t>(e) * d_model + d + 4, wv + 4);
+    float wv[kCols];
 #pragma unroll
-    for (int r = 0; r < kDxRows; ++r) {
-      const float g = *reinterpret_cast<const_f32_t *>(dl + static_cast<uint32_t>((r < rows ? r : rows - 1) * n_experts + e) * 4u);
+    for (int q = 0; q < kCols; q += 4) bwd_load4(w_router + static_cast<int64_t>(e) * d_model + d + q, wv + q);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[r][q] = fmaf(g, wv[q], v[r][q]);
+    for (int r = 0; r < kRows; ++r) {
+      const int at = (r < rows ? r : rows - 1) * n_experts + e;
+      float g;
+      if constexpr (NARROW) g = d_logits[n0 * n_experts + at];
+      else g = *reinterpret_cast<const_f32_t *>(dl + static_cast<uint32_t>(at) * 4u);
+#pragma unroll
+      for (int q = 0; q < kCols; ++q) v[r][q] = fmaf(g, wv[q], v[r][q]);
     }
   }
 #pragma unroll
-  for (int r = 0; r < kDxRows; ++r) {
+  for (int r = 0; r < kRows; ++r) {
     if (r >= rows) break;
-    bwd_store4(d_x + (n0 + r) * d_model + d, v[r]);
-    bwd_store4(d_x + (n0 + r) * d_model + d + 4, v[r] + 4);
+#pragma unroll
+    for (int q = 0; q < kCols; q += 4) bwd_store4(d_x + (n0 + r) * d_model + d + q, v[r] + q);
   }
 }
 
@@ -1869,27 +1900,26 @@ __global__ __launch_bounds__(2 * TW) void wgrad_bf16_thin_kernel(
 // rows scaled by a per-row factor (the gate weight of Eq. (12) on d_out):
 // dst[r, :] = scale[scale_idx ? scale_idx[r] : r] * src[src_idx ? src_idx[r] : r, :]
 // (top-K: r is a sorted position, src_idx its token, scale_idx its slot)
-// A wavefront per 512 columns of a row, eight consecutive ones a lane: 16384 x 2048 30-36 us with four columns a thread and two index divisions, now
-// 22-23; 8192 x 1024 8.4 -> 6.5.
-template <typename T>
+// (A row pass, row_place.)  16384 x 2048 30-36 us with four columns a thread and two index divisions, now 22-23; 8192 x 1024 7.9 -> 6.6;
+// 32768 x 64 4.8 -> 4.7 (6.7 with a row a wavefront); fp32 32768 x 512 22.1 both (25 with 32 bytes a lane).
+template <typename T, bool NARROW>
 __global__ __launch_bounds__(256) void scale_rows_kernel(const T *__restrict__ src, const float *__restrict__ scale,
-                                                         const int32_t *__restrict__ src_idx,
-                                                         const int32_t *__restrict__ scale_idx, int64_t n_rows,
-                                                         int n_cols, T *__restrict__ dst) {
-  const int col_waves = (n_cols + 511) / 512;
-  const int64_t wv_id = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t r = wv_id / col_waves;
-  const int c = static_cast<int>(wv_id % col_waves) * 512 + (threadIdx.x & 63) * 8;
+                                                         const int32_t *__restrict__ src_idx, const int32_t *__restrict__ scale_idx,
+                                                         int64_t n_rows, int n_cols, int lanes_log2, T *__restrict__ dst) {
+  constexpr int kCols = kRowCols<T>;
+  int64_t r;
+  int c;
+  row_place<T, NARROW>(n_cols, lanes_log2, r, c);
   if (r >= n_rows || c >= n_cols) return;
   const int64_t rs = src_idx ? src_idx[r] : r, rg = scale_idx ? scale_idx[r] : r;
   const float g = scale[rg];
-  float v[8];
-  bwd_load4(src + rs * n_cols + c, v);
-  bwd_load4(src + rs * n_cols + c + 4, v + 4);
+  float v[kCols];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] *= g;
-  bwd_store4(dst + r * n_cols + c, v);
-  bwd_store4(dst + r * n_cols + c + 4, v + 4);
+  for (int q = 0; q < kCols; q += 4) bwd_load4(src + rs * n_cols + c + q, v + q);
+#pragma unroll
+  for (int q = 0; q < kCols; ++q) v[q] *= g;
+#pragma unroll
+  for (int q = 0; q < kCols; q += 4) bwd_store4(dst + r * n_cols + c + q, v + q);
 }
 
 // the same contraction on the plain ALUs (fp32, or bf16 shapes the MFMA kernel does not take): 64 x 64 tiles
@@ -2065,16 +2095,22 @@ hipError_t launch_router_backward(int dtype, const float *logits, const int32_t 
   return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t launch_dx_finish_t(const T *dx_in, const float *d_logits, const T *w_router, int64_t n_tok, int d_model, int n_experts,
+                                     T *d_x, hipStream_t s) {
+  const int lg = row_lanes_log2<T>(d_model);
+  const dim3 grid = row_grid<T>(ceil_div(n_tok, lg < 6 ? kDxRows<true> : kDxRows<false>), d_model);
+  const auto kernel = lg < 6 ? &dx_finish_kernel<T, true> : &dx_finish_kernel<T, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, dx_in, d_logits, w_router, n_tok, d_model, n_experts, lg, d_x);
+  return hipGetLastError();
+}
 hipError_t launch_dx_finish(int dtype, const void *dx_in, const float *d_logits, const void *w_router, int64_t n_tok,
                             int d_model, int n_experts, void *d_x, hipStream_t s) {
-  const dim3 grid = grid1d(ceil_div(n_tok, kDxRows) * ceil_div(d_model, 512), 4);
   if (dtype == ROM_DTYPE_BF16)
-    hipLaunchKernelGGL((dx_finish_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(dx_in), d_logits,
-                       static_cast<const bf16_t *>(w_router), n_tok, d_model, n_experts, static_cast<bf16_t *>(d_x));
-  else
-    hipLaunchKernelGGL((dx_finish_kernel<float>), grid, dim3(256), 0, s, static_cast<const float *>(dx_in), d_logits,
-                       static_cast<const float *>(w_router), n_tok, d_model, n_experts, static_cast<float *>(d_x));
-  return hipGetLastError();
+    return launch_dx_finish_t(static_cast<const bf16_t *>(dx_in), d_logits, static_cast<const bf16_t *>(w_router), n_tok, d_model, n_experts,
+                              static_cast<bf16_t *>(d_x), s);
+  return launch_dx_finish_t(static_cast<const float *>(dx_in), d_logits, static_cast<const float *>(w_router), n_tok, d_model, n_experts,
+                            static_cast<float *>(d_x), s);
 }
 
 size_t conv_bwd_partial_bytes(int64_t B, int64_t L, int d_inner) {
@@ -2149,17 +2185,20 @@ hipError_t launch_pack_dxdbl(int dtype, const float *d_dt_low, const float *d_bc
   return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t launch_scale_rows_t(const T *src, const float *scale, const int32_t *src_idx, const int32_t *scale_idx, int64_t n_rows,
+                                      int n_cols, T *dst, hipStream_t s) {
+  const int lg = row_lanes_log2<T>(n_cols);
+  const auto kernel = lg < 6 ? &scale_rows_kernel<T, true> : &scale_rows_kernel<T, false>;
+  hipLaunchKernelGGL(kernel, row_grid<T>(n_rows, n_cols), dim3(256), 0, s, src, scale, src_idx, scale_idx, n_rows, n_cols, lg, dst);
+  return hipGetLastError();
+}
 hipError_t launch_scale_rows(int dtype, const void *src, const float *scale, const int32_t *src_idx,
                              const int32_t *scale_idx, int64_t n_rows, int n_cols, void *dst, hipStream_t s) {
   if (n_cols % 8 != 0) return hipErrorInvalidValue;       // (d_model is a multiple of 8)
-  const dim3 grid = grid1d(n_rows * ceil_div(n_cols, 512), 4);
   if (dtype == ROM_DTYPE_BF16)
-    hipLaunchKernelGGL((scale_rows_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t *>(src), scale,
-                       src_idx, scale_idx, n_rows, n_cols, static_cast<bf16_t *>(dst));
-  else
-    hipLaunchKernelGGL((scale_rows_kernel<float>), grid, dim3(256), 0, s, static_cast<const float *>(src), scale,
-                       src_idx, scale_idx, n_rows, n_cols, static_cast<float *>(dst));
-  return hipGetLastError();
+    return launch_scale_rows_t(static_cast<const bf16_t *>(src), scale, src_idx, scale_idx, n_rows, n_cols, static_cast<bf16_t *>(dst), s);
+  return launch_scale_rows_t(static_cast<const float *>(src), scale, src_idx, scale_idx, n_rows, n_cols, static_cast<float *>(dst), s);
 }
 
 namespace {
