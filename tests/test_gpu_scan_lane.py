@@ -21,9 +21,10 @@ def test_scan_lane(B, L, d_inner, dtype):
     compare_layer(cfg, gpu, x, w, cs, ss)
 
 
-@pytest.mark.parametrize("B,L,d_inner", [(1, 4500, 784), (2, 1500, 1296), (1, 2999, 1040)])
+@pytest.mark.parametrize("B,L,d_inner", [(1, 4500, 784), (1, 5301, 784), (2, 1500, 1296), (1, 2999, 1040)])
 def test_scan_lane_short_chunks(B, L, d_inner):
-    """Calls below 7 Mi (step, channel) pairs, whose chunks may be 32 steps long: remainders of chunks and of channel groups."""
+    """Calls below 7 Mi (step, channel) pairs, whose chunks may be 32 steps long: remainders of chunks and of channel groups.  (The first lies
+    just below the rule's line and takes lane = (channel, state); test_scan_rule.py holds which is which.)"""
     cfg = RomConfig(f"lane_short_{B}_{L}", 950 + L % 89, B, L, 64, d_inner, 16, 4, 8, 4, 1, "bf16", 0)
     cs, ss = make_states(cfg)
     _, gpu, x, w = run_layer(cfg, cs, ss)

@@ -11,7 +11,9 @@ MAIN = """
 #include "rom_scan_rule.h"
 int main() {
   long long B, L; int d;
-  while (std::scanf("%lld %lld %d", &B, &L, &d) == 3) std::printf("%d %d\\n", rom::scan_bwd_chunk(B, L, d), rom::scan_by_lane(B, L, d));
+  while (std::scanf("%lld %lld %d", &B, &L, &d) == 3)
+    std::printf("%d %d %d %d\\n", rom::scan_bwd_chunk(B, L, d), rom::scan_by_lane(B, L, d), rom::scan_by_lane(B, L, d, true),
+                rom::scan_lane_chunks(B, L, d));
 }
 """
 
@@ -56,6 +58,24 @@ def test_lane_scan(rules, B, L, d_inner, want):
 def test_lane_scan_of_few_blocks(rules, B, L, d_inner, want):
     """Both sides of the line for up to three workgroups per CU, where each was measured faster."""
     assert rules(B, L, d_inner)[1] == want
+
+
+@pytest.mark.parametrize("B,L,d_inner,lane,chunks", [
+    (1, 4500, 784, 0, None), (1, 5301, 784, 1, 165), (2, 1500, 1296, 1, 46), (1, 2999, 1040, 1, 93),        # chunks of 32 steps
+])
+def test_lane_scan_in_short_chunks(rules, B, L, d_inner, lane, chunks):
+    """The shapes that test_gpu_scan_lane.py runs for them."""
+    got = rules(B, L, d_inner)
+    assert got[1] == lane and (chunks is None or got[3] == chunks)
+
+
+@pytest.mark.parametrize("B,L,d_inner,want", [
+    (1, 16384, 1536, 1), (1, 16383, 1536, 0), (2, 4096, 3072, 1), (4, 3000, 2048, 0), (4, 3072, 2048, 1), (8, 2048, 1536, 1),
+    (1, 8192, 768, 0), (9, 4096, 1536, 0), (64, 256, 4096, 1), (1, 2048, 1536, 0),
+])
+def test_lane_scan_fp32(rules, B, L, d_inner, want):
+    """24 Mi (step, channel) pairs at no more than three workgroups a CU, or enough wavefronts without chunks."""
+    assert rules(B, L, d_inner)[2] == want
 
 
 CHUNKS = r"""
